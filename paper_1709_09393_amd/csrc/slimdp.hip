@@ -2,6 +2,7 @@
 // and kernel launches only; every step of the path runs in the kernels of slimdp_kernels.h.
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <cmath>
 #include <cstdarg>
 #include <cstdio>
@@ -13,6 +14,7 @@
 
 #include "slimdp.h"
 #include "slimdp_kernels.h"
+#include "slimdp_core.h"
 
 using namespace slimdp;
 
@@ -114,12 +116,15 @@ struct slimdp_ctx {
     // device tables
     uint32_t *d_tile_start = nullptr, *d_tile_seg = nullptr, *d_seg_first_tile = nullptr, *d_flags = nullptr;
     // core selection
-    SegState* c_state = nullptr;
+    CoreState* c_state = nullptr;
+    CorePlan* c_plan = nullptr;            // core sizes per segment (segmented models)
+    std::vector<uint64_t> c_plan_k;        // the sizes c_plan holds
     uint32_t *c_hist = nullptr, *c_gt_bits = nullptr, *c_cand_bits = nullptr, *c_cand_keys = nullptr;
-    uint32_t* c_chunk_sum = nullptr;
-    uint32_t *c_pred = nullptr, *c_skip = nullptr, *c_used = nullptr;   // predicted level-0 threshold bin per segment; "the scoring pass classified against the right bin"
+    uint2 *c_tile_pre = nullptr, *c_group_tail = nullptr;
+    uint32_t *c_pred = nullptr, *c_used = nullptr;   // predicted level-0 threshold bin per segment; the bin the scoring pass sorted against
     bool cls_by_score = false;                       // the last scoring pass classified whole tiles against c_pred
-    uint32_t *c_cnt_gt = nullptr, *c_cnt_cand = nullptr, *c_cnt_sel = nullptr, *c_cnt_tie = nullptr, *c_tie_pre = nullptr;
+    bool hist_clean = true;                          // c_hist is zero once everything enqueued has run (a selection leaves it so)
+    uint32_t *c_cnt_gt = nullptr, *c_cnt_cand = nullptr;
     // explorer selection (batch = worker)
     SegState* e_state = nullptr;
     SegState* e_draw_state = nullptr;      // zone bounds of the announced draw (side stream)
@@ -193,27 +198,28 @@ struct slimdp_ctx {
 
 namespace {
 
-// Tables and the buffers of the core selection (all that a selection without explorers needs).
+constexpr uint32_t CORE_GROUPS = 2048;      // tile groups of the selection passes at most (eight blocks per compute unit)
+
+// Tables and the buffers of the core selection (all that a selection without explorers needs).  The histogram comes
+// first: in the static scratch array it is found at the same place whatever the size of the call before.
 void carve_core(slimdp_ctx* c, Carver& cv)
 {
     const size_t T = c->T, S = c->n_seg;
+    c->c_hist = cv.take<uint32_t>(S * H_STRIDE);
     c->d_tile_start = cv.take<uint32_t>(T + 1);
     c->d_tile_seg = cv.take<uint32_t>(T);
     c->d_seg_first_tile = cv.take<uint32_t>(S + 1);
     c->d_flags = cv.take<uint32_t>(64);
-    c->c_state = cv.take<SegState>(S);
-    c->c_hist = cv.take<uint32_t>(S * H_STRIDE);
+    c->c_state = cv.take<CoreState>(S);
+    c->c_plan = cv.take<CorePlan>(S);
     c->c_gt_bits = cv.take<uint32_t>(T * TILE_WORDS);
     c->c_cand_bits = cv.take<uint32_t>(T * TILE_WORDS);
     c->c_cand_keys = cv.take<uint32_t>(c->keys_stride);
     c->c_cnt_gt = cv.take<uint32_t>(T * SUBS);
     c->c_cnt_cand = cv.take<uint32_t>(T * SUBS);
-    c->c_cnt_sel = cv.take<uint32_t>(T);
-    c->c_cnt_tie = cv.take<uint32_t>(T);
-    c->c_tie_pre = cv.take<uint32_t>(T + 1);
-    c->c_chunk_sum = cv.take<uint32_t>(2 * c->n_chunks);
+    c->c_tile_pre = cv.take<uint2>(T);
+    c->c_group_tail = cv.take<uint2>(CORE_GROUPS);
     c->c_pred = cv.take<uint32_t>(S);
-    c->c_skip = cv.take<uint32_t>(S);
     c->c_used = cv.take<uint32_t>(S);
 }
 
@@ -604,7 +610,7 @@ int slimdp_create(slimdp_ctx** out, uint64_t n, uint32_t max_workers, uint32_t n
     if (e == hipSuccess) e = hipMemcpy(c->d_seg_first_tile, c->tl.seg_first_tile.data(), (n_seg + 1) * 4, hipMemcpyHostToDevice);
     if (e == hipSuccess) e = hipMemset(c->d_flags, 0, 64 * 4);
     if (e == hipSuccess) e = hipMemset(c->c_pred, 0xFF, (size_t)n_seg * 4);      // no prediction yet
-    if (e == hipSuccess) e = hipMemset(c->c_skip, 0, (size_t)n_seg * 4);
+    if (e == hipSuccess) e = hipMemset(c->c_hist, 0, (size_t)n_seg * H_STRIDE * 4);
     if (e == hipSuccess) e = hipStreamCreateWithFlags(&c->side, hipStreamNonBlocking);      // default priority
     if (e == hipSuccess) e = hipEventCreateWithFlags(&c->ev_consumed, hipEventDisableTiming);
     if (e == hipSuccess) e = hipEventCreateWithFlags(&c->ev_drawn, hipEventDisableTiming);
@@ -732,8 +738,9 @@ static int score_impl(slimdp_ctx* ctx, const float* w, const float* const* g, ui
     if (!(c >= 0.0f) || std::isinf(c)) return fail(ctx, SLIMDP_ERR_INVALID_ARG, "slimdp_score: c must be finite and >= 0");
     ctx->hist_pending = false;
     ctx->cls_by_score = false;
-    int rc = fill(ctx, ctx->c_hist, (uint64_t)ctx->n_seg * H_STRIDE, 0u);
-    if (rc) return rc;
+    int rc = SLIMDP_OK;
+    if (!ctx->hist_clean) { rc = fill(ctx, ctx->c_hist, (uint64_t)ctx->n_seg * H_STRIDE, 0u); if (rc) return rc; }
+    ctx->hist_clean = false;
     PtrTab gt = make_tab<PtrTab>(g, W);
     int vec_ok = aligned16(w) && aligned16(score);
     for (uint32_t q = 0; q < W; ++q) vec_ok = vec_ok && aligned16(g[q]);
@@ -903,13 +910,11 @@ static int select_core_impl(slimdp_ctx* ctx, const float* score, const uint64_t*
     if (!score || !k_seg || !core_bits || !core_off || !core_epoch)
         return fail(ctx, SLIMDP_ERR_INVALID_ARG, "slimdp_select_core: NULL argument");
     uint64_t K = 0;
-    std::vector<SegInit> init(ctx->n_seg);
     for (uint32_t s = 0; s < ctx->n_seg; ++s) {
         const uint64_t ns = ctx->seg_off[s + 1] - ctx->seg_off[s];
         if (k_seg[s] > ns)
             return fail(ctx, SLIMDP_ERR_OUT_OF_RANGE, "slimdp_select_core: k_seg[%u]=%llu exceeds the segment size %llu", s,
                         (unsigned long long)k_seg[s], (unsigned long long)ns);
-        init[s] = SegInit{(uint32_t)k_seg[s], 0u, 0u, 0u, 1u};
         K += k_seg[s];
     }
     if (K > 0 && !core_idx) return fail(ctx, SLIMDP_ERR_INVALID_ARG, "slimdp_select_core: core_idx is NULL");
@@ -921,47 +926,60 @@ static int select_core_impl(slimdp_ctx* ctx, const float* score, const uint64_t*
     const uint32_t T = ctx->T, S = ctx->n_seg;
     int rc = wait_for_side(ctx);             // an explorer request on the side stream may still read the bitmap this call rewrites
     if (rc) return rc;
-    rc = init_states(ctx, ctx->c_state, init, 1, 1);
-    if (rc) return rc;
-    const uint32_t P = persistent_blocks(ctx, (uint32_t)ctx->opt_build_blocks, 1);
+    CoreArgs a{};
+    a.tile_start = ctx->d_tile_start; a.tile_seg = ctx->d_tile_seg; a.seg_first_tile = ctx->d_seg_first_tile;
+    a.n = ctx->n; a.T = T; a.n_seg = S;
+    // groups of tiles for the passes over the candidates: a tile per wave at least
+    a.groups = std::min(std::min((T + 3) / 4, (uint32_t)ctx->cus * 8u), CORE_GROUPS);
+    a.k_flat = (uint32_t)K;
+    a.plan = ctx->c_plan; a.hist = ctx->c_hist; a.state = ctx->c_state;
+    a.gt_bits = ctx->c_gt_bits; a.cand_bits = ctx->c_cand_bits; a.cand_keys = ctx->c_cand_keys;
+    a.cnt_gt = ctx->c_cnt_gt; a.cnt_cand = ctx->c_cnt_cand;
+    a.tile_pre = ctx->c_tile_pre; a.group_tail = ctx->c_group_tail; a.flags = ctx->d_flags;
+    if ((T + a.groups - 1) / a.groups > GROUP_MAX)
+        return fail(ctx, SLIMDP_ERR_INVALID_ARG, "slimdp_select_core: %u tiles in %u groups", T, a.groups);
+    if (S > 1 && !std::equal(k_seg, k_seg + S, ctx->c_plan_k.begin(), ctx->c_plan_k.end())) {
+        ctx->c_plan_k.clear();               // whatever happens below: what the device holds is not known yet
+        uint32_t base = 0;
+        for (uint32_t s0 = 0; s0 < S; s0 += PLAN_CHUNK) {
+            CorePlanChunk chunk;
+            const uint32_t cnt = std::min(S - s0, (uint32_t)PLAN_CHUNK);
+            memset(&chunk, 0, sizeof chunk);
+            for (uint32_t j = 0; j < cnt; ++j) { chunk.s[j] = CorePlan{(uint32_t)k_seg[s0 + j], base}; base += (uint32_t)k_seg[s0 + j]; }
+            hipLaunchKernelGGL(k_core_plan, dim3(1), dim3(PLAN_CHUNK), 0, ctx->stream, ctx->c_plan, chunk, s0, cnt);
+            SLIMDP_LAUNCHED(ctx, "k_core_plan");
+        }
+        ctx->c_plan_k.assign(k_seg, k_seg + S);
+    }
     if (!reuse) {
-        rc = fill(ctx, ctx->c_hist, (uint64_t)S * H_STRIDE, 0u);
-        if (rc) return rc;
-        hipLaunchKernelGGL(k_core_hist0, dim3(P), dim3(BLOCK), 0, ctx->stream, score, ctx->d_tile_start, ctx->d_tile_seg, T,
-                           ctx->c_hist);
+        if (!ctx->hist_clean) { rc = fill(ctx, ctx->c_hist, (uint64_t)S * H_STRIDE, 0u); if (rc) return rc; }
+        ctx->hist_clean = false;
+        uint32_t P0 = persistent_blocks(ctx, 4, 1);
+        if (S == 1) P0 = (uint32_t)std::min<uint64_t>((uint64_t)ctx->cus * 4, (ctx->n / 4 + BLOCK - 1) / BLOCK + 1);
+        hipLaunchKernelGGL(k_core_hist0, dim3(P0), dim3(BLOCK), 0, ctx->stream, score, a, (int)aligned16(score));
         SLIMDP_LAUNCHED(ctx, "k_core_hist0");
     }
     // did the scoring pass that made this histogram already sort the whole tiles against a predicted bin?
     const bool classified = reuse && ctx->cls_by_score;
     ctx->cls_by_score = false;
-    const CorePred cp{ctx->c_pred, ctx->c_skip, ctx->c_used, classified ? 1 : 0};
-    hipLaunchKernelGGL(k_threshold, dim3(S, 1), dim3(256), 0, ctx->stream, ctx->c_state, ctx->c_hist, 0, (uint32_t)H_L0, S, 0,
-                       ctx->d_flags, nullptr, 0, SpecTau{nullptr, nullptr, nullptr}, cp);
-    SLIMDP_LAUNCHED(ctx, "k_threshold(0)");
-    hipLaunchKernelGGL(k_core_build, dim3(P), dim3(BLOCK), 0, ctx->stream, score, ctx->d_tile_start, ctx->d_tile_seg, T,
-                       ctx->c_state, ctx->c_skip, ctx->c_hist, ctx->c_gt_bits, ctx->c_cand_bits, ctx->c_cand_keys, ctx->c_cnt_gt,
-                       ctx->c_cnt_cand, (int)aligned16(score), (int)(S == 1 && ctx->opt_strided));
+    ctx->hist_clean = false;
+    const uint32_t P = persistent_blocks(ctx, (uint32_t)ctx->opt_build_blocks, 1);
+    hipLaunchKernelGGL(k_core_build, dim3(P), dim3(BLOCK), 0, ctx->stream, score, a, ctx->c_used, (int)classified, (int)reuse,
+                       (int)aligned16(score), (int)(S == 1 && ctx->opt_strided), S > 1 ? core_bits : nullptr);
     SLIMDP_LAUNCHED(ctx, "k_core_build");
-    MutPtrTab off_tab = make_tab<MutPtrTab, uint32_t*>(&core_off, 1);
-    MutPtrTab idx_tab = make_tab<MutPtrTab, uint32_t*>(&core_idx, 1);
+    hipLaunchKernelGGL(k_core_hist2, dim3(a.groups), dim3(BLOCK), 0, ctx->stream, a);
+    SLIMDP_LAUNCHED(ctx, "k_core_hist2");
     // speculative packing: this selection rates the capture of the scoring pass it reuses and sets the next bound
     const bool spec_sel = ctx->spec.on && ctx->spec.mem && ctx->spec.captured && reuse && ctx->spec.score == score;
     SpecTau sp{nullptr, nullptr, nullptr};
     if (spec_sel) sp = SpecTau{ctx->spec.lo[ctx->spec.cur], ctx->spec.lo[ctx->spec.cur ^ 1], ctx->spec.fail};
-    uint32_t* pub = ctx->tl.word_aligned ? core_bits : nullptr;
-    rc = finish_selection<CORE_KPL, 1>(ctx, 1, ctx->c_state, ctx->c_hist, ctx->c_gt_bits, ctx->c_cand_bits, ctx->c_cand_keys,
-                          ctx->c_cnt_gt, ctx->c_cnt_cand, ctx->c_cnt_sel, ctx->c_cnt_tie, ctx->c_tie_pre, ctx->keys_stride,
-                          true, off_tab, idx_tab, (uint32_t)K, pub, nullptr, nullptr, ctx->c_chunk_sum, sp,
-                          CorePred{ctx->c_pred, nullptr, nullptr, 0});
-    if (rc) return rc;
-    if (!pub) {
-        rc = fill(ctx, core_bits, (ctx->n + 31) / 32, 0u);
-        if (rc) return rc;
-        if (K) {
-            hipLaunchKernelGGL(k_bits_from_idx, dim3(fill_grid(K)), dim3(256), 0, ctx->stream, core_idx, K, ctx->n, core_bits);
-            SLIMDP_LAUNCHED(ctx, "k_bits_from_idx");
-        }
-    }
+    hipLaunchKernelGGL(k_core_count, dim3(a.groups), dim3(BLOCK), 0, ctx->stream, a, sp, ctx->c_pred);
+    SLIMDP_LAUNCHED(ctx, "k_core_count");
+    const uint32_t per_group = ((T + a.groups - 1) / a.groups + 7) / 8;      // at most two tiles per wave and block
+    hipLaunchKernelGGL(k_core_emit, dim3(a.groups * per_group), dim3(BLOCK), 0, ctx->stream, a, per_group, core_idx, core_off,
+                       core_bits, (uint32_t)K);
+    SLIMDP_LAUNCHED(ctx, "k_core_emit");
+    ctx->hist_clean = true;
     *core_epoch = ++ctx->epoch;
     ctx->last_K = K; ctx->have_last_K = true;
     if (spec_sel) { ctx->spec.core_epoch = ctx->epoch; ctx->spec.next_written = true; }
@@ -985,7 +1003,7 @@ int slimdp_select_core(slimdp_ctx* ctx, const float* score, const uint64_t* k_se
 static __device__ __align__(256) unsigned char scratch[SLIMDP_STATIC_SCRATCH_BYTES];
 
 namespace {
-struct StaticDev { void* ptr = nullptr; int cus = 0; };
+struct StaticDev { void* ptr = nullptr; int cus = 0; bool dirty = false; };   // dirty: the histogram may not be clear
 constexpr int STATIC_MAX_DEVICES = 64;
 StaticDev g_static[STATIC_MAX_DEVICES];
 std::mutex g_static_mu;
@@ -1036,14 +1054,16 @@ int slimdp_select_core_static(const float* score, uint64_t n, uint64_t k, uint32
     if (cv.pos > SLIMDP_STATIC_SCRATCH_BYTES)
         return fail(nullptr, SLIMDP_ERR_WORKSPACE, "slimdp_select_core_static: %zu bytes of workspace needed, %u available",
                     cv.pos, (unsigned)SLIMDP_STATIC_SCRATCH_BYTES);
-    // the array keeps the previous call's contents: tables for this n, flags cleared (the histogram is cleared by the selection)
-    hipLaunchKernelGGL(k_flat_tables, dim3((tmp.T + 1 + 255) / 256), dim3(256), 0, tmp.stream, tmp.d_tile_start, tmp.d_tile_seg,
-                       tmp.d_seg_first_tile, tmp.d_flags, tmp.T, (uint32_t)n);
-    e = hipGetLastError();
-    if (e != hipSuccess) return hip_fail(nullptr, e, "k_flat_tables");
+    // the array keeps the previous call's contents: a flat model reads no tables, and the selection leaves the
+    // histogram clear unless a launch failed on the way
+    tmp.hist_clean = !sdv.dirty;
     uint64_t epoch = 0;
     const int rc = select_core_impl(&tmp, score, &k, 0u, core_idx, core_bits, core_off, &epoch);
     if (rc) g_create_error = tmp.err;
+    if (tmp.hist_clean == sdv.dirty) {
+        std::lock_guard<std::mutex> lock(g_static_mu);
+        g_static[device].dirty = !tmp.hist_clean;
+    }
     return rc;
 }
 

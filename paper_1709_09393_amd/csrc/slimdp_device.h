@@ -15,8 +15,9 @@ constexpr int MAXW = SLIMDP_MAX_WORKERS;
 constexpr int BLOCK = 256;                        // threads per block in the tile kernels
 constexpr int EPT = TILE / BLOCK;                 // elements per thread per tile (16)
 
-// Histogram storage per (batch, segment): level 0, level 1, level 2.
-constexpr uint32_t H_L0 = 0, H_L1 = 8192, H_L2 = 12288, H_STRIDE = 16384;
+// Histogram storage per (batch, segment): level 0, level 1, level 2, and the second level-1 region of a core selection
+// (the scoring pass counts into the first against a predicted bin, the selection's own pass into the second).
+constexpr uint32_t H_L0 = 0, H_L1 = 8192, H_L2 = 12288, H_L1B = 12544, H_STRIDE = 16640;
 
 // Core ranking key = raw bits of the score: 13 + 12 + 7 bits.
 constexpr uint32_t CORE_SHIFT0 = 19, CORE_NB0 = 8192, CORE_SHIFT1 = 7, CORE_NB1 = 4096, CORE_NB2 = 128;

@@ -53,18 +53,6 @@ __global__ __launch_bounds__(256) void k_fill_u32(uint32_t* __restrict__ p, uint
         p[i] = v;
 }
 
-// Tile tables of a flat model of n parameters, and the 64 flag words cleared (for a workspace that keeps the
-// contents of an earlier, differently sized call).  grid ceil((T+1)/256).
-__global__ __launch_bounds__(256) void k_flat_tables(uint32_t* __restrict__ tile_start, uint32_t* __restrict__ tile_seg,
-                                                     uint32_t* __restrict__ seg_first_tile, uint32_t* __restrict__ flags,
-                                                     uint32_t T, uint32_t n)
-{
-    const uint32_t t = blockIdx.x * 256 + threadIdx.x;
-    if (t < T) { tile_start[t] = t * TILE; tile_seg[t] = 0; }
-    if (t == T) { tile_start[T] = n; seg_first_tile[0] = 0; seg_first_tile[1] = T; }
-    if (t < 64) flags[t] = 0;
-}
-
 // Writes the selection state of segments [seg0, seg0+count) for every batch.
 // core != 0: fixed score-bit levels; else explorer levels derived from (bound_m1, shift0).
 // Several fills in one launch (a launch costs more than a small fill).
@@ -885,34 +873,6 @@ __global__ __launch_bounds__(1024) void k_sample_bound(const uint32_t* __restric
     }
 }
 
-// Level-0 histogram of a score array that did not come from k_score.
-__global__ __launch_bounds__(BLOCK) void k_core_hist0(const float* __restrict__ S, const uint32_t* __restrict__ tile_start,
-                                                      const uint32_t* __restrict__ tile_seg, uint32_t T,
-                                                      uint32_t* __restrict__ hist)
-{
-    __shared__ uint32_t h[CORE_NB0];
-    for (uint32_t b = threadIdx.x; b < CORE_NB0; b += BLOCK) h[b] = 0;
-    __syncthreads();
-    const uint32_t t0 = (uint32_t)((uint64_t)T * blockIdx.x / gridDim.x);
-    const uint32_t t1 = (uint32_t)((uint64_t)T * (blockIdx.x + 1) / gridDim.x);
-    if (t0 >= t1) return;
-    uint32_t cur_seg = tile_seg[t0];
-    for (uint32_t t = t0; t < t1; ++t) {
-        const uint32_t seg = tile_seg[t];
-        if (seg != cur_seg) {
-            __syncthreads();
-            flush_hist(h, CORE_NB0, hist + (size_t)cur_seg * H_STRIDE + H_L0);
-            __syncthreads();
-            cur_seg = seg;
-        }
-        const uint32_t start = tile_start[t], len = tile_start[t + 1] - start;
-        for (uint32_t l = threadIdx.x; l < len; l += BLOCK)
-            atomicAdd(&h[__float_as_uint(S[(size_t)start + l]) >> CORE_SHIFT0], 1u);
-    }
-    __syncthreads();
-    flush_hist(h, CORE_NB0, hist + (size_t)cur_seg * H_STRIDE + H_L0);
-}
-
 // ---------------------------------------------------------------------------------------
 // Threshold step of one radix level: walk the bins from the largest digit down until
 // `need` keys are covered.  grid (n_seg, nbatch), 256 threads.
@@ -1023,150 +983,6 @@ __global__ __launch_bounds__(256) void k_threshold(SegState* __restrict__ states
             for (uint32_t x = threadIdx.x; x < CORE_NB1; x += 256) h1[x] = 0;
         }
     }
-}
-
-// ---------------------------------------------------------------------------------------
-// K2: core candidates.  One pass over the score: parameters whose level-0 digit is above
-// the threshold bin are certainly in the core (gt bitmap), those in the bin are candidates
-// (bitmap + keys compacted per sub-tile) and feed the level-1 histogram.
-// Every wave owns sub-tile `wid` of each of the block's tiles and needs no block barrier:
-// round `it` covers parameters [256*it, 256*it+256) of the sub-tile in index order (lane L
-// owns 4L..4L+3), the eight bitmap words of a round are OR-reductions over groups of
-// eight lanes, a candidate's place in the key list comes from wave ballots.
-// ---------------------------------------------------------------------------------------
-// The 1024 scores of sub-tile `wid` of a tile as keys: lane L holds parameters 4L..4L+3 of each round of 256.
-__device__ __forceinline__ void core_load_keys(const float* __restrict__ S, uint32_t start, uint32_t len, uint32_t wid,
-                                               uint32_t lane, int vec_ok, uint32_t key[4][4])
-{
-    const uint32_t off = wid * SUB;
-    const uint32_t sub_len = (len > off) ? ((len - off < SUB) ? len - off : SUB) : 0u;
-    const float* src = S + (size_t)start + off;
-    if (vec_ok && sub_len == SUB && (start & 3u) == 0) {
-#pragma unroll
-        for (int it = 0; it < 4; ++it) {
-            const uint4 v = ld4u<NT_BUILD>(reinterpret_cast<const uint32_t*>(src + it * 256 + lane * 4));
-            key[it][0] = v.x; key[it][1] = v.y; key[it][2] = v.z; key[it][3] = v.w;
-        }
-    } else {
-#pragma unroll
-        for (int it = 0; it < 4; ++it)
-#pragma unroll
-            for (int cc = 0; cc < 4; ++cc) {
-                const uint32_t e = (uint32_t)it * 256u + lane * 4u + cc;
-                key[it][cc] = (e < sub_len) ? __float_as_uint(src[e]) : 0u;
-            }
-    }
-}
-
-// One sub-tile's keys against the level-0 threshold bin b1: bitmaps, candidate keys, counts, level-1 histogram (LDS).
-__device__ __forceinline__ void core_classify(const uint32_t key[4][4], uint32_t t, uint32_t start, uint32_t len, uint32_t wid,
-                                              uint32_t lane, uint32_t b1, uint32_t none, uint32_t* __restrict__ h,
-                                              uint32_t* __restrict__ gt_bits, uint32_t* __restrict__ cand_bits,
-                                              uint32_t* __restrict__ cand_keys, uint32_t* __restrict__ cnt_gt,
-                                              uint32_t* __restrict__ cnt_cand)
-{
-    const uint32_t off = wid * SUB;
-    const uint32_t sub_len = (len > off) ? ((len - off < SUB) ? len - off : SUB) : 0u;
-    uint32_t* gwords = gt_bits + (size_t)t * TILE_WORDS + wid * SUB_WORDS;
-    uint32_t* cwords = cand_bits + (size_t)t * TILE_WORDS + wid * SUB_WORDS;
-    uint32_t* ckeys = cand_keys + (size_t)start + off;
-    uint32_t run = 0, ngt = 0;
-#pragma unroll
-    for (int it = 0; it < 4; ++it) {
-        uint32_t fg = 0, fc = 0;
-#pragma unroll
-        for (int cc = 0; cc < 4; ++cc) {
-            const uint32_t e = (uint32_t)it * 256u + lane * 4u + cc;
-            if (e < sub_len && !none) {
-                const uint32_t d = key[it][cc] >> CORE_SHIFT0;
-                if (d > b1) fg |= 1u << cc;
-                else if (d == b1) fc |= 1u << cc;
-            }
-        }
-        const uint32_t vg = or_reduce8(fg << (4u * (lane & 7u))), vc = or_reduce8(fc << (4u * (lane & 7u)));
-        if ((lane & 7u) == 0) { gwords[it * 8 + (lane >> 3)] = vg; cwords[it * 8 + (lane >> 3)] = vc; }
-        ngt += __popc(fg);
-        uint32_t below = 0, total = 0;
-#pragma unroll
-        for (int cc = 0; cc < 4; ++cc) {
-            const unsigned long long bal = __ballot((fc >> cc) & 1u);
-            below += __builtin_amdgcn_mbcnt_hi((uint32_t)(bal >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)bal, 0u));
-            total += (uint32_t)__popcll(bal);
-        }
-        if (fc) {
-            uint32_t pos = run + below;
-#pragma unroll
-            for (int cc = 0; cc < 4; ++cc)
-                if ((fc >> cc) & 1u) {
-                    ckeys[pos++] = key[it][cc];
-                    atomicAdd(&h[(key[it][cc] >> CORE_SHIFT1) & (CORE_NB1 - 1u)], 1u);
-                }
-        }
-        run += total;
-    }
-    ngt = wave_sum(ngt);
-    if (lane == 0) { cnt_cand[(size_t)t * SUBS + wid] = run; cnt_gt[(size_t)t * SUBS + wid] = ngt; }
-}
-
-// skip [n_seg] (may be nullptr): 1 = the scoring pass has already classified every whole, 4-aligned tile of the
-// segment against the right bin; only ragged or unaligned tiles are left.
-__global__ __launch_bounds__(BLOCK) void k_core_build(const float* __restrict__ S, const uint32_t* __restrict__ tile_start,
-                                                      const uint32_t* __restrict__ tile_seg, uint32_t T,
-                                                      const SegState* __restrict__ states, const uint32_t* __restrict__ skip,
-                                                      uint32_t* __restrict__ hist,
-                                                      uint32_t* __restrict__ gt_bits, uint32_t* __restrict__ cand_bits,
-                                                      uint32_t* __restrict__ cand_keys, uint32_t* __restrict__ cnt_gt,
-                                                      uint32_t* __restrict__ cnt_cand, int vec_ok, int strided)
-{
-    __shared__ uint32_t h[CORE_NB1];
-    const uint32_t lane = lane_id(), wid = threadIdx.x >> 6;
-    // a contiguous range of tiles, or (flat model) every gridDim.x-th tile: see k_score
-    uint32_t t0 = (uint32_t)((uint64_t)T * blockIdx.x / gridDim.x);
-    uint32_t t1 = (uint32_t)((uint64_t)T * (blockIdx.x + 1) / gridDim.x);
-    uint32_t tstep = 1;
-    if (strided) { t0 = blockIdx.x; t1 = T; tstep = gridDim.x; }
-    if (t0 >= t1) return;
-    auto done = [&](uint32_t t) {       // already classified by the scoring pass?
-        if (!skip || !skip[tile_seg[t]]) return false;
-        const uint32_t start = tile_start[t];
-        return tile_start[t + 1] - start == TILE && (start & 3u) == 0;
-    };
-    // flat model, prediction held: only a ragged last tile can be left; one block looks at it
-    if (strided && skip && skip[0]) {
-        if (blockIdx.x != 0) return;
-        t0 = T - 1;
-    }
-    for (uint32_t b = threadIdx.x; b < CORE_NB1; b += BLOCK) h[b] = 0;
-    __syncthreads();
-    uint32_t cur_seg = tile_seg[t0];
-    // two tiles a turn: the scores of both are requested before either is worked on
-    for (uint32_t t = t0; t < t1; t += 2 * tstep) {
-        const uint32_t tB = t + tstep;
-        const bool one = !done(t), two = tB < t1 && !done(tB);
-        if (!one && !two) continue;
-        const uint32_t startA = tile_start[t], lenA = tile_start[t + 1] - startA;
-        const uint32_t startB = two ? tile_start[tB] : 0u, lenB = two ? tile_start[tB + 1] - startB : 0u;
-        uint32_t keyA[4][4], keyB[4][4];
-        if (one) core_load_keys(S, startA, lenA, wid, lane, vec_ok, keyA);
-        if (two) core_load_keys(S, startB, lenB, wid, lane, vec_ok, keyB);
-#pragma unroll
-        for (int half = 0; half < 2; ++half) {
-            if (half == 0 ? !one : !two) continue;
-            const uint32_t tt = half ? tB : t;
-            const uint32_t seg = tile_seg[tt];
-            if (seg != cur_seg) {
-                __syncthreads();
-                flush_hist(h, CORE_NB1, hist + (size_t)cur_seg * H_STRIDE + H_L1);
-                __syncthreads();
-                cur_seg = seg;
-            }
-            const uint32_t b1 = states[seg].prefix, none = states[seg].none;
-            if (half == 0) core_classify(keyA, tt, startA, lenA, wid, lane, b1, none, h, gt_bits, cand_bits, cand_keys, cnt_gt, cnt_cand);
-            else core_classify(keyB, tt, startB, lenB, wid, lane, b1, none, h, gt_bits, cand_bits, cand_keys, cnt_gt, cnt_cand);
-        }
-    }
-    __syncthreads();
-    flush_hist(h, CORE_NB1, hist + (size_t)cur_seg * H_STRIDE + H_L1);
 }
 
 // Stand-alone draw over every (worker, tile); each wave owns one sub-tile of the block's

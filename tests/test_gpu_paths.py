@@ -1,0 +1,88 @@
+"""GPU parity at the places where a kernel's split of the work can go wrong: tile and group edges, segments that share
+bitmap words or tiles' groups, remainders, and the sizes at which a call changes its path.  Everything is compared bit for
+bit: the oracle defines every result to the bit (order of sums, single roundings, tie rules, random words)."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_1709_09393_amd import binding, workloads
+
+pytestmark = pytest.mark.gpu
+
+torch = pytest.importorskip("torch")
+
+
+def dev():
+    if not torch.cuda.is_available():
+        pytest.fail("GPU test selected but torch.cuda.is_available() is False")
+    return torch.device("cuda:0")
+
+
+def to_dev(a):
+    a = np.ascontiguousarray(a)
+    return torch.from_numpy(a.view(np.int32) if a.dtype == np.uint32 else a).to(dev())
+
+
+def u32(t):
+    return t.cpu().numpy().view(np.uint32)
+
+
+def offsets(sizes):
+    return [0] + [int(x) for x in np.cumsum(sizes)]
+
+
+# segments inside one bitmap word, across words, empty cores, many tiles, a last word that is not full
+SEGMENTS = {
+    "inside_one_word": [1, 2, 3, 5, 7, 11, 1, 1, 30],
+    "words_shared_by_long_tiles": [4096 + 17, 31, 8192 + 1, 3, 4095, 64, 4097],
+    "groups_and_segments_interleave": [5 * 4096 + 100, 40, 90 * 4096 + 1, 1000, 4096, 4096, 33],
+    "one_tile_each": [4096] * 40 + [13],
+}
+
+
+@pytest.mark.parametrize("values", ["spread", "ties"])
+@pytest.mark.parametrize("name", sorted(SEGMENTS))
+def test_segmented_selection_publishes_lists_offsets_and_shared_bitmap_words(name, values):
+    sizes = SEGMENTS[name]
+    so, n = offsets(sizes), sum(sizes)
+    rng = np.random.default_rng(len(name))
+    S_h = np.abs(rng.standard_normal(n)).astype(np.float32)
+    if values == "ties":
+        S_h = (rng.integers(0, 5, n) / 8.0).astype(np.float32)
+    sd = binding.SlimDP(n, 1, seg_off=so)
+    ts = sd.tile_starts().astype(np.int64)
+    for part in (3, 1, 2):                       # other core sizes on the same context, empty and full cores among them
+        ks = [0 if j % 4 == part else (s if j % 7 == part else s * part // 5) for j, s in enumerate(sizes)]
+        core_bits = torch.full(((n + 31) // 32,), -1, dtype=torch.int32, device=dev())
+        idx, bits, off, _ = sd.select_core(to_dev(S_h), ks, core_bits=core_bits)
+        sd.synchronize()
+        want = oracle.select_core(S_h, ks, so)
+        assert np.array_equal(u32(idx), want)
+        assert np.array_equal(u32(bits), oracle.core_bits(n, want))
+        assert np.array_equal(u32(off), np.searchsorted(want.astype(np.int64), ts).astype(np.uint32))
+    sd.close()
+
+
+@pytest.mark.parametrize("n", [4096 * 4, 4096 * 5 + 1, 4096 * 16, 300_001])
+def test_selection_leaves_clear_counts_whatever_was_counted_before(n):
+    """A selection counts from zero: after another one, after a scoring pass whose histogram nobody used, and after one
+    that sorted against another bin than its own."""
+    wl = workloads.TINY.scaled(n)
+    w, g = to_dev(wl.weights()), [to_dev(x) for x in wl.gradients(0)]
+    rng = np.random.default_rng(n)
+    other = (np.abs(rng.standard_normal(n)) * 1e-3).astype(np.float32)
+    S_o = oracle.score(wl.weights(), wl.gradients(0), wl.c)
+    sd = binding.SlimDP(n, wl.W)
+    k = wl.k
+    for _ in range(2):
+        S = sd.score(w, g, wl.c)                 # counted twice, used once
+        S = sd.score(w, g, wl.c)
+        a = sd.select_core(S, [k], reuse_histogram=True)[0]
+        S = sd.score(w, g, wl.c)                 # counted, then a selection on another array
+        b = sd.select_core(to_dev(other), [k])[0]
+        c = sd.select_core(to_dev(S_o), [n - k])[0]
+        sd.synchronize()
+        assert np.array_equal(u32(a), oracle.select_core(S_o, k))
+        assert np.array_equal(u32(b), oracle.select_core(other, k))
+        assert np.array_equal(u32(c), oracle.select_core(S_o, n - k))
+    sd.close()
