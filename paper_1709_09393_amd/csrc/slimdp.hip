@@ -124,6 +124,7 @@ struct slimdp_ctx {
     uint32_t *c_pred = nullptr, *c_used = nullptr;   // predicted level-0 threshold bin per segment; the bin the scoring pass sorted against
     bool cls_by_score = false;                       // the last scoring pass classified whole tiles against c_pred
     bool hist_clean = true;                          // c_hist is zero once everything enqueued has run (a selection leaves it so)
+    bool recorded = false;                           // a call of this context went into a graph: see device_state_known
     uint32_t *c_cnt_gt = nullptr, *c_cnt_cand = nullptr;
     // explorer selection (batch = worker)
     SegState* e_state = nullptr;
@@ -372,6 +373,18 @@ template <class Tab, class P> Tab make_tab(P const* tab, uint32_t nw)
     if (tab)
         for (uint32_t q = 0; q < nw; ++q) t.p[q] = (decltype(t.p[0]))tab[q];
     return t;
+}
+
+// Whether the device holds what the host's notes say it holds once everything enqueued has run (clear histograms, the
+// segments' core sizes).  A call recorded into a graph runs later, and any number of times: it must set what it needs by
+// itself, and from then on a replay may have left other contents than the eager calls did.
+bool device_state_known(slimdp_ctx* c)
+{
+    if (c->stream && !c->recorded) {         // the default stream cannot be recorded
+        hipStreamCaptureStatus st = hipStreamCaptureStatusNone;
+        if (hipStreamIsCapturing(c->stream, &st) != hipSuccess || st != hipStreamCaptureStatusNone) c->recorded = true;
+    }
+    return !c->recorded;
 }
 
 // The context's stream waits for whatever the side stream still has in flight (an announced draw, asynchronous
@@ -739,7 +752,7 @@ static int score_impl(slimdp_ctx* ctx, const float* w, const float* const* g, ui
     ctx->hist_pending = false;
     ctx->cls_by_score = false;
     int rc = SLIMDP_OK;
-    if (!ctx->hist_clean) { rc = fill(ctx, ctx->c_hist, (uint64_t)ctx->n_seg * H_STRIDE, 0u); if (rc) return rc; }
+    if (!ctx->hist_clean || !device_state_known(ctx)) { rc = fill(ctx, ctx->c_hist, (uint64_t)ctx->n_seg * H_STRIDE, 0u); if (rc) return rc; }
     ctx->hist_clean = false;
     PtrTab gt = make_tab<PtrTab>(g, W);
     int vec_ok = aligned16(w) && aligned16(score);
@@ -938,7 +951,7 @@ static int select_core_impl(slimdp_ctx* ctx, const float* score, const uint64_t*
     a.tile_pre = ctx->c_tile_pre; a.group_tail = ctx->c_group_tail; a.flags = ctx->d_flags;
     if ((T + a.groups - 1) / a.groups > GROUP_MAX)
         return fail(ctx, SLIMDP_ERR_INVALID_ARG, "slimdp_select_core: %u tiles in %u groups", T, a.groups);
-    if (S > 1 && !std::equal(k_seg, k_seg + S, ctx->c_plan_k.begin(), ctx->c_plan_k.end())) {
+    if (S > 1 && (!device_state_known(ctx) || !std::equal(k_seg, k_seg + S, ctx->c_plan_k.begin(), ctx->c_plan_k.end()))) {
         ctx->c_plan_k.clear();               // whatever happens below: what the device holds is not known yet
         uint32_t base = 0;
         for (uint32_t s0 = 0; s0 < S; s0 += PLAN_CHUNK) {
@@ -952,7 +965,7 @@ static int select_core_impl(slimdp_ctx* ctx, const float* score, const uint64_t*
         ctx->c_plan_k.assign(k_seg, k_seg + S);
     }
     if (!reuse) {
-        if (!ctx->hist_clean) { rc = fill(ctx, ctx->c_hist, (uint64_t)S * H_STRIDE, 0u); if (rc) return rc; }
+        if (!ctx->hist_clean || !device_state_known(ctx)) { rc = fill(ctx, ctx->c_hist, (uint64_t)S * H_STRIDE, 0u); if (rc) return rc; }
         ctx->hist_clean = false;
         uint32_t P0 = persistent_blocks(ctx, 4, 1);
         if (S == 1) P0 = (uint32_t)std::min<uint64_t>((uint64_t)ctx->cus * 4, (ctx->n / 4 + BLOCK - 1) / BLOCK + 1);

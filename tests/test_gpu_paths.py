@@ -86,3 +86,45 @@ def test_selection_leaves_clear_counts_whatever_was_counted_before(n):
         assert np.array_equal(u32(b), oracle.select_core(other, k))
         assert np.array_equal(u32(c), oracle.select_core(S_o, n - k))
     sd.close()
+
+
+@pytest.mark.parametrize("segments", [1, 5])
+def test_recorded_selection_replays_beside_eager_ones(segments):
+    """Score and selection recorded into a graph give the eager result on every replay, whatever eager calls (other core
+    sizes, a scoring pass whose histogram nobody used) ran between recording and replay; eager calls stay right after one."""
+    n = 5 * 4096 * 3 + 17
+    wl = workloads.TINY.scaled(n)
+    so = offsets([n]) if segments == 1 else offsets([4096 + 5, 3, 20_000, 30_001, n - 4096 - 5 - 3 - 50_001])
+    sizes = np.diff(so)
+    ks, other = [int(s) // 7 for s in sizes], [int(s) // 2 for s in sizes]
+    w_h, g_h = wl.weights(), wl.gradients(0)
+    w, g = to_dev(w_h), [to_dev(x) for x in g_h]
+    S_o = oracle.score(w_h, g_h, wl.c)
+    want, want_other = oracle.select_core(S_o, ks, so), oracle.select_core(S_o, other, so)
+    st = torch.cuda.Stream()
+    st.wait_stream(torch.cuda.current_stream())
+    sd = binding.SlimDP(n, wl.W, seg_off=so, stream=st)
+    S = torch.empty_like(w)
+    idx = torch.empty(sum(ks), dtype=torch.int32, device=dev())
+    bits = torch.empty((n + 31) // 32, dtype=torch.int32, device=dev())
+    off = torch.empty(sd.T + 1, dtype=torch.int32, device=dev())
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=st):
+        sd.score(w, g, wl.c, out=S)
+        sd.select_core(S, ks, reuse_histogram=True, core_idx=idx, core_bits=bits, core_off=off)
+    S2 = torch.empty_like(w)
+    for turn in range(3):
+        with torch.cuda.stream(st):
+            if turn != 1:
+                got = sd.select_core(to_dev(S_o), other)[0]
+                sd.synchronize()
+                assert np.array_equal(u32(got), want_other)
+            sd.score(w, g, wl.c, out=S2)         # counted, not used
+            idx.zero_()
+            graph.replay()
+        sd.synchronize()
+        assert np.array_equal(u32(S), S_o.view(np.uint32))
+        assert np.array_equal(u32(idx), want)
+        assert np.array_equal(u32(bits), oracle.core_bits(n, want))
+    sd.close()
