@@ -15,6 +15,7 @@
 #include "slimdp.h"
 #include "slimdp_kernels.h"
 #include "slimdp_core.h"
+#include "slimdp_explore.h"
 
 using namespace slimdp;
 
@@ -63,6 +64,21 @@ uint64_t count_tiles(uint64_t n, uint32_t n_seg, const uint64_t* seg_off)
     uint64_t T = 0;
     for (uint32_t s = 0; s < n_seg; ++s) T += (seg_off[s + 1] - seg_off[s] + TILE - 1) / TILE;
     return T;
+}
+
+// Where each segment's list of explorer candidates begins.  The zones of a request for m of n_s parameters hold
+// 2 (6 sqrt(m) + 32) words outside the core on average (explorer_init); the room is for the largest m and eight
+// standard deviations more.
+std::vector<uint32_t> list_starts(uint32_t n_seg, const uint64_t* seg_off)
+{
+    std::vector<uint32_t> first(n_seg + 1, 0u);
+    for (uint32_t s = 0; s < n_seg; ++s) {
+        const uint64_t ns = seg_off[s + 1] - seg_off[s];
+        const double mean = 2.0 * (6.0 * std::sqrt((double)ns) + 32.0);
+        const uint64_t cap = (uint64_t)std::ceil(mean + 8.0 * std::sqrt(mean)) + 64;
+        first[s + 1] = first[s] + (uint32_t)(cap < ns ? cap : ns);          // the sum is at most n
+    }
+    return first;
 }
 
 inline size_t align_up(size_t x, size_t a) { return (x + a - 1) / a * a; }
@@ -129,16 +145,15 @@ struct slimdp_ctx {
     // explorer selection (batch = worker)
     SegState* e_state = nullptr;
     SegState* e_draw_state = nullptr;      // zone bounds of the announced draw (side stream)
-    uint32_t *e_hist = nullptr, *e_sure_bits = nullptr, *e_cand_bits = nullptr;
+    uint32_t *e_sure_bits = nullptr, *e_cand_bits = nullptr;
     uint32_t* e_pair_keys = nullptr;       // narrow zones: per sub-tile a slot of (key, offset) pairs
     uint64_t pair_stride = 0;              // words per worker of the pair slots
     uint32_t* e_cand_keys = nullptr;       // wide zones: candidate keys compacted per sub-tile over the whole index range;
                                            // its own allocation, made by the first request that needs it
-    uint32_t *e_cnt_gt = nullptr, *e_nsure = nullptr, *e_list_count = nullptr, *e_chunk_sum = nullptr, *e_tie_list = nullptr;
-    uint4* e_list = nullptr;
-    uint64_t list_cap = 0;
-    uint32_t n_chunks = 0;
-    uint32_t *e_cnt_cand = nullptr, *e_cnt_sel = nullptr, *e_cnt_tie = nullptr, *e_tie_pre = nullptr;
+    uint32_t *e_cnt_cand = nullptr, *e_cnt_sel = nullptr;
+    uint2* e_list = nullptr;               // candidates outside the core, per (worker, segment): see ExploreLists
+    uint32_t *e_list_count = nullptr, *d_list_first = nullptr;
+    std::vector<uint32_t> list_first;      // n_seg+1
     // host state
     uint64_t epoch = 0;
     bool hist_pending = false;
@@ -185,7 +200,7 @@ struct slimdp_ctx {
         uint64_t iteration = 0;
         uint32_t worker0 = 0, n_workers = 0;
         std::vector<uint64_t> k_seg, m_seg;
-        bool pairs = false;          // drawn in the short-list format
+        bool pairs = false;          // drawn in the format of narrow zones (pairs)
         bool same(uint64_t it, uint32_t w0, uint32_t nw, const uint64_t* k, const uint64_t* m, uint32_t n_seg) const
         {
             if (!valid || it != iteration || w0 != worker0 || nw != n_workers) return false;
@@ -210,7 +225,9 @@ void carve_core(slimdp_ctx* c, Carver& cv)
     c->d_tile_start = cv.take<uint32_t>(T + 1);
     c->d_tile_seg = cv.take<uint32_t>(T);
     c->d_seg_first_tile = cv.take<uint32_t>(S + 1);
-    c->d_flags = cv.take<uint32_t>(64);
+    c->d_list_first = cv.take<uint32_t>(S + 1);
+    c->c_pred = cv.take<uint32_t>(S);
+    c->d_flags = cv.take<uint32_t>(64);          // the tables above and the flags are uploaded in one copy: see slimdp_create
     c->c_state = cv.take<CoreState>(S);
     c->c_plan = cv.take<CorePlan>(S);
     c->c_gt_bits = cv.take<uint32_t>(T * TILE_WORDS);
@@ -220,7 +237,6 @@ void carve_core(slimdp_ctx* c, Carver& cv)
     c->c_cnt_cand = cv.take<uint32_t>(T * SUBS);
     c->c_tile_pre = cv.take<uint2>(T);
     c->c_group_tail = cv.take<uint2>(CORE_GROUPS);
-    c->c_pred = cv.take<uint32_t>(S);
     c->c_used = cv.take<uint32_t>(S);
 }
 
@@ -230,20 +246,13 @@ void carve(slimdp_ctx* c, Carver& cv)
     carve_core(c, cv);
     c->e_state = cv.take<SegState>(B * S);
     c->e_draw_state = cv.take<SegState>(B * S);
-    c->e_hist = cv.take<uint32_t>(B * S * H_STRIDE);
     c->e_sure_bits = cv.take<uint32_t>(B * T * TILE_WORDS);
     c->e_cand_bits = cv.take<uint32_t>(B * T * TILE_WORDS);
-    c->e_cnt_gt = cv.take<uint32_t>(B * T * SUBS);
-    c->e_nsure = cv.take<uint32_t>(B * S);
-    c->e_list_count = cv.take<uint32_t>(64);          // [0] candidates listed, [1] ties listed
-    c->e_tie_list = cv.take<uint32_t>(TIE_CAP);
-    c->e_chunk_sum = cv.take<uint32_t>(2 * B * c->n_chunks);   // tie sums, then offset sums
-    c->e_list = cv.take<uint4>(c->list_cap);
+    c->e_list_count = cv.take<uint32_t>(B * S);
+    c->e_list = cv.take<uint2>(B * (size_t)c->list_first[S]);
     c->e_pair_keys = cv.take<uint32_t>(B * c->pair_stride);
     c->e_cnt_cand = cv.take<uint32_t>(B * T * SUBS);
     c->e_cnt_sel = cv.take<uint32_t>(B * T);
-    c->e_cnt_tie = cv.take<uint32_t>(B * T);
-    c->e_tie_pre = cv.take<uint32_t>(B * (T + 1));
 }
 
 int fail(slimdp_ctx* c, int code, const char* fmt, ...)
@@ -286,19 +295,18 @@ int fill(slimdp_ctx* c, uint32_t* p, uint64_t count, uint32_t v)
     return SLIMDP_OK;
 }
 
-int init_states(slimdp_ctx* c, SegState* st, const std::vector<SegInit>& init, uint32_t nbatch, int core,
-                hipStream_t stream = nullptr)
+// clear: the request's list counters and the rerun flag as well (a draw alone leaves those to the request).
+int init_states(slimdp_ctx* c, SegState* st, const std::vector<SegInit>& init, uint32_t nbatch, bool clear, hipStream_t stream)
 {
-    if (!stream) stream = c->stream;
     for (uint32_t s0 = 0; s0 < c->n_seg; s0 += INIT_CHUNK) {
         SegInitChunk chunk;
         const uint32_t cnt = (c->n_seg - s0 < (uint32_t)INIT_CHUNK) ? c->n_seg - s0 : (uint32_t)INIT_CHUNK;
         memset(&chunk, 0, sizeof chunk);
         for (uint32_t j = 0; j < cnt; ++j) chunk.s[j] = init[s0 + j];
         const uint32_t threads = cnt * nbatch;
-        hipLaunchKernelGGL(k_init_state, dim3((threads + 255) / 256), dim3(256), 0, stream, st, chunk, s0, cnt,
-                           c->n_seg, nbatch, core);
-        SLIMDP_LAUNCHED(c, "k_init_state");
+        hipLaunchKernelGGL(k_explore_init, dim3((threads + 255) / 256), dim3(256), 0, stream, st, chunk, s0, cnt, c->n_seg, nbatch,
+                           clear ? c->e_list_count : nullptr, clear && s0 == 0 ? c->d_flags : nullptr);
+        SLIMDP_LAUNCHED(c, "k_explore_init");
     }
     return SLIMDP_OK;
 }
@@ -309,52 +317,6 @@ uint32_t persistent_blocks(const slimdp_ctx* c, uint32_t per_cu, uint32_t nbatch
     if (p < 32) p = 32;
     if (p > c->T) p = c->T;
     return (uint32_t)p;
-}
-
-// Levels 1, 2, per-tile counts, scan over tiles and ordered emission, shared by the core
-// (after k_core_build, which already filled the level-1 histogram) and the explorer.
-template <int KPL, int BPW>
-int finish_selection(slimdp_ctx* c, uint32_t nbatch, SegState* st, uint32_t* hist, const uint32_t* gt_bits,
-                     const uint32_t* cand_bits, const uint32_t* cand_keys, const uint32_t* cnt_gt,
-                     const uint32_t* cnt_cand, uint32_t* cnt_sel, uint32_t* cnt_tie, uint32_t* tie_pre,
-                     uint64_t keys_stride, bool level1_done, const MutPtrTab& out_off, const MutPtrTab& out_idx,
-                     uint32_t expected, uint32_t* pub_bits, const uint32_t* excl_bits, const uint32_t* gate,
-                     uint32_t* chunk_sum, SpecTau sp = SpecTau{nullptr, nullptr, nullptr},
-                     CorePred cp = CorePred{nullptr, nullptr, nullptr, 0}, hipStream_t stream = nullptr)
-{
-    if (!stream) stream = c->stream;
-    const uint32_t T = c->T, S = c->n_seg;
-    const dim3 wave_grid((T + 3) / 4, (nbatch + BPW - 1) / BPW);     // a wave serves its tile for BPW batches
-    if (!level1_done) {
-        hipLaunchKernelGGL((k_list_hist<KPL, BPW>), wave_grid, dim3(BLOCK), 0, stream, c->n, c->d_tile_start,
-                           c->d_tile_seg, T, S, nbatch, st, hist, (uint32_t)H_L1, 1, cand_keys, cnt_cand, keys_stride, gate);
-        SLIMDP_LAUNCHED(c, "k_list_hist(1)");
-    }
-    hipLaunchKernelGGL(k_threshold, dim3(S, nbatch), dim3(256), 0, stream, st, hist, 1, (uint32_t)H_L1, S, 0, c->d_flags,
-                       nullptr, gate ? 1 : 0, SpecTau{nullptr, nullptr, nullptr}, CorePred{nullptr, nullptr, nullptr, 0});
-    SLIMDP_LAUNCHED(c, "k_threshold(1)");
-    hipLaunchKernelGGL((k_list_hist<KPL, BPW>), wave_grid, dim3(BLOCK), 0, stream, c->n, c->d_tile_start, c->d_tile_seg,
-                       T, S, nbatch, st, hist, (uint32_t)H_L2, 2, cand_keys, cnt_cand, keys_stride, gate);
-    SLIMDP_LAUNCHED(c, "k_list_hist(2)");
-    hipLaunchKernelGGL(k_threshold, dim3(S, nbatch), dim3(256), 0, stream, st, hist, 2, (uint32_t)H_L2, S, 0, c->d_flags,
-                       nullptr, gate ? 1 : 0, sp, cp);
-    SLIMDP_LAUNCHED(c, "k_threshold(2)");
-    hipLaunchKernelGGL((k_count<KPL, BPW>), wave_grid, dim3(BLOCK), 0, stream, c->n, c->d_tile_start, c->d_tile_seg, T, S,
-                       nbatch, st, cand_keys, cnt_cand, cnt_gt, keys_stride, cnt_sel, cnt_tie, gate);
-    SLIMDP_LAUNCHED(c, "k_count");
-    const dim3 scan_grid(c->n_chunks, nbatch);
-    hipLaunchKernelGGL(k_tile_scan<0>, scan_grid, dim3(1024), 0, stream, c->d_tile_seg, c->d_seg_first_tile, T, S, st, cnt_sel,
-                       cnt_tie, tie_pre, chunk_sum, out_off, chunk_sum + (size_t)nbatch * c->n_chunks, gate);
-    SLIMDP_LAUNCHED(c, "k_tile_scan(ties)");
-    hipLaunchKernelGGL(k_tile_scan<1>, scan_grid, dim3(1024), 0, stream, c->d_tile_seg, c->d_seg_first_tile, T, S, st, cnt_sel,
-                       cnt_tie, tie_pre, chunk_sum, out_off, chunk_sum + (size_t)nbatch * c->n_chunks, gate);
-    SLIMDP_LAUNCHED(c, "k_tile_scan(offsets)");
-    hipLaunchKernelGGL((k_emit<KPL, BPW>), wave_grid, dim3(BLOCK), 0, stream, c->n, c->d_tile_start, c->d_tile_seg,
-                       c->d_seg_first_tile, T, S, nbatch, st, gt_bits, cand_bits, cand_keys, keys_stride, tie_pre, out_off,
-                       out_idx, expected, pub_bits, excl_bits, (uint32_t)((c->n + 31) / 32), gate, chunk_sum,
-                       chunk_sum + (size_t)nbatch * c->n_chunks, c->n_chunks, c->d_flags);
-    SLIMDP_LAUNCHED(c, "k_emit");
-    return SLIMDP_OK;
 }
 
 template <class P> bool table_ok(P const* tab, uint32_t nw, bool allow_null_entries = false)
@@ -477,16 +439,14 @@ double pair_overflow_prob(double lambda)
 // words up to the first are taken without ranking (sure zone), only the words between the two
 // become candidates.  The exact rerun with every word a candidate catches a miss on either
 // side.  Returns an error code for impossible requests; *narrow is set when every segment
-// got a narrow candidate zone; *short_list when the zones are so narrow that the candidates
-// of n_workers draws fit the unordered list of the short-list path with room to spare and no
-// sub-tile is likely to see more of them than its pair slot holds (small segments have
-// relatively wide zones: twelve standard deviations of a small m are a large share of it).
+// got a narrow candidate zone; *short_list when no sub-tile is likely to see more candidates
+// than its pair slot holds (small segments have relatively wide zones: twelve standard
+// deviations of a small m are a large share of it).
 int explorer_init(slimdp_ctx* ctx, const char* who, const uint64_t* k_seg, const uint64_t* m_seg, uint32_t n_workers,
                   std::vector<SegInit>& init, uint64_t* M_out, bool* narrow, bool* short_list)
 {
     uint64_t M = 0;
-    bool all_narrow = true, all_short = true;
-    double expect = 0.0;           // candidates of one draw
+    bool all_narrow = true;
     double overflows = 0.0;        // expected number of sub-tiles of the request with more candidates than a pair slot holds
     init.resize(ctx->n_seg);
     for (uint32_t s = 0; s < ctx->n_seg; ++s) {
@@ -495,8 +455,8 @@ int explorer_init(slimdp_ctx* ctx, const char* who, const uint64_t* k_seg, const
             return fail(ctx, SLIMDP_ERR_OUT_OF_RANGE, "%s: segment %u: m=%llu exceeds the %llu parameters outside the core",
                         who, s, (unsigned long long)m_seg[s], (unsigned long long)(k_seg[s] > ns ? 0 : ns - k_seg[s]));
         const uint64_t m = m_seg[s];
+        SegInit in{(uint32_t)m, (uint32_t)M, 0u, 0u, 0u, 0u};
         M += m;
-        SegInit in{(uint32_t)m, 0u, 0u, 0u, 0u};
         if (m > 0) {
             const double avail = (double)(ns - k_seg[s]);
             const double slack = 6.0 * std::sqrt((double)m) + 32.0;
@@ -504,36 +464,27 @@ int explorer_init(slimdp_ctx* ctx, const char* who, const uint64_t* k_seg, const
             if (ctx->opt_force_fallback == 1) { hi = 0.25 * (double)m / avail; lo = 0.5 * hi; }     // too few candidates
             if (ctx->opt_force_fallback == 2) { hi = 2.0 * (double)m / avail; lo = 0.75 * hi; }     // sure zone too large
             uint64_t width = 1ull << 32;                     // number of distinct candidate words
-            if (hi >= 0.25) all_short = false;
-            expect += (hi - (lo > 0.0 ? lo : 0.0)) * avail;
             overflows += pair_overflow_prob((hi - (lo > 0.0 ? lo : 0.0)) * (double)SUB) * ((double)ns / SUB + 2.0) * n_workers;
-            if (hi >= 0.95) {
-                in.bound_m1 = 0xFFFFFFFFu;
-                all_narrow = false;
-            } else {
-                uint64_t B1 = (uint64_t)std::ceil(hi * 4294967296.0);
-                if (B1 < 1) B1 = 1;
-                if (B1 > (1ull << 32)) B1 = 1ull << 32;
-                in.bound_m1 = (uint32_t)(B1 - 1);
-                width = B1;
-                const uint64_t B0 = lo > 0.0 ? (uint64_t)std::floor(lo * 4294967296.0) : 0;
-                if (B0 >= 1 && B0 < B1) {                    // words 0 .. B0-1 are sure, B0 .. B1-1 candidates
-                    in.sure_m1 = (uint32_t)(B0 - 1);
-                    in.has_gt = 1;
-                    width = B1 - B0;
-                }
+            if (hi >= 0.95) all_narrow = false;
+            uint64_t B1 = hi < 1.0 ? (uint64_t)std::ceil(hi * 4294967296.0) : 1ull << 32;
+            if (B1 < 1) B1 = 1;
+            if (B1 > (1ull << 32)) B1 = 1ull << 32;
+            in.bound_m1 = (uint32_t)(B1 - 1);
+            width = B1;
+            const uint64_t B0 = lo > 0.0 ? (uint64_t)std::floor(lo * 4294967296.0) : 0;
+            if (B0 >= 1 && B0 < B1) {                        // words 0 .. B0-1 are sure, B0 .. B1-1 candidates
+                in.sure_m1 = (uint32_t)(B0 - 1);
+                in.has_gt = 1;
+                width = B1 - B0;
             }
-            uint32_t bitlen = 0;
-            while (bitlen < 33 && ((width - 1) >> bitlen) != 0) ++bitlen;
-            in.shift0 = bitlen > 12 ? bitlen - 12 : 0;
+            while (((width - 1) >> in.bits) != 0) ++in.bits;
         }
         init[s] = in;
     }
     *M_out = M;
     *narrow = all_narrow;
-    // an overflowing slot costs the exact rerun (about a thousand times the per-tile tail): taken only if that is unlikely
-    *short_list = all_narrow && all_short && !ctx->opt_per_tile_tail && (uint64_t)ctx->T * TILE <= 0xFFFFFFFFull &&
-                  1.25 * expect * (double)n_workers + 4096.0 <= (double)ctx->list_cap && overflows <= 1e-5;
+    // an overflowing slot costs the exact rerun (a thousand times the whole request): taken only if that is unlikely
+    *short_list = all_narrow && !ctx->opt_per_tile_tail && overflows <= 1e-5;
     return SLIMDP_OK;
 }
 
@@ -555,9 +506,7 @@ uint64_t slimdp_workspace_bytes(uint64_t n, uint32_t max_workers, uint32_t n_seg
     tmp.T = (uint32_t)count_tiles(n, n_seg, seg_off);
     tmp.keys_stride = align_up(n, TILE) + TILE;
     tmp.pair_stride = (uint64_t)tmp.T * SUBS * PAIR_SLOT;
-    tmp.n_chunks = (tmp.T + SCAN_CHUNK - 1) / SCAN_CHUNK;
-    tmp.list_cap = (uint64_t)tmp.maxW * (64ull * tmp.T + 8192ull);
-    if (tmp.list_cap > 0x40000000ull) tmp.list_cap = 0x40000000ull;
+    tmp.list_first = list_starts(n_seg, seg_off);
     Carver cv(nullptr);
     carve(&tmp, cv);
     return align_up(cv.pos, 256);
@@ -597,9 +546,7 @@ int slimdp_create(slimdp_ctx** out, uint64_t n, uint32_t max_workers, uint32_t n
     c->T = (uint32_t)c->tl.tile_seg.size();
     c->keys_stride = align_up(n, TILE) + TILE;
     c->pair_stride = (uint64_t)c->T * SUBS * PAIR_SLOT;
-    c->n_chunks = (c->T + SCAN_CHUNK - 1) / SCAN_CHUNK;
-    c->list_cap = (uint64_t)c->maxW * (64ull * c->T + 8192ull);
-    if (c->list_cap > 0x40000000ull) c->list_cap = 0x40000000ull;
+    c->list_first = list_starts(n_seg, seg_off);
     hipError_t e = hipGetDevice(&c->device);
     if (e != hipSuccess) { int rc = hip_fail(nullptr, e, "hipGetDevice (no usable GPU?)"); delete c; return rc; }
     hipDeviceProp_t prop;
@@ -617,12 +564,18 @@ int slimdp_create(slimdp_ctx** out, uint64_t n, uint32_t max_workers, uint32_t n
     }
     Carver cv(c->ws);
     carve(c, cv);
-    // tables are uploaded once; the copies are synchronous with respect to the host
-    e = hipMemcpy(c->d_tile_start, c->tl.tile_start.data(), (c->T + 1) * 4, hipMemcpyHostToDevice);
-    if (e == hipSuccess) e = hipMemcpy(c->d_tile_seg, c->tl.tile_seg.data(), c->T * 4, hipMemcpyHostToDevice);
-    if (e == hipSuccess) e = hipMemcpy(c->d_seg_first_tile, c->tl.seg_first_tile.data(), (n_seg + 1) * 4, hipMemcpyHostToDevice);
-    if (e == hipSuccess) e = hipMemset(c->d_flags, 0, 64 * 4);
-    if (e == hipSuccess) e = hipMemset(c->c_pred, 0xFF, (size_t)n_seg * 4);      // no prediction yet
+    // the tables, an empty prediction and the cleared flags, in one copy that is synchronous with respect to the host
+    {
+        const size_t words = (size_t)(c->d_flags + 64 - c->d_tile_start);
+        std::vector<uint32_t> up(words, 0u);
+        auto at = [&](const uint32_t* d) { return up.begin() + (d - c->d_tile_start); };
+        std::copy(c->tl.tile_start.begin(), c->tl.tile_start.end(), at(c->d_tile_start));
+        std::copy(c->tl.tile_seg.begin(), c->tl.tile_seg.end(), at(c->d_tile_seg));
+        std::copy(c->tl.seg_first_tile.begin(), c->tl.seg_first_tile.end(), at(c->d_seg_first_tile));
+        std::copy(c->list_first.begin(), c->list_first.end(), at(c->d_list_first));
+        std::fill_n(at(c->c_pred), n_seg, NONE);                              // no prediction yet
+        e = hipMemcpy(c->d_tile_start, up.data(), words * 4, hipMemcpyHostToDevice);
+    }
     if (e == hipSuccess) e = hipMemset(c->c_hist, 0, (size_t)n_seg * H_STRIDE * 4);
     if (e == hipSuccess) e = hipStreamCreateWithFlags(&c->side, hipStreamNonBlocking);      // default priority
     if (e == hipSuccess) e = hipEventCreateWithFlags(&c->ev_consumed, hipEventDisableTiming);
@@ -769,7 +722,7 @@ static int score_impl(slimdp_ctx* ctx, const float* w, const float* const* g, ui
                           &M, &narrow, &pairs) == SLIMDP_OK && narrow && M > 0) {
             rc = wait_for_side(ctx);         // the draw's buffers may still be read by work on the side stream
             if (rc) return rc;
-            rc = init_states(ctx, ctx->e_state, init, ctx->hint.n_workers, 0);
+            rc = init_states(ctx, ctx->e_state, init, ctx->hint.n_workers, false, ctx->stream);
             if (rc) return rc;
             pre.nw = ctx->hint.n_workers; pre.worker0 = ctx->hint.worker0; pre.n_seg = ctx->n_seg;
             pre.states = ctx->e_state; pre.sure_bits = ctx->e_sure_bits; pre.cand_bits = ctx->e_cand_bits;
@@ -1061,7 +1014,6 @@ int slimdp_select_core_static(const float* score, uint64_t n, uint64_t k, uint32
     tmp.seg_off.assign(so, so + 2);
     tmp.T = (uint32_t)count_tiles(n, 1, so);
     tmp.keys_stride = align_up(n, TILE) + TILE;
-    tmp.n_chunks = (tmp.T + SCAN_CHUNK - 1) / SCAN_CHUNK;
     Carver cv(static_cast<char*>(sdv.ptr));
     carve_core(&tmp, cv);
     if (cv.pos > SLIMDP_STATIC_SCRATCH_BYTES)
@@ -1143,16 +1095,8 @@ int slimdp_sample_explore(slimdp_ctx* ctx, const uint32_t* core_bits, const uint
         rc = wait_for_side(ctx);         // an announced draw, or an earlier asynchronous request: their buffers are theirs until done
         if (rc) return rc;
     }
-    rc = init_states(ctx, ctx->e_state, init, B, 0, st);
+    rc = init_states(ctx, ctx->e_state, init, B, true, st);
     if (rc) return rc;
-    {   // histograms, rerun flag, list counters
-        FillJobs fj{};
-        fj.p[0] = ctx->e_hist; fj.count[0] = (uint64_t)B * S * H_STRIDE;
-        fj.p[1] = ctx->d_flags; fj.count[1] = 1;
-        fj.p[2] = ctx->e_list_count; fj.count[2] = 2;
-        hipLaunchKernelGGL(k_fill_multi, dim3(fill_grid(fj.count[0])), dim3(256), 0, st, fj);
-        SLIMDP_LAUNCHED(ctx, "k_fill_multi");
-    }
     const uint32_t P = persistent_blocks(ctx, 8, B);
     const uint32_t n_words = (uint32_t)((ctx->n + 31) / 32);
     const PhiloxKey pk{(uint32_t)ctx->seed, (uint32_t)(ctx->seed >> 32), (uint32_t)iteration, (uint32_t)(iteration >> 32)};
@@ -1172,71 +1116,40 @@ int slimdp_sample_explore(slimdp_ctx* ctx, const uint32_t* core_bits, const uint
                                (PAIRS) ? ctx->pair_stride : ctx->keys_stride, worker0, pk);                              \
         SLIMDP_LAUNCHED(ctx, "k_explore_keys");                                                                          \
     } while (0)
+    const ExploreLists lists{ctx->e_list, ctx->e_list_count, ctx->d_list_first, ctx->list_first[S]};
     if (short_list) {
-        // the few candidates go through one unordered list; any irregularity raises the flag that
-        // switches these kernels off and the exact rerun below on
         constexpr int SBPW = 8;
         if (!cached) LAUNCH_DRAW(1);
-        hipLaunchKernelGGL(k_sure_count<SBPW>, dim3((T + 3) / 4, (B + SBPW - 1) / SBPW), dim3(BLOCK), 0, st, core_bits,
-                           n_words, ctx->n, ctx->d_tile_start, ctx->d_tile_seg, T, S, B, ctx->e_sure_bits, ctx->e_cnt_sel);
-        SLIMDP_LAUNCHED(ctx, "k_sure_count");
-        hipLaunchKernelGGL(k_seg_sum, dim3(S, B), dim3(1024), 0, st, ctx->e_cnt_sel, 1u, ctx->d_seg_first_tile, T, S,
-                           ctx->e_nsure);
-        SLIMDP_LAUNCHED(ctx, "k_seg_sum");
-        hipLaunchKernelGGL(k_cand_gather, dim3((uint32_t)(((uint64_t)B * T + 1023) / 1024)), dim3(1024), 0, st,
-                           core_bits, ctx->n, ctx->d_tile_start, ctx->d_tile_seg, T, S, B, ctx->e_pair_keys, ctx->pair_stride,
-                           ctx->e_cnt_cand, ctx->e_list, ctx->e_list_count, (uint32_t)ctx->list_cap, ctx->d_flags);
-        SLIMDP_LAUNCHED(ctx, "k_cand_gather");
-        const uint32_t hoff[3] = {H_L0, H_L1, H_L2};
-        for (int level = 0; level < 3; ++level) {
-            hipLaunchKernelGGL(k_short_hist, dim3(512), dim3(256), 0, st, ctx->e_list, ctx->e_list_count,
-                               (uint32_t)ctx->list_cap, ctx->e_state, ctx->e_hist, hoff[level], level, ctx->d_flags);
-            SLIMDP_LAUNCHED(ctx, "k_short_hist");
-            hipLaunchKernelGGL(k_threshold, dim3(S, B), dim3(256), 0, st, ctx->e_state, ctx->e_hist, level, hoff[level],
-                               S, level == 0 ? 1 : 0, ctx->d_flags, ctx->e_nsure, 1, SpecTau{nullptr, nullptr, nullptr}, CorePred{nullptr, nullptr, nullptr, 0});
-            SLIMDP_LAUNCHED(ctx, "k_threshold");
-        }
-        hipLaunchKernelGGL(k_short_mark, dim3(512), dim3(256), 0, st, ctx->e_list, ctx->e_list_count,
-                           (uint32_t)ctx->list_cap, ctx->e_state, T, ctx->e_sure_bits, ctx->e_cnt_sel, ctx->e_tie_list,
-                           ctx->e_list_count + 1, ctx->d_flags);
-        SLIMDP_LAUNCHED(ctx, "k_short_mark");
-        hipLaunchKernelGGL(k_short_ties, dim3(1), dim3(1024), 0, st, ctx->e_list, ctx->e_state, T, ctx->e_sure_bits,
-                           ctx->e_cnt_sel, ctx->e_tie_list, ctx->e_list_count + 1, ctx->d_flags);
-        SLIMDP_LAUNCHED(ctx, "k_short_ties");
-        hipLaunchKernelGGL(k_chunk_scan, dim3(ctx->n_chunks, B), dim3(1024), 0, st, T, ctx->e_cnt_sel, off_tab,
-                           ctx->e_chunk_sum, ctx->d_flags);
-        SLIMDP_LAUNCHED(ctx, "k_chunk_scan");
-        constexpr int EBPW = 4;
-        hipLaunchKernelGGL(k_emit_bits<EBPW>, dim3((T + 3) / 4, (B + EBPW - 1) / EBPW), dim3(BLOCK), 0, st, core_bits,
-                           n_words, ctx->n, ctx->d_tile_start, ctx->d_tile_seg, T, S, B, ctx->e_sure_bits, ctx->e_chunk_sum,
-                           ctx->n_chunks, off_tab, idx_tab, (uint32_t)M, ctx->d_flags);
-        SLIMDP_LAUNCHED(ctx, "k_emit_bits");
+        const uint32_t sure_blocks = ((T + 3) / 4) * ((B + SBPW - 1) / SBPW);
+        const uint32_t gather_blocks = B * ((T + 63) / 64);
+        hipLaunchKernelGGL(k_explore_collect<SBPW>, dim3(sure_blocks + gather_blocks), dim3(BLOCK), 0, st, core_bits, n_words, ctx->n,
+                           ctx->d_tile_start, ctx->d_tile_seg, T, S, B, sure_blocks, ctx->e_sure_bits, ctx->e_cnt_sel,
+                           ctx->e_pair_keys, ctx->pair_stride, ctx->e_cnt_cand, lists, ctx->d_flags);
+        SLIMDP_LAUNCHED(ctx, "k_explore_collect");
     } else {
-        // zones that are not narrow: the per-tile tail that the core selection uses
         rc = ensure_wide_keys(ctx);
         if (rc) return rc;
         if (!cached) LAUNCH_DRAW(0);
-        hipLaunchKernelGGL(k_explore_filter, dim3(P, B), dim3(BLOCK), 0, st, core_bits, ctx->n, ctx->d_tile_start,
-                           ctx->d_tile_seg, T, S, ctx->e_state, ctx->e_hist, ctx->e_sure_bits, ctx->e_cnt_gt, ctx->e_cand_bits,
-                           ctx->e_cand_keys, ctx->e_cnt_cand, ctx->keys_stride, n_words);
-        SLIMDP_LAUNCHED(ctx, "k_explore_filter");
-        hipLaunchKernelGGL(k_seg_sum, dim3(S, B), dim3(1024), 0, st, ctx->e_cnt_gt, (uint32_t)SUBS, ctx->d_seg_first_tile,
-                           T, S, ctx->e_nsure);
-        SLIMDP_LAUNCHED(ctx, "k_seg_sum");
-        hipLaunchKernelGGL(k_threshold, dim3(S, B), dim3(256), 0, st, ctx->e_state, ctx->e_hist, 0, (uint32_t)H_L0, S, 1,
-                           ctx->d_flags, ctx->e_nsure, 0, SpecTau{nullptr, nullptr, nullptr}, CorePred{nullptr, nullptr, nullptr, 0});
-        SLIMDP_LAUNCHED(ctx, "k_threshold(0)");
-        rc = finish_selection<EXPL_KPL, 4>(ctx, B, ctx->e_state, ctx->e_hist, ctx->e_sure_bits, ctx->e_cand_bits,
-                              ctx->e_cand_keys, ctx->e_cnt_gt, ctx->e_cnt_cand, ctx->e_cnt_sel, ctx->e_cnt_tie, ctx->e_tie_pre,
-                              ctx->keys_stride, false, off_tab, idx_tab, (uint32_t)M, nullptr, core_bits, ctx->d_flags,
-                              ctx->e_chunk_sum, SpecTau{nullptr, nullptr, nullptr}, CorePred{nullptr, nullptr, nullptr, 0}, st);
-        if (rc) return rc;
+        hipLaunchKernelGGL(k_explore_collect_wide, dim3(P, B), dim3(BLOCK), 0, st, core_bits, n_words, ctx->n, ctx->d_tile_start,
+                           ctx->d_tile_seg, T, S, ctx->e_sure_bits, ctx->e_cnt_sel, ctx->e_cand_bits, ctx->e_cand_keys,
+                           ctx->keys_stride, lists, ctx->d_flags);
+        SLIMDP_LAUNCHED(ctx, "k_explore_collect_wide");
     }
+    // a block of 1024 threads has the shorter chain; small blocks where there are many more of them than run at a time
+    if ((uint64_t)S * B <= 4ull * ctx->cus)
+        hipLaunchKernelGGL(k_explore_select<1024>, dim3(S, B), dim3(1024), 0, st, ctx->e_state, ctx->d_seg_first_tile, T, S, lists,
+                           ctx->e_cnt_sel, ctx->e_sure_bits, off_tab, ctx->d_flags);
+    else
+        hipLaunchKernelGGL(k_explore_select<256>, dim3(S, B), dim3(256), 0, st, ctx->e_state, ctx->d_seg_first_tile, T, S, lists,
+                           ctx->e_cnt_sel, ctx->e_sure_bits, off_tab, ctx->d_flags);
+    SLIMDP_LAUNCHED(ctx, "k_explore_select");
+    constexpr int EBPW = 4;
+    const uint32_t emit_blocks = (T + 15) / 16 > (uint32_t)EBPW ? (T + 15) / 16 : (uint32_t)EBPW;
+    hipLaunchKernelGGL(k_explore_emit<EBPW>, dim3(emit_blocks, (B + EBPW - 1) / EBPW), dim3(1024), 0, st, core_bits, n_words, ctx->n,
+                       ctx->d_tile_start, ctx->d_tile_seg, ctx->d_seg_first_tile, T, S, B, ctx->e_state, worker0, pk,
+                       ctx->e_sure_bits, off_tab, idx_tab, (uint32_t)M, ctx->d_flags);
+    SLIMDP_LAUNCHED(ctx, "k_explore_emit");
 #undef LAUNCH_DRAW
-    // zones missed (flag up): the whole request again, exactly, from the definition; idle otherwise
-    hipLaunchKernelGGL(k_explore_exact, dim3(1, B), dim3(1024), 0, st, core_bits, ctx->n, ctx->d_tile_start,
-                       ctx->d_seg_first_tile, T, S, ctx->e_state, worker0, pk, idx_tab, off_tab, (uint32_t)M, ctx->d_flags);
-    SLIMDP_LAUNCHED(ctx, "k_explore_exact");
     if (async) {
         // a free slot, else the oldest one (the main stream then waits for that request first)
         int slot = -1;
@@ -1286,7 +1199,7 @@ int slimdp_explore_hint(slimdp_ctx* ctx, const uint64_t* k_seg, uint32_t worker0
     // (the event is recorded here, not after every slimdp_sample_explore: an event on a stream costs a gap between kernels)
     SLIMDP_HIP(ctx, hipEventRecord(ctx->ev_consumed, ctx->stream));
     SLIMDP_HIP(ctx, hipStreamWaitEvent(ctx->side, ctx->ev_consumed, 0));
-    rc = init_states(ctx, ctx->e_draw_state, init, n_workers, 0, ctx->side);
+    rc = init_states(ctx, ctx->e_draw_state, init, n_workers, false, ctx->side);
     if (rc) return rc;
     // few waves keep the arithmetic units busy; the wave slots stay with the kernels of the main stream
     const uint32_t P = persistent_blocks(ctx, (uint32_t)ctx->opt_side_blocks, n_workers);

@@ -25,24 +25,18 @@ constexpr uint32_t CORE_SHIFT0 = 19, CORE_NB0 = 8192, CORE_SHIFT1 = 7, CORE_NB1 
 struct PtrTab { const void* p[MAXW]; };           // host pointer tables travel as kernel arguments
 struct MutPtrTab { void* p[MAXW]; };
 
-// Selection state of one (batch, segment): the radix descent towards the threshold key.
+// Explorer request of one (batch, segment).  Words r <= sure_m1 (if has_gt) are taken unless in the core, words up to
+// bound_m1 are candidates with key = bound_m1 - r.
 struct SegState {
     uint32_t need0;     // number of elements to select
-    uint32_t need;      // of those, how many still come from the keys matching `prefix`
-    uint32_t prefix;    // keys still in play satisfy (key >> shift[level-1]) == prefix
-    uint32_t none;      // 1: nothing is selected here
-    uint32_t tau;       // threshold key once all levels are done
-    uint32_t quota;     // how many keys == tau are taken, lowest index first
-    uint32_t bound_m1;  // explorer only: candidates are words r <= bound_m1, key = bound_m1 - r
-    uint32_t tie_all;   // 1: the quota covers every key equal to tau
-    uint32_t shift[3];  // digit of level l = (key >> shift[l]) & (nbins[l] - 1); level 0 unmasked
-    uint32_t nbins[3];
-    uint32_t sure_m1;   // explorer: words r <= sure_m1 are taken without looking at their rank (if has_gt)
-    uint32_t has_gt;    // a bitmap of certainly selected parameters exists (core: always; explorer: narrow zone)
+    uint32_t out_base;  // elements of the segments before this one
+    uint32_t bound_m1, sure_m1, has_gt;
+    uint32_t bits;      // candidate keys are below 2^bits
+    uint32_t pad[2];
 };
-static_assert(sizeof(SegState) == 64, "SegState layout");
+static_assert(sizeof(SegState) == 32, "SegState layout");
 
-struct SegInit { uint32_t need; uint32_t bound_m1; uint32_t shift0; uint32_t sure_m1; uint32_t has_gt; };
+struct SegInit { uint32_t need, out_base, bound_m1, sure_m1, has_gt, bits; };
 constexpr int INIT_CHUNK = 128;
 struct SegInitChunk { SegInit s[INIT_CHUNK]; };
 

@@ -1,17 +1,10 @@
 // Kernels of libslimdp (gfx950).  Included only by slimdp.hip.
 //
-// Shared structure: the index range is cut into tiles of <= 4096 parameters (never across
-// a segment).  Exact "top-need by (key desc, index asc)" selection, used both for the core
-// (keys = score bits) and for the explorer (keys = bound - Philox word over the non-core
-// parameters), is a three-level radix descent:
-//   level 0 histogram over every key (fused into the kernel that produces the keys),
-//   -> keys in the threshold bin become "candidates": a per-tile bitmap plus the candidate
-//      keys of each 1024-parameter sub-tile compacted in index order at
-//      cand_keys[tile_start + 1024*s ...] with their number in cnt_cand[4*tile + s]
-//      (a sub-tile is what one wave handles on its own, without block barriers),
-//   levels 1 and 2 histogram only candidates, giving the threshold key tau and the number
-//   of keys == tau to take (quota, lowest index first),
-//   count per tile -> scan over tiles -> ordered emission of the ascending index list.
+// Shared structure: the index range is cut into tiles of <= 4096 parameters (never across a segment).  The core
+// selection is in slimdp_core.h, the explorer's (what follows the draw) in slimdp_explore.h.  In both, the parameters
+// in doubt ("candidates") are a per-tile bitmap plus the keys of each 1024-parameter sub-tile compacted in index
+// order at cand_keys[tile_start + 1024*s ...] with their number in cnt_cand[4*tile + s] (a sub-tile is what one wave
+// handles on its own, without block barriers).
 #pragma once
 #include "slimdp_device.h"
 
@@ -51,46 +44,6 @@ __global__ __launch_bounds__(256) void k_fill_u32(uint32_t* __restrict__ p, uint
 {
     for (uint64_t i = (uint64_t)blockIdx.x * 256 + threadIdx.x; i < count; i += (uint64_t)gridDim.x * 256)
         p[i] = v;
-}
-
-// Writes the selection state of segments [seg0, seg0+count) for every batch.
-// core != 0: fixed score-bit levels; else explorer levels derived from (bound_m1, shift0).
-// Several fills in one launch (a launch costs more than a small fill).
-struct FillJobs { uint32_t* p[4]; uint64_t count[4]; uint32_t v[4]; };
-__global__ __launch_bounds__(256) void k_fill_multi(FillJobs jobs)
-{
-#pragma unroll
-    for (int j = 0; j < 4; ++j)
-        for (uint64_t i = (uint64_t)blockIdx.x * 256 + threadIdx.x; i < jobs.count[j]; i += (uint64_t)gridDim.x * 256)
-            jobs.p[j][i] = jobs.v[j];
-}
-
-__global__ __launch_bounds__(256) void k_init_state(SegState* __restrict__ st, SegInitChunk chunk, uint32_t seg0,
-                                                    uint32_t count, uint32_t n_seg, uint32_t nbatch, int core)
-{
-    const uint32_t x = blockIdx.x * 256 + threadIdx.x;
-    if (x >= count * nbatch) return;
-    const uint32_t b = x / count, j = x % count;
-    const SegInit in = chunk.s[j];
-    SegState s;
-    s.need0 = in.need; s.need = in.need; s.prefix = 0; s.none = (in.need == 0) ? 1u : 0u;
-    s.tau = NONE; s.quota = 0; s.bound_m1 = in.bound_m1; s.tie_all = 0;
-    s.sure_m1 = in.sure_m1; s.has_gt = core ? 1u : in.has_gt;
-    if (core) {
-        s.shift[0] = CORE_SHIFT0; s.nbins[0] = CORE_NB0;
-        s.shift[1] = CORE_SHIFT1; s.nbins[1] = CORE_NB1;
-        s.shift[2] = 0;           s.nbins[2] = CORE_NB2;
-    } else {
-        // explorer keys are bound_m1 - r for the words sure_m1 < r <= bound_m1 (all r <= bound_m1 without a sure zone)
-        const uint32_t width_m1 = in.has_gt ? in.bound_m1 - in.sure_m1 - 1u : in.bound_m1;
-        const uint32_t sh0 = in.shift0;
-        const uint32_t bits1 = sh0 < 12u ? sh0 : 12u;
-        const uint32_t sh1 = sh0 - bits1;
-        s.shift[0] = sh0; s.nbins[0] = (width_m1 >> sh0) + 1u;
-        s.shift[1] = sh1; s.nbins[1] = 1u << bits1;
-        s.shift[2] = 0;   s.nbins[2] = 1u << sh1;
-    }
-    st[(size_t)b * n_seg + seg0 + j] = s;
 }
 
 // ---------------------------------------------------------------------------------------
@@ -873,117 +826,11 @@ __global__ __launch_bounds__(1024) void k_sample_bound(const uint32_t* __restric
     }
 }
 
-// ---------------------------------------------------------------------------------------
-// Threshold step of one radix level: walk the bins from the largest digit down until
-// `need` keys are covered.  grid (n_seg, nbatch), 256 threads.
-// mode 0: plain.  mode 1: explorer level 0 with zones: a miss on either side raises the
-// rerun flag (flags[0]).  gate != 0: return at once if the flag is already up (the exact
-// rerun k_explore_exact follows and overwrites everything); the kernels of the per-tile tail
-// take the flag word as `gate` the same way (nullptr: always run).
-// ---------------------------------------------------------------------------------------
-// At the last level of a core selection with speculative packing on (st.next != nullptr):
-// fail[seg] tells whether the threshold fell below what the scoring pass captured (cur), and
-// next[seg] becomes the capture bound of the next scoring pass: the new threshold less
-// 2^17 units in the last place (0.8 % to 1.6 %).
+// With speculative packing on (next != nullptr) the last step of a core selection tells per segment whether the threshold
+// fell below what the scoring pass captured (fail, against cur), and next becomes the capture bound of the next scoring
+// pass: the new threshold less 2^17 units in the last place (0.8 % to 1.6 %).
 struct SpecTau { const uint32_t* cur; uint32_t* next; uint32_t* fail; };
-// Core selection whose scoring pass already sorted every whole tile against a PREDICTED level-0 threshold bin
-// (used[seg]: what the scoring pass took, normally pred[seg], the bin of the previous threshold): level 0 tells per
-// segment whether the prediction held
-// (skip[seg] = 1: the candidate pass has nothing left to do for whole tiles), the last level records the bin
-// of the new threshold as the next prediction.  check = 0: the scoring pass did not classify.
-struct CorePred { uint32_t* pred; uint32_t* skip; const uint32_t* used; int check; };
 constexpr uint32_t SPEC_MARGIN = 1u << 17;
-
-__global__ __launch_bounds__(256) void k_threshold(SegState* __restrict__ states, uint32_t* __restrict__ hist,
-                                                   int level, uint32_t hist_off, uint32_t n_seg, int mode,
-                                                   uint32_t* __restrict__ flags, const uint32_t* __restrict__ nsure, int gate,
-                                                   SpecTau sp, CorePred cp)
-{
-    __shared__ uint32_t wtot[4];
-    __shared__ uint32_t sh_bcast[2];
-    if (gate) {          // other blocks of this launch may raise the flag: one read per block
-        if (threadIdx.x == 0) sh_bcast[0] = flags[0];
-        __syncthreads();
-        if (sh_bcast[0] != 0) return;
-    }
-    const uint32_t seg = blockIdx.x, b = blockIdx.y;
-    SegState* st = &states[(size_t)b * n_seg + seg];
-    const uint32_t* hp = hist + ((size_t)b * n_seg + seg) * H_STRIDE + hist_off;
-    if (mode == 1 && st->has_gt) {
-        // the certainly taken ones (word below the sure bound, outside the core) come off the demand
-        const uint32_t ns = nsure[(size_t)b * n_seg + seg];
-        const uint32_t n0 = st->need0;
-        __syncthreads();
-        if (ns > n0) {                        // the sure zone alone is already too large: exact rerun
-            if (threadIdx.x == 0) atomicOr(&flags[0], 1u);
-            return;
-        }
-        if (threadIdx.x == 0) st->need = n0 - ns;
-        __syncthreads();
-    }
-    const uint32_t need = st->need, none = st->none, nb = st->nbins[level];
-    const uint32_t prefix = st->prefix;
-    const uint32_t bits = (level == 0) ? 0u : (st->shift[level - 1] - st->shift[level]);
-    __syncthreads();
-    if (none || need == 0) {
-        if (threadIdx.x == 0) {
-            st->none = 1; st->need = 0; st->tau = NONE; st->quota = 0;
-            if (level == 2 && sp.next) { sp.fail[seg] = 0; sp.next[seg] = NONE; }      // nothing selected, nothing to capture
-            if (cp.skip && level == 0) cp.skip[seg] = 0;
-            if (cp.pred && level == 2) cp.pred[seg] = NONE;
-        }
-        return;
-    }
-    const uint32_t C = (nb + 255u) / 256u;
-    const uint32_t p0 = threadIdx.x * C;
-    uint32_t sum = 0;
-    for (uint32_t p = p0; p < p0 + C && p < nb; ++p) sum += hp[nb - 1u - p];
-    uint32_t total;
-    const uint32_t excl = block_excl_scan<4>(sum, wtot, total);
-    if (total < need) {
-        if (threadIdx.x == 0) {
-            if (mode == 1) atomicOr(&flags[0], 1u);                    // too few candidates: exact rerun
-            else { atomicOr(&flags[1], 2u); st->none = 1; st->need = 0; st->tau = NONE; st->quota = 0; }
-            if (cp.skip && level == 0) cp.skip[seg] = 0;
-        }
-        return;
-    }
-    if (excl < need && need <= excl + sum) {
-        uint32_t run = excl;
-        for (uint32_t p = p0; p < p0 + C && p < nb; ++p) {
-            const uint32_t bin = nb - 1u - p;
-            const uint32_t cnt = hp[bin];
-            if (run + cnt >= need) {
-                const uint32_t np = (level == 0) ? bin : ((prefix << bits) | bin);
-                st->prefix = np;
-                st->need = need - run;
-                if (cp.skip && level == 0) {
-                    const uint32_t ok = (cp.check && cp.used[seg] == np) ? 1u : 0u;
-                    cp.skip[seg] = ok;
-                    sh_bcast[1] = ok;
-                }
-                if (cp.pred && level == 2) cp.pred[seg] = np >> CORE_SHIFT0;
-                if (level == 2) {
-                    st->tau = np; st->quota = need - run; st->tie_all = (need - run == cnt) ? 1u : 0u;
-                    if (sp.next) {
-                        sp.fail[seg] = (np < sp.cur[seg]) ? 1u : 0u;
-                        sp.next[seg] = np > SPEC_MARGIN ? np - SPEC_MARGIN : 0u;
-                    }
-                }
-                break;
-            }
-            run += cnt;
-        }
-    }
-    if (cp.skip && level == 0 && cp.check) {
-        // the scoring pass has already added the level-1 digits of ITS candidates: if they belong to another bin they go
-        __syncthreads();
-        if (sh_bcast[1] == 0) {
-            uint32_t* h1 = hist + ((size_t)b * n_seg + seg) * H_STRIDE + H_L1;
-            for (uint32_t x = threadIdx.x; x < CORE_NB1; x += 256) h1[x] = 0;
-        }
-    }
-}
 
 // Stand-alone draw over every (worker, tile); each wave owns one sub-tile of the block's
 // tiles.  grid (blocks, n_workers).
@@ -1056,7 +903,7 @@ __device__ __forceinline__ void load_sublists(const uint32_t* __restrict__ keys_
     for (int i = 0; i < KPL; ++i) kv[i] = p[16 * i];
 }
 
-constexpr int EXPL_KPL = 2, CORE_KPL = 4;
+constexpr int CORE_KPL = 4;
 
 // Bits [i0, i0 + 64) of a bitmap over all n parameters (i0 need not be word aligned).
 __device__ __forceinline__ void bitmap_window(const uint32_t* __restrict__ bits, uint32_t n_words, uint32_t i0, uint32_t out[2])
@@ -1067,821 +914,6 @@ __device__ __forceinline__ void bitmap_window(const uint32_t* __restrict__ bits,
     const uint32_t a2 = (sh && wi + 2 < n_words) ? bits[wi + 2] : 0u;
     out[0] = sh ? ((a0 >> sh) | (a1 << (32u - sh))) : a0;
     out[1] = sh ? ((a1 >> sh) | (a2 << (32u - sh))) : a1;
-}
-
-// The draw does not know the core; this pass applies it.  Per (worker, tile), one wave:
-//   sure zone: counts the sure parameters outside the core per sub-tile (cnt_gt; k_seg_sum
-//     adds them up per segment); the bitmap itself stays as drawn, the emission masks it again;
-//   candidate zone: candidates inside the core are dropped (bitmap bit cleared, the sub-tile's
-//     key list closed up in place, its count lowered); the remaining keys feed the level-0
-//     histogram.
-// grid (blocks, n_workers), persistent so that the histogram stays in LDS.
-__global__ __launch_bounds__(BLOCK) void k_explore_filter(const uint32_t* __restrict__ core_bits, uint64_t n,
-                                                          const uint32_t* __restrict__ tile_start,
-                                                          const uint32_t* __restrict__ tile_seg, uint32_t T,
-                                                          uint32_t n_seg, const SegState* __restrict__ states,
-                                                          uint32_t* __restrict__ hist, const uint32_t* __restrict__ sure_bits,
-                                                          uint32_t* __restrict__ cnt_gt,
-                                                          uint32_t* __restrict__ cand_bits, uint32_t* __restrict__ cand_keys,
-                                                          uint32_t* __restrict__ cnt_cand, uint64_t keys_stride,
-                                                          uint32_t n_words)
-{
-    __shared__ uint32_t h[4096];
-    __shared__ uint32_t kl[4][SUB];
-    const uint32_t b = blockIdx.y, lane = lane_id(), wid = threadIdx.x >> 6;
-    for (uint32_t x = threadIdx.x; x < 4096; x += BLOCK) h[x] = 0;
-    __syncthreads();
-    const uint32_t t0 = (uint32_t)((uint64_t)T * blockIdx.x / gridDim.x);
-    const uint32_t t1 = (uint32_t)((uint64_t)T * (blockIdx.x + 1) / gridDim.x);
-    if (t0 >= t1) return;
-    // one segment per block range: histogram in LDS; otherwise straight to global memory
-    const uint32_t seg_first = (n_seg == 1) ? 0u : tile_seg[t0];
-    const bool one_seg = (n_seg == 1) || seg_first == tile_seg[t1 - 1];
-    const uint32_t hist_off = H_L0;
-    uint32_t* klw = kl[wid];
-    for (uint32_t t = t0 + wid; t < t1; t += 4) {
-        const TileRef tr = tile_ref(t, n_seg, n, tile_start, tile_seg);
-        const SegState* st = &states[(size_t)b * n_seg + tr.seg];
-        const size_t bt = (size_t)b * T + t;
-        // everything this tile needs is requested here, before any of it is used
-        const uint2 s2 = *reinterpret_cast<const uint2*>(sure_bits + bt * TILE_WORDS + 2 * lane);
-        const uint2 c2 = *reinterpret_cast<const uint2*>(cand_bits + bt * TILE_WORDS + 2 * lane);
-        const uint32_t cnt = cnt_cand[bt * SUBS + (lane >> 4)];
-        uint32_t kw[2];
-        bitmap_window(core_bits, n_words, tr.start + lane * 64u, kw);
-        const uint32_t need0 = st->need0, shift0 = st->shift[0], has_sure = st->has_gt;
-        {
-            uint32_t g = (has_sure && need0) ? __popc(s2.x & ~kw[0]) + __popc(s2.y & ~kw[1]) : 0u;
-            g += __shfl_xor(g, 1, 64); g += __shfl_xor(g, 2, 64); g += __shfl_xor(g, 4, 64); g += __shfl_xor(g, 8, 64);
-            if ((lane & 15u) == 0) cnt_gt[bt * SUBS + (lane >> 4)] = g;
-        }
-        if (need0 == 0) continue;
-        const uint32_t cw[2] = {c2.x, c2.y};
-        if (__ballot((cw[0] | cw[1]) != 0u) == 0ull) continue;
-        const uint32_t nw[2] = {cw[0] & ~kw[0], cw[1] & ~kw[1]};
-        const uint32_t oldc = __popc(cw[0]) + __popc(cw[1]), newc = __popc(nw[0]) + __popc(nw[1]);
-        const uint32_t oi = wave_incl_scan(oldc), ni = wave_incl_scan(newc);
-        const uint32_t og0 = __shfl(oi - oldc, (int)(lane & ~15u), 64), ng0 = __shfl(ni - newc, (int)(lane & ~15u), 64);
-        uint32_t jo = oi - oldc - og0, jn = ni - newc - ng0;        // places in the sub-tile's old and new key list
-        uint32_t* keys = cand_keys + (size_t)b * keys_stride + tr.start;
-        uint32_t* hg = hist + ((size_t)b * n_seg + tr.seg) * H_STRIDE + hist_off;
-#pragma unroll 1
-        for (uint32_t s = 0; s < (uint32_t)SUBS; ++s) {
-            const uint32_t c_s = __shfl(cnt, (int)(16u * s), 64);
-            if (c_s == 0) continue;
-            const bool mine = (lane >> 4) == s;
-            const bool close_up = __ballot(mine && oldc != newc) != 0ull;
-            uint32_t* ks = keys + s * SUB;
-            for (uint32_t j = lane; j < c_s; j += 64) klw[j] = ks[j];   // the whole old list, before any of it is overwritten
-            wave_sync();
-            if (mine) {
-#pragma unroll
-                for (int hh = 0; hh < 2; ++hh) {
-                    uint32_t m = cw[hh];
-                    while (m) {
-                        const uint32_t p = __ffs(m) - 1;
-                        m &= m - 1;
-                        const uint32_t key = klw[jo++];
-                        if ((kw[hh] >> p) & 1u) continue;
-                        if (close_up) ks[jn] = key;
-                        ++jn;
-                        if (one_seg) atomicAdd(&h[key >> shift0], 1u);
-                        else atomicAdd(&hg[key >> shift0], 1u);
-                    }
-                }
-            }
-            wave_sync();
-            if (close_up && lane == 16u * s + 15u) cnt_cand[bt * SUBS + s] = ni - ng0;
-        }
-        if (__ballot(oldc != newc) != 0ull)
-            *reinterpret_cast<uint2*>(cand_bits + bt * TILE_WORDS + 2 * lane) = make_uint2(nw[0], nw[1]);
-    }
-    __syncthreads();
-    if (one_seg) flush_hist(h, 4096, hist + ((size_t)b * n_seg + seg_first) * H_STRIDE + hist_off);
-}
-
-// =======================================================================================
-// Explorer, exact rerun.  When the zones of a draw missed (flags[0] raised; once in about
-// 10^9 draws, or forced by a test switch) this kernel redoes the whole request from the
-// definition, slowly and with no assumption: per worker one block walks every segment,
-// finds the need-th smallest Philox word among the parameters outside the core by a
-// three-pass radix descent over ALL of them (11 + 11 + 10 bits, words recomputed in every
-// pass), then emits tile by tile in index order, ties at the threshold word going to the
-// lowest indices.  grid (1, n_workers), 1024 threads; returns at once while the flag is down.
-// =======================================================================================
-__device__ __forceinline__ uint32_t explore_word(uint32_t i, uint32_t worker, PhiloxKey pk)
-{
-    uint32_t r[4];
-    philox4x32_10(i >> 2, worker, pk.it_lo, pk.it_hi, pk.seed_lo, pk.seed_hi, r);
-    const uint32_t c = i & 3u;
-    return c == 0 ? r[0] : c == 1 ? r[1] : c == 2 ? r[2] : r[3];
-}
-
-__global__ __launch_bounds__(1024) void k_explore_exact(const uint32_t* __restrict__ core_bits, uint64_t n,
-                                                        const uint32_t* __restrict__ tile_start,
-                                                        const uint32_t* __restrict__ seg_first_tile, uint32_t T, uint32_t n_seg,
-                                                        const SegState* __restrict__ states, uint32_t worker0, PhiloxKey pk,
-                                                        MutPtrTab out_idx, MutPtrTab out_off, uint32_t expected,
-                                                        uint32_t* __restrict__ flags)
-{
-    constexpr uint32_t NBIN = 2048;
-    __shared__ uint32_t h[NBIN];
-    __shared__ uint32_t wtot[16];
-    __shared__ uint32_t sh[4];
-    if (flags[0] == 0) return;                       // nobody raises the flag while this kernel runs
-    const uint32_t b = blockIdx.y, worker = worker0 + b, tid = threadIdx.x;
-    uint32_t* out = static_cast<uint32_t*>(out_idx.p[b]);
-    uint32_t* off = static_cast<uint32_t*>(out_off.p[b]);
-    uint32_t run = 0;                                // indices emitted so far (uniform)
-    for (uint32_t seg = 0; seg < n_seg; ++seg) {
-        const uint32_t f0 = seg_first_tile[seg], f1 = seg_first_tile[seg + 1];
-        uint32_t need = states[(size_t)b * n_seg + seg].need0;
-        // ---- the need-th smallest word: descent over bits 31..21, 20..10, 9..0
-        uint32_t prefix = 0, short_of = 0;
-        const uint32_t shifts[3] = {21u, 10u, 0u}, nbits[3] = {11u, 11u, 10u};
-        for (int p = 0; p < 3 && need != 0 && !short_of; ++p) {
-            for (uint32_t x = tid; x < NBIN; x += 1024) h[x] = 0;
-            __syncthreads();
-            const uint32_t hi_shift = shifts[p] + nbits[p];        // bits above this pass's digit
-            for (uint32_t t = f0; t < f1; ++t) {
-                const uint32_t start = tile_start[t], len = tile_start[t + 1] - start;
-                for (uint32_t e = tid; e < len; e += 1024) {
-                    const uint32_t i = start + e;
-                    if ((core_bits[i >> 5] >> (i & 31u)) & 1u) continue;
-                    const uint32_t r = explore_word(i, worker, pk);
-                    if (hi_shift < 32u && (r >> hi_shift) != prefix) continue;
-                    atomicAdd(&h[(r >> shifts[p]) & ((1u << nbits[p]) - 1u)], 1u);
-                }
-            }
-            __syncthreads();
-            // the bin that holds the need-th smallest: two bins per thread, ascending
-            const uint32_t c0 = h[2 * tid], c1 = h[2 * tid + 1];
-            uint32_t total;
-            const uint32_t excl = block_excl_scan<16>(c0 + c1, wtot, total);
-            if (tid == 0) sh[2] = (total < need) ? 1u : 0u;
-            if (excl < need && need <= excl + c0) { sh[0] = 2 * tid; sh[1] = need - excl; }
-            else if (excl + c0 < need && need <= excl + c0 + c1) { sh[0] = 2 * tid + 1; sh[1] = need - excl - c0; }
-            __syncthreads();
-            if (sh[2]) { short_of = 1; if (tid == 0) atomicOr(&flags[1], 2u); }     // fewer eligible parameters than requested
-            else { prefix = (prefix << nbits[p]) | sh[0]; need = sh[1]; }
-            __syncthreads();
-        }
-        // words below tau are taken, of the words equal to tau the first `need` in index order
-        const uint32_t tau = short_of ? 0xFFFFFFFFu : prefix;
-        const uint32_t take_all = short_of;
-        const uint32_t want = states[(size_t)b * n_seg + seg].need0;
-        uint32_t ties_seen = 0;                      // uniform
-        // ---- ordered emission, tile by tile (four consecutive parameters per thread)
-        for (uint32_t t = f0; t < f1; ++t) {
-            const uint32_t start = tile_start[t], len = tile_start[t + 1] - start;
-            uint32_t sel = 0, tie = 0;
-            if (want != 0) {
-#pragma unroll
-                for (int c = 0; c < 4; ++c) {
-                    const uint32_t e = 4u * tid + c;
-                    if (e >= len) continue;
-                    const uint32_t i = start + e;
-                    if ((core_bits[i >> 5] >> (i & 31u)) & 1u) continue;
-                    const uint32_t r = explore_word(i, worker, pk);
-                    if (take_all || r < tau) sel |= 1u << c;
-                    else if (r == tau) tie |= 1u << c;
-                }
-            }
-            uint32_t tie_total;
-            const uint32_t tie_excl = block_excl_scan<16>(__popc(tie), wtot, tie_total);
-            uint32_t rank = ties_seen + tie_excl;
-#pragma unroll
-            for (int c = 0; c < 4; ++c)
-                if ((tie >> c) & 1u) { if (rank < need) sel |= 1u << c; ++rank; }
-            ties_seen += tie_total;
-            uint32_t sel_total;
-            uint32_t o = run + block_excl_scan<16>(__popc(sel), wtot, sel_total);
-            if (tid == 0) off[t] = run;
-#pragma unroll
-            for (int c = 0; c < 4; ++c)
-                if ((sel >> c) & 1u) { if (o < expected) out[o] = start + 4u * tid + c; ++o; }
-            run += sel_total;
-        }
-    }
-    if (tid == 0) {
-        off[T] = run;
-        if (run != expected) atomicOr(&flags[1], 1u);
-    }
-}
-
-// =======================================================================================
-// Explorer, short-list path (every segment's candidate zone is narrow, draw with PAIRS = 1).
-// The few candidates outside the core are collected into one unordered list; the radix
-// descent, the decision against tau and the tie ranks run over that list; the chosen
-// candidates are then set in the sure bitmap, which alone drives the ordered emission.
-// Every kernel of the path returns at once when flags[0] is raised (the exact rerun with
-// the per-tile path follows), except where noted.
-// =======================================================================================
-// list entry: x = key, y = t * TILE + offset inside the tile, z = b * n_seg + seg, w = b
-constexpr uint32_t FLAG_RERUN = 1u;
-
-// Sure parameters outside the core, counted per tile (cnt_sel).  One wave per tile, serving
-// BPW batches.  grid (ceil(T/4), ceil(nbatch / BPW)).  Runs whatever the flag.
-template <int BPW>
-__global__ __launch_bounds__(BLOCK) void k_sure_count(const uint32_t* __restrict__ core_bits, uint32_t n_words, uint64_t n,
-                                                      const uint32_t* __restrict__ tile_start,
-                                                      const uint32_t* __restrict__ tile_seg, uint32_t T, uint32_t n_seg,
-                                                      uint32_t nbatch, const uint32_t* __restrict__ sure_bits,
-                                                      uint32_t* __restrict__ cnt_sel)
-{
-    const uint32_t t = blockIdx.x * 4 + (threadIdx.x >> 6), b0 = blockIdx.y * BPW, lane = lane_id();
-    if (t >= T) return;
-    const TileRef tr = tile_ref(t, n_seg, n, tile_start, tile_seg);
-    uint2 s2[BPW];
-#pragma unroll
-    for (int bb = 0; bb < BPW; ++bb) {
-        s2[bb] = make_uint2(0u, 0u);
-        if (b0 + bb < nbatch)
-            s2[bb] = *reinterpret_cast<const uint2*>(sure_bits + ((size_t)(b0 + bb) * T + t) * TILE_WORDS + 2 * lane);
-    }
-    uint32_t kw[2];
-    bitmap_window(core_bits, n_words, tr.start + lane * 64u, kw);
-#pragma unroll
-    for (int bb = 0; bb < BPW; ++bb) {
-        if (b0 + bb >= nbatch) break;
-        const uint32_t tot = wave_sum(__popc(s2[bb].x & ~kw[0]) + __popc(s2[bb].y & ~kw[1]));
-        if (lane == 0) cnt_sel[(size_t)(b0 + bb) * T + t] = tot;
-    }
-}
-
-// nsure[b][seg] = sum of `per` consecutive counts for every tile of the segment.  No atomics:
-// thousands of them on one cache line take longer than this whole kernel.
-// grid (n_seg, nbatch), 1024 threads.
-__global__ __launch_bounds__(1024) void k_seg_sum(const uint32_t* __restrict__ counts, uint32_t per,
-                                                  const uint32_t* __restrict__ seg_first_tile, uint32_t T, uint32_t n_seg,
-                                                  uint32_t* __restrict__ nsure)
-{
-    __shared__ uint32_t wtot[16];
-    const uint32_t seg = blockIdx.x, b = blockIdx.y;
-    const size_t x0 = ((size_t)b * T + seg_first_tile[seg]) * per, x1 = ((size_t)b * T + seg_first_tile[seg + 1]) * per;
-    uint32_t sum = 0;
-    for (size_t x = x0 + threadIdx.x; x < x1; x += 1024) sum += counts[x];
-    uint32_t total;
-    (void)block_excl_scan<16>(sum, wtot, total);
-    if (threadIdx.x == 0) nsure[(size_t)b * n_seg + seg] = total;
-}
-
-// Candidates outside the core -> list.  One thread per (batch, tile); a block reserves its
-// share of the list with one atomic.  A sub-tile with more pairs than its slot holds, or a
-// full list, raises the rerun flag.  keys_stride: words per batch of the pair slots.  grid ceil(nbatch * T / 1024), 1024 threads.
-__global__ __launch_bounds__(1024) void k_cand_gather(const uint32_t* __restrict__ core_bits, uint64_t n,
-                                                      const uint32_t* __restrict__ tile_start,
-                                                      const uint32_t* __restrict__ tile_seg, uint32_t T, uint32_t n_seg,
-                                                      uint32_t nbatch, const uint32_t* __restrict__ cand_keys,
-                                                      uint64_t keys_stride, const uint32_t* __restrict__ cnt_cand,
-                                                      uint4* __restrict__ list, uint32_t* __restrict__ list_count,
-                                                      uint32_t list_cap, uint32_t* __restrict__ flags)
-{
-    __shared__ uint32_t wtot[16];
-    __shared__ uint32_t sh_base;
-    if (threadIdx.x == 0) sh_base = flags[0];      // other blocks may raise the flag: one read per block
-    __syncthreads();
-    if (sh_base != 0) return;
-    const uint32_t x = blockIdx.x * 1024 + threadIdx.x;
-    const bool live = x < nbatch * T;
-    const uint32_t b = live ? x / T : 0u, t = live ? x % T : 0u;
-    uint4 c4 = make_uint4(0u, 0u, 0u, 0u);
-    if (live) c4 = *reinterpret_cast<const uint4*>(cnt_cand + (size_t)x * SUBS);
-    uint32_t cs[SUBS] = {c4.x, c4.y, c4.z, c4.w};
-    bool over = false;
-#pragma unroll
-    for (int sub = 0; sub < SUBS; ++sub)
-        if (cs[sub] > PAIR_CAP) { over = true; cs[sub] = 0; }
-    if (over) atomicOr(&flags[0], FLAG_RERUN);
-    uint32_t mine = 0;
-    TileRef tr{0u, 0u, 0u};
-    const uint32_t* keys = cand_keys;
-    if (cs[0] | cs[1] | cs[2] | cs[3]) {
-        tr = tile_ref(t, n_seg, n, tile_start, tile_seg);
-        keys = cand_keys + (size_t)b * keys_stride + (size_t)t * SUBS * PAIR_SLOT;
-#pragma unroll 1
-        for (int sub = 0; sub < SUBS; ++sub)
-            for (uint32_t j = 0; j < cs[sub]; ++j) {
-                const uint32_t i = tr.start + sub * SUB + keys[sub * PAIR_SLOT + 2 * j + 1];
-                mine += ((core_bits[i >> 5] >> (i & 31u)) & 1u) ^ 1u;
-            }
-    }
-    uint32_t total;
-    const uint32_t excl = block_excl_scan<16>(mine, wtot, total);
-    if (total == 0) return;
-    if (threadIdx.x == 0) sh_base = atomicAdd(list_count, total);
-    __syncthreads();
-    const uint32_t base = sh_base;
-    if (base + total > list_cap || base + total < base) {
-        if (threadIdx.x == 0) atomicOr(&flags[0], FLAG_RERUN);
-        return;
-    }
-    if (mine == 0) return;
-    uint32_t o = base + excl;
-#pragma unroll 1
-    for (int sub = 0; sub < SUBS; ++sub)
-        for (uint32_t j = 0; j < cs[sub]; ++j) {
-            const uint32_t key = keys[sub * PAIR_SLOT + 2 * j], e = keys[sub * PAIR_SLOT + 2 * j + 1];
-            const uint32_t i = tr.start + sub * SUB + e;
-            if ((core_bits[i >> 5] >> (i & 31u)) & 1u) continue;
-            list[o++] = make_uint4(key, t * TILE + sub * SUB + e, b * n_seg + tr.seg, b);
-        }
-}
-
-// Histogram of one radix level over the list.  grid: any, grid-stride.
-__global__ __launch_bounds__(256) void k_short_hist(const uint4* __restrict__ list, const uint32_t* __restrict__ list_count,
-                                                    uint32_t list_cap, const SegState* __restrict__ states,
-                                                    uint32_t* __restrict__ hist, uint32_t hist_off, int level,
-                                                    const uint32_t* __restrict__ flags)
-{
-    if (flags[0] != 0) return;
-    const uint32_t cnt = min(list_count[0], list_cap);
-    for (uint32_t j = blockIdx.x * 256 + threadIdx.x; j < cnt; j += gridDim.x * 256) {
-        const uint4 e = list[j];
-        const SegState* st = &states[e.z];
-        if (st->none) continue;
-        uint32_t digit;
-        if (level == 0) digit = e.x >> st->shift[0];
-        else {
-            if ((e.x >> st->shift[level - 1]) != st->prefix) continue;
-            digit = (e.x >> st->shift[level]) & (st->nbins[level] - 1u);
-        }
-        atomicAdd(&hist[(size_t)e.z * H_STRIDE + hist_off + digit], 1u);
-    }
-}
-
-// Decision of every list entry against its segment's tau.  A chosen candidate is added to
-// the sure bitmap and to its tile's count.  Entries equal to tau: all taken if the quota
-// covers them all, otherwise they go to the tie list for k_short_ties (a full tie list raises
-// the rerun flag).
-constexpr uint32_t TIE_CAP = 4096;
-__device__ __forceinline__ void short_take(const uint4 e, uint32_t T, uint32_t* __restrict__ sure_bits,
-                                           uint32_t* __restrict__ cnt_sel)
-{
-    const uint32_t t = e.y / TILE, o = e.y % TILE;
-    atomicOr(&sure_bits[((size_t)e.w * T + t) * TILE_WORDS + (o >> 5)], 1u << (o & 31u));
-    atomicAdd(&cnt_sel[(size_t)e.w * T + t], 1u);
-}
-
-__global__ __launch_bounds__(256) void k_short_mark(const uint4* __restrict__ list, const uint32_t* __restrict__ list_count,
-                                                    uint32_t list_cap, const SegState* __restrict__ states, uint32_t T,
-                                                    uint32_t* __restrict__ sure_bits, uint32_t* __restrict__ cnt_sel,
-                                                    uint32_t* __restrict__ tie_list, uint32_t* __restrict__ tie_count,
-                                                    uint32_t* __restrict__ flags)
-{
-    if (flags[0] != 0) return;
-    const uint32_t cnt = min(list_count[0], list_cap);
-    for (uint32_t j = blockIdx.x * 256 + threadIdx.x; j < cnt; j += gridDim.x * 256) {
-        const uint4 e = list[j];
-        const SegState* st = &states[e.z];
-        if (st->none) continue;
-        const uint32_t tau = st->tau;
-        if (e.x > tau || (e.x == tau && st->tie_all)) short_take(e, T, sure_bits, cnt_sel);
-        else if (e.x == tau && st->quota != 0) {
-            const uint32_t slot = atomicAdd(tie_count, 1u);
-            if (slot < TIE_CAP) tie_list[slot] = j;
-            else atomicOr(&flags[0], FLAG_RERUN);
-        }
-    }
-}
-
-// Ties that the quota covers only in part: the quota goes to the lowest positions.  Every
-// entry equal to its segment's tau is on the tie list, so the rank of a tied entry is the
-// number of tie-list entries of its segment below it.  One block; nothing to do as a rule.
-__global__ __launch_bounds__(1024) void k_short_ties(const uint4* __restrict__ list, const SegState* __restrict__ states,
-                                                     uint32_t T, uint32_t* __restrict__ sure_bits,
-                                                     uint32_t* __restrict__ cnt_sel, const uint32_t* __restrict__ tie_list,
-                                                     const uint32_t* __restrict__ tie_count, const uint32_t* __restrict__ flags)
-{
-    if (flags[0] != 0) return;
-    const uint32_t nt = min(tie_count[0], TIE_CAP);
-    for (uint32_t q = threadIdx.x; q < nt; q += 1024) {
-        const uint4 e = list[tie_list[q]];
-        uint32_t rank = 0;
-        for (uint32_t p = 0; p < nt; ++p) {
-            const uint4 o = list[tie_list[p]];
-            rank += (o.z == e.z && o.y < e.y) ? 1u : 0u;
-        }
-        if (rank < states[e.z].quota) short_take(e, T, sure_bits, cnt_sel);
-    }
-}
-
-// Exclusive prefix of the tile counts inside chunks of SCAN_CHUNK tiles, and the chunk sums.
-// grid (ceil(T / SCAN_CHUNK), nbatch), 1024 threads.
-constexpr uint32_t SCAN_CHUNK = 8192, SCAN_PER = SCAN_CHUNK / 1024;
-__device__ __forceinline__ uint32_t scan_phys(uint32_t x) { return x + (x >> 3); }     // one pad word per thread row
-
-// vals: SCAN_CHUNK*9/8 words; wtot: 16 words.  Values of the chunk are already in vals
-// (physical layout).  On return vals holds each value's exclusive prefix inside the chunk.
-__device__ __forceinline__ uint32_t scan_chunk(uint32_t* vals, uint32_t* wtot)
-{
-    uint32_t s = 0;
-    const uint32_t row = threadIdx.x * (SCAN_PER + 1);
-#pragma unroll
-    for (uint32_t e = 0; e < SCAN_PER; ++e) { const uint32_t v = vals[row + e]; vals[row + e] = s; s += v; }
-    uint32_t total;
-    const uint32_t base = block_excl_scan<16>(s, wtot, total);
-#pragma unroll
-    for (uint32_t e = 0; e < SCAN_PER; ++e) vals[row + e] += base;
-    __syncthreads();
-    return total;
-}
-
-__global__ __launch_bounds__(1024) void k_chunk_scan(uint32_t T, const uint32_t* __restrict__ cnt_sel, MutPtrTab out_off,
-                                                     uint32_t* __restrict__ chunk_sum, const uint32_t* __restrict__ flags)
-{
-    __shared__ uint32_t vals[SCAN_CHUNK + SCAN_CHUNK / 8];
-    __shared__ uint32_t wtot[16];
-    if (flags[0] != 0) return;
-    const uint32_t b = blockIdx.y, c0 = blockIdx.x * SCAN_CHUNK;
-    const uint32_t* cs = cnt_sel + (size_t)b * T;
-    uint32_t* off = static_cast<uint32_t*>(out_off.p[b]);
-    for (uint32_t x = threadIdx.x; x < SCAN_CHUNK; x += 1024) vals[scan_phys(x)] = (c0 + x < T) ? cs[c0 + x] : 0u;
-    __syncthreads();
-    const uint32_t total = scan_chunk(vals, wtot);
-    for (uint32_t x = threadIdx.x; x < SCAN_CHUNK && c0 + x < T; x += 1024) off[c0 + x] = vals[scan_phys(x)];
-    if (threadIdx.x == 0) chunk_sum[(size_t)b * gridDim.x + blockIdx.x] = total;
-}
-
-// Ordered emission from the sure bitmap (chosen candidates included) minus the core.  One
-// wave per tile and BPW batches; the wave also turns its tile's chunk-relative offset into
-// the final one.  grid (ceil(T/4), ceil(nbatch/BPW)).
-template <int BPW>
-__global__ __launch_bounds__(BLOCK) void k_emit_bits(const uint32_t* __restrict__ core_bits, uint32_t n_words, uint64_t n,
-                                                     const uint32_t* __restrict__ tile_start,
-                                                     const uint32_t* __restrict__ tile_seg, uint32_t T, uint32_t n_seg,
-                                                     uint32_t nbatch, const uint32_t* __restrict__ sure_bits,
-                                                     const uint32_t* __restrict__ chunk_sum, uint32_t n_chunks,
-                                                     MutPtrTab out_off, MutPtrTab out_idx, uint32_t expected,
-                                                     uint32_t* __restrict__ flags)
-{
-    if (flags[0] != 0) return;
-    const uint32_t t = blockIdx.x * 4 + (threadIdx.x >> 6), b0 = blockIdx.y * BPW, lane = lane_id();
-    if (t >= T) return;
-    const TileRef tr = tile_ref(t, n_seg, n, tile_start, tile_seg);
-    const uint32_t chunk = t / SCAN_CHUNK;
-    uint2 s2[BPW];
-    uint32_t off_t[BPW];
-#pragma unroll
-    for (int bb = 0; bb < BPW; ++bb) {
-        s2[bb] = make_uint2(0u, 0u); off_t[bb] = 0;
-        if (b0 + bb < nbatch) {
-            s2[bb] = *reinterpret_cast<const uint2*>(sure_bits + ((size_t)(b0 + bb) * T + t) * TILE_WORDS + 2 * lane);
-            off_t[bb] = static_cast<const uint32_t*>(out_off.p[b0 + bb])[t];
-        }
-    }
-    uint32_t kw[2];
-    bitmap_window(core_bits, n_words, tr.start + lane * 64u, kw);
-#pragma unroll
-    for (int bb = 0; bb < BPW; ++bb) {
-        const uint32_t b = b0 + bb;
-        if (b >= nbatch) break;
-        uint32_t first = off_t[bb];
-        for (uint32_t c = 0; c < chunk; ++c) first += chunk_sum[(size_t)b * n_chunks + c];
-        const uint32_t fm0 = s2[bb].x & ~kw[0], fm1 = s2[bb].y & ~kw[1];
-        const uint32_t ocnt = __popc(fm0) + __popc(fm1);
-        const uint32_t incl = wave_incl_scan(ocnt);
-        uint32_t* out = static_cast<uint32_t*>(out_idx.p[b]);
-        uint32_t* off = static_cast<uint32_t*>(out_off.p[b]);
-        if (lane == 0) off[t] = first;
-        if (t == T - 1 && lane == 63) {
-            off[T] = first + incl;
-            if (first + incl != expected) atomicOr(&flags[1], 1u);
-        }
-        uint32_t o = first + incl - ocnt;
-        uint32_t m = fm0;
-        while (m) {
-            const uint32_t p = __ffs(m) - 1;
-            m &= m - 1;
-            if (o < expected) out[o] = tr.start + lane * 64u + p;     // never beyond the caller's list
-            ++o;
-        }
-        m = fm1;
-        while (m) {
-            const uint32_t p = __ffs(m) - 1;
-            m &= m - 1;
-            if (o < expected) out[o] = tr.start + lane * 64u + 32u + p;
-            ++o;
-        }
-    }
-}
-
-// ---------------------------------------------------------------------------------------
-// Levels 1 and 2: histogram of the candidates that still match the prefix.  One wave per
-// tile, 16 lanes per sub-tile list; equal digits inside a wave are merged before the
-// global atomic.  grid (ceil(T/4), nbatch).
-// ---------------------------------------------------------------------------------------
-template <int KPL, int BPW>
-__global__ __launch_bounds__(BLOCK) void k_list_hist(uint64_t n, const uint32_t* __restrict__ tile_start,
-                                                     const uint32_t* __restrict__ tile_seg, uint32_t T, uint32_t n_seg,
-                                                     uint32_t nbatch, const SegState* __restrict__ states,
-                                                     uint32_t* __restrict__ hist, uint32_t hist_off, int level,
-                                                     const uint32_t* __restrict__ cand_keys,
-                                                     const uint32_t* __restrict__ cnt_cand, uint64_t keys_stride,
-                                                     const uint32_t* __restrict__ gate)
-{
-    const uint32_t t = blockIdx.x * 4 + (threadIdx.x >> 6), b0 = blockIdx.y * BPW, lane = lane_id();
-    if (t >= T || (gate && gate[0] != 0)) return;
-    const TileRef tr = tile_ref(t, n_seg, n, tile_start, tile_seg);
-    // one wave serves the tile for BPW batches: all their loads are requested before any is used
-    uint32_t kv[BPW][KPL], cnt[BPW];
-#pragma unroll
-    for (int bb = 0; bb < BPW; ++bb) {
-        const uint32_t b = b0 + bb;
-        cnt[bb] = 0;
-        if (b < nbatch) {
-            load_sublists<KPL>(cand_keys + (size_t)b * keys_stride + tr.start, lane, kv[bb]);
-            cnt[bb] = cnt_cand[((size_t)b * T + t) * SUBS + (lane >> 4)];
-        }
-    }
-#pragma unroll
-    for (int bb = 0; bb < BPW; ++bb) {
-        const uint32_t b = b0 + bb;
-        if (b >= nbatch) break;
-        const SegState* st = &states[(size_t)b * n_seg + tr.seg];
-        if (st->none) continue;
-        const uint32_t pshift = st->shift[level - 1], shift = st->shift[level], mask = st->nbins[level] - 1u;
-        const uint32_t prefix = st->prefix;
-        const uint32_t c = cnt[bb];
-        const uint32_t maxcnt = max(max(__shfl(c, 0, 64), __shfl(c, 16, 64)), max(__shfl(c, 32, 64), __shfl(c, 48, 64)));
-        const uint32_t* keys = cand_keys + (size_t)b * keys_stride + tr.start + (lane >> 4) * SUB;
-        uint32_t* hp = hist + ((size_t)b * n_seg + tr.seg) * H_STRIDE + hist_off;
-        for (uint32_t j0 = 0; j0 < maxcnt; j0 += 16) {
-            const uint32_t j = j0 + (lane & 15u);
-            uint32_t k = 0;
-            if (j0 < 16u * KPL) {
-#pragma unroll
-                for (int i = 0; i < KPL; ++i) if (j0 == 16u * i) k = kv[bb][i];
-            } else if (j < c) {
-                k = keys[j];
-            }
-            bool part = (j < c) && (k >> pshift) == prefix;
-            const uint32_t digit = (k >> shift) & mask;
-            unsigned long long active = __ballot(part);
-            while (active) {
-                const int leader = __ffsll((long long)active) - 1;
-                const uint32_t d = __shfl(digit, leader, 64);
-                const unsigned long long same = __ballot(part && digit == d);
-                if ((int)lane == leader) atomicAdd(&hp[d], (uint32_t)__popcll(same));
-                if (digit == d) part = false;
-                active &= ~same;
-            }
-        }
-    }
-}
-
-// ---------------------------------------------------------------------------------------
-// Per-tile counts once tau is known: selected-for-sure (gt + keys > tau) and ties (== tau).
-// One wave per tile and BPW batches.  grid (ceil(T/4), ceil(nbatch/BPW)).
-// ---------------------------------------------------------------------------------------
-template <int KPL, int BPW>
-__global__ __launch_bounds__(BLOCK) void k_count(uint64_t n, const uint32_t* __restrict__ tile_start,
-                                                 const uint32_t* __restrict__ tile_seg, uint32_t T, uint32_t n_seg,
-                                                 uint32_t nbatch, const SegState* __restrict__ states,
-                                                 const uint32_t* __restrict__ cand_keys, const uint32_t* __restrict__ cnt_cand,
-                                                 const uint32_t* __restrict__ cnt_gt, uint64_t keys_stride,
-                                                 uint32_t* __restrict__ cnt_sel, uint32_t* __restrict__ cnt_tie,
-                                                 const uint32_t* __restrict__ gate)
-{
-    const uint32_t t = blockIdx.x * 4 + (threadIdx.x >> 6), b0 = blockIdx.y * BPW, lane = lane_id();
-    if (t >= T || (gate && gate[0] != 0)) return;
-    const TileRef tr = tile_ref(t, n_seg, n, tile_start, tile_seg);
-    uint32_t kv[BPW][KPL], cnt[BPW];
-#pragma unroll
-    for (int bb = 0; bb < BPW; ++bb) {
-        const uint32_t b = b0 + bb;
-        cnt[bb] = 0;
-        if (b < nbatch) {
-            load_sublists<KPL>(cand_keys + (size_t)b * keys_stride + tr.start, lane, kv[bb]);
-            cnt[bb] = cnt_cand[((size_t)b * T + t) * SUBS + (lane >> 4)];
-        }
-    }
-    uint32_t gtc[BPW];
-#pragma unroll
-    for (int bb = 0; bb < BPW; ++bb) {
-        gtc[bb] = 0;
-        if (cnt_gt && b0 + bb < nbatch) {
-            const uint4 g4 = *reinterpret_cast<const uint4*>(cnt_gt + ((size_t)(b0 + bb) * T + t) * SUBS);
-            gtc[bb] = g4.x + g4.y + g4.z + g4.w;
-        }
-    }
-#pragma unroll
-    for (int bb = 0; bb < BPW; ++bb) {
-        const uint32_t b = b0 + bb;
-        if (b >= nbatch) break;
-        const SegState* st = &states[(size_t)b * n_seg + tr.seg];
-        uint32_t sel = 0, tie = 0;
-        if (!st->none) {
-            const uint32_t tau = st->tau, c = cnt[bb];
-            const uint32_t* keys = cand_keys + (size_t)b * keys_stride + tr.start + (lane >> 4) * SUB;
-#pragma unroll
-            for (int i = 0; i < KPL; ++i) {
-                const uint32_t k = kv[bb][i];
-                if ((lane & 15u) + 16u * i < c) {
-                    sel += (k > tau) ? 1u : 0u;
-                    tie += (k == tau) ? 1u : 0u;
-                }
-            }
-            for (uint32_t j = (lane & 15u) + 16u * KPL; j < c; j += 16) {
-                const uint32_t k = keys[j];
-                sel += (k > tau) ? 1u : 0u;
-                tie += (k == tau) ? 1u : 0u;
-            }
-            sel = wave_sum(sel);
-            tie = wave_sum(tie);
-        }
-        if (st->has_gt && st->need0) sel += gtc[bb];
-        if (lane == 0) { cnt_sel[(size_t)b * T + t] = sel; cnt_tie[(size_t)b * T + t] = tie; }
-    }
-}
-
-// ---------------------------------------------------------------------------------------
-// Scan over tiles in chunks of SCAN_CHUNK tiles, one block per chunk and batch; a value
-// of the whole array is its chunk-relative prefix plus the sums of the chunks before it
-// (chunk_base).  Two passes: PASS 0 over the tie counts (tie_pre), PASS 1 over what each
-// tile emits (certain ones plus the ties it takes under its segment's quota) -> out_off.
-// The emission turns the chunk-relative offsets into final ones.
-// grid (ceil(T / SCAN_CHUNK), nbatch), 1024 threads.
-// ---------------------------------------------------------------------------------------
-__device__ __forceinline__ uint32_t chunk_base(const uint32_t* __restrict__ sums, uint32_t chunk)
-{
-    uint32_t base = 0;
-    for (uint32_t c = 0; c < chunk; ++c) base += sums[c];
-    return base;
-}
-
-template <int PASS>
-__global__ __launch_bounds__(1024) void k_tile_scan(const uint32_t* __restrict__ tile_seg,
-                                                    const uint32_t* __restrict__ seg_first_tile, uint32_t T, uint32_t n_seg,
-                                                    const SegState* __restrict__ states, const uint32_t* __restrict__ cnt_sel,
-                                                    const uint32_t* __restrict__ cnt_tie, uint32_t* __restrict__ tie_pre,
-                                                    uint32_t* __restrict__ tie_sum, MutPtrTab out_off,
-                                                    uint32_t* __restrict__ off_sum, const uint32_t* __restrict__ gate)
-{
-    __shared__ uint32_t vals[SCAN_CHUNK + SCAN_CHUNK / 8];
-    __shared__ uint32_t wtot[16];
-    if (gate && gate[0] != 0) return;
-    const uint32_t b = blockIdx.y, c0 = blockIdx.x * SCAN_CHUNK, n_chunks = gridDim.x;
-    const uint32_t* cs = cnt_sel + (size_t)b * T;
-    const uint32_t* ct = cnt_tie + (size_t)b * T;
-    uint32_t* tp = tie_pre + (size_t)b * (T + 1);
-    const uint32_t* ts = tie_sum + (size_t)b * n_chunks;
-    for (uint32_t x = threadIdx.x; x < SCAN_CHUNK; x += 1024) {
-        const uint32_t t = c0 + x;
-        uint32_t v = 0;
-        if (t < T) {
-            const uint32_t c = ct[t];
-            if (PASS == 0) v = c;
-            else {
-                // ties before this tile inside its segment, against the segment's quota
-                const SegState* st = states + (size_t)b * n_seg;
-                const uint32_t seg = (n_seg == 1) ? 0u : tile_seg[t];
-                uint32_t before = tp[t] + chunk_base(ts, blockIdx.x);
-                if (n_seg != 1) {
-                    const uint32_t f = seg_first_tile[seg];
-                    before -= tp[f] + chunk_base(ts, f / SCAN_CHUNK);
-                }
-                const uint32_t q = st[seg].quota;
-                const uint32_t room = (q > before) ? q - before : 0u;
-                v = cs[t] + (room < c ? room : c);
-            }
-        }
-        vals[scan_phys(x)] = v;
-    }
-    __syncthreads();
-    const uint32_t total = scan_chunk(vals, wtot);
-    uint32_t* dst = (PASS == 0) ? tp : static_cast<uint32_t*>(out_off.p[b]);
-    for (uint32_t x = threadIdx.x; x < SCAN_CHUNK && c0 + x < T; x += 1024) dst[c0 + x] = vals[scan_phys(x)];
-    if (threadIdx.x == 0) ((PASS == 0) ? tie_sum : off_sum)[(size_t)b * n_chunks + blockIdx.x] = total;
-}
-
-// ---------------------------------------------------------------------------------------
-// K3: ordered emission.  One wave per (tile, batch), each lane owning two consecutive
-// bitmap words: decide every candidate against tau, hand out the tie quota in index
-// order, and write the tile's chosen indices at its offset.  grid (ceil(T/4), nbatch).
-// ---------------------------------------------------------------------------------------
-template <int KPL, int BPW>
-__global__ __launch_bounds__(BLOCK) void k_emit(uint64_t n, const uint32_t* __restrict__ tile_start,
-                                                const uint32_t* __restrict__ tile_seg,
-                                                const uint32_t* __restrict__ seg_first_tile, uint32_t T, uint32_t n_seg,
-                                                uint32_t nbatch, const SegState* __restrict__ states,
-                                                const uint32_t* __restrict__ gt_bits, const uint32_t* __restrict__ cand_bits,
-                                                const uint32_t* __restrict__ cand_keys, uint64_t keys_stride,
-                                                const uint32_t* __restrict__ tie_pre, MutPtrTab out_off, MutPtrTab out_idx,
-                                                uint32_t expected, uint32_t* __restrict__ pub_bits,
-                                                const uint32_t* __restrict__ excl_bits, uint32_t n_words,
-                                                const uint32_t* __restrict__ gate, const uint32_t* __restrict__ tie_sum,
-                                                const uint32_t* __restrict__ off_sum, uint32_t n_chunks,
-                                                uint32_t* __restrict__ flags)
-{
-    __shared__ uint32_t kb[4][SUBS * 16 * KPL];
-    const uint32_t wid = threadIdx.x >> 6;
-    const uint32_t t = blockIdx.x * 4 + wid, b0 = blockIdx.y * BPW, lane = lane_id();
-    if (t >= T || (gate && gate[0] != 0)) return;
-    const TileRef tr = tile_ref(t, n_seg, n, tile_start, tile_seg);
-    const uint32_t start = tr.start, len = tr.len, seg = tr.seg;
-    // one wave serves the tile for BPW batches: all their loads are requested before any is used
-    uint2 c2[BPW];
-    uint32_t kv[BPW][KPL], off_t[BPW], tp_t[BPW];
-    uint2 g2[BPW];
-#pragma unroll
-    for (int bb = 0; bb < BPW; ++bb) {
-        const uint32_t b = b0 + bb;
-        c2[bb] = make_uint2(0u, 0u); g2[bb] = make_uint2(0u, 0u); off_t[bb] = 0; tp_t[bb] = 0;
-        if (b < nbatch) {
-            if (gt_bits) g2[bb] = *reinterpret_cast<const uint2*>(gt_bits + ((size_t)b * T + t) * TILE_WORDS + 2 * lane);
-            c2[bb] = *reinterpret_cast<const uint2*>(cand_bits + ((size_t)b * T + t) * TILE_WORDS + 2 * lane);
-            load_sublists<KPL>(cand_keys + (size_t)b * keys_stride + start, lane, kv[bb]);
-            off_t[bb] = static_cast<const uint32_t*>(out_off.p[b])[t];
-            tp_t[bb] = tie_pre[(size_t)b * (T + 1) + t];
-        }
-    }
-    uint32_t xw[2] = {0u, 0u};      // parameters that the certainly-selected bitmap must not contribute (explorer: the core)
-    if (excl_bits) bitmap_window(excl_bits, n_words, start + lane * 64u, xw);
-    uint32_t* kbw = kb[wid];
-#pragma unroll
-    for (int bb = 0; bb < BPW; ++bb) {
-        const uint32_t b = b0 + bb;
-        if (b >= nbatch) break;
-        const SegState* st = &states[(size_t)b * n_seg + seg];
-        const uint32_t* keys = cand_keys + (size_t)b * keys_stride + start;
-        const uint32_t* tp = tie_pre + (size_t)b * (T + 1);
-        const uint32_t none = st->none, tau = st->tau, quota = st->quota;
-        uint32_t cw[2] = {0u, 0u}, gw[2] = {0u, 0u};
-        if (!none) { cw[0] = c2[bb].x; cw[1] = c2[bb].y; }
-        if (st->has_gt && st->need0) { gw[0] = g2[bb].x & ~xw[0]; gw[1] = g2[bb].y & ~xw[1]; }
-        wave_sync();
-#pragma unroll
-        for (int i = 0; i < KPL; ++i) kbw[(lane >> 4) * (16 * KPL) + (lane & 15u) + 16 * i] = kv[bb][i];
-        wave_sync();
-        const uint32_t pos = sublist_pos(lane, __popc(cw[0]) + __popc(cw[1]));
-        const uint32_t sub = pos >> 10;
-        uint32_t j = pos & (SUB - 1u);
-        uint32_t selmask[2] = {0u, 0u}, tiemask[2] = {0u, 0u};
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            uint32_t m = cw[h];
-            while (m) {
-                const uint32_t p = __ffs(m) - 1;
-                m &= m - 1;
-                const uint32_t k = (j < 16u * KPL) ? kbw[sub * (16 * KPL) + j] : keys[sub * SUB + j];
-                ++j;
-                if (k > tau) selmask[h] |= 1u << p;
-                else if (k == tau) tiemask[h] |= 1u << p;
-            }
-        }
-        const uint32_t tcnt = __popc(tiemask[0]) + __popc(tiemask[1]);
-        uint32_t taken[2] = {0u, 0u};
-        if (__ballot(tcnt != 0)) {
-            const uint32_t* ts = tie_sum + (size_t)b * n_chunks;
-            uint32_t tp_seg = 0;
-            if (n_seg != 1) {
-                const uint32_t f = seg_first_tile[seg];
-                tp_seg = tp[f] + chunk_base(ts, f / SCAN_CHUNK);
-            }
-            const uint32_t tbase = tp_t[bb] + chunk_base(ts, t / SCAN_CHUNK) - tp_seg + wave_incl_scan(tcnt) - tcnt;
-            uint32_t take = (quota > tbase) ? quota - tbase : 0u;
-#pragma unroll
-            for (int h = 0; h < 2; ++h) {
-                uint32_t m = tiemask[h];
-                while (m && take) { const uint32_t low = m & (0u - m); taken[h] |= low; m ^= low; --take; }
-            }
-        }
-        const uint32_t fm0 = gw[0] | selmask[0] | taken[0], fm1 = gw[1] | selmask[1] | taken[1];
-        const uint32_t ocnt = __popc(fm0) + __popc(fm1);
-        uint32_t* out = static_cast<uint32_t*>(out_idx.p[b]);
-        // the tile's offset so far counts from its chunk: make it final, for this emission and for the caller
-        const uint32_t first = off_t[bb] + chunk_base(off_sum + (size_t)b * n_chunks, t / SCAN_CHUNK);
-        const uint32_t oincl = wave_incl_scan(ocnt);
-        uint32_t* off = static_cast<uint32_t*>(out_off.p[b]);
-        if (lane == 0) off[t] = first;
-        if (t == T - 1 && lane == 63) {
-            off[T] = first + oincl;
-            if (first + oincl != expected) atomicOr(&flags[1], 1u);
-        }
-        uint32_t o = first + oincl - ocnt;
-        {
-            uint32_t m = fm0;
-            while (m) {
-                const uint32_t p = __ffs(m) - 1;
-                m &= m - 1;
-                if (o < expected) out[o] = start + lane * 64u + p;     // never beyond the caller's list
-                ++o;
-            }
-            m = fm1;
-            while (m) {
-                const uint32_t p = __ffs(m) - 1;
-                m &= m - 1;
-                if (o < expected) out[o] = start + lane * 64u + 32u + p;
-                ++o;
-            }
-        }
-        if (pub_bits) {
-            uint32_t* pb = pub_bits + (start >> 5) + 2 * lane;
-            if (lane * 64u < len) pb[0] = fm0;
-            if (lane * 64u + 32u < len) pb[1] = fm1;
-        }
-    }
 }
 
 // Segmented models: the public bitmap is built from the index list (tiles may start inside a word).

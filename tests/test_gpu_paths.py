@@ -128,3 +128,36 @@ def test_recorded_selection_replays_beside_eager_ones(segments):
         assert np.array_equal(u32(idx), want)
         assert np.array_equal(u32(bits), oracle.core_bits(n, want))
     sd.close()
+
+
+@pytest.mark.parametrize("per_tile_tail", [0, 1])
+@pytest.mark.parametrize("W", [1, 5, 9])
+@pytest.mark.parametrize("name", sorted(SEGMENTS) + ["one_segment", "more_blocks_than_run_at_a_time"])
+def test_explorer_lists_and_offsets_at_the_edges_of_segments_and_zones(name, W, per_tile_tail):
+    """Requests from nothing to everything outside the core (no sure zone, no candidates wanted, every candidate wanted), in both
+    formats of the draw, over segments that share waves, blocks and bitmap words."""
+    sizes = SEGMENTS.get(name) or ([300_001] if name == "one_segment" else [4096 + 7, 900] * 130)
+    so, n = offsets(sizes), sum(sizes)
+    rng = np.random.default_rng(len(name))
+    ks = [0 if j % 4 == 3 else s // 7 for j, s in enumerate(sizes)]
+    core = oracle.select_core(np.abs(rng.standard_normal(n)).astype(np.float32), ks, so)
+    bits = to_dev(oracle.core_bits(n, core))
+    sd = binding.SlimDP(n, W, seg_off=so, seed=workloads.EXPLORE_SEED)
+    sd.set_option("explore_per_tile_tail", per_tile_tail)
+    ts = sd.tile_starts().astype(np.int64)
+    left = [s - k for s, k in zip(sizes, ks)]
+    requests = {
+        "few": [a // 50 for a in left],
+        "nothing in some": [0 if j % 3 == 1 else a // 3 for j, a in enumerate(left)],
+        "all but one": [max(a - 1, 0) for a in left],
+        "all": left,
+        "most": [a - a // 30 for a in left],
+    }
+    for it, (what, ms) in enumerate(requests.items()):
+        idx, off = sd.sample_explore(bits, ks, it, ms, 3, W)
+        sd.synchronize()
+        for q in {0, W - 1}:
+            want = oracle.sample_explore(n, core, workloads.EXPLORE_SEED, it, 3 + q, ms, so)
+            assert np.array_equal(u32(idx[q]), want), what
+            assert np.array_equal(u32(off[q]), np.searchsorted(want.astype(np.int64), ts).astype(np.uint32)), what
+    sd.close()
