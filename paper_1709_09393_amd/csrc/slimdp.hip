@@ -761,9 +761,9 @@ static int score_impl(slimdp_ctx* ctx, const float* w, const float* const* g, ui
             SLIMDP_LAUNCHED(ctx, "k_sample_bound");
         }
     }
-    // flat model, aligned arrays, 1/2/4/8 workers: the pipelined kernel
+    // flat model, aligned arrays, up to 8 or 16 workers (two rounds of W + 1 vectors in registers): the pipelined kernel
     if (ctx->n_seg == 1 && vec_ok && ctx->opt_strided && ctx->opt_score_pipeline && ctx->n < (1ull << 30) &&
-        (W == 1 || W == 2 || W == 4 || W == 8)) {
+        (W <= 8 || W == 16)) {
         const dim3 fgrid(persistent_blocks(ctx, SCOREF_MINB, 1)), fblock(BLOCK);
         const ClsArgs cls{ctx->c_pred, ctx->c_used, (int)ctx->opt_core_predict, ctx->c_gt_bits, ctx->c_cand_bits, ctx->c_cand_keys, ctx->c_cnt_gt, ctx->c_cnt_cand};
 #define LAUNCH_FLAT_Q(WT, PRE, SPEC, DENSE)                                                                           \
@@ -777,15 +777,21 @@ static int score_impl(slimdp_ctx* ctx, const float* w, const float* const* g, ui
     } while (0)
 #define LAUNCH_FLAT(WT)                                                                                               \
     do {                                                                                                              \
+        constexpr int CAP = (WT) == 1 || (WT) == 2 || (WT) == 4 || (WT) == 8 || (WT) == 16;                           \
         if (w_new) LAUNCH_FLAT_S(WT, 0, 1);                                                                           \
-        else if (capture) LAUNCH_FLAT_S(WT, 1, 0);                                                                    \
+        else if (capture) LAUNCH_FLAT_S(WT, CAP, 0);                                                                  \
         else LAUNCH_FLAT_S(WT, 0, 0);                                                                                 \
     } while (0)
         switch (W) {
             case 1: LAUNCH_FLAT(1); break;
             case 2: LAUNCH_FLAT(2); break;
+            case 3: LAUNCH_FLAT(3); break;
             case 4: LAUNCH_FLAT(4); break;
-            default: LAUNCH_FLAT(8); break;
+            case 5: LAUNCH_FLAT(5); break;
+            case 6: LAUNCH_FLAT(6); break;
+            case 7: LAUNCH_FLAT(7); break;
+            case 8: LAUNCH_FLAT(8); break;
+            default: LAUNCH_FLAT(16); break;
         }
 #undef LAUNCH_FLAT
 #undef LAUNCH_FLAT_S

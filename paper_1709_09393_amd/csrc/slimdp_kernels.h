@@ -505,10 +505,14 @@ __global__ __launch_bounds__(BLOCK, SCORE_MINB) void k_score(const float* __rest
 // K1 for a flat model whose arrays are 16-byte aligned: the same results as k_score, with
 // the loads of the NEXT round of 256 parameters per wave (the next tile's first round after
 // a tile's last) requested before the current round is worked on, so that a wave always has
-// two rounds of nine 16-byte loads in flight, also while it draws explorer zones.  Whole
+// two rounds of W + 1 16-byte loads in flight, also while it draws explorer zones.  Whole
 // arrays are addressed through one descriptor each (n < 2^30 parameters: byte offsets fit 32
 // bits); block b takes the whole tiles b, b + gridDim.x, ...; the ragged last tile, if any,
 // goes to one block after its loop, element by element.
+// Every number of workers whose two rounds fit the registers comes here (1 to 8, and 16 with two parts of capture staging
+// and no round keys in registers), because a selection then finds its candidates sorted: k_core_build falls from 209 to
+// 14 us at 138*10^6 parameters and 16 workers (scoring with draws and capture itself 2,558 -> 2,190 us), from 50 to
+// 12 us at 20*10^6 and 3 workers (94 -> 82 us).
 // ---------------------------------------------------------------------------------------
 #ifndef SCOREF_MINB
 #define SCOREF_MINB 2
@@ -536,11 +540,12 @@ __global__ __launch_bounds__(BLOCK, SCOREF_MINB) void k_score_flat(const float* 
                                                                    float* __restrict__ S, uint64_t n, uint32_t* __restrict__ hist,
                                                                    PreArgs pre, SpecArgs spec, ClsArgs cls, float* __restrict__ w_new, float lr)
 {
-    static_assert(WT >= 1 && WT <= 8, "two rounds of W + 1 vectors must fit the registers");
+    static_assert(WT >= 1 && WT <= 16, "two rounds of W + 1 vectors must fit the registers");
+    constexpr uint32_t STAGED = WT <= 8 ? 256 : 128;      // captured entries staged at a time: two blocks share a unit's LDS
     static_assert(!(SPEC && DENSE), "a dense update is never followed by a pack of the same updates");
     constexpr uint32_t NB = CORE_NB0 / 2;
     __shared__ uint32_t h[NB];
-    __shared__ __align__(16) float stage[SPEC ? 4 * 256 * WT : 4];
+    __shared__ __align__(16) float stage[SPEC ? 4 * STAGED * WT : 4];
     __shared__ uint32_t h1[CORE_NB1];                // level-1 digits of the candidates of the predicted bin
     const uint32_t lane = lane_id(), wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const uint32_t T_full = (uint32_t)(n / TILE), T = (uint32_t)((n + TILE - 1) / TILE);
@@ -571,8 +576,9 @@ __global__ __launch_bounds__(BLOCK, SCOREF_MINB) void k_score_flat(const float* 
 #pragma unroll
         for (int k = 0; k < WT; ++k) x[k] = buffer_load4_aux<SCOREF_LD_AUX>(rg[k], o);
     };
+    constexpr bool KEYS_IN_VGPRS = WT <= 8;      // 20 registers; with 16 workers' rounds beside them they would spill
     PhiloxRoundKeys rkeys;
-    if (PRE) rkeys = philox_round_keys(pre.pk.seed_lo, pre.pk.seed_hi);
+    if constexpr (PRE && KEYS_IN_VGPRS) rkeys = philox_round_keys(pre.pk.seed_lo, pre.pk.seed_hi);
     auto draw = [&](uint32_t t, uint32_t len, uint32_t r) {      // this round's share of the announced draws
         if (PRE) {
 #pragma unroll 1
@@ -582,8 +588,15 @@ __global__ __launch_bounds__(BLOCK, SCOREF_MINB) void k_score_flat(const float* 
                 out.cand_bits = pre.cand_bits + (size_t)b * T * TILE_WORDS;
                 out.cand_keys = pre.cand_keys + (size_t)b * pre.keys_stride;
                 out.cnt_cand = pre.cnt_cand + (size_t)b * T * SUBS;
-                explore_subtile_fast<(PRE == 2) ? 1 : 0>(pre.worker0 + b, t, wid, t * TILE, len, pre_bound, pre_sure,
-                                                         pre_has_sure, pre_skip, out, pre.pk, rkeys);
+                if constexpr (KEYS_IN_VGPRS) {
+                    explore_subtile_fast<(PRE == 2) ? 1 : 0>(pre.worker0 + b, t, wid, t * TILE, len, pre_bound, pre_sure,
+                                                             pre_has_sure, pre_skip, out, pre.pk, rkeys);
+                } else {
+                    PhiloxKey pk = pre.pk;
+                    asm volatile("" : "+s"(pk.seed_lo), "+s"(pk.seed_hi));       // round keys computed anew, not kept
+                    explore_subtile_fast<(PRE == 2) ? 1 : 0>(pre.worker0 + b, t, wid, t * TILE, len, pre_bound, pre_sure,
+                                                             pre_has_sure, pre_skip, out, pk, pk);
+                }
             }
         }
     };
@@ -679,43 +692,47 @@ __global__ __launch_bounds__(BLOCK, SCOREF_MINB) void k_score_flat(const float* 
             // the round's entries go through the wave's staging area in LDS, so that every 128-byte line of the capture is
             // written by one store instruction, whole (a line written piecewise by several instructions can leave the
             // cache half-written and costs a read-modify-write in memory)
-            float* stf = stage + wid * (256 * WT);
-            if (f) {
-                uint32_t pos = below;
+            float* stf = stage + wid * (STAGED * WT);
+            auto part = [&](uint32_t eb) {            // entries eb .. eb + STAGED - 1 of the round
+                if (f) {
+                    uint32_t pos = below - eb;
 #pragma unroll
-                for (int cc = 0; cc < 4; ++cc) {
-                    if ((f >> cc) & 1u) {
-                        if (WT >= 4) {
+                    for (int cc = 0; cc < 4; ++cc) {
+                        if ((f >> cc) & 1u) {
+                            if (STAGED < 256 && pos >= STAGED) {
+                                // in another part
+                            } else if (WT >= 4 && WT % 4 == 0) {
 #pragma unroll
-                            for (int k = 0; k < WT; k += 4) {
-                                float4 q;
-                                q.x = cc == 0 ? x[k].x : cc == 1 ? x[k].y : cc == 2 ? x[k].z : x[k].w;
-                                q.y = cc == 0 ? x[k + 1].x : cc == 1 ? x[k + 1].y : cc == 2 ? x[k + 1].z : x[k + 1].w;
-                                q.z = cc == 0 ? x[k + 2].x : cc == 1 ? x[k + 2].y : cc == 2 ? x[k + 2].z : x[k + 2].w;
-                                q.w = cc == 0 ? x[k + 3].x : cc == 1 ? x[k + 3].y : cc == 2 ? x[k + 3].z : x[k + 3].w;
-                                *reinterpret_cast<float4*>(stf + pos * WT + k) = q;
+                                for (int k = 0; k < WT; k += 4) {
+                                    float4 q;
+                                    q.x = cc == 0 ? x[k].x : cc == 1 ? x[k].y : cc == 2 ? x[k].z : x[k].w;
+                                    q.y = cc == 0 ? x[k + 1].x : cc == 1 ? x[k + 1].y : cc == 2 ? x[k + 1].z : x[k + 1].w;
+                                    q.z = cc == 0 ? x[k + 2].x : cc == 1 ? x[k + 2].y : cc == 2 ? x[k + 2].z : x[k + 2].w;
+                                    q.w = cc == 0 ? x[k + 3].x : cc == 1 ? x[k + 3].y : cc == 2 ? x[k + 3].z : x[k + 3].w;
+                                    *reinterpret_cast<float4*>(stf + pos * WT + k) = q;
+                                }
+                            } else {
+#pragma unroll
+                                for (int k = 0; k < WT; ++k)
+                                    stf[pos * WT + k] = cc == 0 ? x[k].x : cc == 1 ? x[k].y : cc == 2 ? x[k].z : x[k].w;
                             }
-                        } else {
-#pragma unroll
-                            for (int k = 0; k < WT; ++k)
-                                stf[pos * WT + k] = cc == 0 ? x[k].x : cc == 1 ? x[k].y : cc == 2 ? x[k].z : x[k].w;
+                            ++pos;
                         }
-                        ++pos;
                     }
                 }
-            }
-            if (lane < padded - total) {          // fill the round's last line
+                if (lane < padded - total && (STAGED == 256 || total + lane - eb < STAGED)) {      // fill the round's last line
 #pragma unroll
-                for (int k = 0; k < WT; ++k) stf[(total + lane) * WT + k] = 0.0f;
-            }
-            wave_sync();
-            {
+                    for (int k = 0; k < WT; ++k) stf[(total + lane - eb) * WT + k] = 0.0f;
+                }
+                wave_sync();
                 const __amdgpu_buffer_rsrc_t rv = buffer_of(spec.vals + ((size_t)t * SUBS + wid) * SPEC_CAP * WT, SPEC_CAP * WT * 4u);
-                const uint32_t nchunk = padded * WT / 4u;          // 16-byte pieces: a multiple of 8 (whole lines)
+                const uint32_t nchunk = min(padded - eb, STAGED) * WT / 4u;          // 16-byte pieces: a multiple of 8 (whole lines)
                 for (uint32_t cidx = lane; cidx < nchunk; cidx += 64)
-                    buffer_store4_aux<SCOREF_CAP_AUX>(rv, spec_run * WT * 4u + cidx * 16u, *reinterpret_cast<const float4*>(stf + cidx * 4u));
-            }
-            wave_sync();
+                    buffer_store4_aux<SCOREF_CAP_AUX>(rv, (spec_run + eb) * WT * 4u + cidx * 16u, *reinterpret_cast<const float4*>(stf + cidx * 4u));
+                wave_sync();
+            };
+            part(0);
+            if (STAGED < 256 && padded > STAGED) part(STAGED);       // uniform
             spec_run += padded;
         }
     };
