@@ -714,7 +714,7 @@ static int score_impl(slimdp_ctx* ctx, const float* w, const float* const* g, ui
     PreArgs pre{};
     bool presample = false, pairs = false;
     if (ctx->opt_hint_mode == 0) ctx->pre.valid = false;      // a draw made on the side stream stays valid
-    if (ctx->hint.valid && ctx->opt_hint_mode == 0 && ctx->tl.quad_aligned) {
+    if (ctx->hint.valid && ctx->opt_hint_mode == 0) {
         std::vector<SegInit> init;
         uint64_t M = 0;
         bool narrow = false;
@@ -1111,12 +1111,12 @@ int slimdp_sample_explore(slimdp_ctx* ctx, const uint32_t* core_bits, const uint
 #define LAUNCH_DRAW(PAIRS)                                                                                               \
     do {                                                                                                                 \
         if (ctx->tl.quad_aligned)                                                                                        \
-            hipLaunchKernelGGL((k_explore_keys<1, PAIRS>), dim3(P, B), dim3(BLOCK), 0, st, ctx->d_tile_start,   \
+            hipLaunchKernelGGL((k_explore_keys<0, PAIRS>), dim3(P, B), dim3(BLOCK), 0, st, ctx->d_tile_start,   \
                                ctx->d_tile_seg, T, S, ctx->e_state, ctx->e_sure_bits, ctx->e_cand_bits,                  \
                                (PAIRS) ? ctx->e_pair_keys : ctx->e_cand_keys, ctx->e_cnt_cand,                           \
                                (PAIRS) ? ctx->pair_stride : ctx->keys_stride, worker0, pk);                              \
         else                                                                                                             \
-            hipLaunchKernelGGL((k_explore_keys<0, PAIRS>), dim3(P, B), dim3(BLOCK), 0, st, ctx->d_tile_start,   \
+            hipLaunchKernelGGL((k_explore_keys<1, PAIRS>), dim3(P, B), dim3(BLOCK), 0, st, ctx->d_tile_start,   \
                                ctx->d_tile_seg, T, S, ctx->e_state, ctx->e_sure_bits, ctx->e_cand_bits,                  \
                                (PAIRS) ? ctx->e_pair_keys : ctx->e_cand_keys, ctx->e_cnt_cand,                           \
                                (PAIRS) ? ctx->pair_stride : ctx->keys_stride, worker0, pk);                              \
@@ -1211,13 +1211,13 @@ int slimdp_explore_hint(slimdp_ctx* ctx, const uint64_t* k_seg, uint32_t worker0
     const uint32_t P = persistent_blocks(ctx, (uint32_t)ctx->opt_side_blocks, n_workers);
     const PhiloxKey pk{(uint32_t)ctx->seed, (uint32_t)(ctx->seed >> 32), (uint32_t)iteration, (uint32_t)(iteration >> 32)};
     const dim3 grid(P, n_workers), block(BLOCK);
-#define LAUNCH_SIDE_DRAW(FAST, PAIRS)                                                                                   \
-    hipLaunchKernelGGL((k_explore_keys<FAST, PAIRS>), grid, block, 0, ctx->side, ctx->d_tile_start, ctx->d_tile_seg,    \
+#define LAUNCH_SIDE_DRAW(MIS, PAIRS)                                                                                    \
+    hipLaunchKernelGGL((k_explore_keys<MIS, PAIRS>), grid, block, 0, ctx->side, ctx->d_tile_start, ctx->d_tile_seg,    \
                        ctx->T, ctx->n_seg, ctx->e_draw_state, ctx->e_sure_bits, ctx->e_cand_bits,                       \
                        (PAIRS) ? ctx->e_pair_keys : ctx->e_cand_keys, ctx->e_cnt_cand,                                  \
                        (PAIRS) ? ctx->pair_stride : ctx->keys_stride, worker0, pk)
-    if (ctx->tl.quad_aligned) { if (short_list) LAUNCH_SIDE_DRAW(1, 1); else LAUNCH_SIDE_DRAW(1, 0); }
-    else { if (short_list) LAUNCH_SIDE_DRAW(0, 1); else LAUNCH_SIDE_DRAW(0, 0); }
+    if (ctx->tl.quad_aligned) { if (short_list) LAUNCH_SIDE_DRAW(0, 1); else LAUNCH_SIDE_DRAW(0, 0); }
+    else { if (short_list) LAUNCH_SIDE_DRAW(1, 1); else LAUNCH_SIDE_DRAW(1, 0); }
 #undef LAUNCH_SIDE_DRAW
     SLIMDP_LAUNCHED(ctx, "k_explore_keys(side stream)");
     SLIMDP_HIP(ctx, hipEventRecord(ctx->ev_drawn, ctx->side));

@@ -60,7 +60,6 @@ __global__ __launch_bounds__(256) void k_fill_u32(uint32_t* __restrict__ p, uint
 // PAIRS = 1 (every segment's candidate zone is narrow): no candidate bitmap; the sub-tile's
 // slot holds (key, offset inside the sub-tile) pairs, at most PAIR_CAP of them: the count still
 // reports any beyond, which the gathering pass turns into the exact rerun.
-// wa, wb, wp: 32 words of LDS each, private to the calling wave (generic variant only).
 // ---------------------------------------------------------------------------------------
 struct PhiloxKey { uint32_t seed_lo, seed_hi, it_lo, it_hi; };
 // PAIRS = 1: a sub-tile's (key, offset) pairs live in a slot of PAIR_SLOT words at
@@ -80,84 +79,6 @@ __device__ __forceinline__ void wave_sync()
     __builtin_amdgcn_wave_barrier();
 }
 
-// Any tile start (tiles of a segmented model may begin inside a Philox block).
-template <int PAIRS>
-__device__ __forceinline__ void explore_subtile(uint32_t worker, uint32_t t, uint32_t sub, uint32_t start, uint32_t len,
-                                                uint32_t bound_m1, uint32_t sure_m1, uint32_t has_sure, uint32_t skip,
-                                                uint32_t* wa, uint32_t* wb, uint32_t* wp, DrawOut out, PhiloxKey pk)
-{
-    const uint32_t lane = lane_id();
-    const uint32_t off = sub * SUB;
-    const uint32_t sub_len = (len > off) ? ((len - off < SUB) ? len - off : SUB) : 0u;
-    const size_t wbase = (size_t)t * TILE_WORDS + sub * SUB_WORDS;
-    if (sub_len == 0 || skip) {                                   // uniform over the wave
-        if (lane < SUB_WORDS) {
-            if (!PAIRS) out.cand_bits[wbase + lane] = 0;
-            out.sure_bits[wbase + lane] = 0;
-        }
-        if (lane == 0) out.cnt_cand[(size_t)t * SUBS + sub] = 0;
-        return;
-    }
-    if (lane < SUB_WORDS) { wa[lane] = 0; wb[lane] = 0; }
-    wave_sync();
-    const uint32_t base = start + off;
-    const uint32_t g0 = base >> 2, g1 = (base + sub_len - 1u) >> 2;     // Philox blocks touched: at most 257
-    uint32_t key[5][4];
-    uint32_t is_cand = 0;
-#pragma unroll
-    for (int it = 0; it < 5; ++it) {
-        if (g1 - g0 < (uint32_t)it * 64u) break;                   // uniform: the 5th round only for unaligned starts
-        const uint32_t gi = g0 + (uint32_t)it * 64u + lane;
-        if (gi <= g1) {
-            uint32_t r[4];
-            philox4x32_10(gi, worker, pk.it_lo, pk.it_hi, pk.seed_lo, pk.seed_hi, r);
-            const uint32_t i0 = gi << 2;
-#pragma unroll
-            for (int cc = 0; cc < 4; ++cc) {
-                const uint32_t e = i0 + cc - base;                  // wraps below the sub-tile start
-                key[it][cc] = bound_m1 - r[cc];
-                if (e < sub_len) {
-                    if (has_sure && r[cc] <= sure_m1) atomicOr(&wa[e >> 5], 1u << (e & 31));
-                    else if (r[cc] <= bound_m1) {
-                        atomicOr(&wb[e >> 5], 1u << (e & 31));
-                        is_cand |= 1u << (it * 4 + cc);
-                    }
-                }
-            }
-        }
-    }
-    wave_sync();
-    const uint32_t cw = (lane < SUB_WORDS) ? wb[lane] : 0u;
-    const uint32_t pc = __popc(cw);
-    const uint32_t incl = wave_incl_scan(pc);
-    if (lane < SUB_WORDS) {
-        wp[lane] = incl - pc;
-        if (!PAIRS) out.cand_bits[wbase + lane] = cw;
-        out.sure_bits[wbase + lane] = wa[lane];
-    }
-    if (lane == SUB_WORDS - 1) out.cnt_cand[(size_t)t * SUBS + sub] = incl;
-    wave_sync();
-    if (is_cand) {
-#pragma unroll
-        for (int it = 0; it < 5; ++it) {
-#pragma unroll
-            for (int cc = 0; cc < 4; ++cc) {
-                if (is_cand & (1u << (it * 4 + cc))) {
-                    const uint32_t gi = g0 + (uint32_t)it * 64u + lane;
-                    const uint32_t e = (gi << 2) + cc - base;
-                    const uint32_t rank = wp[e >> 5] + __popc(wb[e >> 5] & mask_below(e & 31));
-                    if (!PAIRS) out.cand_keys[(size_t)base + rank] = key[it][cc];
-                    else if (rank < PAIR_CAP) {
-                        out.cand_keys[((size_t)t * SUBS + sub) * PAIR_SLOT + 2u * rank] = key[it][cc];
-                        out.cand_keys[((size_t)t * SUBS + sub) * PAIR_SLOT + 2u * rank + 1u] = e;
-                    }
-                }
-            }
-        }
-    }
-    wave_sync();
-}
-
 // Which of a lane's four parameters e0 .. e0+3 lie inside a ragged sub-tile of sub_len parameters.
 __device__ __forceinline__ uint32_t inside_mask(uint32_t e0, uint32_t sub_len)
 {
@@ -165,11 +86,14 @@ __device__ __forceinline__ uint32_t inside_mask(uint32_t e0, uint32_t sub_len)
     return (left >= 4u) ? 15u : ((1u << left) - 1u);
 }
 
-// The same for a sub-tile that starts on a Philox block (start + 1024*sub divisible by 4):
-// no LDS at all.  Round `it` covers the 256 parameters [256*it, 256*it+256) of the sub-tile
-// in index order (lane L owns parameters 4L..4L+3 of the round), so a candidate's place in
-// the key list is the number of candidates in earlier rounds plus a wave ballot count, and
-// the eight bitmap words of the round are OR-reductions over groups of eight lanes.
+// No LDS: round `it` covers the 256 parameters [256*it, 256*it+256) of the sub-tile in index order (lane L owns
+// parameters 4L..4L+3 of the round: one Philox block), so a candidate's place in the key list is the number of
+// candidates in earlier rounds plus a wave ballot count, and the eight bitmap words of the round are
+// OR-reductions over groups of eight lanes.
+// MIS = 1: tiles may begin inside a Philox block (segmented models).  Everything above then counts from the start of that
+// block, mis = start mod 4 positions earlier; the bitmaps are shifted down by mis at the end, and the block that holds the
+// sub-tile's last mis parameters is computed apart, from wave-uniform values, that is by the scalar unit beside the
+// vector one.  (As a fifth round through LDS bitmaps the draw of 7*10^6 parameters for 4 workers took 36 us.)
 // KEYS: PhiloxKey, or PhiloxRoundKeys of a caller that draws under one key many times (pk then only names the iteration).
 __device__ __forceinline__ void philox_words(uint32_t c0, uint32_t worker, const PhiloxKey& pk, const PhiloxKey&, uint32_t r[4])
 {
@@ -179,10 +103,10 @@ __device__ __forceinline__ void philox_words(uint32_t c0, uint32_t worker, const
 {
     philox4x32_10(c0, worker, pk.it_lo, pk.it_hi, rk, r);
 }
-template <int PAIRS, class KEYS = PhiloxKey>
-__device__ __forceinline__ void explore_subtile_fast(uint32_t worker, uint32_t t, uint32_t sub, uint32_t start, uint32_t len,
-                                                     uint32_t bound_m1, uint32_t sure_m1, uint32_t has_sure, uint32_t skip,
-                                                     DrawOut out, PhiloxKey pk, const KEYS& keys)
+template <int PAIRS, int MIS, class KEYS = PhiloxKey>
+__device__ __forceinline__ void explore_subtile(uint32_t worker, uint32_t t, uint32_t sub, uint32_t start, uint32_t len,
+                                                uint32_t bound_m1, uint32_t sure_m1, uint32_t has_sure, uint32_t skip,
+                                                DrawOut out, PhiloxKey pk, const KEYS& keys)
 {
     const uint32_t lane = lane_id();
     const uint32_t off = sub * SUB;
@@ -200,20 +124,29 @@ __device__ __forceinline__ void explore_subtile_fast(uint32_t worker, uint32_t t
         if (lane == 0) buffer_store1(rn, 0u, 0u);
         return;
     }
-    const uint32_t base = start + off;
+    const uint32_t base = start + off, mis = MIS ? base & 3u : 0u, g0 = base >> 2;
+    const uint32_t end = sub_len + mis;                              // positions mis .. end - 1 belong to the sub-tile
     uint32_t* ckeys = PAIRS ? out.cand_keys + ((size_t)t * SUBS + sub) * PAIR_SLOT : out.cand_keys + (size_t)base;
     const uint32_t sure_excl = has_sure ? sure_m1 + 1u : 0u;         // sure_m1 < bound_m1: no overflow
     const uint32_t width_m1 = bound_m1 - sure_excl;                  // candidate words are sure_excl .. bound_m1
     uint32_t run = 0, sword = 0, cword = 0;
+    // a candidate's key and place, by the lane that owns it
+    auto put = [&](uint32_t pos, uint32_t word, uint32_t e) {
+        if (!PAIRS) ckeys[pos] = bound_m1 - word;
+        else if (pos < PAIR_CAP) { ckeys[2u * pos] = bound_m1 - word; ckeys[2u * pos + 1u] = e - mis; }
+    };
 #pragma unroll
     for (int it = 0; it < 4; ++it) {
-        const uint32_t e0 = (uint32_t)it * 256u + lane * 4u;      // first of this lane's four parameters
+        const uint32_t e0 = (uint32_t)it * 256u + lane * 4u;      // first of this lane's four positions
         uint32_t r[4];
-        philox_words((base + e0) >> 2, worker, pk, keys, r);
+        philox_words(g0 + (e0 >> 2), worker, pk, keys, r);
+        uint32_t inside = 15u;
+        if (end != SUB) inside = inside_mask(e0, end);                // uniform: a ragged or shifted sub-tile
+        if (MIS && it == 0 && lane == 0) inside &= ~((1u << mis) - 1u);
         // sure flags of the four parameters, without branches (word below sure_excl)
         uint32_t fs = (r[0] < sure_excl ? 1u : 0u) | (r[1] < sure_excl ? 2u : 0u) | (r[2] < sure_excl ? 4u : 0u) |
                       (r[3] < sure_excl ? 8u : 0u);
-        if (sub_len != SUB) fs &= inside_mask(e0, sub_len);           // uniform: a ragged sub-tile
+        if (MIS || end != SUB) fs &= inside;
         // bitmap words: lanes 8j..8j+7 make word j of this round
         const uint32_t vs = or_reduce8(fs << (4u * (lane & 7u)));
         if ((lane & 7u) == (uint32_t)it) sword = vs;       // all eight lanes of a group hold the word: lane `it` of the group keeps it
@@ -225,7 +158,7 @@ __device__ __forceinline__ void explore_subtile_fast(uint32_t worker, uint32_t t
         if (__ballot(dmin <= width_m1) != 0ull) {                     // uniform
             uint32_t fc = (d0 <= width_m1 ? 1u : 0u) | (d1 <= width_m1 ? 2u : 0u) | (d2 <= width_m1 ? 4u : 0u) |
                           (d3 <= width_m1 ? 8u : 0u);
-            if (sub_len != SUB) fc &= inside_mask(e0, sub_len);
+            if (MIS || end != SUB) fc &= inside;
             if (!PAIRS) {
                 const uint32_t vc = or_reduce8(fc << (4u * (lane & 7u)));
                 if ((lane & 7u) == (uint32_t)it) cword = vc;
@@ -241,28 +174,42 @@ __device__ __forceinline__ void explore_subtile_fast(uint32_t worker, uint32_t t
             if (fc) {
                 uint32_t pos = run + below;
 #pragma unroll
-                for (int cc = 0; cc < 4; ++cc) {
-                    if ((fc >> cc) & 1u) {
-                        if (!PAIRS) ckeys[pos] = bound_m1 - r[cc];
-                        else if (pos < PAIR_CAP) { ckeys[2u * pos] = bound_m1 - r[cc]; ckeys[2u * pos + 1u] = e0 + cc; }
-                        ++pos;
-                    }
-                }
+                for (int cc = 0; cc < 4; ++cc)
+                    if ((fc >> cc) & 1u) put(pos++, r[cc], e0 + cc);
             }
             run += total;
         }
     }
-    // the 32 bitmap words of the sub-tile in one store of one whole line by lanes 0..31 in address order (scattered
-    // words make the memory side read the line first): word 8 * it + j sits in lane 8 * j + it
-    {
-        const int src = (int)(8u * (lane & 7u) + ((lane >> 3) & 3u));
-        const uint32_t sw = __shfl(sword, src, 64);
-        if (lane < SUB_WORDS) buffer_store1(rs, lane * 4u, sw);
-        if (!PAIRS) {
-            const uint32_t cw = __shfl(cword, src, 64);
-            if (lane < SUB_WORDS) buffer_store1(rc, lane * 4u, cw);
+    // the block beyond the four rounds: positions SUB .. end - 1, at most three (uniform)
+    uint32_t xs = 0, xc = 0;
+    if (MIS && end > SUB) {
+        uint32_t r[4];
+        philox4x32_10(g0 + SUB / 4u, worker, pk.it_lo, pk.it_hi, pk.seed_lo, pk.seed_hi, r);
+#pragma unroll
+        for (uint32_t cc = 0; cc < 3; ++cc) {
+            if (SUB + cc >= end) break;
+            if (r[cc] < sure_excl) xs |= 1u << cc;
+            else if (r[cc] - sure_excl <= width_m1) {
+                xc |= 1u << cc;
+                if (lane == 0) put(run, r[cc], SUB + cc);
+                ++run;
+            }
         }
     }
+    // the 32 bitmap words of the sub-tile in one store of one whole line by lanes 0..31 in address order (scattered
+    // words make the memory side read the line first): word 8 * it + j sits in lane 8 * j + it
+    const int src = (int)(8u * (lane & 7u) + ((lane >> 3) & 3u));
+    auto store = [&](const __amdgpu_buffer_rsrc_t& dst, uint32_t word, uint32_t extra) {
+        uint32_t v = __shfl(word, src, 64);
+        if (MIS && mis) {                                              // uniform
+            uint32_t next = __shfl_down(v, 1, 64);
+            if (lane == SUB_WORDS - 1u) next = extra;
+            v = (v >> mis) | (next << (32u - mis));
+        }
+        if (lane < SUB_WORDS) buffer_store1(dst, lane * 4u, v);
+    };
+    store(rs, sword, xs);
+    if (!PAIRS) store(rc, cword, xc);
     if (lane == 0) buffer_store1(rn, 0u, run);
 }
 
@@ -284,7 +231,7 @@ __device__ __forceinline__ void flush_hist(uint32_t* lds, uint32_t nb, uint32_t*
 }
 
 // PRE != 0 additionally draws the explorer zones of pre.nw workers for every tile
-// (explore_subtile_fast<PRE - 1>): integer work that runs while other waves wait for memory.
+// (explore_subtile): integer work that runs while other waves wait for memory.
 struct PreArgs {
     uint32_t nw, worker0, n_seg;
     const SegState* states;
@@ -415,7 +362,7 @@ __global__ __launch_bounds__(BLOCK, SCORE_MINB) void k_score(const float* __rest
                     out.cand_bits = pre.cand_bits + (size_t)b * T * TILE_WORDS;
                     out.cand_keys = pre.cand_keys + (size_t)b * pre.keys_stride;
                     out.cnt_cand = pre.cnt_cand + (size_t)b * T * SUBS;
-                    explore_subtile_fast<(PRE == 2) ? 1 : 0>(pre.worker0 + b, t, wid, start, len, pre_bound, pre_sure,
+                    explore_subtile<(PRE == 2) ? 1 : 0, 1>(pre.worker0 + b, t, wid, start, len, pre_bound, pre_sure,
                                                              pre_has_sure, pre_skip, out, pre.pk, pre.pk);
                 }
             }
@@ -589,12 +536,12 @@ __global__ __launch_bounds__(BLOCK, SCOREF_MINB) void k_score_flat(const float* 
                 out.cand_keys = pre.cand_keys + (size_t)b * pre.keys_stride;
                 out.cnt_cand = pre.cnt_cand + (size_t)b * T * SUBS;
                 if constexpr (KEYS_IN_VGPRS) {
-                    explore_subtile_fast<(PRE == 2) ? 1 : 0>(pre.worker0 + b, t, wid, t * TILE, len, pre_bound, pre_sure,
+                    explore_subtile<(PRE == 2) ? 1 : 0, 0>(pre.worker0 + b, t, wid, t * TILE, len, pre_bound, pre_sure,
                                                              pre_has_sure, pre_skip, out, pre.pk, rkeys);
                 } else {
                     PhiloxKey pk = pre.pk;
                     asm volatile("" : "+s"(pk.seed_lo), "+s"(pk.seed_hi));       // round keys computed anew, not kept
-                    explore_subtile_fast<(PRE == 2) ? 1 : 0>(pre.worker0 + b, t, wid, t * TILE, len, pre_bound, pre_sure,
+                    explore_subtile<(PRE == 2) ? 1 : 0, 0>(pre.worker0 + b, t, wid, t * TILE, len, pre_bound, pre_sure,
                                                              pre_has_sure, pre_skip, out, pk, pk);
                 }
             }
@@ -851,7 +798,7 @@ constexpr uint32_t SPEC_MARGIN = 1u << 17;
 
 // Stand-alone draw over every (worker, tile); each wave owns one sub-tile of the block's
 // tiles.  grid (blocks, n_workers).
-template <int FAST, int PAIRS>
+template <int MIS, int PAIRS>
 __global__ __launch_bounds__(BLOCK) void k_explore_keys(const uint32_t* __restrict__ tile_start,
                                                         const uint32_t* __restrict__ tile_seg, uint32_t T,
                                                         uint32_t n_seg, const SegState* __restrict__ states,
@@ -859,7 +806,6 @@ __global__ __launch_bounds__(BLOCK) void k_explore_keys(const uint32_t* __restri
                                                         uint32_t* __restrict__ cand_keys, uint32_t* __restrict__ cnt_cand,
                                                         uint64_t keys_stride, uint32_t worker0, PhiloxKey pk)
 {
-    __shared__ uint32_t wa[FAST ? 1 : 4][SUB_WORDS], wb[FAST ? 1 : 4][SUB_WORDS], wp[FAST ? 1 : 4][SUB_WORDS];
     const uint32_t b = blockIdx.y, worker = worker0 + b, wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
     const uint32_t t0 = (uint32_t)((uint64_t)T * blockIdx.x / gridDim.x);
     const uint32_t t1 = (uint32_t)((uint64_t)T * (blockIdx.x + 1) / gridDim.x);
@@ -875,11 +821,7 @@ __global__ __launch_bounds__(BLOCK) void k_explore_keys(const uint32_t* __restri
         const uint32_t sure_m1 = st->sure_m1, has_sure = st->has_gt;
         const uint32_t skip = st->need0 == 0;
         const uint32_t start = tile_start[t], len = tile_start[t + 1] - start;
-        if (FAST)
-            explore_subtile_fast<PAIRS>(worker, t, wid, start, len, bound_m1, sure_m1, has_sure, skip, out, pk, pk);
-        else
-            explore_subtile<PAIRS>(worker, t, wid, start, len, bound_m1, sure_m1, has_sure, skip, wa[FAST ? 0 : wid],
-                            wb[FAST ? 0 : wid], wp[FAST ? 0 : wid], out, pk);
+        explore_subtile<PAIRS, MIS>(worker, t, wid, start, len, bound_m1, sure_m1, has_sure, skip, out, pk, pk);
     }
 }
 
