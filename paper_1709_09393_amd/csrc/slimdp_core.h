@@ -418,6 +418,7 @@ __global__ __launch_bounds__(BLOCK) void k_core_emit(CoreArgs a, uint32_t per_gr
                                                      uint32_t* __restrict__ out_off, uint32_t* __restrict__ pub_bits, uint32_t expected)
 {
     __shared__ uint32_t kb[4][SUBS * 16 * CORE_KPL];
+    __shared__ uint16_t stage[4][EMIT_STAGE];
     __shared__ uint2 part[4];
     const uint32_t lane = lane_id(), wid = threadIdx.x >> 6;
     const uint32_t g = blockIdx.x / per_group, r = blockIdx.x % per_group;
@@ -494,23 +495,7 @@ __global__ __launch_bounds__(BLOCK) void k_core_emit(CoreArgs a, uint32_t per_gr
             out_off[a.T] = first + oincl;
             if (first + oincl != expected) atomicOr(&a.flags[1], 1u);
         }
-        uint32_t o = first + oincl - ocnt;
-        {
-            uint32_t m = fm0;
-            while (m) {
-                const uint32_t p = __ffs(m) - 1;
-                m &= m - 1;
-                if (o < expected) out_idx[o] = tr.start + lane * 64u + p;     // never beyond the caller's list
-                ++o;
-            }
-            m = fm1;
-            while (m) {
-                const uint32_t p = __ffs(m) - 1;
-                m &= m - 1;
-                if (o < expected) out_idx[o] = tr.start + lane * 64u + 32u + p;
-                ++o;
-            }
-        }
+        emit_indices(fm0, fm1, oincl, tr.start, first, expected, stage[wid], out_idx);
         // the public bitmap: whole words directly; words shared with a neighbouring tile (cleared by k_core_build) by OR
         const uint32_t sft = tr.start & 31u;
         uint32_t* pb = pub_bits + (tr.start >> 5) + 2 * lane;

@@ -502,6 +502,7 @@ __global__ __launch_bounds__(1024, 8) void k_explore_emit(const uint32_t* __rest
                                                        PhiloxKey pk, const uint32_t* __restrict__ sure_bits, MutPtrTab out_off,
                                                        MutPtrTab out_idx, uint32_t expected, uint32_t* __restrict__ flags)
 {
+    __shared__ uint16_t stage[16][EMIT_STAGE];
     const uint32_t b0 = blockIdx.y * BPW;
     if (flags[0] != 0) {                         // nobody raises the flag while this kernel runs
         const uint32_t b = b0 + blockIdx.x;
@@ -534,21 +535,7 @@ __global__ __launch_bounds__(1024, 8) void k_explore_emit(const uint32_t* __rest
         const uint32_t incl = wave_incl_scan(ocnt);
         uint32_t* out = static_cast<uint32_t*>(out_idx.p[b]);
         if (t == T - 1 && lane == 63 && off_t[bb] + incl != expected) atomicOr(&flags[1], 1u);
-        uint32_t o = off_t[bb] + incl - ocnt;
-        uint32_t m = fm0;
-        while (m) {
-            const uint32_t p = __ffs(m) - 1;
-            m &= m - 1;
-            if (o < expected) out[o] = tr.start + lane * 64u + p;     // never beyond the caller's list
-            ++o;
-        }
-        m = fm1;
-        while (m) {
-            const uint32_t p = __ffs(m) - 1;
-            m &= m - 1;
-            if (o < expected) out[o] = tr.start + lane * 64u + 32u + p;
-            ++o;
-        }
+        emit_indices(fm0, fm1, incl, tr.start, off_t[bb], expected, stage[threadIdx.x >> 6], out);
     }
 }
 
