@@ -1401,9 +1401,8 @@ __global__ __launch_bounds__(2 * BLOCK) void k_pack_stream_ws(PtrTab g, uint32_t
 // Explorers: each entry of the tile takes a ticket at its position (LDS byte counter).  A
 // position with one or two entries is summed in ticket order -- with at most two addends
 // the binary32 sum does not depend on their order.  Positions with three or more entries
-// (rare), or with two on top of a core sum (only if a list overlaps the core), go to a short
-// list that one thread replays in worker order.  Tiles with more
-// explorer entries than the fast path holds in registers, or with too many such positions,
+// (rare), or with two on top of a core sum (only if a list overlaps the core), are summed in worker order, a
+// barrier to a worker.  Tiles with more explorer entries than the fast path holds in registers
 // take the generic path: entries staged through LDS and applied one worker at a time.
 //
 // All loads of a tile (its w, its core slice, its explorer entries) are requested in one
@@ -1424,10 +1423,12 @@ __device__ __forceinline__ float core_sum(const PtrTab& core_val, uint32_t nw, u
     return a;
 }
 
-constexpr int MERGE_R = 4;                 // explorer entries per thread kept in registers
-constexpr uint32_t MERGE_HOT_CAP = 128;
+// R: explorer entries per thread kept in registers.  Four serve the tiles of the paper's ratios; denser requests get a
+// variant with more, chosen on the host from the expected number (slimdp_merge): a tile that does not fit takes the
+// generic path, which stages its entries through LDS 256 at a time.
 constexpr uint32_t MERGE_STAGE = 256;
 
+template <int R>
 __global__ __launch_bounds__(BLOCK) void k_merge(float* __restrict__ w, float lr, uint32_t nw,
                                                  const uint32_t* __restrict__ tile_start,
                                                  const uint32_t* __restrict__ core_idx, const uint32_t* __restrict__ core_off,
@@ -1437,10 +1438,7 @@ __global__ __launch_bounds__(BLOCK) void k_merge(float* __restrict__ w, float lr
     __shared__ float acc[TILE];
     __shared__ uint32_t cnt[TILE / 4];     // one byte per position: bit 7 = core, low bits = explorer entries
     __shared__ uint32_t elo[MAXW], ecn[MAXW];
-    __shared__ uint16_t hpos[MERGE_HOT_CAP];
-    __shared__ uint8_t hq[MERGE_HOT_CAP];
-    __shared__ float hval[MERGE_HOT_CAP];
-    __shared__ uint32_t hcount;
+    __shared__ uint32_t hot;               // some position has more entries than ticket order can sum
     __shared__ uint16_t spos[MERGE_STAGE];
     __shared__ float sval[MERGE_STAGE];
     const uint32_t t = blockIdx.x;
@@ -1470,7 +1468,7 @@ __global__ __launch_bounds__(BLOCK) void k_merge(float* __restrict__ w, float lr
         }
     }
     for (uint32_t x = threadIdx.x; x < TILE / 4; x += BLOCK) cnt[x] = 0;
-    if (threadIdx.x == 0) hcount = 0;
+    if (threadIdx.x == 0) hot = 0;
     if (threadIdx.x < nw) {
         const uint32_t* eo = static_cast<const uint32_t*>(expl_off.p[threadIdx.x]);
         const uint32_t lo = eo[t];
@@ -1480,13 +1478,13 @@ __global__ __launch_bounds__(BLOCK) void k_merge(float* __restrict__ w, float lr
     __syncthreads();
     uint32_t E = 0;
     for (uint32_t q = 0; q < nw; ++q) E += ecn[q];
-    const bool fast = E <= (uint32_t)(BLOCK * MERGE_R);
+    const bool fast = E <= (uint32_t)(BLOCK * R);
     // explorer entries of the fast path: requested now, held in registers
-    uint32_t epos[MERGE_R], eq[MERGE_R], etk[MERGE_R];
-    float eval[MERGE_R];
+    uint32_t epos[R], eq[R], etk[R];
+    float eval[R];
     if (fast) {
 #pragma unroll
-        for (int i = 0; i < MERGE_R; ++i) {
+        for (int i = 0; i < R; ++i) {
             const uint32_t x = threadIdx.x + (uint32_t)i * BLOCK;
             epos[i] = 0xFFFFFFFFu; eq[i] = 0; etk[i] = 0; eval[i] = 0.0f;
             if (x < E) {
@@ -1508,7 +1506,7 @@ __global__ __launch_bounds__(BLOCK) void k_merge(float* __restrict__ w, float lr
     }
     if (fast) {
 #pragma unroll
-        for (int i = 0; i < MERGE_R; ++i) {
+        for (int i = 0; i < R; ++i) {
             if (epos[i] != 0xFFFFFFFFu) {
                 const uint32_t sh = 8u * (epos[i] & 3u);
                 etk[i] = (atomicAdd(&cnt[epos[i] >> 2], 1u << sh) >> sh) & 0x7Fu;
@@ -1516,12 +1514,11 @@ __global__ __launch_bounds__(BLOCK) void k_merge(float* __restrict__ w, float lr
         }
     }
     __syncthreads();
-    uint32_t nhot = 0;
     if (fast) {
         // first and second entry of a position, in ticket order; the rest is replayed in worker order
-        uint32_t tot[MERGE_R];
+        uint32_t tot[R];
 #pragma unroll
-        for (int i = 0; i < MERGE_R; ++i) {
+        for (int i = 0; i < R; ++i) {
             tot[i] = 0;
             if (epos[i] != 0xFFFFFFFFu) {
                 const uint32_t byte = (cnt[epos[i] >> 2] >> (8u * (epos[i] & 3u))) & 0xFFu;
@@ -1532,39 +1529,31 @@ __global__ __launch_bounds__(BLOCK) void k_merge(float* __restrict__ w, float lr
                 if (tot[i] <= 2u) {
                     if (etk[i] == 0) acc[epos[i]] = ((byte & 0x80u) ? acc[epos[i]] : 0.0f) + eval[i];
                 } else {
-                    const uint32_t slot = atomicAdd(&hcount, 1u);
-                    if (slot < MERGE_HOT_CAP) { hpos[slot] = (uint16_t)epos[i]; hq[slot] = (uint8_t)eq[i]; hval[slot] = eval[i]; }
+                    hot = 1u;
+                    if (etk[i] == 0 && !(byte & 0x80u)) acc[epos[i]] = 0.0f;
                 }
             }
         }
         __syncthreads();
 #pragma unroll
-        for (int i = 0; i < MERGE_R; ++i)
+        for (int i = 0; i < R; ++i)
             if (epos[i] != 0xFFFFFFFFu && tot[i] == 2u && etk[i] == 1u) acc[epos[i]] = acc[epos[i]] + eval[i];
-        nhot = hcount;
-        if (nhot && nhot <= MERGE_HOT_CAP && threadIdx.x == 0) {
-            for (uint32_t i = 0; i < nhot; ++i) {
-                const uint32_t pos = hpos[i];
-                if (!((cnt[pos >> 2] >> (8u * (pos & 3u))) & 0x80u)) acc[pos] = 0.0f;
+        // positions with more: every worker's entries in turn, straight from the registers (a serial replay from a list, by one
+        // thread a position, took longer than the generic path where a third of the tile's positions are sent)
+        if (hot) {                               // uniform: written before the barrier above
+            for (uint32_t q = 0; q < nw; ++q) {
+#pragma unroll
+                for (int i = 0; i < R; ++i)
+                    if (epos[i] != 0xFFFFFFFFu && tot[i] > 2u && eq[i] == q) acc[epos[i]] = acc[epos[i]] + eval[i];
+                __syncthreads();
             }
-            for (uint32_t q = 0; q < nw; ++q)
-                for (uint32_t i = 0; i < nhot; ++i)
-                    if (hq[i] == q) acc[hpos[i]] = acc[hpos[i]] + hval[i];
         }
     }
     __syncthreads();
-    if (!fast || nhot > MERGE_HOT_CAP) {
+    if (!fast) {
         // generic path: every explorer entry staged through LDS, applied one worker at a time.
         // The counters keep their core bits; a set low bit now means "an explorer sum is in acc".
         for (uint32_t x = threadIdx.x; x < TILE / 4; x += BLOCK) cnt[x] &= 0x80808080u;
-        if (nhot > MERGE_HOT_CAP) {       // the fast path wrote partial sums over core sums: redo the core
-            __syncthreads();
-            for (uint32_t j = c0 + threadIdx.x; j < c1; j += BLOCK) {
-                const uint32_t pos = core_idx[j] - start;
-                const float a = core_sum(core_val, nw, j);
-                if (pos < len) acc[pos] = a;
-            }
-        }
         __syncthreads();
         uint8_t* hit = reinterpret_cast<uint8_t*>(cnt);
         for (uint32_t cb = 0; cb < E; cb += MERGE_STAGE) {

@@ -161,3 +161,39 @@ def test_explorer_lists_and_offsets_at_the_edges_of_segments_and_zones(name, W, 
             assert np.array_equal(u32(idx[q]), want), what
             assert np.array_equal(u32(off[q]), np.searchsorted(want.astype(np.int64), ts).astype(np.uint32)), what
     sd.close()
+
+
+@pytest.mark.parametrize("overlap", [False, True])
+@pytest.mark.parametrize("W,pct", [(1, 2), (3, 17), (8, 6), (8, 11), (9, 10), (16, 17), (32, 3)])
+def test_merge_variants_by_explorer_density(W, pct, overlap):
+    """Entries per tile for 4, 8 and 16 registers a thread and for the staged path, most positions sent by several workers; with
+    overlap the lists also meet the core, whose sum then comes first."""
+    n = 4096 * 6 + 1111
+    rng = np.random.default_rng(W * 100 + pct)
+    w_h = rng.standard_normal(n).astype(np.float32)
+    core = oracle.select_core(np.abs(rng.standard_normal(n)).astype(np.float32), n // 10)
+    sd = binding.SlimDP(n, W)
+    ts = sd.tile_starts().astype(np.int64)
+    bits, off = torch.empty((n + 31) // 32, dtype=torch.int32, device=dev()), torch.empty(sd.T + 1, dtype=torch.int32, device=dev())
+    _, off, epoch = sd.import_core(to_dev(core), [len(core)], bits, off)
+    pool = np.arange(n) if overlap else np.setdiff1d(np.arange(n), core)
+    m = len(pool) * pct // 100
+    idx = [np.sort(rng.choice(pool, m, replace=False)).astype(np.uint32) for _ in range(W)]
+    val = [(rng.standard_normal(m) * 10.0 ** rng.integers(-3, 4, m)).astype(np.float32) for _ in range(W)]
+    core_val = [(rng.standard_normal(len(core)) * 10.0 ** rng.integers(-3, 4, len(core))).astype(np.float32) for _ in range(W)]
+    w = to_dev(w_h)
+    sd.merge(w, 0.1, epoch, to_dev(core), off, [to_dev(x) for x in core_val], [to_dev(x) for x in idx],
+             [to_dev(np.searchsorted(x.astype(np.int64), ts).astype(np.uint32)) for x in idx], [to_dev(x) for x in val])
+    sd.synchronize()
+    # the interface's order: +0, the core values in worker order, then the explorer values in worker order, one fused step
+    acc, sent = np.zeros(n, np.float32), np.zeros(n, bool)
+    for v in core_val:
+        acc[core] = acc[core] + v
+    sent[core] = True
+    for i, v in zip(idx, val):
+        acc[i] = acc[i] + v
+        sent[i] = True
+    exact = w_h.astype(np.longdouble) - np.longdouble(np.float32(0.1)) * acc.astype(np.longdouble)     # 64 bits hold the product; one rounding
+    want = np.where(sent, exact.astype(np.float32), w_h)
+    assert np.array_equal(u32(w), want.view(np.uint32))
+    sd.close()
