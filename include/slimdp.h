@@ -139,7 +139,7 @@ int slimdp_synchronize(slimdp_ctx* ctx);
  *       storing waves apart; 0: one set of waves, with pack_nbuf tiles in LDS); results do not depend on them.
  *   "explore_force_fallback" (0/1/2), "explore_per_tile_tail" (0/1): test switches: make
  *       the explorer's first zones miss (1: too few candidates, 2: sure zone too large) so
- *       that the exact rerun runs; never take the short-list tail.
+ *       that the exact rerun runs; draw candidates as bitmaps and keys, never as pairs.
  *   "core_predict" (0/1/2, default 1): flat models with 16-byte aligned arrays: slimdp_score also sorts every whole tile
  *       against the threshold bin of the previous selection, so that slimdp_select_core(..REUSE_HISTOGRAM) need not read
  *       the scores again when its histogram confirms that bin (otherwise it does, as without the option).  0 switches

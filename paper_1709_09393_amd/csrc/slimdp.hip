@@ -719,7 +719,9 @@ static int score_impl(slimdp_ctx* ctx, const float* w, const float* const* g, ui
         uint64_t M = 0;
         bool narrow = false;
         if (explorer_init(ctx, "slimdp_score(hint)", ctx->hint.k_seg.data(), ctx->hint.m_seg.data(), ctx->hint.n_workers, init,
-                          &M, &narrow, &pairs) == SLIMDP_OK && narrow && M > 0) {
+                          &M, &narrow, &pairs) == SLIMDP_OK && narrow && M > 0 &&
+            // tiles inside random blocks: the first request, not a scoring pass, allocates the wide buffer
+            (pairs || ctx->e_cand_keys || ctx->tl.quad_aligned)) {
             rc = wait_for_side(ctx);         // the draw's buffers may still be read by work on the side stream
             if (rc) return rc;
             rc = init_states(ctx, ctx->e_state, init, ctx->hint.n_workers, false, ctx->stream);

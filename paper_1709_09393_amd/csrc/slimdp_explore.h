@@ -11,7 +11,8 @@
 //   k_explore_emit      bitmap minus core -> ascending index lists; the exact rerun if a zone missed
 // A segment's slack is 6 sqrt(m) + 32 on each side of m, so its list has at most 12 sqrt(n_s) + 64 entries and some spread:
 // one block ranks it in the time of a launch or two (19 k of 138 M parameters; 1.7 k of 10^6), where levels, thresholds,
-// marks, ties and scans as kernels of their own made sixteen launches of 2 to 8 us each.
+// marks, ties and scans as kernels of their own made sixteen launches of 2 to 8 us each.  A whole iteration of 10^6
+// parameters went from 219 to 139 us, of 7*10^6 in 57 segments from 370 to 263 us, of 20*10^6 from 501 to 471 us.
 #pragma once
 #include "slimdp_kernels.h"
 
@@ -247,7 +248,9 @@ __global__ __launch_bounds__(BLOCK) void k_explore_collect_wide(const uint32_t* 
 // wanted, ties at the threshold key going to the lowest positions.  The list's first KEEP * NT entries stay in registers
 // from the first level to the last, longer ones are read again.  A chosen candidate is set in the sure bitmap and added to its
 // tile's count; the prefix of the counts gives the tile offsets (every wave owns a run of tiles, whose sums
-// are known beforehand).  Bound by latency: a chain of some ten trips to the L2 and as many block barriers.
+// are known beforehand).  Bound by latency: a chain of some ten trips to the L2 and as many block barriers; 10 us at 10^6
+// parameters, 55 us for the 20,400 entries of 20*10^6 at 17 %.  More blocks to a list, each marking a share, take
+// 43 us there, but are slower on short lists (14 -> 17 us for 228 of them) and beside a kernel that fills the chip.
 // A demand that the zones cannot meet raises the rerun flag.  grid (n_seg, n_workers), NT threads.
 // ---------------------------------------------------------------------------------------
 constexpr uint32_t TIE_CAP = 1024;
