@@ -144,6 +144,7 @@ __device__ __forceinline__ uint32_t block_excl_scan(uint32_t v, uint32_t* wtot, 
 __device__ __forceinline__ uint32_t elem_vec(int j) { return (uint32_t)(j >> 2) * 1024u + threadIdx.x * 4u + (uint32_t)(j & 3); }
 __device__ __forceinline__ uint32_t elem_scl(int j) { return (uint32_t)j * BLOCK + threadIdx.x; }
 
+__device__ __forceinline__ uint32_t mask_below(uint32_t bit) { return (1u << bit) - 1u; }   // bit in 0..31
 
 // Accesses to data that is touched once (streamed): NT != 0 marks them non-temporal, so that they do not
 // push lines that will be used again out of the caches.  A non-temporal store must cover whole 128-byte lines

@@ -204,7 +204,7 @@ __device__ __forceinline__ void explore_subtile(uint32_t worker, uint32_t t, uin
         if (MIS && mis) {                                              // uniform
             uint32_t next = __shfl_down(v, 1, 64);
             if (lane == SUB_WORDS - 1u) next = extra;
-            v = (v >> mis) | (next << (32u - mis));
+            v = (v >> mis) | (next << ((32u - mis) & 31u));          // mis is 1 to 3
         }
         if (lane < SUB_WORDS) buffer_store1(dst, lane * 4u, v);
     };
