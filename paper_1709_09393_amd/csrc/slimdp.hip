@@ -338,8 +338,9 @@ template <class Tab, class P> Tab make_tab(P const* tab, uint32_t nw)
 }
 
 // Whether the device holds what the host's notes say it holds once everything enqueued has run (clear histograms, the
-// segments' core sizes).  A call recorded into a graph runs later, and any number of times: it must set what it needs by
-// itself, and from then on a replay may have left other contents than the eager calls did.
+// segments' core sizes).  A call recorded into a graph runs later, any number of times or never: it must set what it needs
+// by itself, and from then on a replay may have left other contents than the eager calls did.  Every call that goes by
+// such a note, or leaves one, asks here before it looks at the note: one that did not ask would go unnoticed when recorded.
 bool device_state_known(slimdp_ctx* c)
 {
     if (c->stream && !c->recorded) {         // the default stream cannot be recorded
@@ -705,7 +706,8 @@ static int score_impl(slimdp_ctx* ctx, const float* w, const float* const* g, ui
     ctx->hist_pending = false;
     ctx->cls_by_score = false;
     int rc = SLIMDP_OK;
-    if (!ctx->hist_clean || !device_state_known(ctx)) { rc = fill(ctx, ctx->c_hist, (uint64_t)ctx->n_seg * H_STRIDE, 0u); if (rc) return rc; }
+    const bool known = device_state_known(ctx);
+    if (!known || !ctx->hist_clean) { rc = fill(ctx, ctx->c_hist, (uint64_t)ctx->n_seg * H_STRIDE, 0u); if (rc) return rc; }
     ctx->hist_clean = false;
     PtrTab gt = make_tab<PtrTab>(g, W);
     int vec_ok = aligned16(w) && aligned16(score);
@@ -900,6 +902,7 @@ static int select_core_impl(slimdp_ctx* ctx, const float* score, const uint64_t*
     const uint32_t T = ctx->T, S = ctx->n_seg;
     int rc = wait_for_side(ctx);             // an explorer request on the side stream may still read the bitmap this call rewrites
     if (rc) return rc;
+    const bool known = device_state_known(ctx);
     CoreArgs a{};
     a.tile_start = ctx->d_tile_start; a.tile_seg = ctx->d_tile_seg; a.seg_first_tile = ctx->d_seg_first_tile;
     a.n = ctx->n; a.T = T; a.n_seg = S;
@@ -912,7 +915,7 @@ static int select_core_impl(slimdp_ctx* ctx, const float* score, const uint64_t*
     a.tile_pre = ctx->c_tile_pre; a.group_tail = ctx->c_group_tail; a.flags = ctx->d_flags;
     if ((T + a.groups - 1) / a.groups > GROUP_MAX)
         return fail(ctx, SLIMDP_ERR_INVALID_ARG, "slimdp_select_core: %u tiles in %u groups", T, a.groups);
-    if (S > 1 && (!device_state_known(ctx) || !std::equal(k_seg, k_seg + S, ctx->c_plan_k.begin(), ctx->c_plan_k.end()))) {
+    if (S > 1 && (!known || !std::equal(k_seg, k_seg + S, ctx->c_plan_k.begin(), ctx->c_plan_k.end()))) {
         ctx->c_plan_k.clear();               // whatever happens below: what the device holds is not known yet
         uint32_t base = 0;
         for (uint32_t s0 = 0; s0 < S; s0 += PLAN_CHUNK) {
@@ -926,7 +929,7 @@ static int select_core_impl(slimdp_ctx* ctx, const float* score, const uint64_t*
         ctx->c_plan_k.assign(k_seg, k_seg + S);
     }
     if (!reuse) {
-        if (!ctx->hist_clean || !device_state_known(ctx)) { rc = fill(ctx, ctx->c_hist, (uint64_t)S * H_STRIDE, 0u); if (rc) return rc; }
+        if (!known || !ctx->hist_clean) { rc = fill(ctx, ctx->c_hist, (uint64_t)S * H_STRIDE, 0u); if (rc) return rc; }
         ctx->hist_clean = false;
         uint32_t P0 = persistent_blocks(ctx, 4, 1);
         if (S == 1) P0 = (uint32_t)std::min<uint64_t>((uint64_t)ctx->cus * 4, (ctx->n / 4 + BLOCK - 1) / BLOCK + 1);
@@ -953,7 +956,7 @@ static int select_core_impl(slimdp_ctx* ctx, const float* score, const uint64_t*
     hipLaunchKernelGGL(k_core_emit, dim3(a.groups * per_group), dim3(BLOCK), 0, ctx->stream, a, per_group, core_idx, core_off,
                        core_bits, (uint32_t)K);
     SLIMDP_LAUNCHED(ctx, "k_core_emit");
-    ctx->hist_clean = true;
+    ctx->hist_clean = known;                 // a recorded selection has cleared nothing yet
     *core_epoch = ++ctx->epoch;
     ctx->last_K = K; ctx->have_last_K = true;
     if (spec_sel) { ctx->spec.core_epoch = ctx->epoch; ctx->spec.next_written = true; }
@@ -1028,7 +1031,7 @@ int slimdp_select_core_static(const float* score, uint64_t n, uint64_t k, uint32
         return fail(nullptr, SLIMDP_ERR_WORKSPACE, "slimdp_select_core_static: %zu bytes of workspace needed, %u available",
                     cv.pos, (unsigned)SLIMDP_STATIC_SCRATCH_BYTES);
     // the array keeps the previous call's contents: a flat model reads no tables, and the selection leaves the
-    // histogram clear unless a launch failed on the way
+    // histogram clear unless it was only recorded or a launch failed on the way
     tmp.hist_clean = !sdv.dirty;
     uint64_t epoch = 0;
     const int rc = select_core_impl(&tmp, score, &k, 0u, core_idx, core_bits, core_off, &epoch);

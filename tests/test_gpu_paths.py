@@ -130,6 +130,87 @@ def test_recorded_selection_replays_beside_eager_ones(segments):
     sd.close()
 
 
+@pytest.mark.parametrize("recorded", ["score and select", "select", "score"])
+@pytest.mark.parametrize("segments", [1, 5])
+def test_eager_calls_stay_right_after_calls_that_were_only_recorded(segments, recorded):
+    """The first recording begins after an eager scoring pass whose counts nobody used; eager passes follow before the first
+    replay (which may never come) and between replays."""
+    n = 5 * 4096 * 3 + 17
+    wl = workloads.TINY.scaled(n)
+    so = offsets([n]) if segments == 1 else offsets([4096 + 5, 3, 20_000, 30_001, n - 4096 - 5 - 3 - 50_001])
+    ks = [int(s) // 7 for s in np.diff(so)]
+    w_h, g_h = wl.weights(), wl.gradients(0)
+    w, g = to_dev(w_h), [to_dev(x) for x in g_h]
+    want = oracle.select_core(oracle.score(w_h, g_h, wl.c), ks, so)
+    st = torch.cuda.Stream()
+    st.wait_stream(torch.cuda.current_stream())
+    sd = binding.SlimDP(n, wl.W, seg_off=so, stream=st)
+    S = torch.empty_like(w)
+    idx = torch.empty(sum(ks), dtype=torch.int32, device=dev())
+    bits = torch.empty((n + 31) // 32, dtype=torch.int32, device=dev())
+    off = torch.empty(sd.T + 1, dtype=torch.int32, device=dev())
+    torch.cuda.synchronize()
+
+    def right():
+        sd.synchronize()
+        return np.array_equal(u32(idx), want) and np.array_equal(u32(bits), oracle.core_bits(n, want)) and int(u32(off)[-1]) == len(want)
+
+    with torch.cuda.stream(st):
+        sd.score(w, g, wl.c, out=S)              # counted, not used
+    sd.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=st):
+        if "score" in recorded:
+            sd.score(w, g, wl.c, out=S)
+        if "select" in recorded:
+            sd.select_core(S, ks, reuse_histogram=True, core_idx=idx, core_bits=bits, core_off=off)
+    with torch.cuda.stream(st):
+        for _ in range(3):
+            idx.zero_()
+            sd.score(w, g, wl.c, out=S)
+            sd.select_core(S, ks, reuse_histogram=True, core_idx=idx, core_bits=bits, core_off=off)
+            assert right(), "eager"
+            idx.zero_()
+            if recorded == "select":
+                sd.score(w, g, wl.c, out=S)
+            graph.replay()
+            if recorded == "score":              # counted by the replay, not used
+                sd.score(w, g, wl.c, out=S)
+                sd.select_core(S, ks, reuse_histogram=True, core_idx=idx, core_bits=bits, core_off=off)
+            assert right(), "replay"
+            sd.score(w, g, wl.c, out=S)          # counted, not used
+    sd.close()
+
+
+def test_static_selection_recorded_between_eager_calls():
+    n, k = 50_003, 7_000
+    rng = np.random.default_rng(5)
+    one, two = (np.abs(rng.standard_normal(n)).astype(np.float32) for _ in range(2))
+    S = to_dev(one)
+    out = [torch.empty(c, dtype=torch.int32, device=dev()) for c in (k, (n + 31) // 32, binding.num_tiles(n) + 1)]
+    st = torch.cuda.Stream()
+    st.wait_stream(torch.cuda.current_stream())
+
+    def check(values):
+        st.synchronize()
+        assert np.array_equal(u32(out[0]), oracle.select_core(values, k))
+        out[0].zero_()
+        torch.cuda.synchronize()
+
+    with torch.cuda.stream(st):
+        binding.select_core_static(S, k, *out)
+        check(one)
+        graph = torch.cuda.CUDAGraph()
+        with torch.cuda.graph(graph, stream=st):
+            binding.select_core_static(S, k, *out)
+        for values in (one, two, one):
+            S.copy_(to_dev(values))
+            binding.select_core_static(S, k, *out)
+            check(values)
+            graph.replay()
+            check(values)
+
+
 @pytest.mark.parametrize("per_tile_tail", [0, 1])
 @pytest.mark.parametrize("W", [1, 5, 9])
 @pytest.mark.parametrize("name", sorted(SEGMENTS) + ["one_segment", "more_blocks_than_run_at_a_time"])
