@@ -263,9 +263,9 @@ __global__ __launch_bounds__(BLOCK) void k_core_build(const float* __restrict__ 
             if (!ok) atomicOr(&a.flags[1], 2u);
         }
         uint32_t tt = t, te = seg_t1;
-        if (skip) {                                      // a ragged last tile at most; one block looks at it
+        if (skip) {                                      // a ragged last tile at most; one block looks at it, whatever its own range
             tt = a.T - 1u;
-            if (blockIdx.x != 0 || (a.n % TILE) == 0) te = tt;
+            te = (blockIdx.x == 0 && (a.n % TILE) != 0) ? a.T : tt;
         }
         if (!ok) te = tt;
         // two tiles a turn: the scores of both are requested before either is worked on

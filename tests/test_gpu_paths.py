@@ -88,6 +88,29 @@ def test_selection_leaves_clear_counts_whatever_was_counted_before(n):
     sd.close()
 
 
+@pytest.mark.parametrize("n", [5, 4096 * 3 + 1, 4096 * 40 + 4095])
+def test_ragged_tile_is_sorted_also_when_tiles_are_dealt_in_ranges_after_the_scoring_pass(n):
+    """Whole tiles are sorted by the scoring pass (its prediction holds from the second iteration on), the ragged one by the
+    selection, whose blocks take ranges of tiles when "strided_tiles" is switched off in between."""
+    W, k = 2, max(1, n // 3)
+    rng = np.random.default_rng(n)
+    w_h = rng.standard_normal(n).astype(np.float32)
+    g_h = [(1e-3 * rng.standard_normal(n)).astype(np.float32) for _ in range(W)]
+    sd = binding.SlimDP(n, W)
+    w, g = to_dev(w_h), [to_dev(x) for x in g_h]
+    for turn in range(4):
+        S = sd.score(w, g, 1.0)
+        sd.set_option("strided_tiles", 0 if turn else 1)
+        idx = sd.select_core(S, [k], reuse_histogram=True)[0]
+        sd.set_option("strided_tiles", 1)
+        sd.synchronize()
+        assert np.array_equal(u32(idx), oracle.select_core(oracle.score(w_h, g_h, 1.0), k)), turn
+        tail = n % 4096                          # the next iteration's ragged tile is another one
+        w_h[n - tail:] = w_h[n - tail:][::-1].copy()
+        w.copy_(to_dev(w_h))
+    sd.close()
+
+
 @pytest.mark.parametrize("segments", [1, 5])
 def test_recorded_selection_replays_beside_eager_ones(segments):
     """Score and selection recorded into a graph give the eager result on every replay, whatever eager calls (other core
