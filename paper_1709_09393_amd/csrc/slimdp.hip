@@ -214,7 +214,8 @@ struct slimdp_ctx {
 
 namespace {
 
-constexpr uint32_t CORE_GROUPS = 2048;      // tile groups of the selection passes at most (eight blocks per compute unit)
+// every number of tiles that the interface serves fits the groups' table
+static_assert(core_groups((uint32_t)(SLIMDP_MAX_N / TILE + SLIMDP_MAX_SEGMENTS), 1u) <= CORE_GROUPS, "groups of tiles");
 
 // Tables and the buffers of the core selection (all that a selection without explorers needs).  The histogram comes
 // first: in the static scratch array it is found at the same place whatever the size of the call before.
@@ -906,15 +907,12 @@ static int select_core_impl(slimdp_ctx* ctx, const float* score, const uint64_t*
     CoreArgs a{};
     a.tile_start = ctx->d_tile_start; a.tile_seg = ctx->d_tile_seg; a.seg_first_tile = ctx->d_seg_first_tile;
     a.n = ctx->n; a.T = T; a.n_seg = S;
-    // groups of tiles for the passes over the candidates: a tile per wave at least
-    a.groups = std::min(std::min((T + 3) / 4, (uint32_t)ctx->cus * 8u), CORE_GROUPS);
+    a.groups = core_groups(T, (uint32_t)ctx->cus);
     a.k_flat = (uint32_t)K;
     a.plan = ctx->c_plan; a.hist = ctx->c_hist; a.state = ctx->c_state;
     a.gt_bits = ctx->c_gt_bits; a.cand_bits = ctx->c_cand_bits; a.cand_keys = ctx->c_cand_keys;
     a.cnt_gt = ctx->c_cnt_gt; a.cnt_cand = ctx->c_cnt_cand;
     a.tile_pre = ctx->c_tile_pre; a.group_tail = ctx->c_group_tail; a.flags = ctx->d_flags;
-    if ((T + a.groups - 1) / a.groups > GROUP_MAX)
-        return fail(ctx, SLIMDP_ERR_INVALID_ARG, "slimdp_select_core: %u tiles in %u groups", T, a.groups);
     if (S > 1 && (!known || !std::equal(k_seg, k_seg + S, ctx->c_plan_k.begin(), ctx->c_plan_k.end()))) {
         ctx->c_plan_k.clear();               // whatever happens below: what the device holds is not known yet
         uint32_t base = 0;

@@ -16,6 +16,7 @@
 // whole iteration of 10^6 parameters 207 -> 173 us, of 7*10^6 in 57 segments 367 -> 333 us, of 138*10^6 2.39 -> 2.31 ms.
 #pragma once
 #include "slimdp_kernels.h"
+#include "slimdp_split.h"
 
 namespace slimdp {
 
@@ -43,14 +44,6 @@ struct CoreArgs {
     uint2* group_tail;             // [groups] the same summed over the group's last segment
     uint32_t* flags;
 };
-
-// Tiles are dealt to the blocks of the last three passes in contiguous groups; which group holds tile t.
-__device__ __forceinline__ uint32_t group_first(uint32_t g, uint32_t T, uint32_t groups) { return (uint32_t)((uint64_t)T * g / groups); }
-__device__ __forceinline__ uint32_t group_of(uint32_t t, uint32_t T, uint32_t groups)
-{
-    return (uint32_t)((((uint64_t)t + 1u) * groups - 1u) / T);
-}
-constexpr uint32_t GROUP_MAX = 1024;            // tiles per group at most (LDS counters of k_core_count)
 
 __device__ __forceinline__ uint32_t seg_of_tile(const CoreArgs& a, uint32_t t) { return a.n_seg == 1 ? 0u : a.tile_seg[t]; }
 __device__ __forceinline__ uint32_t seg_end_tile(const CoreArgs& a, uint32_t seg) { return a.n_seg == 1 ? a.T : a.seg_first_tile[seg + 1]; }
