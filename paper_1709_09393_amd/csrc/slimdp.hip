@@ -566,8 +566,10 @@ int slimdp_create(slimdp_ctx** out, uint64_t n, uint32_t max_workers, uint32_t n
     }
     Carver cv(c->ws);
     carve(c, cv);
-    // the tables, an empty prediction and the cleared flags, in one copy that is synchronous with respect to the host
-    {
+    // A clear histogram; the tables, an empty prediction and the cleared flags, in one copy.  Both run on the default
+    // stream, and the context's stream need not wait for that one (a non-blocking stream does not): the host waits here.
+    e = hipMemset(c->c_hist, 0, (size_t)n_seg * H_STRIDE * 4);
+    if (e == hipSuccess) {
         const size_t words = (size_t)(c->d_flags + 64 - c->d_tile_start);
         std::vector<uint32_t> up(words, 0u);
         auto at = [&](const uint32_t* d) { return up.begin() + (d - c->d_tile_start); };
@@ -578,7 +580,7 @@ int slimdp_create(slimdp_ctx** out, uint64_t n, uint32_t max_workers, uint32_t n
         std::fill_n(at(c->c_pred), n_seg, NONE);                              // no prediction yet
         e = hipMemcpy(c->d_tile_start, up.data(), words * 4, hipMemcpyHostToDevice);
     }
-    if (e == hipSuccess) e = hipMemset(c->c_hist, 0, (size_t)n_seg * H_STRIDE * 4);
+    if (e == hipSuccess) e = hipStreamSynchronize(nullptr);
     if (e == hipSuccess) e = hipStreamCreateWithFlags(&c->side, hipStreamNonBlocking);      // default priority
     if (e == hipSuccess) e = hipEventCreateWithFlags(&c->ev_consumed, hipEventDisableTiming);
     if (e == hipSuccess) e = hipEventCreateWithFlags(&c->ev_drawn, hipEventDisableTiming);

@@ -88,6 +88,31 @@ def test_selection_leaves_clear_counts_whatever_was_counted_before(n):
     sd.close()
 
 
+@pytest.mark.parametrize("reuse", [False, True])
+def test_first_call_of_a_context_on_a_stream_of_its_own_starts_from_clear_counts(reuse):
+    """1.3 GB of histograms (20,000 segments) are clear before a stream that does not wait for the default one counts into
+    them."""
+    sizes = [3] * 20_000
+    so, n = offsets(sizes), sum(sizes)
+    ks = [1 + j % 2 for j in range(len(sizes))]
+    rng = np.random.default_rng(11)
+    w_h, g_h = rng.standard_normal(n).astype(np.float32), [rng.standard_normal(n).astype(np.float32)]
+    S_h = oracle.score(w_h, g_h, 1.0)
+    want = oracle.select_core(S_h, ks, so)
+    w, g, S = to_dev(w_h), [to_dev(x) for x in g_h], to_dev(S_h)
+    st = torch.cuda.Stream()
+    torch.cuda.synchronize()
+    for _ in range(3):
+        sd = binding.SlimDP(n, 1, seg_off=so, stream=st)
+        with torch.cuda.stream(st):
+            if reuse:
+                sd.score(w, g, 1.0, out=S)
+            idx = sd.select_core(S, ks, reuse_histogram=reuse)[0]
+        sd.synchronize()
+        assert np.array_equal(u32(idx), want)
+        sd.close()
+
+
 @pytest.mark.parametrize("n", [5, 4096 * 3 + 1, 4096 * 40 + 4095])
 def test_ragged_tile_is_sorted_also_when_tiles_are_dealt_in_ranges_after_the_scoring_pass(n):
     """Whole tiles are sorted by the scoring pass (its prediction holds from the second iteration on), the ragged one by the
