@@ -292,6 +292,34 @@ def test_explorer_lists_and_offsets_at_the_edges_of_segments_and_zones(name, W, 
     sd.close()
 
 
+@pytest.mark.parametrize("chosen", [1023, 1024, 1025, 2048, 4095, 4096])
+def test_emission_of_tiles_that_hold_few_and_many(chosen):
+    """Core and explorer lists of tiles at the edge between the two ways of writing them, up to every parameter of a tile, beside
+    tiles that hold next to nothing, and a ragged tile that is taken whole."""
+    T, tail = 5, 777
+    n = T * 4096 + tail
+    rng = np.random.default_rng(chosen)
+    score = rng.random(n).astype(np.float32) * 0.5
+    for t in (0, 3):                             # these tiles hold `chosen` of the core each, the ragged one all it has
+        score[t * 4096 + rng.choice(4096, chosen, replace=False)] += 1.0
+    score[T * 4096:] += 1.0
+    k = 2 * chosen + tail
+    sd = binding.SlimDP(n, 2, seed=workloads.EXPLORE_SEED)
+    ts = sd.tile_starts().astype(np.int64)
+    idx, bits, off, _ = sd.select_core(to_dev(score), [k])
+    want = oracle.select_core(score, k)
+    m = (n - k) * chosen // 4096                  # about as dense in the tiles without a core, everything at last
+    eidx, eoff = sd.sample_explore(bits, [k], 3, [m], 0, 2)
+    sd.synchronize()
+    assert np.array_equal(u32(idx), want)
+    assert np.array_equal(u32(off), np.searchsorted(want.astype(np.int64), ts).astype(np.uint32))
+    for q in range(2):
+        e = oracle.sample_explore(n, want, workloads.EXPLORE_SEED, 3, q, m)
+        assert np.array_equal(u32(eidx[q]), e)
+        assert np.array_equal(u32(eoff[q]), np.searchsorted(e.astype(np.int64), ts).astype(np.uint32))
+    sd.close()
+
+
 @pytest.mark.parametrize("overlap", [False, True])
 @pytest.mark.parametrize("W,pct", [(1, 2), (3, 17), (8, 6), (8, 11), (9, 10), (16, 17), (32, 3)])
 def test_merge_variants_by_explorer_density(W, pct, overlap):
