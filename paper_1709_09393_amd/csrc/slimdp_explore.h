@@ -369,22 +369,24 @@ __global__ __launch_bounds__(NT) void k_explore_select(const SegState* __restric
         }
     }
     __syncthreads();
-    // tile offsets: the counts were added to by other waves of this block, hence the atomic loads
+    // Tile offsets: the counts were added to by other waves of this block, hence the atomic loads.  Consecutive lanes take
+    // consecutive tiles; eight tiles to a lane made every load and store touch sixteen lines: 43 us for 33,779 tiles.
     uint32_t* off = static_cast<uint32_t*>(out_off.p[b]) + f0;
     uint32_t run = base;
     for (uint32_t w = 0; w < wid; ++w) run += wsum[w];
     for (uint32_t x0 = w0; x0 < w1; x0 += 512) {
-        uint32_t v[8], sum = 0;
-        const uint32_t x = x0 + lane * 8u;
+        uint32_t v[8];
 #pragma unroll
-        for (int e = 0; e < 8; ++e) v[e] = (x + e < w1) ? __hip_atomic_load(&cs[x + e], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0u;
+        for (uint32_t e = 0; e < 8; ++e) {
+            const uint32_t x = x0 + e * 64u + lane;
+            v[e] = x < w1 ? __hip_atomic_load(&cs[x], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0u;
+        }
 #pragma unroll
-        for (int e = 0; e < 8; ++e) sum += v[e];
-        const uint32_t incl = wave_incl_scan(sum);
-        uint32_t o = run + incl - sum;
-#pragma unroll
-        for (int e = 0; e < 8; ++e) { if (x + e < w1) off[x + e] = o; o += v[e]; }
-        run += __shfl(incl, 63, 64);
+        for (uint32_t e = 0; e < 8; ++e) {
+            const uint32_t x = x0 + e * 64u + lane, incl = wave_incl_scan(v[e]);
+            if (x < w1) off[x] = run + incl - v[e];
+            run += __shfl(incl, 63, 64);
+        }
     }
     if (f1 == T && tid == 0) off[nt] = base + need0;
 }
