@@ -383,6 +383,7 @@ __global__ __launch_bounds__(NT) void k_explore_select(const SegState* __restric
         }
 #pragma unroll
         for (uint32_t e = 0; e < 8; ++e) {
+            if (x0 + e * 64u >= w1) break;                   // uniform: a scan costs a short segment a microsecond
             const uint32_t x = x0 + e * 64u + lane, incl = wave_incl_scan(v[e]);
             if (x < w1) off[x] = run + incl - v[e];
             run += __shfl(incl, 63, 64);
