@@ -249,7 +249,7 @@ void carve(slimdp_ctx* c, Carver& cv)
     c->e_draw_state = cv.take<SegState>(B * S);
     c->e_sure_bits = cv.take<uint32_t>(B * T * TILE_WORDS);
     c->e_cand_bits = cv.take<uint32_t>(B * T * TILE_WORDS);
-    c->e_list_count = cv.take<uint32_t>(B * S);
+    c->e_list_count = cv.take<uint32_t>(B * align_up(S, 32));
     c->e_list = cv.take<uint2>(B * (size_t)c->list_first[S]);
     c->e_pair_keys = cv.take<uint32_t>(B * c->pair_stride);
     c->e_cnt_cand = cv.take<uint32_t>(B * T * SUBS);
@@ -306,7 +306,7 @@ int init_states(slimdp_ctx* c, SegState* st, const std::vector<SegInit>& init, u
         for (uint32_t j = 0; j < cnt; ++j) chunk.s[j] = init[s0 + j];
         const uint32_t threads = cnt * nbatch;
         hipLaunchKernelGGL(k_explore_init, dim3((threads + 255) / 256), dim3(256), 0, stream, st, chunk, s0, cnt, c->n_seg, nbatch,
-                           clear ? c->e_list_count : nullptr, clear && s0 == 0 ? c->d_flags : nullptr);
+                           clear ? c->e_list_count : nullptr, (uint32_t)align_up(c->n_seg, 32), clear && s0 == 0 ? c->d_flags : nullptr);
         SLIMDP_LAUNCHED(c, "k_explore_init");
     }
     return SLIMDP_OK;
@@ -1127,7 +1127,7 @@ int slimdp_sample_explore(slimdp_ctx* ctx, const uint32_t* core_bits, const uint
                                (PAIRS) ? ctx->pair_stride : ctx->keys_stride, worker0, pk);                              \
         SLIMDP_LAUNCHED(ctx, "k_explore_keys");                                                                          \
     } while (0)
-    const ExploreLists lists{ctx->e_list, ctx->e_list_count, ctx->d_list_first, ctx->list_first[S]};
+    const ExploreLists lists{ctx->e_list, ctx->e_list_count, ctx->d_list_first, ctx->list_first[S], (uint32_t)align_up(S, 32)};
     if (short_list) {
         constexpr int SBPW = 8;
         if (!cached) LAUNCH_DRAW(1);

@@ -21,7 +21,7 @@ namespace slimdp {
 // Writes the selection state of segments [seg0, seg0+count) for every batch.  counts, flags: also cleared, if given.
 __global__ __launch_bounds__(256) void k_explore_init(SegState* __restrict__ st, SegInitChunk chunk, uint32_t seg0, uint32_t count,
                                                       uint32_t n_seg, uint32_t nbatch, uint32_t* __restrict__ counts,
-                                                      uint32_t* __restrict__ flags)
+                                                      uint32_t count_stride, uint32_t* __restrict__ flags)
 {
     const uint32_t x = blockIdx.x * 256 + threadIdx.x;
     if (x == 0 && flags) flags[0] = 0;
@@ -34,12 +34,15 @@ __global__ __launch_bounds__(256) void k_explore_init(SegState* __restrict__ st,
     s.pad[0] = s.pad[1] = 0;
     const size_t o = (size_t)b * n_seg + seg0 + j;
     st[o] = s;
-    if (counts) counts[o] = 0;
+    if (counts) counts[(size_t)b * count_stride + seg0 + j] = 0;
 }
 
 // Lists: entry (key, tile * TILE + offset inside the tile); batch b's segment s has its entries at
-// list[b * stride + first[s]] .. , at most first[s + 1] - first[s] of them (more raise the rerun flag).
-struct ExploreLists { uint2* list; uint32_t* count; const uint32_t* first; uint64_t stride; };
+// list[b * stride + first[s]] .. , at most first[s + 1] - first[s] of them (more raise the rerun flag), counted in
+// count[b * count_stride + s].  Every batch's counters have lines of their own (count_stride is a multiple of 32): atomics
+// on one line take turns, whichever word they meet.  3 workers' counters of a flat model in one line kept
+// k_explore_collect_wide at 99 us for 20*10^6 parameters (60 now), 8 workers' k_explore_collect at 75 for 138*10^6 (44 now).
+struct ExploreLists { uint2* list; uint32_t* count; const uint32_t* first; uint64_t stride; uint32_t count_stride; };
 constexpr uint32_t FLAG_RERUN = 1u;
 
 // Sure parameters outside the core of one tile, for batches b0 .. b0+BPW-1, by one wave.
@@ -117,7 +120,7 @@ __global__ __launch_bounds__(BLOCK) void k_explore_collect(const uint32_t* __res
     // room in the lists: one reservation a block inside a segment, else one for each segment that a wave meets
     uint32_t at = NONE;
     auto reserve = [&](uint32_t seg, uint32_t total) {
-        const uint32_t base = atomicAdd(&lists.count[(size_t)b * n_seg + seg], total);
+        const uint32_t base = atomicAdd(&lists.count[(size_t)b * lists.count_stride + seg], total);
         const uint32_t cap = lists.first[seg + 1] - lists.first[seg];
         if (base + total <= cap && base + total >= base) return base;
         atomicOr(&flags[0], FLAG_RERUN);
@@ -177,7 +180,7 @@ __global__ __launch_bounds__(BLOCK) void k_explore_collect_wide(const uint32_t* 
     // room for cnt entries in the list of segment seg; NULL: the list is full
     auto reserve = [&](uint32_t seg, uint32_t cnt) -> uint2* {
         uint32_t base = 0;
-        if (lane == 0) base = atomicAdd(&lists.count[(size_t)b * n_seg + seg], cnt);
+        if (lane == 0) base = atomicAdd(&lists.count[(size_t)b * lists.count_stride + seg], cnt);
         base = __shfl(base, 0, 64);
         const uint32_t first = lists.first[seg], cap = lists.first[seg + 1] - first;
         if (base + cnt > cap || base + cnt < base) {
@@ -268,7 +271,7 @@ __global__ __launch_bounds__(NT) void k_explore_select(const SegState* __restric
     const SegState* st = states + (size_t)b * n_seg + seg;
     const uint32_t f0 = n_seg == 1 ? 0u : seg_first_tile[seg], f1 = n_seg == 1 ? T : seg_first_tile[seg + 1];
     const uint32_t cap = lists.first[seg + 1] - lists.first[seg];
-    const uint32_t cnt = lists.count[(size_t)b * n_seg + seg];
+    const uint32_t cnt = lists.count[(size_t)b * lists.count_stride + seg];
     const uint2* list = lists.list + (size_t)b * lists.stride + lists.first[seg];
     const uint32_t need0 = st->need0, base = st->out_base, bits = st->bits;
     if (cnt > cap) return;                                   // the rerun flag is up
