@@ -1369,19 +1369,25 @@ int slimdp_merge(slimdp_ctx* ctx, float* w, float lr, uint64_t core_epoch, uint3
     if (rc) return rc;
     rc = wait_for_lists(ctx, n_workers, expl_idx, expl_off, m_w);
     if (rc) return rc;
-    // explorer entries a tile is expected to hold, with six standard deviations: the variant that keeps them in registers.
-    // 20*10^6 parameters, 3 workers, 1,776 entries a tile: 79 us with four entries per thread (staged path), 66 with eight.
+    // Entries a tile is expected to hold, with six standard deviations: the variant that keeps them in registers (the staged
+    // path costs 20*10^6 parameters, 3 workers, 1,776 entries a tile 79 us, eight entries per thread 66).  Sixteen take 104
+    // registers, four blocks to a compute unit instead of seven: that pays only while the tiles are few enough to run in
+    // two turns (8 workers, 3,200 a tile: 245 tiles 22.9 against 26.6 us staged, 1,954 tiles 63.7 against 66.8, but 2,100
+    // tiles 81 against 69, 33,779 tiles 1,027 against 734).  With more tiles eight serve as long as half of them fit
+    // (1,950 a tile, 138*10^6 parameters, 2 workers: 414 against 434 us staged and 593 with sixteen).
     double per_tile = 0.0;
     for (uint32_t q = 0; q < n_workers; ++q) per_tile += (double)m_w[q] * TILE / (double)ctx->n;
     const double room = per_tile + 6.0 * std::sqrt(per_tile);
+    const bool few_tiles = ctx->T <= 8u * (uint32_t)ctx->cus;
 #define LAUNCH_MERGE(R)                                                                                                        \
     hipLaunchKernelGGL(k_merge<R>, dim3(ctx->T), dim3(BLOCK), 0, ctx->stream, w, lr, n_workers, ctx->d_tile_start, core_idx,  \
                        core_off, make_tab<PtrTab>(core_val, n_workers), make_tab<PtrTab>(expl_idx, n_workers),                \
                        make_tab<PtrTab>(expl_off, n_workers), make_tab<PtrTab>(expl_val, n_workers), (int)aligned16(w),       \
                        ctx->n, ctx->n_seg)
-    if (room <= 4.0 * BLOCK || room > 16.0 * BLOCK) LAUNCH_MERGE(4);
-    else if (room <= 8.0 * BLOCK) LAUNCH_MERGE(8);
-    else LAUNCH_MERGE(16);
+    if (room <= 4.0 * BLOCK) LAUNCH_MERGE(4);
+    else if ((few_tiles ? room : per_tile) <= 8.0 * BLOCK) LAUNCH_MERGE(8);
+    else if (few_tiles && room <= 16.0 * BLOCK) LAUNCH_MERGE(16);
+    else LAUNCH_MERGE(4);
 #undef LAUNCH_MERGE
     SLIMDP_LAUNCHED(ctx, "k_merge");
     return SLIMDP_OK;

@@ -325,7 +325,16 @@ def test_emission_of_tiles_that_hold_few_and_many(chosen):
 def test_merge_variants_by_explorer_density(W, pct, overlap):
     """Entries per tile for 4, 8 and 16 registers a thread and for the staged path, most positions sent by several workers; with
     overlap the lists also meet the core, whose sum then comes first."""
-    n = 4096 * 6 + 1111
+    check_merge(4096 * 6 + 1111, W, pct, overlap)
+
+
+@pytest.mark.parametrize("pct", [26, 30])
+def test_merge_variants_over_more_tiles_than_run_in_two_turns(pct):
+    """About 1,920 and 2,210 entries a tile: tiles on both sides of what eight registers a thread hold, and none of them."""
+    check_merge(4096 * 2100 + 5, 2, pct, False)
+
+
+def check_merge(n, W, pct, overlap):
     rng = np.random.default_rng(W * 100 + pct)
     w_h = rng.standard_normal(n).astype(np.float32)
     core = oracle.select_core(np.abs(rng.standard_normal(n)).astype(np.float32), n // 10)
