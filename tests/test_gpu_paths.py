@@ -259,6 +259,82 @@ def test_static_selection_recorded_between_eager_calls():
             check(values)
 
 
+@pytest.mark.parametrize("draw", ["none", "pairs", "wide"])
+@pytest.mark.parametrize("dense", [False, True])
+@pytest.mark.parametrize("W", [6, 7])
+def test_numbers_of_workers_with_a_scoring_kernel_of_their_own(W, dense, draw):
+    """Six and seven workers in the pipelined scoring kernel: alone, with an announced draw in either format, and after a dense
+    update; the second iteration against the first one's threshold.  One size has several tiles to a block."""
+    n = 4096 * (520 if draw == "pairs" and not dense else 9) + 77
+    wl = workloads.TINY.scaled(n, W=W)
+    sd = binding.SlimDP(n, W, seed=workloads.EXPLORE_SEED)
+    sd.set_option("explore_per_tile_tail", int(draw == "wide"))
+    w_h = wl.weights()
+    w = to_dev(w_h)
+    for t in range(2):
+        g_h = wl.gradients(t)
+        g = [to_dev(x) for x in g_h]
+        if draw != "none":
+            sd.explore_hint([wl.k], t, [wl.m], 0, W)
+        if dense:
+            S = sd.dense_update_score(w, g, wl.lr, wl.c)
+            w_h, S_o = oracle.dense_update_score(w_h, g_h, wl.lr, wl.c)
+        else:
+            S, S_o = sd.score(w, g, wl.c), oracle.score(w_h, g_h, wl.c)
+        core, bits, _, _ = sd.select_core(S, [wl.k], reuse_histogram=True)
+        idx, _ = sd.sample_explore(bits, [wl.k], t, [wl.m], 0, W)
+        sd.synchronize()
+        core_o = oracle.select_core(S_o, wl.k)
+        assert np.array_equal(u32(S), S_o.view(np.uint32)) and np.array_equal(u32(w), w_h.view(np.uint32)), t
+        assert np.array_equal(u32(core), core_o) and np.array_equal(u32(bits), oracle.core_bits(n, core_o)), t
+        for q in (0, W - 1):
+            assert np.array_equal(u32(idx[q]), oracle.sample_explore(n, core_o, workloads.EXPLORE_SEED, t, q, wl.m)), (t, q)
+    sd.close()
+
+
+# kept parameters in the four rounds of 256 of a sub-tile.  Its capture holds 256 entries, a round beginning on a line
+# (two entries of sixteen workers): the first group fits, the second has entries that the pack must gather
+FITS = [(127, 0, 128, 0), (128, 128, 0, 0), (256, 0, 0, 0), (129, 126, 0, 0), (0, 0, 0, 256), (3, 125, 126, 0), (129, 0, 0, 125), (0, 0, 0, 0)]
+SPILLS = [(129, 127, 0, 0), (1, 255, 0, 0), (256, 1, 0, 0), (129, 129, 129, 129), (256, 256, 256, 256), (127, 127, 2, 0)]
+
+
+@pytest.mark.parametrize("spills", [False, True])
+@pytest.mark.parametrize("W", [1, 8, 16])
+def test_capture_of_clustered_parameters(W, spills):
+    """Rounds at the edges of what is staged at a time (128 entries of sixteen workers, 256 of fewer) and of a sub-tile's
+    capture.  Where everything fits, the updates are zeroed before the pack: its values can only be those kept."""
+    tiles, tail = 7, 50
+    n = tiles * 4096 + tail
+    rng = np.random.default_rng(W)
+    line = 32 // W                               # entries of a line of 128 bytes
+    groups = [f for f in FITS if sum((x + line - 1) // line * line for x in f) <= 256] + (SPILLS if spills else [])
+    big = np.zeros(n, bool)
+    for j in range(tiles * 4):
+        for r, count in enumerate(groups[j % len(groups)]):
+            big[j * 1024 + r * 256 + rng.choice(256, count, replace=False)] = True
+    w_h = np.where(big, 1.0 + rng.random(n), 0.01 * rng.random(n)).astype(np.float32)
+    k, m = int(big.sum()), 7
+    sd = binding.SlimDP(n, W, seed=workloads.EXPLORE_SEED)
+    sd.set_option("speculative_pack", 1)
+    w = to_dev(w_h)
+    for t in range(3):                           # the first selection sets the bound that the second pass captures under
+        g_h = [(1e-3 * rng.standard_normal(n)).astype(np.float32) for _ in range(W)]
+        g = [to_dev(x) for x in g_h]
+        S = sd.score(w, g, 1.0)
+        core, bits, off, epoch = sd.select_core(S, [k], reuse_histogram=True)
+        idx, eoff = sd.sample_explore(bits, [k], t, [m], 0, W)
+        clobber = t > 0 and not spills
+        if clobber:
+            for x in g:
+                x.zero_()
+        core_val, _ = sd.pack(g, core, off, idx, eoff, epoch, updates_as_scored=True)
+        sd.synchronize()
+        assert np.array_equal(u32(core), np.flatnonzero(big).astype(np.uint32)), t
+        for q in range(W):
+            assert np.array_equal(u32(core_val[q]), g_h[q][big].view(np.uint32)), (t, q)
+    sd.close()
+
+
 @pytest.mark.parametrize("per_tile_tail", [0, 1])
 @pytest.mark.parametrize("W", [1, 5, 9])
 @pytest.mark.parametrize("name", sorted(SEGMENTS) + ["one_segment", "more_blocks_than_run_at_a_time"])
