@@ -83,10 +83,12 @@ int slimdp_destroy(slimdp_ctx* ctx);
 uint64_t slimdp_workspace_bytes(uint64_t n, uint32_t max_workers, uint32_t n_seg,
                                 const uint64_t* seg_off);
 /* Device bytes that switching option "speculative_pack" on allocates on top; 0 if the arguments are invalid.
- * Explorer requests whose candidates do not fit the small per-sub-tile slots (m_seg at least a quarter of what lies
- * outside the core, or segments so small that the candidate zone, about 12 sqrt(m_seg) + 64 words wide, covers more
- * than a few parameters in a thousand) allocate once more, 4 * max_workers * (n rounded up to tiles + one tile)
- * bytes, on their first occurrence.  Pure host function. */
+ * Explorer requests whose candidates do not fit the small per-sub-tile slots allocate once more, 4 * max_workers *
+ * (n rounded up to tiles + one tile) bytes, on their first occurrence: where some sub-tile of 1,024 parameters is likely to
+ * see more than 16 candidates (the zone of a segment is about 12 sqrt(m_seg) + 64 words wide, so small segments: from
+ * 2 to 4 in 1,000 of what lies outside the core), or where m_seg and half that zone reach 95 % of what lies outside the core.
+ * An announced draw (slimdp_explore_hint) of that kind allocates as well, except in slimdp_score on models whose segments
+ * begin at indices that are no multiples of 4: there it goes unused until a request has allocated.  Pure host function. */
 uint64_t slimdp_capture_bytes(uint64_t n, uint32_t max_workers, uint32_t n_seg, const uint64_t* seg_off);
 /* Number of tiles T; 0 if the arguments are invalid.  Pure host function. */
 uint64_t slimdp_num_tiles(uint64_t n, uint32_t n_seg, const uint64_t* seg_off);

@@ -1,5 +1,6 @@
 // libslimdp host side: the C ABI of include/slimdp.h.  Argument checks, workspace carving
-// and kernel launches only; every step of the path runs in the kernels of slimdp_kernels.h.
+// and kernel launches only; every step of the path runs in the kernels of slimdp_kernels.h,
+// slimdp_core.h and slimdp_explore.h.
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
@@ -186,9 +187,9 @@ struct slimdp_ctx {
     int64_t opt_pack_nbuf = 2;
     int64_t opt_pack_kernel = 1;           // general pack: 1 = loading and storing waves apart, 0 = one set of waves
     int64_t opt_pull_kernel = 1;           // local overwrite of a pull: 1 = a pass that streams the local models, 0 = scattered writes
-    int64_t opt_build_blocks = 4;
+    int64_t opt_build_blocks = 4;          // blocks per compute unit of the core candidate pass
     int64_t opt_pack_core_blocks = 0;      // blocks per compute unit of the pack from the capture (0: one per 1024 list entries)
-    int64_t opt_core_predict = 1;          // the flat scoring kernel sorts whole tiles against the predicted threshold bin (0: never; 2: test, a wrong bin)          // blocks per compute unit of the core candidate pass
+    int64_t opt_core_predict = 1;          // the flat scoring kernel sorts whole tiles against the predicted threshold bin (0: never; 2: test, a wrong bin)
     int64_t opt_score_pipeline = 1;        // flat aligned models: the scoring kernel with two rounds of loads in flight
     int64_t opt_expected_core = -1;        // core size the next selection will ask for (flat model), if the caller says
     int64_t opt_estimate_bias = 0;         // test switch: added to a sampled capture bound
@@ -725,7 +726,8 @@ static int score_impl(slimdp_ctx* ctx, const float* w, const float* const* g, ui
         bool narrow = false;
         if (explorer_init(ctx, "slimdp_score(hint)", ctx->hint.k_seg.data(), ctx->hint.m_seg.data(), ctx->hint.n_workers, init,
                           &M, &narrow, &pairs) == SLIMDP_OK && narrow && M > 0 &&
-            // tiles inside random blocks: the first request, not a scoring pass, allocates the wide buffer
+            // tiles inside random blocks: the first request, not a scoring pass, allocates the wide buffer (until then
+            // such an announcement goes unused and the request draws for itself)
             (pairs || ctx->e_cand_keys || ctx->tl.quad_aligned)) {
             rc = wait_for_side(ctx);         // the draw's buffers may still be read by work on the side stream
             if (rc) return rc;
@@ -768,7 +770,7 @@ static int score_impl(slimdp_ctx* ctx, const float* w, const float* const* g, ui
             SLIMDP_LAUNCHED(ctx, "k_sample_bound");
         }
     }
-    // flat model, aligned arrays, up to 8 or 16 workers (two rounds of W + 1 vectors in registers): the pipelined kernel
+    // flat model, aligned arrays, a number of workers that the pipelined kernel is instantiated for (see there)
     if (ctx->n_seg == 1 && vec_ok && ctx->opt_strided && ctx->opt_score_pipeline && ctx->n < (1ull << 30) &&
         (W <= 8 || W == 16)) {
         const dim3 fgrid(persistent_blocks(ctx, SCOREF_MINB, 1)), fblock(BLOCK);

@@ -251,9 +251,10 @@ __global__ __launch_bounds__(BLOCK) void k_explore_collect_wide(const uint32_t* 
 // wanted, ties at the threshold key going to the lowest positions.  The list's first KEEP * NT entries stay in registers
 // from the first level to the last, longer ones are read again.  A chosen candidate is set in the sure bitmap and added to its
 // tile's count; the prefix of the counts gives the tile offsets (every wave owns a run of tiles, whose sums
-// are known beforehand).  Bound by latency: a chain of some ten trips to the L2 and as many block barriers; 10 us at 10^6
-// parameters, 55 us for the 20,400 entries of 20*10^6 at 17 %.  More blocks to a list, each marking a share, take
-// 43 us there, but are slower on short lists (14 -> 17 us for 228 of them) and beside a kernel that fills the chip.
+// are known beforehand).  Bound by latency: a chain of some ten trips to the L2 and as many block barriers, and by the
+// atomics that mark the chosen, two misses each, from one compute unit: 11 us at 10^6 parameters, 54 us for the 20,400
+// entries of 20*10^6 at 17 %, 53 us for 19,000 entries in 33,779 tiles.  More blocks to a list, each marking a share, take
+// 43 us for the 20,400, but are slower on short lists (14 -> 17 us for 228 of them) and beside a kernel that fills the chip.
 // A demand that the zones cannot meet raises the rerun flag.  grid (n_seg, n_workers), NT threads.
 // ---------------------------------------------------------------------------------------
 constexpr uint32_t TIE_CAP = 1024;

@@ -456,10 +456,12 @@ __global__ __launch_bounds__(BLOCK, SCORE_MINB) void k_score(const float* __rest
 // arrays are addressed through one descriptor each (n < 2^30 parameters: byte offsets fit 32
 // bits); block b takes the whole tiles b, b + gridDim.x, ...; the ragged last tile, if any,
 // goes to one block after its loop, element by element.
-// Every number of workers whose two rounds fit the registers comes here (1 to 8, and 16 with two parts of capture staging
-// and no round keys in registers), because a selection then finds its candidates sorted: k_core_build falls from 209 to
-// 14 us at 138*10^6 parameters and 16 workers (scoring with draws and capture itself 2,558 -> 2,190 us), from 50 to
-// 12 us at 20*10^6 and 3 workers (94 -> 82 us).
+// 1 to 8 and 16 workers come here (16 with two parts of capture staging and no round keys in registers), because a
+// selection then finds its candidates sorted: k_core_build falls from 209 to 14 us at 138*10^6 parameters and 16 workers
+// (scoring with draws and capture itself 2,558 -> 2,190 us), from 50 to 12 us at 20*10^6 and 3 workers (94 -> 82 us).
+// 9 to 15 would fit as well: they have no instantiation (six each, in a library that takes over a minute to compile) and
+// pay for it with k_score and a second pass over the scores (20*10^6 parameters: 308 us with 9 workers, 304 here with
+// 16).  More than 16 do not fit: two rounds of 18 vectors alone are 144 registers beside the ones the pass needs.
 // ---------------------------------------------------------------------------------------
 #ifndef SCOREF_MINB
 #define SCOREF_MINB 2

@@ -52,7 +52,7 @@ def run_iteration(wl, iteration=0, w_h=None, sd=None, force_fallback=False, chec
     if own:
         sd = binding.SlimDP(wl.n, wl.W, seg_off=seg_off, seed=workloads.EXPLORE_SEED)
     sd.set_option("explore_force_fallback", int(force_fallback))
-    sd.set_option("explore_per_tile_tail", int(per_tile_tail))      # 1: never the short-list explorer path
+    sd.set_option("explore_per_tile_tail", int(per_tile_tail))      # 1: candidates as bitmaps and keys, never as pairs
     w = to_dev(w_h)
     g = [to_dev(x) for x in g_h]
     sd.set_option("explore_hint_mode", hint_mode)
@@ -222,7 +222,7 @@ def test_general_pack_kernels(pack_kernel, nbuf):
 
 def test_many_small_segments():
     """1,500 segments of 1 to 200 parameters (most tiles hold a few dozen parameters, many segments get k = 0 or m = 0):
-    per-segment rankings, the explorer's per-tile tail (such zones are not narrow) and every list's tile offsets."""
+    per-segment rankings, the explorer's wide format (bitmaps and keys) and every list's tile offsets."""
     rng = np.random.default_rng(3)
     sizes = rng.integers(1, 201, 1500)
     seg_off = tuple(int(x) for x in np.concatenate([[0], np.cumsum(sizes)]))
@@ -252,7 +252,7 @@ def test_explore_exact_rerun_gives_the_same_sets(mode, hint, per_tile_tail):
 
 @pytest.mark.parametrize("hint", [False, True])
 def test_explore_per_tile_tail_with_narrow_zones(hint):
-    """The general explorer tail (the one that also serves wide zones) on workloads that would take the short list."""
+    """The explorer's wide format (the one that serves wide zones) on workloads that would be drawn as pairs."""
     for wl in (workloads.TINY.scaled(200_003), workloads.GOOGLENET.scaled(300_001),
                workloads.STRESS.scaled(150_001, W=5), workloads.TINY.scaled(20_005, core_pct=10, explore_pct=60)):
         got, want = run_iteration(wl, hint=hint, per_tile_tail=True)
@@ -290,8 +290,8 @@ def test_hinted_draw_segmented_and_stress_and_rerun(hint_mode):
 @pytest.mark.parametrize("per_tile_tail", [False, True])
 def test_explorer_ties_at_the_threshold_take_the_lower_index(per_tile_tail):
     """Two equal Philox words exactly at the threshold, the demand covering one of them: both explorer tails
-    must hand it to the lower index.  Pairs early in the ranking go through the short list, late ones through
-    the per-tile tail with a wide zone."""
+    must hand it to the lower index.  Pairs early in the ranking are drawn as pairs, late ones in
+    the wide format."""
     n, seed = 1 << 20, 9
     r = oracle.explore_words(seed, 0, 0, 0, n)
     order = np.argsort(r, kind="stable")
