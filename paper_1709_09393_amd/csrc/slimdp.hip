@@ -321,6 +321,15 @@ uint32_t persistent_blocks(const slimdp_ctx* c, uint32_t per_cu, uint32_t nbatch
     return (uint32_t)p;
 }
 
+// How many workers a wave of the stand-alone draw takes in turn: as many as share the lanes' part of the random words, while
+// the tiles alone make per_cu blocks for every compute unit.
+uint32_t draw_group(const slimdp_ctx* c, uint32_t per_cu, uint32_t n_workers)
+{
+    uint32_t g = n_workers;
+    while (g > 1 && (uint64_t)c->T * ((n_workers + g - 1) / g) < (uint64_t)c->cus * per_cu) g = (g + 1) / 2;
+    return g;
+}
+
 template <class P> bool table_ok(P const* tab, uint32_t nw, bool allow_null_entries = false)
 {
     if (!tab) return false;
@@ -1111,6 +1120,10 @@ int slimdp_sample_explore(slimdp_ctx* ctx, const uint32_t* core_bits, const uint
     rc = init_states(ctx, ctx->e_state, init, B, true, st);
     if (rc) return rc;
     const uint32_t P = persistent_blocks(ctx, 8, B);
+    const uint32_t G = draw_group(ctx, 4, B);
+    // a tile or a few to a block, so that no unit is left with a whole turn more than the others (20*10^6 parameters, 3 workers:
+    // 36 us with at most eight blocks a unit, 33 with one tile to a block)
+    const dim3 draw_grid(persistent_blocks(ctx, 32, (B + G - 1) / G), (B + G - 1) / G);
     const uint32_t n_words = (uint32_t)((ctx->n + 31) / 32);
     const PhiloxKey pk{(uint32_t)ctx->seed, (uint32_t)(ctx->seed >> 32), (uint32_t)iteration, (uint32_t)(iteration >> 32)};
     MutPtrTab off_tab = make_tab<MutPtrTab>(expl_off, B);
@@ -1118,15 +1131,15 @@ int slimdp_sample_explore(slimdp_ctx* ctx, const uint32_t* core_bits, const uint
 #define LAUNCH_DRAW(PAIRS)                                                                                               \
     do {                                                                                                                 \
         if (ctx->tl.quad_aligned)                                                                                        \
-            hipLaunchKernelGGL((k_explore_keys<0, PAIRS>), dim3(P, B), dim3(BLOCK), 0, st, ctx->d_tile_start,   \
+            hipLaunchKernelGGL((k_explore_keys<0, PAIRS>), draw_grid, dim3(BLOCK), 0, st, ctx->d_tile_start,        \
                                ctx->d_tile_seg, T, S, ctx->e_state, ctx->e_sure_bits, ctx->e_cand_bits,                  \
                                (PAIRS) ? ctx->e_pair_keys : ctx->e_cand_keys, ctx->e_cnt_cand,                           \
-                               (PAIRS) ? ctx->pair_stride : ctx->keys_stride, worker0, pk);                              \
+                               (PAIRS) ? ctx->pair_stride : ctx->keys_stride, worker0, B, G, pk);                        \
         else                                                                                                             \
-            hipLaunchKernelGGL((k_explore_keys<1, PAIRS>), dim3(P, B), dim3(BLOCK), 0, st, ctx->d_tile_start,   \
+            hipLaunchKernelGGL((k_explore_keys<1, PAIRS>), draw_grid, dim3(BLOCK), 0, st, ctx->d_tile_start,        \
                                ctx->d_tile_seg, T, S, ctx->e_state, ctx->e_sure_bits, ctx->e_cand_bits,                  \
                                (PAIRS) ? ctx->e_pair_keys : ctx->e_cand_keys, ctx->e_cnt_cand,                           \
-                               (PAIRS) ? ctx->pair_stride : ctx->keys_stride, worker0, pk);                              \
+                               (PAIRS) ? ctx->pair_stride : ctx->keys_stride, worker0, B, G, pk);                        \
         SLIMDP_LAUNCHED(ctx, "k_explore_keys");                                                                          \
     } while (0)
     const ExploreLists lists{ctx->e_list, ctx->e_list_count, ctx->d_list_first, ctx->list_first[S], (uint32_t)align_up(S, 32)};
@@ -1215,14 +1228,15 @@ int slimdp_explore_hint(slimdp_ctx* ctx, const uint64_t* k_seg, uint32_t worker0
     rc = init_states(ctx, ctx->e_draw_state, init, n_workers, false, ctx->side);
     if (rc) return rc;
     // few waves keep the arithmetic units busy; the wave slots stay with the kernels of the main stream
-    const uint32_t P = persistent_blocks(ctx, (uint32_t)ctx->opt_side_blocks, n_workers);
+    const uint32_t G = draw_group(ctx, (uint32_t)ctx->opt_side_blocks, n_workers), groups = (n_workers + G - 1) / G;
+    const uint32_t P = persistent_blocks(ctx, (uint32_t)ctx->opt_side_blocks, groups);
     const PhiloxKey pk{(uint32_t)ctx->seed, (uint32_t)(ctx->seed >> 32), (uint32_t)iteration, (uint32_t)(iteration >> 32)};
-    const dim3 grid(P, n_workers), block(BLOCK);
+    const dim3 grid(P, groups), block(BLOCK);
 #define LAUNCH_SIDE_DRAW(MIS, PAIRS)                                                                                    \
     hipLaunchKernelGGL((k_explore_keys<MIS, PAIRS>), grid, block, 0, ctx->side, ctx->d_tile_start, ctx->d_tile_seg,    \
                        ctx->T, ctx->n_seg, ctx->e_draw_state, ctx->e_sure_bits, ctx->e_cand_bits,                       \
                        (PAIRS) ? ctx->e_pair_keys : ctx->e_cand_keys, ctx->e_cnt_cand,                                  \
-                       (PAIRS) ? ctx->pair_stride : ctx->keys_stride, worker0, pk)
+                       (PAIRS) ? ctx->pair_stride : ctx->keys_stride, worker0, n_workers, G, pk)
     if (ctx->tl.quad_aligned) { if (short_list) LAUNCH_SIDE_DRAW(0, 1); else LAUNCH_SIDE_DRAW(0, 0); }
     else { if (short_list) LAUNCH_SIDE_DRAW(1, 1); else LAUNCH_SIDE_DRAW(1, 0); }
 #undef LAUNCH_SIDE_DRAW

@@ -111,6 +111,46 @@ __device__ __forceinline__ uint32_t or_reduce8(uint32_t v)
     return v;
 }
 
+// Distances of four words above a bound, and whether they are below it: the borrow of the subtraction is shifted into acc
+// by an addition with carry (the first word's ends up highest).  Eight instructions; from the comparisons the compiler
+// makes masks, selects and ors, sixteen.  All four borrows are written before the first is read: a mask that the
+// vector unit wrote may be read by it two instructions later.
+__device__ __forceinline__ void sub4_borrow(const uint32_t r[4], uint32_t bound, uint32_t d[4], uint32_t& acc)
+{
+    uint64_t m0, m1, m2, m3;
+    asm("v_subrev_co_u32_e64 %0, %5, %9, %10\n\t"
+        "v_subrev_co_u32_e64 %1, %6, %9, %11\n\t"
+        "v_subrev_co_u32_e64 %2, %7, %9, %12\n\t"
+        "v_subrev_co_u32_e64 %3, %8, %9, %13\n\t"
+        "v_addc_co_u32_e64 %4, vcc, %4, %4, %5\n\t"
+        "v_addc_co_u32_e64 %4, vcc, %4, %4, %6\n\t"
+        "v_addc_co_u32_e64 %4, vcc, %4, %4, %7\n\t"
+        "v_addc_co_u32_e64 %4, vcc, %4, %4, %8"
+        : "=&v"(d[0]), "=&v"(d[1]), "=&v"(d[2]), "=&v"(d[3]), "+&v"(acc), "=&s"(m0), "=&s"(m1), "=&s"(m2), "=&s"(m3)
+        : "s"(bound), "v"(r[0]), "v"(r[1]), "v"(r[2]), "v"(r[3])
+        : "vcc");
+}
+
+// Four rounds of four flags a lane (bit 4 * round + i of v) to bitmap words: lanes 8j .. 8j+7 make word j of every round, and
+// lane 8j + 2 * round (and the one beside it) gets it.  Nibbles are paired with the neighbouring lane's, the bytes then cross
+// an 8-lane group in two exchanges (half-row mirror, lane pairs): ten instructions for four words, where a reduction
+// for each of them took six.
+__device__ __forceinline__ uint32_t transpose_flags(uint32_t v)
+{
+    const uint32_t lane = lane_id();
+    v = (v | (v << 8)) & 0x00FF00FFu;
+    v = ((v | (v << 4)) & 0x0F0F0F0Fu) << (4u * (lane & 1u));                          // byte r = round r, own nibble in place
+    v |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0xB1, 0xF, 0xF, true);       // quad_perm [1,0,3,2]
+    // lanes 0..3 of a group keep rounds 0 and 1, lanes 4..7 rounds 2 and 3, of their pair and of the one mirrored (p and 3 - p)
+    uint32_t o = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x141, 0xF, 0xF, true);      // row_half_mirror
+    v = __builtin_amdgcn_perm(o, v, (lane & 4u) ? 0x03070206u : 0x05010400u);          // bytes: (lower pair, higher pair) of either round
+    // of the two the lanes of pairs 0 and 2 keep the first, those of pairs 1 and 3 the second
+    o = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x4E, 0xF, 0xF, true);        // quad_perm [2,3,0,1]
+    // pairs in order: own (p, 3 - p) and the neighbour's
+    const uint32_t sel = (lane & 2u) ? ((lane & 4u) ? 0x03070602u : 0x07030206u) : ((lane & 4u) ? 0x05010004u : 0x01050400u);
+    return __builtin_amdgcn_perm(o, v, sel);
+}
+
 __device__ __forceinline__ uint32_t wave_sum(uint32_t v)
 {
 #pragma unroll
@@ -209,26 +249,51 @@ __device__ __forceinline__ void philox4x32_10(uint32_t c0, uint32_t c1, uint32_t
     out[0] = c0; out[1] = c1; out[2] = c2; out[3] = c3;
 }
 
-// The same with the ten round keys handed over (key + round * Weyl constant): a kernel that draws many words under
-// one key computes them once and, made opaque to the compiler, keeps them in vector registers; left to itself the
-// compiler holds them in scalar registers, runs out of those and reloads each with a lane read before every use.
-struct PhiloxRoundKeys { uint32_t k0[10], k1[10]; };
+// The explorer's draw calls it for many workers with the same first word: word (c0, worker, it_lo, it_hi).  The worker enters
+// at c1, and what the first three rounds do with the rest does not depend on it: of their six products per lane one is left
+// to each worker (two more are the same for the whole wave).  What is left over from them, per lane and c0:
+struct PhiloxCommon { uint32_t x, y, z, d; };
+__device__ __forceinline__ PhiloxCommon philox_common(uint32_t c0, uint32_t it_lo, uint32_t it_hi, uint32_t k0, uint32_t k1)
+{
+    const uint64_t p0 = (uint64_t)0xD2511F53u * c0;
+    const uint32_t c2 = (uint32_t)(p0 >> 32) ^ (it_hi ^ k1);
+    const uint64_t p1 = (uint64_t)0xCD9E8D57u * c2;
+    const uint32_t c0b = (uint32_t)(p1 >> 32) ^ ((uint32_t)((uint64_t)0xCD9E8D57u * it_lo) ^ (k0 + 0x9E3779B9u));
+    const uint64_t q = (uint64_t)0xD2511F53u * c0b;
+    PhiloxCommon c;
+    c.x = (uint32_t)p0 ^ (k1 + 0xBB67AE85u);
+    c.y = (uint32_t)p1 ^ (k0 + 2u * 0x9E3779B9u);
+    c.z = (uint32_t)(q >> 32) ^ (k1 + 2u * 0xBB67AE85u);
+    c.d = (uint32_t)q;
+    return c;
+}
+// The keys of the seven rounds that follow (key + round * Weyl constant).  A kernel that draws many words under one key
+// computes them once and, made opaque to the compiler, keeps them in vector registers; left to itself the compiler holds
+// them in scalar registers, runs out of those and reloads each with a lane read before every use.
+struct PhiloxRoundKeys { uint32_t k0[7], k1[7]; };
+template <bool HELD>
 __device__ __forceinline__ PhiloxRoundKeys philox_round_keys(uint32_t k0, uint32_t k1)
 {
     PhiloxRoundKeys rk;
 #pragma unroll
-    for (int r = 0; r < 10; ++r) {
-        rk.k0[r] = k0 + (uint32_t)r * 0x9E3779B9u;
-        rk.k1[r] = k1 + (uint32_t)r * 0xBB67AE85u;
-        asm volatile("" : "+v"(rk.k0[r]), "+v"(rk.k1[r]));
+    for (int r = 0; r < 7; ++r) {
+        rk.k0[r] = k0 + (uint32_t)(r + 3) * 0x9E3779B9u;
+        rk.k1[r] = k1 + (uint32_t)(r + 3) * 0xBB67AE85u;
+        if (HELD) asm volatile("" : "+v"(rk.k0[r]), "+v"(rk.k1[r]));
     }
     return rk;
 }
-__device__ __forceinline__ void philox4x32_10(uint32_t c0, uint32_t c1, uint32_t c2, uint32_t c3, const PhiloxRoundKeys& rk,
-                                              uint32_t out[4])
+// The rest for one worker: vh, vl = high and low word of the second round's product that only the worker decides (philox_worker).
+__device__ __forceinline__ uint64_t philox_worker(uint32_t worker, uint32_t it_lo, uint32_t k0)
 {
+    return (uint64_t)0xD2511F53u * ((uint32_t)(((uint64_t)0xCD9E8D57u * it_lo) >> 32) ^ worker ^ k0);
+}
+__device__ __forceinline__ void philox_words(const PhiloxCommon& c, uint64_t v, const PhiloxRoundKeys& rk, uint32_t out[4])
+{
+    const uint64_t e = (uint64_t)0xCD9E8D57u * (c.x ^ (uint32_t)(v >> 32));
+    uint32_t c0 = (uint32_t)(e >> 32) ^ c.y, c1 = (uint32_t)e, c2 = c.z ^ (uint32_t)v, c3 = c.d;
 #pragma unroll
-    for (int r = 0; r < 10; ++r) {
+    for (int r = 0; r < 7; ++r) {
         const uint64_t p0 = (uint64_t)0xD2511F53u * c0;
         const uint64_t p1 = (uint64_t)0xCD9E8D57u * c2;
         const uint32_t n0 = __builtin_amdgcn_bitop3_b32((uint32_t)(p1 >> 32), c1, rk.k0[r], 0x96);

@@ -88,25 +88,47 @@ __device__ __forceinline__ uint32_t inside_mask(uint32_t e0, uint32_t sub_len)
 
 // No LDS: round `it` covers the 256 parameters [256*it, 256*it+256) of the sub-tile in index order (lane L owns
 // parameters 4L..4L+3 of the round: one Philox block), so a candidate's place in the key list is the number of
-// candidates in earlier rounds plus a wave ballot count, and the eight bitmap words of the round are
-// OR-reductions over groups of eight lanes.
+// candidates in earlier rounds plus a wave ballot count.  Bound by the vector unit: 15 wide multiplications and 17
+// exclusive ors for four words, then a subtraction whose borrow is the sure flag and an addition with carry that files it
+// for each of them; the four rounds' flags become bitmap words together (transpose_flags): 51 instructions a round and worker,
+// 93 % of the issue slots when it runs alone.  With every worker's words from the beginning, masks and a reduction for each
+// round's words (67 instructions): 138*10^6 parameters, 8 workers 535 -> 407 us, 20*10^6 and 3 workers 38 -> 33 us.
 // MIS = 1: tiles may begin inside a Philox block (segmented models).  Everything above then counts from the start of that
 // block, mis = start mod 4 positions earlier; the bitmaps are shifted down by mis at the end, and the block that holds the
 // sub-tile's last mis parameters is computed apart, from wave-uniform values, that is by the scalar unit beside the
 // vector one.  (As a fifth round through LDS bitmaps the draw of 7*10^6 parameters for 4 workers took 36 us.)
-// KEYS: PhiloxKey, or PhiloxRoundKeys of a caller that draws under one key many times (pk then only names the iteration).
-__device__ __forceinline__ void philox_words(uint32_t c0, uint32_t worker, const PhiloxKey& pk, const PhiloxKey&, uint32_t r[4])
+// What a lane's four blocks share between the workers (philox_common): the caller keeps it, for as many workers as it draws.
+struct DrawLanes {
+    PhiloxCommon c[4];
+    __device__ __forceinline__ PhiloxCommon operator()(int it) const { return c[it]; }
+};
+struct ParkedLanes {             // the same in LDS: [round][lane], written and read by one wave
+    const uint4* at;
+    __device__ __forceinline__ PhiloxCommon operator()(int it) const
+    {
+        const uint4 v = at[it * 64 + (int)lane_id()];
+        return PhiloxCommon{v.x, v.y, v.z, v.w};
+    }
+};
+__device__ __forceinline__ DrawLanes draw_lanes(uint32_t start, uint32_t sub, const PhiloxKey& pk)
 {
-    philox4x32_10(c0, worker, pk.it_lo, pk.it_hi, pk.seed_lo, pk.seed_hi, r);
+    DrawLanes d;
+    const uint32_t g = ((start + sub * SUB) >> 2) + lane_id();
+#pragma unroll
+    for (uint32_t it = 0; it < 4; ++it) d.c[it] = philox_common(g + it * 64u, pk.it_lo, pk.it_hi, pk.seed_lo, pk.seed_hi);
+    return d;
 }
-__device__ __forceinline__ void philox_words(uint32_t c0, uint32_t worker, const PhiloxKey& pk, const PhiloxRoundKeys& rk, uint32_t r[4])
+__device__ __forceinline__ void park_lanes(uint4* at, const DrawLanes& d)
 {
-    philox4x32_10(c0, worker, pk.it_lo, pk.it_hi, rk, r);
+    wave_sync();
+#pragma unroll
+    for (int it = 0; it < 4; ++it) at[it * 64 + (int)lane_id()] = make_uint4(d.c[it].x, d.c[it].y, d.c[it].z, d.c[it].d);
+    wave_sync();
 }
-template <int PAIRS, int MIS, class KEYS = PhiloxKey>
+template <int PAIRS, int MIS, class LANES>
 __device__ __forceinline__ void explore_subtile(uint32_t worker, uint32_t t, uint32_t sub, uint32_t start, uint32_t len,
                                                 uint32_t bound_m1, uint32_t sure_m1, uint32_t has_sure, uint32_t skip,
-                                                DrawOut out, PhiloxKey pk, const KEYS& keys)
+                                                const DrawOut& out, const PhiloxKey& pk, const PhiloxRoundKeys& keys, const LANES& lanes)
 {
     const uint32_t lane = lane_id();
     const uint32_t off = sub * SUB;
@@ -124,12 +146,13 @@ __device__ __forceinline__ void explore_subtile(uint32_t worker, uint32_t t, uin
         if (lane == 0) buffer_store1(rn, 0u, 0u);
         return;
     }
-    const uint32_t base = start + off, mis = MIS ? base & 3u : 0u, g0 = base >> 2;
+    const uint32_t base = start + off, mis = MIS ? base & 3u : 0u;
     const uint32_t end = sub_len + mis;                              // positions mis .. end - 1 belong to the sub-tile
     uint32_t* ckeys = PAIRS ? out.cand_keys + ((size_t)t * SUBS + sub) * PAIR_SLOT : out.cand_keys + (size_t)base;
     const uint32_t sure_excl = has_sure ? sure_m1 + 1u : 0u;         // sure_m1 < bound_m1: no overflow
     const uint32_t width_m1 = bound_m1 - sure_excl;                  // candidate words are sure_excl .. bound_m1
-    uint32_t run = 0, sword = 0, cword = 0;
+    const uint64_t v = philox_worker(worker, pk.it_lo, pk.seed_lo);
+    uint32_t run = 0, sure = 0, cand = 0;                            // flags of the rounds so far, the last one lowest
     // a candidate's key and place, by the lane that owns it
     auto put = [&](uint32_t pos, uint32_t word, uint32_t e) {
         if (!PAIRS) ckeys[pos] = bound_m1 - word;
@@ -138,30 +161,19 @@ __device__ __forceinline__ void explore_subtile(uint32_t worker, uint32_t t, uin
 #pragma unroll
     for (int it = 0; it < 4; ++it) {
         const uint32_t e0 = (uint32_t)it * 256u + lane * 4u;      // first of this lane's four positions
-        uint32_t r[4];
-        philox_words(g0 + (e0 >> 2), worker, pk, keys, r);
-        uint32_t inside = 15u;
-        if (end != SUB) inside = inside_mask(e0, end);                // uniform: a ragged or shifted sub-tile
-        if (MIS && it == 0 && lane == 0) inside &= ~((1u << mis) - 1u);
-        // sure flags of the four parameters, without branches (word below sure_excl)
-        uint32_t fs = (r[0] < sure_excl ? 1u : 0u) | (r[1] < sure_excl ? 2u : 0u) | (r[2] < sure_excl ? 4u : 0u) |
-                      (r[3] < sure_excl ? 8u : 0u);
-        if (MIS || end != SUB) fs &= inside;
-        // bitmap words: lanes 8j..8j+7 make word j of this round
-        const uint32_t vs = or_reduce8(fs << (4u * (lane & 7u)));
-        if ((lane & 7u) == (uint32_t)it) sword = vs;       // all eight lanes of a group hold the word: lane `it` of the group keeps it
-        // candidate zone sure_excl <= word <= bound: one test for the four (the smallest distance above sure_excl;
-        // words below it wrap to huge distances); the per-parameter work only when some lane of the wave has one,
-        // which is rare with a narrow zone
-        const uint32_t d0 = r[0] - sure_excl, d1 = r[1] - sure_excl, d2 = r[2] - sure_excl, d3 = r[3] - sure_excl;
-        const uint32_t dmin = min(min(d0, d1), min(d2, d3));
+        uint32_t r[4], d[4];
+        philox_words(lanes(it), v, keys, r);
+        sub4_borrow(r, sure_excl, d, sure);        // a word inside the sure zone wraps to a huge distance
+        // candidate zone sure_excl <= word <= bound: one test for the four; the per-parameter work only when some lane of
+        // the wave has one, which is rare with a narrow zone
+        const uint32_t dmin = min(min(d[0], d[1]), min(d[2], d[3]));
+        uint32_t fc = 0;
         if (__ballot(dmin <= width_m1) != 0ull) {                     // uniform
-            uint32_t fc = (d0 <= width_m1 ? 1u : 0u) | (d1 <= width_m1 ? 2u : 0u) | (d2 <= width_m1 ? 4u : 0u) |
-                          (d3 <= width_m1 ? 8u : 0u);
-            if (MIS || end != SUB) fc &= inside;
-            if (!PAIRS) {
-                const uint32_t vc = or_reduce8(fc << (4u * (lane & 7u)));
-                if ((lane & 7u) == (uint32_t)it) cword = vc;
+            fc = (d[0] <= width_m1 ? 1u : 0u) | (d[1] <= width_m1 ? 2u : 0u) | (d[2] <= width_m1 ? 4u : 0u) |
+                 (d[3] <= width_m1 ? 8u : 0u);
+            if (MIS || end != SUB) {                                  // a ragged or shifted sub-tile
+                fc &= inside_mask(e0, end);
+                if (MIS && it == 0 && lane == 0) fc &= ~((1u << mis) - 1u);
             }
             // place in the list: candidates of lower lanes in this round, all four components
             uint32_t below = 0, total = 0;
@@ -179,12 +191,21 @@ __device__ __forceinline__ void explore_subtile(uint32_t worker, uint32_t t, uin
             }
             run += total;
         }
+        if (!PAIRS) cand |= fc << (4 * it);
+    }
+    sure = __brev(sure) >> 16;                                       // bit 4 * round + component
+    if (MIS || end != SUB) {
+        uint32_t in = 0;
+#pragma unroll
+        for (int it = 0; it < 4; ++it) in |= inside_mask((uint32_t)it * 256u + lane * 4u, end) << (4 * it);
+        if (MIS && lane == 0) in &= ~((1u << mis) - 1u);
+        sure &= in;
     }
     // the block beyond the four rounds: positions SUB .. end - 1, at most three (uniform)
     uint32_t xs = 0, xc = 0;
     if (MIS && end > SUB) {
         uint32_t r[4];
-        philox4x32_10(g0 + SUB / 4u, worker, pk.it_lo, pk.it_hi, pk.seed_lo, pk.seed_hi, r);
+        philox4x32_10((base >> 2) + SUB / 4u, worker, pk.it_lo, pk.it_hi, pk.seed_lo, pk.seed_hi, r);
 #pragma unroll
         for (uint32_t cc = 0; cc < 3; ++cc) {
             if (SUB + cc >= end) break;
@@ -197,19 +218,19 @@ __device__ __forceinline__ void explore_subtile(uint32_t worker, uint32_t t, uin
         }
     }
     // the 32 bitmap words of the sub-tile in one store of one whole line by lanes 0..31 in address order (scattered
-    // words make the memory side read the line first): word 8 * it + j sits in lane 8 * j + it
-    const int src = (int)(8u * (lane & 7u) + ((lane >> 3) & 3u));
-    auto store = [&](const __amdgpu_buffer_rsrc_t& dst, uint32_t word, uint32_t extra) {
-        uint32_t v = __shfl(word, src, 64);
+    // words make the memory side read the line first): word 8 * round + j sits in lane 8 * j + 2 * round
+    const int src = (int)(8u * (lane & 7u) + 2u * ((lane >> 3) & 3u));
+    auto store = [&](const __amdgpu_buffer_rsrc_t& dst, uint32_t flags, uint32_t extra) {
+        uint32_t w = __shfl(transpose_flags(flags), src, 64);
         if (MIS && mis) {                                              // uniform
-            uint32_t next = __shfl_down(v, 1, 64);
+            uint32_t next = __shfl_down(w, 1, 64);
             if (lane == SUB_WORDS - 1u) next = extra;
-            v = (v >> mis) | (next << ((32u - mis) & 31u));          // mis is 1 to 3
+            w = (w >> mis) | (next << ((32u - mis) & 31u));          // mis is 1 to 3
         }
-        if (lane < SUB_WORDS) buffer_store1(dst, lane * 4u, v);
+        if (lane < SUB_WORDS) buffer_store1(dst, lane * 4u, w);
     };
-    store(rs, sword, xs);
-    if (!PAIRS) store(rc, cword, xc);
+    store(rs, sure, xs);
+    if (!PAIRS) store(rc, cand, xc);
     if (lane == 0) buffer_store1(rn, 0u, run);
 }
 
@@ -354,7 +375,9 @@ __global__ __launch_bounds__(BLOCK, SCORE_MINB) void k_score(const float* __rest
                     for (int k = 0; k < WT; ++k) x[k] = buffer_load4_aux<SCORE_LD_AUX>(rg[k], lane_bytes);
                 }
             }
-            if (PRE) {          // ... do this round's share of the integer work while they fly ...
+            if (PRE && (uint32_t)r < pre.nw) {          // ... do this round's share of the integer work while they fly ...
+                const DrawLanes lanes = draw_lanes(start, wid, pre.pk);
+                const PhiloxRoundKeys rk = philox_round_keys<false>(pre.pk.seed_lo, pre.pk.seed_hi);
 #pragma unroll 1
                 for (uint32_t b = (uint32_t)r; b < pre.nw; b += 4) {
                     DrawOut out;
@@ -363,7 +386,7 @@ __global__ __launch_bounds__(BLOCK, SCORE_MINB) void k_score(const float* __rest
                     out.cand_keys = pre.cand_keys + (size_t)b * pre.keys_stride;
                     out.cnt_cand = pre.cnt_cand + (size_t)b * T * SUBS;
                     explore_subtile<(PRE == 2) ? 1 : 0, 1>(pre.worker0 + b, t, wid, start, len, pre_bound, pre_sure,
-                                                             pre_has_sure, pre_skip, out, pre.pk, pre.pk);
+                                                             pre_has_sure, pre_skip, out, pre.pk, rk, lanes);
                 }
             }
             if (vec) {          // ... then score them
@@ -525,11 +548,25 @@ __global__ __launch_bounds__(BLOCK, SCOREF_MINB) void k_score_flat(const float* 
 #pragma unroll
         for (int k = 0; k < WT; ++k) x[k] = buffer_load4_aux<SCOREF_LD_AUX>(rg[k], o);
     };
-    constexpr bool KEYS_IN_VGPRS = WT <= 8;      // 20 registers; with 16 workers' rounds beside them they would spill
+    // 14 and 16 registers from a tile's first round to its last; with 16 workers' rounds beside them they would spill: the
+    // keys are computed anew and the lanes' part waits in LDS
+    constexpr bool HELD = WT <= 8;
+    __shared__ uint4 parked[PRE && !HELD ? 4 : 1][256];
     PhiloxRoundKeys rkeys;
-    if constexpr (PRE && KEYS_IN_VGPRS) rkeys = philox_round_keys(pre.pk.seed_lo, pre.pk.seed_hi);
+    DrawLanes lanes;
+    if constexpr (PRE && HELD) rkeys = philox_round_keys<true>(pre.pk.seed_lo, pre.pk.seed_hi);
     auto draw = [&](uint32_t t, uint32_t len, uint32_t r) {      // this round's share of the announced draws
-        if (PRE) {
+        if (PRE && r < pre.nw) {
+            PhiloxKey pk = pre.pk;
+            if constexpr (!HELD) {
+                asm volatile("" : "+s"(pk.seed_lo), "+s"(pk.seed_hi));
+                rkeys = philox_round_keys<false>(pk.seed_lo, pk.seed_hi);
+            }
+            if (r == 0) {
+                const DrawLanes d = draw_lanes(t * TILE, wid, pk);
+                if constexpr (HELD) lanes = d;
+                else park_lanes(parked[wid], d);
+            }
 #pragma unroll 1
             for (uint32_t b = r; b < pre.nw; b += 4) {
                 DrawOut out;
@@ -537,15 +574,12 @@ __global__ __launch_bounds__(BLOCK, SCOREF_MINB) void k_score_flat(const float* 
                 out.cand_bits = pre.cand_bits + (size_t)b * T * TILE_WORDS;
                 out.cand_keys = pre.cand_keys + (size_t)b * pre.keys_stride;
                 out.cnt_cand = pre.cnt_cand + (size_t)b * T * SUBS;
-                if constexpr (KEYS_IN_VGPRS) {
+                if constexpr (HELD)
                     explore_subtile<(PRE == 2) ? 1 : 0, 0>(pre.worker0 + b, t, wid, t * TILE, len, pre_bound, pre_sure,
-                                                             pre_has_sure, pre_skip, out, pre.pk, rkeys);
-                } else {
-                    PhiloxKey pk = pre.pk;
-                    asm volatile("" : "+s"(pk.seed_lo), "+s"(pk.seed_hi));       // round keys computed anew, not kept
+                                                             pre_has_sure, pre_skip, out, pk, rkeys, lanes);
+                else
                     explore_subtile<(PRE == 2) ? 1 : 0, 0>(pre.worker0 + b, t, wid, t * TILE, len, pre_bound, pre_sure,
-                                                             pre_has_sure, pre_skip, out, pk, pk);
-                }
+                                                             pre_has_sure, pre_skip, out, pk, rkeys, ParkedLanes{parked[wid]});
             }
         }
     };
@@ -798,32 +832,39 @@ __global__ __launch_bounds__(1024) void k_sample_bound(const uint32_t* __restric
 struct SpecTau { const uint32_t* cur; uint32_t* next; uint32_t* fail; };
 constexpr uint32_t SPEC_MARGIN = 1u << 17;
 
-// Stand-alone draw over every (worker, tile); each wave owns one sub-tile of the block's
-// tiles.  grid (blocks, n_workers).
+// Stand-alone draw over every (worker, tile); each wave owns one sub-tile of the block's tiles and draws it for per_group
+// workers in turn.  grid (blocks, ceil(n_workers / per_group)).
 template <int MIS, int PAIRS>
 __global__ __launch_bounds__(BLOCK) void k_explore_keys(const uint32_t* __restrict__ tile_start,
                                                         const uint32_t* __restrict__ tile_seg, uint32_t T,
                                                         uint32_t n_seg, const SegState* __restrict__ states,
                                                         uint32_t* __restrict__ sure_bits, uint32_t* __restrict__ cand_bits,
                                                         uint32_t* __restrict__ cand_keys, uint32_t* __restrict__ cnt_cand,
-                                                        uint64_t keys_stride, uint32_t worker0, PhiloxKey pk)
+                                                        uint64_t keys_stride, uint32_t worker0, uint32_t n_workers, uint32_t per_group,
+                                                        PhiloxKey pk)
 {
-    const uint32_t b = blockIdx.y, worker = worker0 + b, wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const uint32_t wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+    const uint32_t b0 = blockIdx.y * per_group, b1 = min(b0 + per_group, n_workers);
     const uint32_t t0 = (uint32_t)((uint64_t)T * blockIdx.x / gridDim.x);
     const uint32_t t1 = (uint32_t)((uint64_t)T * (blockIdx.x + 1) / gridDim.x);
-    DrawOut out;
-    out.sure_bits = sure_bits + (size_t)b * T * TILE_WORDS;
-    out.cand_bits = cand_bits + (size_t)b * T * TILE_WORDS;
-    out.cand_keys = cand_keys + (size_t)b * keys_stride;
-    out.cnt_cand = cnt_cand + (size_t)b * T * SUBS;
+    const PhiloxRoundKeys rk = philox_round_keys<true>(pk.seed_lo, pk.seed_hi);
     for (uint32_t t = t0; t < t1; ++t) {
         const uint32_t seg = (n_seg == 1) ? 0u : tile_seg[t];
-        const SegState* st = &states[(size_t)b * n_seg + seg];
+        const SegState* st = &states[seg];                 // the same for every worker
         const uint32_t bound_m1 = st->bound_m1;
         const uint32_t sure_m1 = st->sure_m1, has_sure = st->has_gt;
         const uint32_t skip = st->need0 == 0;
         const uint32_t start = tile_start[t], len = tile_start[t + 1] - start;
-        explore_subtile<PAIRS, MIS>(worker, t, wid, start, len, bound_m1, sure_m1, has_sure, skip, out, pk, pk);
+        const DrawLanes lanes = draw_lanes(start, wid, pk);
+#pragma unroll 1
+        for (uint32_t b = b0; b < b1; ++b) {
+            DrawOut out;
+            out.sure_bits = sure_bits + (size_t)b * T * TILE_WORDS;
+            out.cand_bits = cand_bits + (size_t)b * T * TILE_WORDS;
+            out.cand_keys = cand_keys + (size_t)b * keys_stride;
+            out.cnt_cand = cnt_cand + (size_t)b * T * SUBS;
+            explore_subtile<PAIRS, MIS>(worker0 + b, t, wid, start, len, bound_m1, sure_m1, has_sure, skip, out, pk, rk, lanes);
+        }
     }
 }
 
