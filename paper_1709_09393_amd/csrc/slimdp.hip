@@ -172,6 +172,7 @@ struct slimdp_ctx {
         uint32_t* fail = nullptr;               // per segment: the selection's threshold fell below the capture bound
         uint2* bits = nullptr;
         float* vals = nullptr;
+        float* evals = nullptr;                 // explorer capture (flat models)
         int cur = 0;
         bool next_written = false;              // a selection has refreshed lo[cur ^ 1] since the last capture
         bool bound_valid = false;               // lo[cur] comes from a selection (else: nothing, or a sampled estimate)
@@ -183,6 +184,9 @@ struct slimdp_ctx {
         uint32_t W = 0;
         int vec_ok = 0;
         uint64_t core_epoch = 0;                // 0: no selection on the captured score yet
+        // explorer values kept beside it: slots a sub-tile and worker (0: none), for how many workers; void once another draw
+        // has gone to the bitmap that tells which they are
+        uint32_t expl_slots = 0;
     } spec;
     int64_t opt_pack_nbuf = 2;
     int64_t opt_pack_kernel = 1;           // general pack: 1 = loading and storing waves apart, 0 = one set of waves
@@ -190,6 +194,7 @@ struct slimdp_ctx {
     int64_t opt_build_blocks = 4;          // blocks per compute unit of the core candidate pass
     int64_t opt_pack_core_blocks = 0;      // blocks per compute unit of the pack from the capture (0: one per 1024 list entries)
     int64_t opt_core_predict = 1;          // the flat scoring kernel sorts whole tiles against the predicted threshold bin (0: never; 2: test, a wrong bin)
+    int64_t opt_explore_keep = 1;          // the scoring pass keeps the explorers' values beside the core's: 1 by size, 2 whenever it can, 0 never
     int64_t opt_score_pipeline = 1;        // flat aligned models: the scoring kernel with two rounds of loads in flight
     int64_t opt_expected_core = -1;        // core size the next selection will ask for (flat model), if the caller says
     int64_t opt_estimate_bias = 0;         // test switch: added to a sampled capture bound
@@ -328,6 +333,23 @@ uint32_t draw_group(const slimdp_ctx* c, uint32_t per_cu, uint32_t n_workers)
     uint32_t g = n_workers;
     while (g > 1 && (uint64_t)c->T * ((n_workers + g - 1) / g) < (uint64_t)c->cus * per_cu) g = (g + 1) / 2;
     return g;
+}
+
+// Room of the explorer capture: the pipelined scoring kernel's, which serves flat models and up to 16 workers.
+size_t expl_capture_words(uint64_t T, uint32_t max_workers, uint32_t n_seg)
+{
+    return n_seg == 1 ? (size_t)T * SUBS * std::min(max_workers, 16u) * EXPL_SLOTS_MAX : 0;
+}
+
+// Slots for the explorer values of a sub-tile, from the share of the words in the sure zone: of its 256 blocks of four those
+// with a sure parameter, two standard deviations more (what does not fit, under one in a thousand, is gathered).  Above EXPL_SLOTS_MAX nothing is
+// kept: 6 % of the parameters, where a gather reads nearly every line anyway.
+uint32_t expl_slots(const SegInit& in)
+{
+    if (!in.has_gt) return 0;
+    const double p = ((double)in.sure_m1 + 1.0) / 4294967296.0, full = 1.0 - std::pow(1.0 - p, 4.0);
+    const double want = 256.0 * full + 2.0 * std::sqrt(256.0 * full * (1.0 - full));
+    return want <= 32.0 ? 32u : want <= (double)EXPL_SLOTS_MAX ? EXPL_SLOTS_MAX : 0u;
 }
 
 template <class P> bool table_ok(P const* tab, uint32_t nw, bool allow_null_entries = false)
@@ -532,6 +554,7 @@ uint64_t slimdp_capture_bytes(uint64_t n, uint32_t max_workers, uint32_t n_seg, 
     cv.take<uint32_t>(n_seg); cv.take<uint32_t>(n_seg); cv.take<uint32_t>(n_seg);
     cv.take<uint2>((size_t)T * TILE_WORDS);
     cv.take<float>((size_t)max_workers * T * SUBS * SPEC_CAP);
+    cv.take<float>(expl_capture_words(T, max_workers, n_seg));
     cv.take<uint32_t>((size_t)T * SAMPLE_PER);
     return align_up(cv.pos, 256);
 }
@@ -650,6 +673,7 @@ int slimdp_set_option(slimdp_ctx* ctx, const char* name, int64_t value)
     if (strcmp(name, "pack_kernel") == 0 && (value == 0 || value == 1)) { ctx->opt_pack_kernel = value; return SLIMDP_OK; }
     if (strcmp(name, "pull_kernel") == 0 && (value == 0 || value == 1)) { ctx->opt_pull_kernel = value; return SLIMDP_OK; }
     if (strcmp(name, "expected_core") == 0 && value >= -1 && (value < 0 || (uint64_t)value <= ctx->n)) { ctx->opt_expected_core = value; return SLIMDP_OK; }
+    if (strcmp(name, "explore_keep") == 0 && value >= 0 && value <= 2) { ctx->opt_explore_keep = value; return SLIMDP_OK; }
     if (strcmp(name, "score_pipeline") == 0 && (value == 0 || value == 1)) { ctx->opt_score_pipeline = value; return SLIMDP_OK; }
     if (strcmp(name, "capture_estimate_bias") == 0) { ctx->opt_estimate_bias = value; return SLIMDP_OK; }
     if (strcmp(name, "speculative_pack") == 0) {
@@ -663,6 +687,7 @@ int slimdp_set_option(slimdp_ctx* ctx, const char* name, int64_t value)
                 ctx->spec.fail = cv.take<uint32_t>(S);
                 ctx->spec.bits = cv.take<uint2>((size_t)ctx->T * TILE_WORDS);
                 ctx->spec.vals = cv.take<float>((size_t)ctx->maxW * ctx->T * SUBS * SPEC_CAP);
+                ctx->spec.evals = cv.take<float>(expl_capture_words(ctx->T, ctx->maxW, ctx->n_seg));
                 ctx->spec.sample = cv.take<uint32_t>((size_t)ctx->T * SAMPLE_PER);
             };
             carve_spec(sizing);
@@ -728,6 +753,8 @@ static int score_impl(slimdp_ctx* ctx, const float* w, const float* const* g, ui
     // an announced explorer draw rides along if every segment has a narrow candidate bound
     PreArgs pre{};
     bool presample = false, pairs = false;
+    uint32_t slots = 0;
+    ctx->spec.expl_slots = 0;
     if (ctx->opt_hint_mode == 0) ctx->pre.valid = false;      // a draw made on the side stream stays valid
     if (ctx->hint.valid && ctx->opt_hint_mode == 0) {
         std::vector<SegInit> init;
@@ -749,6 +776,7 @@ static int score_impl(slimdp_ctx* ctx, const float* w, const float* const* g, ui
             pre.keys_stride = pairs ? ctx->pair_stride : ctx->keys_stride;
             pre.pk = PhiloxKey{(uint32_t)ctx->seed, (uint32_t)(ctx->seed >> 32), (uint32_t)ctx->hint.iteration,
                                (uint32_t)(ctx->hint.iteration >> 32)};
+            slots = pairs && ctx->n_seg == 1 ? expl_slots(init[0]) : 0;
             presample = true;
         }
     }
@@ -783,13 +811,25 @@ static int score_impl(slimdp_ctx* ctx, const float* w, const float* const* g, ui
     if (ctx->n_seg == 1 && vec_ok && ctx->opt_strided && ctx->opt_score_pipeline && ctx->n < (1ull << 30) &&
         (W <= 8 || W == 16)) {
         const dim3 fgrid(persistent_blocks(ctx, SCOREF_MINB, 1)), fblock(BLOCK);
+        // The explorers' values too: a gather of 2 % of the parameters reads 44 % of the updates' lines, which costs little only
+        // while they come from the caches (256 MB), and one worker's too little for the scoring pass to earn it.  Whole iteration
+        // with and without, us: 138*10^6 parameters, 8 workers 2,140 / 2,320 (5 %: 2,475 / 2,827), 16*10^6 and 8 339 / 355, 8*10^6 and 8
+        // 232 / 237, 32*10^6 and 2 316 / 322, but 8*10^6 and 4 185 / 184, 10^6 and 4 (scoring and pack alone) 31 / 24, 64*10^6 and 1 481 / 475.
+        // Fewer workers announced than scored: the draw for its own sake.  A context with recorded calls: a replay may draw
+        // again between a scoring pass and its pack, unknown to the host.
+        if (!capture || pre.nw < W || !known || ctx->opt_explore_keep == 0 ||
+            (ctx->opt_explore_keep == 1 && (W < 2 || ctx->n * W * 4u < (256ull << 20))))
+            slots = 0;
+        pre.vals = ctx->spec.evals; pre.slots = slots;
+        ctx->spec.expl_slots = slots;
         const ClsArgs cls{ctx->c_pred, ctx->c_used, (int)ctx->opt_core_predict, ctx->c_gt_bits, ctx->c_cand_bits, ctx->c_cand_keys, ctx->c_cnt_gt, ctx->c_cnt_cand};
 #define LAUNCH_FLAT_Q(WT, PRE, SPEC, DENSE)                                                                           \
     hipLaunchKernelGGL((k_score_flat<WT, PRE, SPEC, DENSE>), fgrid, fblock, 0, ctx->stream, w, gt, c, score, ctx->n,  \
                        ctx->c_hist, pre, sa, cls, w_new, lr)
 #define LAUNCH_FLAT_S(WT, SPEC, DENSE)                                                                                \
     do {                                                                                                              \
-        if (presample && pairs) LAUNCH_FLAT_Q(WT, 2, SPEC, DENSE);                                                    \
+        if (presample && pairs && (SPEC) && slots) LAUNCH_FLAT_Q(WT, ((SPEC) ? 3 : 2), SPEC, DENSE);                  \
+        else if (presample && pairs) LAUNCH_FLAT_Q(WT, 2, SPEC, DENSE);                                               \
         else if (presample) LAUNCH_FLAT_Q(WT, 1, SPEC, DENSE);                                                        \
         else LAUNCH_FLAT_Q(WT, 0, SPEC, DENSE);                                                                       \
     } while (0)
@@ -1100,6 +1140,7 @@ int slimdp_sample_explore(slimdp_ctx* ctx, const uint32_t* core_bits, const uint
     if (rc) return rc;
     if (M > 0 && !table_ok(expl_idx, n_workers)) return fail(ctx, SLIMDP_ERR_INVALID_ARG, "slimdp_sample_explore: NULL expl_idx entry");
     const uint32_t T = ctx->T, S = ctx->n_seg, B = n_workers;
+    (void)device_state_known(ctx);           // a recorded request draws again when it is replayed
     // zones already drawn inside slimdp_score for exactly this request, in the format this call wants?
     const bool cached = ctx->pre.same(iteration, worker0, n_workers, k_seg, m_seg, S) && ctx->pre.pairs == short_list;
     ctx->pre.valid = false;
@@ -1145,7 +1186,7 @@ int slimdp_sample_explore(slimdp_ctx* ctx, const uint32_t* core_bits, const uint
     const ExploreLists lists{ctx->e_list, ctx->e_list_count, ctx->d_list_first, ctx->list_first[S], (uint32_t)align_up(S, 32)};
     if (short_list) {
         constexpr int SBPW = 8;
-        if (!cached) LAUNCH_DRAW(1);
+        if (!cached) { ctx->spec.expl_slots = 0; LAUNCH_DRAW(1); }
         const uint32_t sure_blocks = ((T + 3) / 4) * ((B + SBPW - 1) / SBPW);
         const uint32_t gather_blocks = B * ((T + 63) / 64);
         hipLaunchKernelGGL(k_explore_collect<SBPW>, dim3(sure_blocks + gather_blocks), dim3(BLOCK), 0, st, core_bits, n_words, ctx->n,
@@ -1155,7 +1196,7 @@ int slimdp_sample_explore(slimdp_ctx* ctx, const uint32_t* core_bits, const uint
     } else {
         rc = ensure_wide_keys(ctx);
         if (rc) return rc;
-        if (!cached) LAUNCH_DRAW(0);
+        if (!cached) { ctx->spec.expl_slots = 0; LAUNCH_DRAW(0); }
         hipLaunchKernelGGL(k_explore_collect_wide, dim3(P, B), dim3(BLOCK), 0, st, core_bits, n_words, ctx->n, ctx->d_tile_start,
                            ctx->d_tile_seg, T, S, ctx->e_sure_bits, ctx->e_cnt_sel, ctx->e_cand_bits, ctx->e_cand_keys,
                            ctx->keys_stride, lists, ctx->d_flags);
@@ -1221,12 +1262,14 @@ int slimdp_explore_hint(slimdp_ctx* ctx, const uint64_t* k_seg, uint32_t worker0
     }
     if (!narrow || M == 0) return SLIMDP_OK;  // nothing worth drawing ahead: slimdp_sample_explore draws itself
     if (!short_list) { rc = ensure_wide_keys(ctx); if (rc) return rc; }
+    (void)device_state_known(ctx);
     // the draw starts now on the side stream, once the previous draw's buffers have been read
     // (the event is recorded here, not after every slimdp_sample_explore: an event on a stream costs a gap between kernels)
     SLIMDP_HIP(ctx, hipEventRecord(ctx->ev_consumed, ctx->stream));
     SLIMDP_HIP(ctx, hipStreamWaitEvent(ctx->side, ctx->ev_consumed, 0));
     rc = init_states(ctx, ctx->e_draw_state, init, n_workers, false, ctx->side);
     if (rc) return rc;
+    ctx->spec.expl_slots = 0;
     // few waves keep the arithmetic units busy; the wave slots stay with the kernels of the main stream
     const uint32_t G = draw_group(ctx, (uint32_t)ctx->opt_side_blocks, n_workers), groups = (n_workers + G - 1) / G;
     const uint32_t P = persistent_blocks(ctx, (uint32_t)ctx->opt_side_blocks, groups);
@@ -1333,7 +1376,14 @@ int slimdp_pack(slimdp_ctx* ctx, uint32_t n_workers, const float* const* g, cons
         for (uint32_t q = 0; q < n_workers; ++q) { mt.c[q] = (uint32_t)m_w[q]; if (m_w[q] > mmax) mmax = m_w[q]; }
         rc = wait_for_lists(ctx, n_workers, expl_idx, expl_off, m_w);    // the core values above did not need the explorer lists; these do
         if (rc) return rc;
-        if (mmax) {
+        if (mmax && ctx->spec.expl_slots && device_state_known(ctx)) {
+            hipLaunchKernelGGL(k_pack_expl_spec, dim3((ctx->T + 3) / 4, (n_workers + PEXP - 1) / PEXP), dim3(BLOCK), 0, ctx->stream,
+                               make_tab<PtrTab>(g, n_workers), n_workers, ctx->n, ctx->T, (uint32_t)(ctx->n / TILE),
+                               make_tab<PtrTab>(expl_idx, n_workers), make_tab<PtrTab>(expl_off, n_workers), mt, ctx->e_sure_bits,
+                               ctx->e_pair_keys, ctx->pair_stride, ctx->e_cnt_cand, ctx->spec.evals, ctx->spec.expl_slots, n_workers,
+                               make_tab<MutPtrTab>(expl_val, n_workers));
+            SLIMDP_LAUNCHED(ctx, "k_pack_expl_spec");
+        } else if (mmax) {
             uint64_t blocks = (mmax + 1023) / 1024;
             if (blocks > 2048) blocks = 2048;
             hipLaunchKernelGGL(k_pack_expl_gather, dim3((uint32_t)blocks, n_workers), dim3(256), 0, ctx->stream,

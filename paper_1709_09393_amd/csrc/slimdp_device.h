@@ -115,9 +115,10 @@ __device__ __forceinline__ uint32_t or_reduce8(uint32_t v)
 // by an addition with carry (the first word's ends up highest).  Eight instructions; from the comparisons the compiler
 // makes masks, selects and ors, sixteen.  All four borrows are written before the first is read: a mask that the
 // vector unit wrote may be read by it two instructions later.
-__device__ __forceinline__ void sub4_borrow(const uint32_t r[4], uint32_t bound, uint32_t d[4], uint32_t& acc)
+struct Masks4 { uint64_t m0, m1, m2, m3; };
+__device__ __forceinline__ Masks4 sub4_borrow(const uint32_t r[4], uint32_t bound, uint32_t d[4], uint32_t& acc)
 {
-    uint64_t m0, m1, m2, m3;
+    Masks4 m;
     asm("v_subrev_co_u32_e64 %0, %5, %9, %10\n\t"
         "v_subrev_co_u32_e64 %1, %6, %9, %11\n\t"
         "v_subrev_co_u32_e64 %2, %7, %9, %12\n\t"
@@ -126,20 +127,30 @@ __device__ __forceinline__ void sub4_borrow(const uint32_t r[4], uint32_t bound,
         "v_addc_co_u32_e64 %4, vcc, %4, %4, %6\n\t"
         "v_addc_co_u32_e64 %4, vcc, %4, %4, %7\n\t"
         "v_addc_co_u32_e64 %4, vcc, %4, %4, %8"
-        : "=&v"(d[0]), "=&v"(d[1]), "=&v"(d[2]), "=&v"(d[3]), "+&v"(acc), "=&s"(m0), "=&s"(m1), "=&s"(m2), "=&s"(m3)
+        : "=&v"(d[0]), "=&v"(d[1]), "=&v"(d[2]), "=&v"(d[3]), "+&v"(acc), "=&s"(m.m0), "=&s"(m.m1), "=&s"(m.m2), "=&s"(m.m3)
         : "s"(bound), "v"(r[0]), "v"(r[1]), "v"(r[2]), "v"(r[3])
         : "vcc");
+    return m;
+}
+// The component of x that belongs to the first of sub4_borrow's masks in which the lane is set (x.w if none is).
+__device__ __forceinline__ float first_masked(const float4& x, const Masks4& m)
+{
+    float v;
+    asm("v_cndmask_b32_e64 %0, %1, %2, %5\n\t"
+        "v_cndmask_b32_e64 %0, %0, %3, %6\n\t"
+        "v_cndmask_b32_e64 %0, %0, %4, %7"
+        : "=&v"(v) : "v"(x.w), "v"(x.z), "v"(x.y), "v"(x.x), "s"(m.m2), "s"(m.m1), "s"(m.m0));
+    return v;
 }
 
 // Four rounds of four flags a lane (bit 4 * round + i of v) to bitmap words: lanes 8j .. 8j+7 make word j of every round, and
 // lane 8j + 2 * round (and the one beside it) gets it.  Nibbles are paired with the neighbouring lane's, the bytes then cross
 // an 8-lane group in two exchanges (half-row mirror, lane pairs): ten instructions for four words, where a reduction
 // for each of them took six.
-__device__ __forceinline__ uint32_t transpose_flags(uint32_t v)
+__device__ __forceinline__ uint32_t transpose_spread(uint32_t v)             // one round a byte, in its low half
 {
     const uint32_t lane = lane_id();
-    v = (v | (v << 8)) & 0x00FF00FFu;
-    v = ((v | (v << 4)) & 0x0F0F0F0Fu) << (4u * (lane & 1u));                          // byte r = round r, own nibble in place
+    v <<= 4u * (lane & 1u);
     v |= (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0xB1, 0xF, 0xF, true);       // quad_perm [1,0,3,2]
     // lanes 0..3 of a group keep rounds 0 and 1, lanes 4..7 rounds 2 and 3, of their pair and of the one mirrored (p and 3 - p)
     uint32_t o = (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x141, 0xF, 0xF, true);      // row_half_mirror
@@ -149,6 +160,12 @@ __device__ __forceinline__ uint32_t transpose_flags(uint32_t v)
     // pairs in order: own (p, 3 - p) and the neighbour's
     const uint32_t sel = (lane & 2u) ? ((lane & 4u) ? 0x03070602u : 0x07030206u) : ((lane & 4u) ? 0x05010004u : 0x01050400u);
     return __builtin_amdgcn_perm(o, v, sel);
+}
+
+__device__ __forceinline__ uint32_t transpose_flags(uint32_t v)              // one round a nibble of the low half word
+{
+    v = (v | (v << 8)) & 0x00FF00FFu;
+    return transpose_spread((v | (v << 4)) & 0x0F0F0F0Fu);
 }
 
 __device__ __forceinline__ uint32_t wave_sum(uint32_t v)

@@ -253,6 +253,11 @@ __device__ __forceinline__ void flush_hist(uint32_t* lds, uint32_t nb, uint32_t*
 
 // PRE != 0 additionally draws the explorer zones of pre.nw workers for every tile
 // (explore_subtile): integer work that runs while other waves wait for memory.
+// Explorer capture (flat models, narrow zones, speculative packing): the update values of the parameters in the sure zones,
+// kept by the scoring pass for the pack.  A sub-tile has PreArgs::slots values for each worker scored, in the order of
+// the parameters' blocks of four: the first sure parameter of every block that has one.  Which those are is told by the
+// sure bitmap as the draw left it.
+constexpr uint32_t EXPL_SLOTS_MAX = 64;
 struct PreArgs {
     uint32_t nw, worker0, n_seg;
     const SegState* states;
@@ -262,6 +267,8 @@ struct PreArgs {
     uint32_t* cnt_cand;
     uint64_t keys_stride;
     PhiloxKey pk;
+    float* vals;             // explorer capture (see ExplCapture); slots: entries a sub-tile and worker, 0: none
+    uint32_t slots;
 };
 
 // SPEC = 1 (speculative packing, WT != 0 only) keeps, for every parameter of a full aligned
@@ -525,10 +532,7 @@ __global__ __launch_bounds__(BLOCK, SCOREF_MINB) void k_score_flat(const float* 
     for (uint32_t b = threadIdx.x; b < CORE_NB1; b += BLOCK) h1[b] = 0;
     __syncthreads();
     const uint32_t bytes = (uint32_t)(n * 4u);
-    const __amdgpu_buffer_rsrc_t rw = buffer_of(w, bytes), rS = buffer_of(S, bytes), rn = buffer_of(DENSE ? w_new : S, bytes);
-    __amdgpu_buffer_rsrc_t rg[WT];
-#pragma unroll
-    for (int k = 0; k < WT; ++k) rg[k] = buffer_of(g.p[k], bytes);
+    const __amdgpu_buffer_rsrc_t rS = buffer_of(S, bytes), rn = buffer_of(DENSE ? w_new : S, bytes);
     uint32_t pre_bound = 0, pre_sure = 0, pre_has_sure = 0, pre_skip = 1;
     if (PRE) {
         const SegState* st = &pre.states[0];
@@ -542,19 +546,37 @@ __global__ __launch_bounds__(BLOCK, SCOREF_MINB) void k_score_flat(const float* 
     uint32_t crun = 0, ngt = 0, gw[4], cw[4];
     // byte offset of this lane's vector in round r of this wave's sub-tile of tile t
     auto voff = [&](uint32_t t, uint32_t r) { return (t * TILE + wid * SUB + r * 256u) * 4u + lane * 16u; };
+    // a scalar base and a 32-bit lane offset (whole arrays are below 2^32 bytes): a descriptor would take four scalar registers
+    // of each array, and they are short here
     auto fetch = [&](float4 (&x)[WT + 1], uint32_t t, uint32_t r) {
         const uint32_t o = voff(t, r);
-        x[WT] = buffer_load4_aux<SCOREF_LD_AUX>(rw, o);
+        x[WT] = ld4<1>(reinterpret_cast<const float*>(reinterpret_cast<const char*>(w) + o));
 #pragma unroll
-        for (int k = 0; k < WT; ++k) x[k] = buffer_load4_aux<SCOREF_LD_AUX>(rg[k], o);
+        for (int k = 0; k < WT; ++k) x[k] = ld4<1>(reinterpret_cast<const float*>(static_cast<const char*>(g.p[k]) + o));
     };
+    // PRE = 3: a round draws its own 256 parameters for every worker, so that the flags meet the update values in registers;
+    // otherwise a round draws the whole sub-tile for its share of the workers
+    constexpr bool KEEP_EXPL = PRE == 3;
+    constexpr int PAIRS_W = (WT + 1) / 2;
+    constexpr bool PACK_FILL = WT > 8;           // the workers' fill counts as bytes: registers are short there
+    __shared__ __align__(16) float estage[KEEP_EXPL ? 4 * WT * EXPL_SLOTS_MAX : 4];
+    uint32_t esure[KEEP_EXPL ? PAIRS_W : 1], efill[KEEP_EXPL ? (PACK_FILL ? WT / 4 : WT) : 1];
+    uint32_t ecount = 0;                         // lane b: candidates of worker b in this sub-tile
     // 14 and 16 registers from a tile's first round to its last; with 16 workers' rounds beside them they would spill: the
     // keys are computed anew and the lanes' part waits in LDS
     constexpr bool HELD = WT <= 8;
-    __shared__ uint4 parked[PRE && !HELD ? 4 : 1][256];
+    __shared__ uint4 parked[PRE && !HELD && !KEEP_EXPL ? 4 : 1][PRE && !HELD && !KEEP_EXPL ? 256 : 1];
     PhiloxRoundKeys rkeys;
     DrawLanes lanes;
     if constexpr (PRE && HELD) rkeys = philox_round_keys<true>(pre.pk.seed_lo, pre.pk.seed_hi);
+    auto out_of = [&](uint32_t b) {
+        DrawOut out;
+        out.sure_bits = pre.sure_bits + (size_t)b * T * TILE_WORDS;
+        out.cand_bits = pre.cand_bits + (size_t)b * T * TILE_WORDS;
+        out.cand_keys = pre.cand_keys + (size_t)b * pre.keys_stride;
+        out.cnt_cand = pre.cnt_cand + (size_t)b * T * SUBS;
+        return out;
+    };
     auto draw = [&](uint32_t t, uint32_t len, uint32_t r) {      // this round's share of the announced draws
         if (PRE && r < pre.nw) {
             PhiloxKey pk = pre.pk;
@@ -569,18 +591,110 @@ __global__ __launch_bounds__(BLOCK, SCOREF_MINB) void k_score_flat(const float* 
             }
 #pragma unroll 1
             for (uint32_t b = r; b < pre.nw; b += 4) {
-                DrawOut out;
-                out.sure_bits = pre.sure_bits + (size_t)b * T * TILE_WORDS;
-                out.cand_bits = pre.cand_bits + (size_t)b * T * TILE_WORDS;
-                out.cand_keys = pre.cand_keys + (size_t)b * pre.keys_stride;
-                out.cnt_cand = pre.cnt_cand + (size_t)b * T * SUBS;
+                const DrawOut out = out_of(b);
                 if constexpr (HELD)
-                    explore_subtile<(PRE == 2) ? 1 : 0, 0>(pre.worker0 + b, t, wid, t * TILE, len, pre_bound, pre_sure,
+                    explore_subtile<(PRE >= 2) ? 1 : 0, 0>(pre.worker0 + b, t, wid, t * TILE, len, pre_bound, pre_sure,
                                                              pre_has_sure, pre_skip, out, pk, rkeys, lanes);
                 else
-                    explore_subtile<(PRE == 2) ? 1 : 0, 0>(pre.worker0 + b, t, wid, t * TILE, len, pre_bound, pre_sure,
+                    explore_subtile<(PRE >= 2) ? 1 : 0, 0>(pre.worker0 + b, t, wid, t * TILE, len, pre_bound, pre_sure,
                                                              pre_has_sure, pre_skip, out, pk, rkeys, ParkedLanes{parked[wid]});
             }
+        }
+    };
+    // One round of a whole tile for every worker that is scored.  A lane with a sure parameter among its four leaves the
+    // first one's update value in the worker's line of the wave's stage, lanes in order: about 20 values a sub-tile at the
+    // paper's ratio, 4 % of the sure ones are not the first in their lane and are not kept.  Two workers at a time: the
+    // chains of multiplications are long, and eight waves to a unit leave little else to fill them with.
+    auto draw_round = [&](float4 (&x)[WT + 1], uint32_t t, uint32_t r) {
+        PhiloxKey pk = pre.pk;
+        uint32_t worker0 = pre.worker0;
+        asm volatile("" : "+s"(worker0));                        // the workers' scalars are computed anew, not kept
+        if constexpr (!HELD) {
+            asm volatile("" : "+s"(pk.seed_lo), "+s"(pk.seed_hi));
+            rkeys = philox_round_keys<false>(pk.seed_lo, pk.seed_hi);
+        }
+        const PhiloxCommon c = philox_common(((t * TILE + wid * SUB) >> 2) + r * 64u + lane, pk.it_lo, pk.it_hi, pk.seed_lo, pk.seed_hi);
+        const uint32_t sure_excl = pre_has_sure ? pre_sure + 1u : 0u, width_m1 = pre_bound - sure_excl;
+        float* es = estage + wid * (WT * EXPL_SLOTS_MAX);
+        auto candidates = [&](int b, const uint32_t (&d)[4]) {      // rare
+            uint32_t* slot = pre.cand_keys + (size_t)b * pre.keys_stride + ((size_t)t * SUBS + wid) * PAIR_SLOT;
+            uint32_t e0 = d[0], e1 = d[1], e2 = d[2], e3 = d[3];
+#pragma unroll 1
+            for (uint32_t k = 0; k < 4; ++k) {
+                const uint64_t bal = __ballot(e0 <= width_m1);
+                const uint32_t before = __builtin_amdgcn_readlane(ecount, b);
+                const uint32_t pos = __builtin_amdgcn_mbcnt_hi((uint32_t)(bal >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)bal, before));
+                if (e0 <= width_m1 && pos < PAIR_CAP) { slot[2u * pos] = width_m1 - e0; slot[2u * pos + 1u] = r * 256u + lane * 4u + k; }
+                if (lane == (uint32_t)b) ecount += (uint32_t)__popcll(bal);
+                e0 = e1; e1 = e2; e2 = e3;
+            }
+        };
+        auto keep = [&](int b, const Masks4& m) {
+            const uint64_t any = (m.m0 | m.m1) | (m.m2 | m.m3);
+            const uint32_t fill = PACK_FILL ? (efill[b / 4] >> (8 * (b % 4))) & 0xFFu : efill[b];
+            const uint32_t at = __builtin_amdgcn_mbcnt_hi((uint32_t)(any >> 32), __builtin_amdgcn_mbcnt_lo((uint32_t)any, fill));
+            const float v = first_masked(x[b], m);
+            if (__builtin_amdgcn_inverse_ballot_w64(any) && at < pre.slots) es[(uint32_t)b * EXPL_SLOTS_MAX + at] = v;
+            uint32_t& f = efill[PACK_FILL ? b / 4 : b];
+            f += (uint32_t)__popcll(any) << (PACK_FILL ? 8 * (b % 4) : 0);
+            asm("" : "+v"(f));                                    // in a vector register: the scalar ones are short
+        };
+#pragma unroll
+        for (int p = 0; p < PAIRS_W; ++p) {
+            const int A = 2 * p, B = 2 * p + 1 < WT ? 2 * p + 1 : A;
+            if (r == 0) {
+                esure[p] = 0;
+                if (PACK_FILL) { if (p % 2 == 0) efill[p / 2] = 0; }
+                else { efill[A] = 0; efill[B] = 0; }
+            }
+            uint32_t wa[4], wb[4], da[4], db[4];
+            philox_words(c, philox_worker(worker0 + A, pk.it_lo, pk.seed_lo), rkeys, wa);
+            philox_words(c, philox_worker(worker0 + B, pk.it_lo, pk.seed_lo), rkeys, wb);
+            const Masks4 ma = sub4_borrow(wa, sure_excl, da, esure[p]);
+            uint32_t dmin = min(min(da[0], da[1]), min(da[2], da[3]));
+            Masks4 mb = ma;
+            if (B != A) {
+                mb = sub4_borrow(wb, sure_excl, db, esure[p]);
+                dmin = min(dmin, min(min(db[0], db[1]), min(db[2], db[3])));
+            } else esure[p] <<= 4;
+            if (__ballot(dmin <= width_m1) != 0ull) {             // uniform
+                candidates(A, da);
+                if (B != A) candidates(B, db);
+            }
+            if (pre.slots) {                                     // uniform
+                keep(A, ma);
+                if (B != A) keep(B, mb);
+            }
+        }
+        if (r == 3) {
+            // every worker's 32 bitmap words through the wave's (now idle) stage of the core capture: whole lines
+            uint32_t* sb = reinterpret_cast<uint32_t*>(stage + wid * (STAGED * WT));
+            wave_sync();
+#pragma unroll
+            for (int p = 0; p < PAIRS_W; ++p) {
+                const uint32_t v = __brev(esure[p]);             // bit 8 * round + 4 * (second worker) + component
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    if (2 * p + h >= WT) continue;
+                    const uint32_t word = transpose_spread((v >> (4 * h)) & 0x0F0F0F0Fu);
+                    if ((lane & 1u) == 0) sb[(2 * p + h) * SUB_WORDS + 4u * (lane & 6u) + (lane >> 3)] = word;      // word 8 * round + j
+                }
+            }
+            wave_sync();
+#pragma unroll
+            for (int p = 0; p < PAIRS_W; ++p) {
+                const uint32_t b = 2u * p + (lane >> 5);
+                if (b < (uint32_t)WT) pre.sure_bits[((size_t)b * T + t) * TILE_WORDS + wid * SUB_WORDS + (lane & 31u)] = sb[p * 64 + lane];
+            }
+            if (lane < (uint32_t)WT) pre.cnt_cand[((size_t)lane * T + t) * SUBS + wid] = ecount;
+            ecount = 0;
+            if (pre.slots) {
+                const __amdgpu_buffer_rsrc_t rv = buffer_of(pre.vals + ((size_t)t * SUBS + wid) * WT * pre.slots, WT * pre.slots * 4u);
+                const uint32_t sh = pre.slots == 32u ? 3u : 4u;   // 16-byte pieces of a worker's line, as a power of two
+                for (uint32_t k = lane; k < ((uint32_t)WT << sh); k += 64)
+                    buffer_store4_aux<SCOREF_CAP_AUX>(rv, k * 16u, *reinterpret_cast<const float4*>(es + (k >> sh) * EXPL_SLOTS_MAX + (k & ((1u << sh) - 1u)) * 4u));
+            }
+            wave_sync();
         }
     };
     uint32_t spec_run = 0;
@@ -725,11 +839,19 @@ __global__ __launch_bounds__(BLOCK, SCOREF_MINB) void k_score_flat(const float* 
 #pragma unroll 1
     for (; t < T_full; t += gridDim.x) {
         const uint32_t tn = t + gridDim.x;
-        fetch(xb, t, 1); draw(t, TILE, 0); work(xa, t, 0);
-        fetch(xa, t, 2); draw(t, TILE, 1); work(xb, t, 1);
-        fetch(xb, t, 3); draw(t, TILE, 2); work(xa, t, 2);
-        if (tn < T_full) fetch(xa, tn, 0);
-        draw(t, TILE, 3); work(xb, t, 3);
+        if constexpr (KEEP_EXPL) {
+            fetch(xb, t, 1); draw_round(xa, t, 0); work(xa, t, 0);
+            fetch(xa, t, 2); draw_round(xb, t, 1); work(xb, t, 1);
+            fetch(xb, t, 3); draw_round(xa, t, 2); work(xa, t, 2);
+            if (tn < T_full) fetch(xa, tn, 0);
+            draw_round(xb, t, 3); work(xb, t, 3);
+        } else {
+            fetch(xb, t, 1); draw(t, TILE, 0); work(xa, t, 0);
+            fetch(xa, t, 2); draw(t, TILE, 1); work(xb, t, 1);
+            fetch(xb, t, 3); draw(t, TILE, 2); work(xa, t, 2);
+            if (tn < T_full) fetch(xa, tn, 0);
+            draw(t, TILE, 3); work(xb, t, 3);
+        }
     }
     // the ragged last tile
     if (T != T_full && blockIdx.x == T_full % gridDim.x) {
@@ -746,7 +868,19 @@ __global__ __launch_bounds__(BLOCK, SCOREF_MINB) void k_score_flat(const float* 
             S[e] = sc;
             atomicAdd(&h[(__float_as_uint(sc) >> CORE_SHIFT0) & (NB - 1u)], 1u);
         }
-        for (uint32_t r = 0; r < 4; ++r) draw(T_full, len, r);
+        if constexpr (!KEEP_EXPL)
+            for (uint32_t r = 0; r < 4; ++r) draw(T_full, len, r);
+    }
+    // the ragged tile, and workers announced beyond those scored: a whole sub-tile of a worker at a time, nothing kept
+    if constexpr (KEEP_EXPL) {
+        const PhiloxRoundKeys rk = philox_round_keys<false>(pre.pk.seed_lo, pre.pk.seed_hi);
+        for (uint32_t tt = pre.nw > (uint32_t)WT ? blockIdx.x : (blockIdx.x == T_full % gridDim.x ? T_full : T); tt < T; tt += gridDim.x) {
+            const DrawLanes d = draw_lanes(tt * TILE, wid, pre.pk);
+            const uint32_t len = tt < T_full ? TILE : (uint32_t)(n - (uint64_t)T_full * TILE);
+#pragma unroll 1
+            for (uint32_t b = tt < T_full ? (uint32_t)WT : 0u; b < pre.nw; ++b)
+                explore_subtile<1, 0>(pre.worker0 + b, tt, wid, tt * TILE, len, pre_bound, pre_sure, pre_has_sure, pre_skip, out_of(b), pre.pk, rk, d);
+        }
     }
     __syncthreads();
     flush_hist(h, NB, hist + H_L0);
@@ -1248,6 +1382,99 @@ __global__ __launch_bounds__(256) void k_pack_expl_gather(PtrTab g, uint64_t n, 
         for (int u = 0; u < 4; ++u) v[u] = (j + u * stride < cnt && i[u] < n) ? ld1<NT_EXPLG>(src + i[u]) : 0.f;
 #pragma unroll
         for (int u = 0; u < 4; ++u) if (j + u * stride < cnt) out[j + u * stride] = v[u];
+    }
+}
+
+// Explorer values from the scoring pass's capture.  A list entry is looked up by its own index: a parameter that is set in the
+// draw's sure bitmap, is the first such of its block of four and lies within the slots was kept, whatever list names it;
+// the others (4 % at the paper's ratio, chosen candidates, the ragged tile) are gathered.  A later request may have marked
+// chosen candidates in the bitmap (or be about to): the slots of the draw's candidates name those bits, and they are taken out.
+// One wave per tile and four workers, every load of a step requested for all four before any is used: a chain of three
+// trips to memory.  grid (ceil(T / 4), ceil(nw / 4)).
+constexpr int PEXP = 4;
+__global__ __launch_bounds__(BLOCK) void k_pack_expl_spec(PtrTab g, uint32_t nw, uint64_t n, uint32_t T, uint32_t T_full, PtrTab expl_idx,
+                                                          PtrTab expl_off, CountTab m_w, const uint32_t* __restrict__ sure_bits,
+                                                          const uint32_t* __restrict__ pairs, uint64_t pair_stride,
+                                                          const uint32_t* __restrict__ cnt_cand, const float* __restrict__ vals,
+                                                          uint32_t slots, uint32_t drawn, MutPtrTab expl_val)
+{
+    __shared__ uint32_t wd[4][PEXP][TILE_WORDS];
+    __shared__ uint16_t pre[4][PEXP][TILE_WORDS];
+    const uint32_t wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), lane = lane_id();
+    const uint32_t t = blockIdx.x * 4 + wid, q0 = blockIdx.y * PEXP;
+    if (t >= T) return;
+    const uint32_t start = t * TILE;
+    uint32_t lo[PEXP], hi[PEXP], i0[PEXP], i1[PEXP], cc[PEXP];
+    uint2 w2[PEXP];
+#pragma unroll
+    for (int u = 0; u < PEXP; ++u) {
+        const uint32_t q = q0 + u;
+        lo[u] = hi[u] = 0; w2[u] = make_uint2(0u, 0u); cc[u] = 0;
+        if (q < nw) {
+            const uint32_t* eo = static_cast<const uint32_t*>(expl_off.p[q]);
+            lo[u] = eo[t]; hi[u] = min(eo[t + 1], m_w.c[q]);
+            if (t < T_full && q < drawn) {
+                w2[u] = *reinterpret_cast<const uint2*>(sure_bits + ((size_t)q * T + t) * TILE_WORDS + 2 * lane);
+                cc[u] = cnt_cand[((size_t)q * T + t) * SUBS + (lane >> 4)];
+            }
+        }
+    }
+#pragma unroll
+    for (int u = 0; u < PEXP; ++u) {
+        const uint32_t q = q0 + u, j = lo[u] + lane;
+        i0[u] = i1[u] = 0xFFFFFFFFu;
+        if (j < hi[u]) i0[u] = static_cast<const uint32_t*>(expl_idx.p[q])[j];
+        if (j + 64u < hi[u]) i1[u] = static_cast<const uint32_t*>(expl_idx.p[q])[j + 64u];
+        // a candidate of sub-tile lane / 16, if it has so many
+        if ((lane & 15u) < cc[u]) cc[u] = (lane >> 4) * SUB + pairs[(size_t)q * pair_stride + ((size_t)t * SUBS + (lane >> 4)) * PAIR_SLOT + 2u * (lane & 15u) + 1u];
+        else cc[u] = 0xFFFFFFFFu;
+    }
+#pragma unroll
+    for (int u = 0; u < PEXP; ++u) *reinterpret_cast<uint2*>(&wd[wid][u][2 * lane]) = w2[u];
+    wave_sync();
+#pragma unroll
+    for (int u = 0; u < PEXP; ++u)
+        if (cc[u] < TILE) atomicAnd(&wd[wid][u][cc[u] >> 5], ~(1u << (cc[u] & 31u)));
+    wave_sync();
+    auto blocks_of = [](uint32_t w) { w |= w >> 1; w |= w >> 2; return w & 0x11111111u; };        // blocks of four with a bit set
+#pragma unroll
+    for (int u = 0; u < PEXP; ++u) {
+        const uint2 w = *reinterpret_cast<const uint2*>(&wd[wid][u][2 * lane]);
+        const uint32_t a = __popc(blocks_of(w.x)), s = a + __popc(blocks_of(w.y));
+        const uint32_t excl = wave_incl_scan(s) - s, group0 = __shfl(excl, (int)(lane & ~15u), 64);
+        pre[wid][u][2 * lane] = (uint16_t)(excl - group0);
+        pre[wid][u][2 * lane + 1] = (uint16_t)(excl - group0 + a);
+    }
+    wave_sync();
+    auto source = [&](int u, uint32_t i) -> const float* {
+        const uint32_t q = q0 + u, pos = i - start;
+        const float* src = static_cast<const float*>(g.p[q]) + i;
+        if (pos < TILE) {
+            const uint32_t w = wd[wid][u][pos >> 5], bit = pos & 31u;
+            const uint32_t at = pre[wid][u][pos >> 5] + __popc(blocks_of(w) & mask_below(bit & 28u));
+            // set, and no bit of its block of four below it
+            if ((((w >> (bit & 28u)) & 15u) & ((2u << (bit & 3u)) - 1u)) == (1u << (bit & 3u)) && at < slots)
+                src = vals + (((size_t)t * SUBS + (pos >> 10)) * drawn + q) * slots + at;
+        }
+        return src;
+    };
+    float v0[PEXP], v1[PEXP];
+#pragma unroll
+    for (int u = 0; u < PEXP; ++u) {
+        v0[u] = v1[u] = 0.0f;
+        if (i0[u] < n) v0[u] = ld1<NT_EXPLG>(source(u, i0[u]));
+        if (i1[u] < n) v1[u] = ld1<NT_EXPLG>(source(u, i1[u]));
+    }
+#pragma unroll
+    for (int u = 0; u < PEXP; ++u) {
+        const uint32_t j = lo[u] + lane;
+        float* out = static_cast<float*>(expl_val.p[q0 + u < MAXW ? q0 + u : 0]);
+        if (j < hi[u]) out[j] = v0[u];
+        if (j + 64u < hi[u]) out[j + 64u] = v1[u];
+        for (uint32_t k = j + 128u; k < hi[u]; k += 64) {
+            const uint32_t i = static_cast<const uint32_t*>(expl_idx.p[q0 + u])[k];
+            out[k] = i < n ? *source(u, i) : 0.0f;
+        }
     }
 }
 

@@ -335,6 +335,52 @@ def test_capture_of_clustered_parameters(W, spills):
     sd.close()
 
 
+@pytest.mark.parametrize("W,pct", [(1, 2), (2, 1), (4, 5), (8, 2), (16, 2), (16, 5)])
+def test_explorer_values_kept_by_the_scoring_pass(W, pct):
+    """The draw by rounds and the values it keeps (32 or 64 slots a sub-tile, a ragged tile, more workers announced than scored),
+    and packs whose lists are not, or no longer, the ones that were drawn with it."""
+    n, more = 4096 * (220 if pct < 5 else 520) + 777, 2          # narrow zones
+    wl = workloads.TINY.scaled(n)
+    k = n // 10
+    m = (n - k) * pct // 100
+    rng = np.random.default_rng(W * 10 + pct)
+    sd = binding.SlimDP(n, W + more, seed=workloads.EXPLORE_SEED)
+    sd.set_option("speculative_pack", 1)
+    sd.set_option("explore_keep", 2)
+    ts = sd.tile_starts().astype(np.int64)
+    w = to_dev(wl.weights())
+    for t, how in enumerate(["as drawn", "as drawn", "updates gone", "more workers", "another draw between", "other lists"]):
+        first, drawn = (3, W + more) if how == "more workers" else (0, W)
+        g_h = [(1e-3 * rng.standard_normal(n)).astype(np.float32) for _ in range(W)]
+        g = [to_dev(x) for x in g_h]
+        sd.explore_hint([k], t, [m], first, drawn)
+        S = sd.score(w, g, 1.0)
+        core, bits, off, epoch = sd.select_core(S, [k], reuse_histogram=True)
+        idx, eoff = sd.sample_explore(bits, [k], t, [m], first, drawn)
+        core_h = u32(core)
+        for q in {0, drawn - 1}:
+            want = oracle.sample_explore(n, core_h, workloads.EXPLORE_SEED, t, first + q, m)
+            assert np.array_equal(u32(idx[q]), want), (how, q)
+            assert np.array_equal(u32(eoff[q]), np.searchsorted(want.astype(np.int64), ts).astype(np.uint32)), (how, q)
+        if how == "another draw between":
+            sd.sample_explore(bits, [k], t + 100, [m], 0, W)
+        if how == "other lists":
+            idx = [to_dev(np.sort(rng.choice(n, m, replace=False)).astype(np.uint32)) for _ in range(W)]
+            eoff = [to_dev(np.searchsorted(u32(x).astype(np.int64), ts).astype(np.uint32)) for x in idx]
+        if how == "updates gone":                # the pack finds the kept values and, in place of the others, nothing
+            for x in g:
+                x.zero_()
+        _, expl_val = sd.pack(g, core, off, idx[:W], eoff[:W], epoch, updates_as_scored=True)
+        sd.synchronize()
+        for q in range(W):
+            got, want = u32(expl_val[q]), g_h[q][u32(idx[q])].view(np.uint32)
+            if how == "updates gone":
+                assert np.all((got == want) | (got == 0)) and np.mean(got == want) > 0.8
+            else:
+                assert np.array_equal(got, want), (how, q)
+    sd.close()
+
+
 @pytest.mark.parametrize("per_tile_tail", [0, 1])
 @pytest.mark.parametrize("W", [1, 5, 9])
 @pytest.mark.parametrize("name", sorted(SEGMENTS) + ["one_segment", "more_blocks_than_run_at_a_time"])
