@@ -144,8 +144,21 @@ struct slimdp_ctx {
     bool recorded = false;                           // a call of this context went into a graph: see device_state_known
     uint32_t *c_cnt_gt = nullptr, *c_cnt_cand = nullptr;
     // explorer selection (batch = worker)
-    SegState* e_state = nullptr;
+    SegState* e_state = nullptr;           // per segment, the same for every worker
     SegState* e_draw_state = nullptr;      // zone bounds of the announced draw (side stream)
+    std::vector<SegInit> e_state_holds, e_draw_holds;      // what they hold; empty: not known
+    bool lists_clean = true;               // the lists' counters and the coming request's rerun flag are zero
+    uint32_t rerun_turn = 0;               // which of the two rerun flags that is
+    // sizes and zones of the last requests, kept while the sizes stay the same
+    struct Plan {
+        bool valid = false;
+        std::vector<uint64_t> k_seg, m_seg;
+        uint32_t n_workers = 0;
+        int64_t force = 0, tail = 0;
+        std::vector<SegInit> init;
+        uint64_t M = 0;
+        bool narrow = false, pairs = false;
+    } plan;
     uint32_t *e_sure_bits = nullptr, *e_cand_bits = nullptr;
     uint32_t* e_pair_keys = nullptr;       // narrow zones: per sub-tile a slot of (key, offset) pairs
     uint64_t pair_stride = 0;              // words per worker of the pair slots
@@ -251,8 +264,8 @@ void carve(slimdp_ctx* c, Carver& cv)
 {
     const size_t T = c->T, S = c->n_seg, B = c->maxW;
     carve_core(c, cv);
-    c->e_state = cv.take<SegState>(B * S);
-    c->e_draw_state = cv.take<SegState>(B * S);
+    c->e_state = cv.take<SegState>(S);
+    c->e_draw_state = cv.take<SegState>(S);
     c->e_sure_bits = cv.take<uint32_t>(B * T * TILE_WORDS);
     c->e_cand_bits = cv.take<uint32_t>(B * T * TILE_WORDS);
     c->e_list_count = cv.take<uint32_t>(B * align_up(S, 32));
@@ -302,19 +315,28 @@ int fill(slimdp_ctx* c, uint32_t* p, uint64_t count, uint32_t v)
     return SLIMDP_OK;
 }
 
-// clear: the request's list counters and the rerun flag as well (a draw alone leaves those to the request).
-int init_states(slimdp_ctx* c, SegState* st, const std::vector<SegInit>& init, uint32_t nbatch, bool clear, hipStream_t stream)
+RerunFlag rerun_flag(const slimdp_ctx* c) { return RerunFlag{c->d_flags + 2 * c->rerun_turn, c->d_flags + 2 * (c->rerun_turn ^ 1u)}; }
+
+// Brings st to init, unless it holds that already; clear: the list counters and the rerun flag as well.  Only where the host knows
+// what the device holds (known) is anything left out.
+int init_states(slimdp_ctx* c, SegState* st, std::vector<SegInit>& holds, const std::vector<SegInit>& init, bool known, bool clear, uint32_t nbatch,
+                hipStream_t stream)
 {
+    const bool same = known && holds.size() == init.size() && memcmp(holds.data(), init.data(), init.size() * sizeof(SegInit)) == 0;
+    if (same && !clear) return SLIMDP_OK;
+    holds.clear();
     for (uint32_t s0 = 0; s0 < c->n_seg; s0 += INIT_CHUNK) {
         SegInitChunk chunk;
         const uint32_t cnt = (c->n_seg - s0 < (uint32_t)INIT_CHUNK) ? c->n_seg - s0 : (uint32_t)INIT_CHUNK;
         memset(&chunk, 0, sizeof chunk);
         for (uint32_t j = 0; j < cnt; ++j) chunk.s[j] = init[s0 + j];
-        const uint32_t threads = cnt * nbatch;
-        hipLaunchKernelGGL(k_explore_init, dim3((threads + 255) / 256), dim3(256), 0, stream, st, chunk, s0, cnt, c->n_seg, nbatch,
-                           clear ? c->e_list_count : nullptr, (uint32_t)align_up(c->n_seg, 32), clear && s0 == 0 ? c->d_flags : nullptr);
+        const uint32_t threads = cnt * (clear ? nbatch : 1u);
+        hipLaunchKernelGGL(k_explore_init, dim3((threads + 255) / 256), dim3(256), 0, stream, st, chunk, s0, cnt, nbatch,
+                           clear ? c->e_list_count : nullptr, (uint32_t)align_up(c->n_seg, 32),
+                           clear && s0 == 0 ? rerun_flag(c).now : nullptr);
         SLIMDP_LAUNCHED(c, "k_explore_init");
     }
+    if (known) holds = init;
     return SLIMDP_OK;
 }
 
@@ -383,6 +405,19 @@ bool device_state_known(slimdp_ctx* c)
     return !c->recorded;
 }
 
+// Whether an explorer request runs on the context's own stream although the options would have it on the side stream: an event
+// and a wait across streams, there and back, leave the device idle for some 20 us, and beside other work the request's chain is
+// slower.  Measured whole iterations, own stream / side stream, us, by tiles times workers:
+//   to be drawn first   10^6 parameters, 4 workers (980) 46 / 91; 2*10^6, 8 (3,900) 69 / 118; 7*10^6 in 57 segments, 4 (7,000) 119 / 134;
+//                       10^7 in 57 segments, 4 (9,900) 157 / 146; 8*10^6, 8 (15,600) 158 / 143; 138*10^6, 8 1,820 / 1,480
+//   drawn already       8*10^6, 8 (15,600) 207 / 226; 16*10^6, 8 (31,000) 330 / 335; 64*10^6, 4 (62,500) 658 / 644; 138*10^6, 8 2,150 / 2,115;
+//                       but 138*10^6, 2 (67,500) 1,016 / 1,133: one or two workers' pack is too short to hide it
+bool stays_on_main(const slimdp_ctx* c, uint32_t n_workers, bool drawn)
+{
+    const uint64_t work = (uint64_t)c->T * n_workers;
+    return drawn ? work <= 32000 || n_workers <= 2 : work <= 8500;
+}
+
 // The context's stream waits for whatever the side stream still has in flight (an announced draw, asynchronous
 // explorer requests) before it touches what that work reads or writes.
 int wait_for_side(slimdp_ctx* c)
@@ -417,7 +452,8 @@ int wait_for_lists(slimdp_ctx* c, uint32_t nw, const uint32_t* const* expl_idx, 
             for (uint32_t b = 0; b < p.nw && !touches; ++b) {
                 const uintptr_t i0 = reinterpret_cast<uintptr_t>(expl_idx ? expl_idx[a] : nullptr);
                 const uintptr_t o0 = reinterpret_cast<uintptr_t>(expl_off ? expl_off[a] : nullptr);
-                if (i0 && i0 < p.idx[b] + p.idx_bytes && p.idx[b] < i0 + (m_w ? m_w[a] : 0) * 4 + 4) touches = true;
+                // exactly: an array that begins where another ends is no part of it
+                if (i0 && i0 < p.idx[b] + p.idx_bytes && p.idx[b] < i0 + std::max<uint64_t>(m_w ? m_w[a] * 4 : 0, 4)) touches = true;
                 if (o0 && o0 < p.off[b] + p.off_bytes && p.off[b] < o0 + p.off_bytes) touches = true;
             }
         if (touches && (hit < 0 || p.seq > c->pend[hit].seq)) hit = j;
@@ -522,6 +558,24 @@ int explorer_init(slimdp_ctx* ctx, const char* who, const uint64_t* k_seg, const
     return SLIMDP_OK;
 }
 
+// The same, kept while the sizes stay what they were (the announcement, the scoring pass and the request of every iteration
+// ask for it: 0.2 us a segment each).
+int explorer_plan(slimdp_ctx* ctx, const char* who, const uint64_t* k_seg, const uint64_t* m_seg, uint32_t n_workers)
+{
+    slimdp_ctx::Plan& p = ctx->plan;
+    const uint32_t S = ctx->n_seg;
+    if (p.valid && p.n_workers == n_workers && p.force == ctx->opt_force_fallback && p.tail == ctx->opt_per_tile_tail &&
+        std::equal(k_seg, k_seg + S, p.k_seg.begin()) && std::equal(m_seg, m_seg + S, p.m_seg.begin()))
+        return SLIMDP_OK;
+    p.valid = false;
+    const int rc = explorer_init(ctx, who, k_seg, m_seg, n_workers, p.init, &p.M, &p.narrow, &p.pairs);
+    if (rc) return rc;
+    p.k_seg.assign(k_seg, k_seg + S); p.m_seg.assign(m_seg, m_seg + S);
+    p.n_workers = n_workers; p.force = ctx->opt_force_fallback; p.tail = ctx->opt_per_tile_tail;
+    p.valid = true;
+    return SLIMDP_OK;
+}
+
 }  // namespace
 
 extern "C" {
@@ -602,6 +656,7 @@ int slimdp_create(slimdp_ctx** out, uint64_t n, uint32_t max_workers, uint32_t n
     // A clear histogram; the tables, an empty prediction and the cleared flags, in one copy.  Both run on the default
     // stream, and the context's stream need not wait for that one (a non-blocking stream does not): the host waits here.
     e = hipMemset(c->c_hist, 0, (size_t)n_seg * H_STRIDE * 4);
+    if (e == hipSuccess) e = hipMemset(c->e_list_count, 0, max_workers * align_up(n_seg, 32) * 4);
     if (e == hipSuccess) {
         const size_t words = (size_t)(c->d_flags + 64 - c->d_tile_start);
         std::vector<uint32_t> up(words, 0u);
@@ -757,17 +812,16 @@ static int score_impl(slimdp_ctx* ctx, const float* w, const float* const* g, ui
     ctx->spec.expl_slots = 0;
     if (ctx->opt_hint_mode == 0) ctx->pre.valid = false;      // a draw made on the side stream stays valid
     if (ctx->hint.valid && ctx->opt_hint_mode == 0) {
-        std::vector<SegInit> init;
-        uint64_t M = 0;
-        bool narrow = false;
-        if (explorer_init(ctx, "slimdp_score(hint)", ctx->hint.k_seg.data(), ctx->hint.m_seg.data(), ctx->hint.n_workers, init,
-                          &M, &narrow, &pairs) == SLIMDP_OK && narrow && M > 0 &&
+        const slimdp_ctx::Plan& plan = ctx->plan;
+        if (explorer_plan(ctx, "slimdp_score(hint)", ctx->hint.k_seg.data(), ctx->hint.m_seg.data(), ctx->hint.n_workers) == SLIMDP_OK &&
+            plan.narrow && plan.M > 0 &&
             // tiles inside random blocks: the first request, not a scoring pass, allocates the wide buffer (until then
             // such an announcement goes unused and the request draws for itself)
-            (pairs || ctx->e_cand_keys || ctx->tl.quad_aligned)) {
+            (plan.pairs || ctx->e_cand_keys || ctx->tl.quad_aligned)) {
+            pairs = plan.pairs;
             rc = wait_for_side(ctx);         // the draw's buffers may still be read by work on the side stream
             if (rc) return rc;
-            rc = init_states(ctx, ctx->e_state, init, ctx->hint.n_workers, false, ctx->stream);
+            rc = init_states(ctx, ctx->e_state, ctx->e_state_holds, plan.init, known, false, 0, ctx->stream);
             if (rc) return rc;
             pre.nw = ctx->hint.n_workers; pre.worker0 = ctx->hint.worker0; pre.n_seg = ctx->n_seg;
             pre.states = ctx->e_state; pre.sure_bits = ctx->e_sure_bits; pre.cand_bits = ctx->e_cand_bits;
@@ -776,7 +830,7 @@ static int score_impl(slimdp_ctx* ctx, const float* w, const float* const* g, ui
             pre.keys_stride = pairs ? ctx->pair_stride : ctx->keys_stride;
             pre.pk = PhiloxKey{(uint32_t)ctx->seed, (uint32_t)(ctx->seed >> 32), (uint32_t)ctx->hint.iteration,
                                (uint32_t)(ctx->hint.iteration >> 32)};
-            slots = pairs && ctx->n_seg == 1 ? expl_slots(init[0]) : 0;
+            slots = pairs && ctx->n_seg == 1 ? expl_slots(plan.init[0]) : 0;
             presample = true;
         }
     }
@@ -1133,21 +1187,20 @@ int slimdp_sample_explore(slimdp_ctx* ctx, const uint32_t* core_bits, const uint
     if (n_workers == 0 || n_workers > ctx->maxW)
         return fail(ctx, SLIMDP_ERR_INVALID_ARG, "slimdp_sample_explore: n_workers=%u outside [1, %u]", n_workers, ctx->maxW);
     if (!table_ok(expl_off, n_workers)) return fail(ctx, SLIMDP_ERR_INVALID_ARG, "slimdp_sample_explore: NULL expl_off entry");
-    uint64_t M = 0;
-    std::vector<SegInit> init;
-    bool narrow = false, short_list = false;
-    int rc = explorer_init(ctx, "slimdp_sample_explore", k_seg, m_seg, n_workers, init, &M, &narrow, &short_list);
+    int rc = explorer_plan(ctx, "slimdp_sample_explore", k_seg, m_seg, n_workers);
     if (rc) return rc;
+    const uint64_t M = ctx->plan.M;
+    const bool short_list = ctx->plan.pairs;
     if (M > 0 && !table_ok(expl_idx, n_workers)) return fail(ctx, SLIMDP_ERR_INVALID_ARG, "slimdp_sample_explore: NULL expl_idx entry");
     const uint32_t T = ctx->T, S = ctx->n_seg, B = n_workers;
-    (void)device_state_known(ctx);           // a recorded request draws again when it is replayed
+    const bool known = device_state_known(ctx);      // a recorded request draws again when it is replayed
     // zones already drawn inside slimdp_score for exactly this request, in the format this call wants?
     const bool cached = ctx->pre.same(iteration, worker0, n_workers, k_seg, m_seg, S) && ctx->pre.pairs == short_list;
     ctx->pre.valid = false;
     ctx->hint.valid = false;
     // Option "explore_async": the whole request runs on the library's side stream, beside whatever the caller enqueues
     // on the context's stream after this call; the calls that take the lists make the context's stream wait for them.
-    const bool async = ctx->opt_explore_async != 0;
+    const bool async = ctx->opt_explore_async != 0 && !stays_on_main(ctx, B, cached);
     hipStream_t st = async ? ctx->side : ctx->stream;
     if (async) {
         // everything enqueued so far comes first: the selection that wrote core_bits, readers of the output arrays
@@ -1158,8 +1211,10 @@ int slimdp_sample_explore(slimdp_ctx* ctx, const uint32_t* core_bits, const uint
         rc = wait_for_side(ctx);         // an announced draw, or an earlier asynchronous request: their buffers are theirs until done
         if (rc) return rc;
     }
-    rc = init_states(ctx, ctx->e_state, init, B, true, st);
+    rc = init_states(ctx, ctx->e_state, ctx->e_state_holds, ctx->plan.init, known, !known || !ctx->lists_clean, ctx->maxW, st);
     if (rc) return rc;
+    ctx->lists_clean = false;
+    const RerunFlag rerun = rerun_flag(ctx);
     const uint32_t P = persistent_blocks(ctx, 8, B);
     const uint32_t G = draw_group(ctx, 4, B);
     // a tile or a few to a block, so that no unit is left with a whole turn more than the others (20*10^6 parameters, 3 workers:
@@ -1191,7 +1246,7 @@ int slimdp_sample_explore(slimdp_ctx* ctx, const uint32_t* core_bits, const uint
         const uint32_t gather_blocks = B * ((T + 63) / 64);
         hipLaunchKernelGGL(k_explore_collect<SBPW>, dim3(sure_blocks + gather_blocks), dim3(BLOCK), 0, st, core_bits, n_words, ctx->n,
                            ctx->d_tile_start, ctx->d_tile_seg, T, S, B, sure_blocks, ctx->e_sure_bits, ctx->e_cnt_sel,
-                           ctx->e_pair_keys, ctx->pair_stride, ctx->e_cnt_cand, lists, ctx->d_flags);
+                           ctx->e_pair_keys, ctx->pair_stride, ctx->e_cnt_cand, lists, rerun.now);
         SLIMDP_LAUNCHED(ctx, "k_explore_collect");
     } else {
         rc = ensure_wide_keys(ctx);
@@ -1199,23 +1254,35 @@ int slimdp_sample_explore(slimdp_ctx* ctx, const uint32_t* core_bits, const uint
         if (!cached) { ctx->spec.expl_slots = 0; LAUNCH_DRAW(0); }
         hipLaunchKernelGGL(k_explore_collect_wide, dim3(P, B), dim3(BLOCK), 0, st, core_bits, n_words, ctx->n, ctx->d_tile_start,
                            ctx->d_tile_seg, T, S, ctx->e_sure_bits, ctx->e_cnt_sel, ctx->e_cand_bits, ctx->e_cand_keys,
-                           ctx->keys_stride, lists, ctx->d_flags);
+                           ctx->keys_stride, lists, rerun.now);
         SLIMDP_LAUNCHED(ctx, "k_explore_collect_wide");
     }
     // a block of 1024 threads has the shorter chain; small blocks where there are many more of them than run at a time
     if ((uint64_t)S * B <= 4ull * ctx->cus)
         hipLaunchKernelGGL(k_explore_select<1024>, dim3(S, B), dim3(1024), 0, st, ctx->e_state, ctx->d_seg_first_tile, T, S, lists,
-                           ctx->e_cnt_sel, ctx->e_sure_bits, off_tab, ctx->d_flags);
+                           ctx->e_cnt_sel, ctx->e_sure_bits, off_tab, rerun.now);
     else
         hipLaunchKernelGGL(k_explore_select<256>, dim3(S, B), dim3(256), 0, st, ctx->e_state, ctx->d_seg_first_tile, T, S, lists,
-                           ctx->e_cnt_sel, ctx->e_sure_bits, off_tab, ctx->d_flags);
+                           ctx->e_cnt_sel, ctx->e_sure_bits, off_tab, rerun.now);
     SLIMDP_LAUNCHED(ctx, "k_explore_select");
     constexpr int EBPW = 4;
-    const uint32_t emit_blocks = (T + 15) / 16 > (uint32_t)EBPW ? (T + 15) / 16 : (uint32_t)EBPW;
-    hipLaunchKernelGGL(k_explore_emit<EBPW>, dim3(emit_blocks, (B + EBPW - 1) / EBPW), dim3(1024), 0, st, core_bits, n_words, ctx->n,
-                       ctx->d_tile_start, ctx->d_tile_seg, ctx->d_seg_first_tile, T, S, B, ctx->e_state, worker0, pk,
-                       ctx->e_sure_bits, off_tab, idx_tab, (uint32_t)M, ctx->d_flags);
-    SLIMDP_LAUNCHED(ctx, "k_explore_emit");
+#define LAUNCH_EMIT(NT)                                                                                                          \
+    do {                                                                                                                         \
+        const uint32_t blocks = (T + (NT) / 64 - 1) / ((NT) / 64);                                                               \
+        hipLaunchKernelGGL((k_explore_emit<EBPW, NT>), dim3(std::max(blocks, (uint32_t)EBPW), (B + EBPW - 1) / EBPW), dim3(NT), 0, st,  \
+                           core_bits, n_words, ctx->n, ctx->d_tile_start, ctx->d_tile_seg, ctx->d_seg_first_tile, T, S, B,       \
+                           ctx->e_state, worker0, pk, ctx->e_sure_bits, off_tab, idx_tab, (uint32_t)M, rerun, ctx->d_flags);     \
+        SLIMDP_LAUNCHED(ctx, "k_explore_emit");                                                                                  \
+    } while (0)
+    if (async) {
+        LAUNCH_EMIT(256);
+        hipLaunchKernelGGL(k_explore_rerun, dim3(B), dim3(1024), 0, st, core_bits, ctx->d_tile_start, ctx->d_seg_first_tile, T, S,
+                           ctx->e_state, worker0, pk, off_tab, idx_tab, (uint32_t)M, rerun, ctx->d_flags);
+        SLIMDP_LAUNCHED(ctx, "k_explore_rerun");
+    } else LAUNCH_EMIT(1024);
+#undef LAUNCH_EMIT
+    ctx->lists_clean = known;                // a recorded request has cleared nothing yet
+    ctx->rerun_turn ^= 1u;
 #undef LAUNCH_DRAW
     if (async) {
         // a free slot, else the oldest one (the main stream then waits for that request first)
@@ -1231,7 +1298,7 @@ int slimdp_sample_explore(slimdp_ctx* ctx, const uint32_t* core_bits, const uint
         slimdp_ctx::PendingExplore& p = ctx->pend[slot];
         SLIMDP_HIP(ctx, hipEventRecord(p.ev, ctx->side));
         p.live = true; p.seq = ++ctx->pend_seq; p.nw = B;
-        p.idx_bytes = M * 4 + 4; p.off_bytes = ((uint64_t)T + 1) * 4;
+        p.idx_bytes = std::max<uint64_t>(M * 4, 4); p.off_bytes = ((uint64_t)T + 1) * 4;
         for (uint32_t q = 0; q < B; ++q) {
             p.idx[q] = reinterpret_cast<uintptr_t>(expl_idx ? expl_idx[q] : nullptr);
             p.off[q] = reinterpret_cast<uintptr_t>(expl_off[q]);
@@ -1248,11 +1315,9 @@ int slimdp_explore_hint(slimdp_ctx* ctx, const uint64_t* k_seg, uint32_t worker0
     if (!k_seg || !m_seg) return fail(ctx, SLIMDP_ERR_INVALID_ARG, "slimdp_explore_hint: NULL argument");
     if (n_workers == 0 || n_workers > ctx->maxW)
         return fail(ctx, SLIMDP_ERR_INVALID_ARG, "slimdp_explore_hint: n_workers=%u outside [1, %u]", n_workers, ctx->maxW);
-    std::vector<SegInit> init;
-    uint64_t M = 0;
-    bool narrow = false, short_list = false;
-    int rc = explorer_init(ctx, "slimdp_explore_hint", k_seg, m_seg, n_workers, init, &M, &narrow, &short_list);
+    int rc = explorer_plan(ctx, "slimdp_explore_hint", k_seg, m_seg, n_workers);
     if (rc) return rc;
+    const bool short_list = ctx->plan.pairs;
     ctx->hint.iteration = iteration; ctx->hint.worker0 = worker0; ctx->hint.n_workers = n_workers;
     ctx->hint.k_seg.assign(k_seg, k_seg + ctx->n_seg);
     ctx->hint.m_seg.assign(m_seg, m_seg + ctx->n_seg);
@@ -1260,14 +1325,15 @@ int slimdp_explore_hint(slimdp_ctx* ctx, const uint64_t* k_seg, uint32_t worker0
         ctx->hint.valid = true;
         return SLIMDP_OK;
     }
-    if (!narrow || M == 0) return SLIMDP_OK;  // nothing worth drawing ahead: slimdp_sample_explore draws itself
+    if (!ctx->plan.narrow || ctx->plan.M == 0) return SLIMDP_OK;  // nothing worth drawing ahead: slimdp_sample_explore draws itself
     if (!short_list) { rc = ensure_wide_keys(ctx); if (rc) return rc; }
-    (void)device_state_known(ctx);
+    if (stays_on_main(ctx, n_workers, false)) return SLIMDP_OK;      // nor this: the request will draw
+    const bool known = device_state_known(ctx);
     // the draw starts now on the side stream, once the previous draw's buffers have been read
     // (the event is recorded here, not after every slimdp_sample_explore: an event on a stream costs a gap between kernels)
     SLIMDP_HIP(ctx, hipEventRecord(ctx->ev_consumed, ctx->stream));
     SLIMDP_HIP(ctx, hipStreamWaitEvent(ctx->side, ctx->ev_consumed, 0));
-    rc = init_states(ctx, ctx->e_draw_state, init, n_workers, false, ctx->side);
+    rc = init_states(ctx, ctx->e_draw_state, ctx->e_draw_holds, ctx->plan.init, known, false, 0, ctx->side);
     if (rc) return rc;
     ctx->spec.expl_slots = 0;
     // few waves keep the arithmetic units busy; the wave slots stay with the kernels of the main stream
@@ -1348,48 +1414,49 @@ int slimdp_pack(slimdp_ctx* ctx, uint32_t n_workers, const float* const* g, cons
     const bool spec = as_scored && ctx->spec.on && ctx->spec.captured && ctx->spec.core_epoch == core_epoch;
     if (spec) {
         ctx->spec.captured = false;      // one capture serves one pack
+        bool side_busy = false;
+        for (int j = 0; j < slimdp_ctx::N_PENDING; ++j) side_busy = side_busy || ctx->pend[j].live;
+        uint64_t core_blocks = 0;
         if (k && ctx->n_seg == 1) {
-            // flat model: tile = index / 4096; all tiles but a ragged last one are full
-            const uint32_t T_full = (uint32_t)(ctx->n / TILE);
             // many short blocks: work on the side stream (an asynchronous explorer request) gets its turn between them
-            uint64_t blocks = (k + 1023) / 1024;
-            if (blocks > 32768) blocks = 32768;
+            core_blocks = (k + 1023) / 1024;
+            if (core_blocks > 32768) core_blocks = 32768;
             // while an explorer request runs on the side stream: few resident blocks, so that its small kernels find free
             // slots at once (measured: 2.54 -> 2.48 ms per step with one block per compute unit)
-            bool side_busy = false;
-            for (int j = 0; j < slimdp_ctx::N_PENDING; ++j) side_busy = side_busy || ctx->pend[j].live;
             const uint64_t per_cu = ctx->opt_pack_core_blocks > 0 ? (uint64_t)ctx->opt_pack_core_blocks : (side_busy ? 1u : 0u);
-            if (per_cu > 0 && blocks > (uint64_t)ctx->cus * per_cu) blocks = (uint64_t)ctx->cus * per_cu;
-            hipLaunchKernelGGL(k_pack_core_flat, dim3((uint32_t)blocks), dim3(256), 0, ctx->stream, make_tab<PtrTab>(g, n_workers),
-                               n_workers, ctx->n, T_full, core_idx, (uint32_t)k, ctx->spec.bits, ctx->spec.vals, ctx->spec.fail,
-                               ctx->spec.vec_ok, make_tab<MutPtrTab>(core_val, n_workers));
-            SLIMDP_LAUNCHED(ctx, "k_pack_core_flat");
+            if (per_cu > 0 && core_blocks > (uint64_t)ctx->cus * per_cu) core_blocks = (uint64_t)ctx->cus * per_cu;
         } else if (k) {
-            hipLaunchKernelGGL(k_pack_core_spec, dim3((ctx->T + 3) / 4), dim3(BLOCK), 0, ctx->stream, make_tab<PtrTab>(g, n_workers),
-                               n_workers, ctx->n, ctx->d_tile_start, ctx->d_tile_seg, ctx->T, core_idx, core_off, ctx->spec.bits,
-                               ctx->spec.vals, ctx->spec.fail, ctx->spec.vec_ok,
-                               make_tab<MutPtrTab>(core_val, n_workers));
-            SLIMDP_LAUNCHED(ctx, "k_pack_core_spec");
+            core_blocks = (ctx->T + 3) / 4;
         }
         CountTab mt{};
         uint64_t mmax = 0;
         for (uint32_t q = 0; q < n_workers; ++q) { mt.c[q] = (uint32_t)m_w[q]; if (m_w[q] > mmax) mmax = m_w[q]; }
-        rc = wait_for_lists(ctx, n_workers, expl_idx, expl_off, m_w);    // the core values above did not need the explorer lists; these do
+        uint64_t gather_blocks = (mmax + 1023) / 1024;
+        if (gather_blocks > 2048) gather_blocks = 2048;
+        auto launch = [&](uint64_t cb, uint64_t gb) {
+            if (cb + gb == 0) return;
+            const dim3 grid((uint32_t)(cb + gb * n_workers));
+            auto go = [&](auto kernel) {
+                hipLaunchKernelGGL(kernel, grid, dim3(BLOCK), 0, ctx->stream, (uint32_t)cb, (uint32_t)gb, make_tab<PtrTab>(g, n_workers), n_workers,
+                                   ctx->n, ctx->d_tile_start, ctx->d_tile_seg, ctx->T, core_idx, core_off, (uint32_t)k, ctx->spec.bits,
+                                   ctx->spec.vals, ctx->spec.fail, ctx->spec.vec_ok, make_tab<MutPtrTab>(core_val, n_workers),
+                                   make_tab<PtrTab>(expl_idx, n_workers), mt, make_tab<MutPtrTab>(expl_val, n_workers));
+            };
+            if (ctx->n_seg == 1) go(k_pack_spec<1>); else go(k_pack_spec<0>);
+        };
+        const bool kept = mmax && ctx->spec.expl_slots && device_state_known(ctx);
+        // the core values do not need the explorer lists: while a request is on its way they go first
+        if (side_busy || kept) { launch(core_blocks, 0); SLIMDP_LAUNCHED(ctx, "k_pack_spec"); core_blocks = 0; }
+        rc = wait_for_lists(ctx, n_workers, expl_idx, expl_off, m_w);
         if (rc) return rc;
-        if (mmax && ctx->spec.expl_slots && device_state_known(ctx)) {
+        if (!kept) { launch(core_blocks, gather_blocks); SLIMDP_LAUNCHED(ctx, "k_pack_spec"); }
+        if (kept) {
             hipLaunchKernelGGL(k_pack_expl_spec, dim3((ctx->T + 3) / 4, (n_workers + PEXP - 1) / PEXP), dim3(BLOCK), 0, ctx->stream,
                                make_tab<PtrTab>(g, n_workers), n_workers, ctx->n, ctx->T, (uint32_t)(ctx->n / TILE),
                                make_tab<PtrTab>(expl_idx, n_workers), make_tab<PtrTab>(expl_off, n_workers), mt, ctx->e_sure_bits,
                                ctx->e_pair_keys, ctx->pair_stride, ctx->e_cnt_cand, ctx->spec.evals, ctx->spec.expl_slots, n_workers,
                                make_tab<MutPtrTab>(expl_val, n_workers));
             SLIMDP_LAUNCHED(ctx, "k_pack_expl_spec");
-        } else if (mmax) {
-            uint64_t blocks = (mmax + 1023) / 1024;
-            if (blocks > 2048) blocks = 2048;
-            hipLaunchKernelGGL(k_pack_expl_gather, dim3((uint32_t)blocks, n_workers), dim3(256), 0, ctx->stream,
-                               make_tab<PtrTab>(g, n_workers), ctx->n, make_tab<PtrTab>(expl_idx, n_workers), mt,
-                               make_tab<MutPtrTab>(expl_val, n_workers));
-            SLIMDP_LAUNCHED(ctx, "k_pack_expl_gather");
         }
         return SLIMDP_OK;
     }

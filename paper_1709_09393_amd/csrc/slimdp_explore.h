@@ -18,23 +18,25 @@
 
 namespace slimdp {
 
-// Writes the selection state of segments [seg0, seg0+count) for every batch.  counts, flags: also cleared, if given.
+// Writes the selection state of segments [seg0, seg0+count): where the sizes differ from those of the request before.  counts,
+// rerun: cleared, if given (nbatch batches of n_seg counters each): after a call that left them in doubt; otherwise the last
+// reader of either clears it, and a request of the sizes of the one before starts with its draw or its collection.
+// As a launch of every request, and another of every announced draw, this took 2 to 6 us each.
 __global__ __launch_bounds__(256) void k_explore_init(SegState* __restrict__ st, SegInitChunk chunk, uint32_t seg0, uint32_t count,
-                                                      uint32_t n_seg, uint32_t nbatch, uint32_t* __restrict__ counts,
-                                                      uint32_t count_stride, uint32_t* __restrict__ flags)
+                                                      uint32_t nbatch, uint32_t* __restrict__ counts, uint32_t count_stride,
+                                                      uint32_t* __restrict__ rerun)
 {
     const uint32_t x = blockIdx.x * 256 + threadIdx.x;
-    if (x == 0 && flags) flags[0] = 0;
-    if (x >= count * nbatch) return;
-    const uint32_t b = x / count, j = x % count;
-    const SegInit in = chunk.s[j];
-    SegState s;
-    s.need0 = in.need; s.out_base = in.out_base;
-    s.bound_m1 = in.bound_m1; s.sure_m1 = in.sure_m1; s.has_gt = in.has_gt; s.bits = in.bits;
-    s.pad[0] = s.pad[1] = 0;
-    const size_t o = (size_t)b * n_seg + seg0 + j;
-    st[o] = s;
-    if (counts) counts[(size_t)b * count_stride + seg0 + j] = 0;
+    if (x == 0 && rerun) rerun[0] = 0;
+    if (x < count) {
+        const SegInit in = chunk.s[x];
+        SegState s;
+        s.need0 = in.need; s.out_base = in.out_base;
+        s.bound_m1 = in.bound_m1; s.sure_m1 = in.sure_m1; s.has_gt = in.has_gt; s.bits = in.bits;
+        s.pad[0] = s.pad[1] = 0;
+        st[seg0 + x] = s;
+    }
+    if (counts && x < count * nbatch) counts[(size_t)(x / count) * count_stride + seg0 + x % count] = 0;
 }
 
 // Lists: entry (key, tile * TILE + offset inside the tile); batch b's segment s has its entries at
@@ -44,6 +46,8 @@ __global__ __launch_bounds__(256) void k_explore_init(SegState* __restrict__ st,
 // k_explore_collect_wide at 99 us for 20*10^6 parameters (60 now), 8 workers' k_explore_collect at 75 for 138*10^6 (44 now).
 struct ExploreLists { uint2* list; uint32_t* count; const uint32_t* first; uint64_t stride; uint32_t count_stride; };
 constexpr uint32_t FLAG_RERUN = 1u;
+// The rerun flag has two words, which requests use in turn: the emission of one clears the other's.
+struct RerunFlag { uint32_t *now, *next; };
 
 // Sure parameters outside the core of one tile, for batches b0 .. b0+BPW-1, by one wave.
 template <int BPW>
@@ -84,7 +88,7 @@ __global__ __launch_bounds__(BLOCK) void k_explore_collect(const uint32_t* __res
                                                            const uint32_t* __restrict__ sure_bits, uint32_t* __restrict__ cnt_sel,
                                                            const uint32_t* __restrict__ pairs, uint64_t pair_stride,
                                                            const uint32_t* __restrict__ cnt_cand, ExploreLists lists,
-                                                           uint32_t* __restrict__ flags)
+                                                           uint32_t* __restrict__ rerun)
 {
     __shared__ uint32_t wtot[4], room;
     const uint32_t lane = lane_id(), wid = threadIdx.x >> 6;
@@ -98,7 +102,7 @@ __global__ __launch_bounds__(BLOCK) void k_explore_collect(const uint32_t* __res
     const uint32_t per = (T + 63u) / 64u, gb = blockIdx.x - sure_blocks;
     const uint32_t b = gb / per, t0 = (gb % per) * 64u, x = t0 * SUBS + threadIdx.x, t = x / SUBS;      // b < nbatch
     uint32_t c = t < T ? cnt_cand[(size_t)b * T * SUBS + x] : 0u;
-    if (c > PAIR_CAP) { atomicOr(&flags[0], FLAG_RERUN); c = 0; }
+    if (c > PAIR_CAP) { atomicOr(rerun, FLAG_RERUN); c = 0; }
     // the first four pairs are held, more are read again
     const uint32_t* slot = pairs + (size_t)b * pair_stride + (size_t)x * PAIR_SLOT;
     uint4 p01 = make_uint4(0u, 0u, 0u, 0u), p23 = p01;
@@ -123,7 +127,7 @@ __global__ __launch_bounds__(BLOCK) void k_explore_collect(const uint32_t* __res
         const uint32_t base = atomicAdd(&lists.count[(size_t)b * lists.count_stride + seg], total);
         const uint32_t cap = lists.first[seg + 1] - lists.first[seg];
         if (base + total <= cap && base + total >= base) return base;
-        atomicOr(&flags[0], FLAG_RERUN);
+        atomicOr(rerun, FLAG_RERUN);
         return NONE;
     };
     if (seg_lo == seg_hi) {
@@ -167,7 +171,7 @@ __global__ __launch_bounds__(BLOCK) void k_explore_collect_wide(const uint32_t* 
                                                                 const uint32_t* __restrict__ sure_bits, uint32_t* __restrict__ cnt_sel,
                                                                 const uint32_t* __restrict__ cand_bits,
                                                                 const uint32_t* __restrict__ cand_keys, uint64_t keys_stride,
-                                                                ExploreLists lists, uint32_t* __restrict__ flags)
+                                                                ExploreLists lists, uint32_t* __restrict__ rerun)
 {
     __shared__ uint32_t kb[4][SUBS * 16 * WIDE_KPL];
     __shared__ uint2 stage[4][WIDE_STAGE];
@@ -184,7 +188,7 @@ __global__ __launch_bounds__(BLOCK) void k_explore_collect_wide(const uint32_t* 
         base = __shfl(base, 0, 64);
         const uint32_t first = lists.first[seg], cap = lists.first[seg + 1] - first;
         if (base + cnt > cap || base + cnt < base) {
-            if (lane == 0) atomicOr(&flags[0], FLAG_RERUN);
+            if (lane == 0) atomicOr(rerun, FLAG_RERUN);
             return nullptr;
         }
         return lists.list + (size_t)b * lists.stride + first + base;
@@ -262,20 +266,25 @@ constexpr int KEEP = 8;
 template <int NT>
 __global__ __launch_bounds__(NT) void k_explore_select(const SegState* __restrict__ states, const uint32_t* __restrict__ seg_first_tile,
                                                        uint32_t T, uint32_t n_seg, ExploreLists lists, uint32_t* __restrict__ cnt_sel,
-                                                       uint32_t* __restrict__ sure_bits, MutPtrTab out_off, uint32_t* __restrict__ flags)
+                                                       uint32_t* __restrict__ sure_bits, MutPtrTab out_off, uint32_t* __restrict__ rerun)
 {
     constexpr int NWV = NT / 64, NBIN = 4096, PER = NBIN / NT;
     __shared__ uint32_t hist[NBIN];
     __shared__ uint32_t wsum[NWV], wtot[NWV], sh[4], ntie;
     __shared__ uint32_t tpos[TIE_CAP];
     const uint32_t seg = blockIdx.x, b = blockIdx.y, tid = threadIdx.x, lane = lane_id(), wid = tid >> 6;
-    const SegState* st = states + (size_t)b * n_seg + seg;
+    const SegState* st = states + seg;
     const uint32_t f0 = n_seg == 1 ? 0u : seg_first_tile[seg], f1 = n_seg == 1 ? T : seg_first_tile[seg + 1];
     const uint32_t cap = lists.first[seg + 1] - lists.first[seg];
-    const uint32_t cnt = lists.count[(size_t)b * lists.count_stride + seg];
+    uint32_t* counter = lists.count + (size_t)b * lists.count_stride + seg;
+    const uint32_t cnt = *counter;
     const uint2* list = lists.list + (size_t)b * lists.stride + lists.first[seg];
     const uint32_t need0 = st->need0, base = st->out_base, bits = st->bits;
-    if (cnt > cap) return;                                   // the rerun flag is up
+    if (cnt > cap) {                                         // the rerun flag is up
+        __syncthreads();
+        if (tid == 0) *counter = 0;
+        return;
+    }
     uint32_t key[KEEP], pos[KEEP];
 #pragma unroll
     for (int i = 0; i < KEEP; ++i) {
@@ -296,12 +305,13 @@ __global__ __launch_bounds__(NT) void k_explore_select(const SegState* __restric
     }
     if (tid == 0) ntie = 0;
     __syncthreads();
+    if (tid == 0) *counter = 0;                              // read by every thread; clear for the next request
     uint32_t nsure = 0;
 #pragma unroll
     for (int w = 0; w < NWV; ++w) nsure += wsum[w];
     __syncthreads();                                         // the marks below add to wsum
     if (nsure > need0 || need0 - nsure > cnt) {              // a zone missed: the request again, exactly
-        if (tid == 0) atomicOr(&flags[0], FLAG_RERUN);
+        if (tid == 0) atomicOr(rerun, FLAG_RERUN);
         return;
     }
     // keys >> shift above `prefix` are taken, those equal to it are `equal` many, of which `need` are wanted
@@ -362,7 +372,7 @@ __global__ __launch_bounds__(NT) void k_explore_select(const SegState* __restric
         __syncthreads();
         const uint32_t nt_all = ntie;
         if (nt_all > TIE_CAP) {
-            if (tid == 0) atomicOr(&flags[0], FLAG_RERUN);
+            if (tid == 0) atomicOr(rerun, FLAG_RERUN);
             return;
         }
         for (uint32_t q = tid; q < nt_all; q += NT) {
@@ -397,7 +407,7 @@ __global__ __launch_bounds__(NT) void k_explore_select(const SegState* __restric
 }
 
 // =======================================================================================
-// Explorer, exact rerun.  When the zones of a draw missed (flags[0] raised; once in about
+// Explorer, exact rerun.  When the zones of a draw missed (the rerun flag is up; once in about
 // 10^9 draws, or forced by a test switch) this routine redoes the whole request from the
 // definition, slowly and with no assumption: per worker one block walks every segment,
 // finds the need-th smallest Philox word among the parameters outside the core by a
@@ -413,7 +423,7 @@ __device__ __forceinline__ uint32_t explore_word(uint32_t i, uint32_t worker, Ph
     return c == 0 ? r[0] : c == 1 ? r[1] : c == 2 ? r[2] : r[3];
 }
 
-__device__ void explore_exact(const uint32_t* __restrict__ core_bits, const uint32_t* __restrict__ tile_start,
+__device__ __forceinline__ void explore_exact(const uint32_t* __restrict__ core_bits, const uint32_t* __restrict__ tile_start,
                               const uint32_t* __restrict__ seg_first_tile, uint32_t T, uint32_t n_seg,
                               const SegState* __restrict__ states, uint32_t worker, PhiloxKey pk, uint32_t* __restrict__ out,
                               uint32_t* __restrict__ off, uint32_t expected, uint32_t* __restrict__ flags)
@@ -500,28 +510,36 @@ __device__ void explore_exact(const uint32_t* __restrict__ core_bits, const uint
     }
 }
 
-// Ordered emission from the sure bitmap (chosen candidates included) minus the core.  One wave per tile and BPW
-// batches.  With the rerun flag up the first BPW blocks of a batch group redo the request instead, one batch each
-// (k_explore_select and everything before it is void then).  At most 64 registers: two blocks to a compute unit.  grid (max(BPW, ceil(T / 16)), ceil(nbatch / BPW)), 1024 threads.
-template <int BPW>
-__global__ __launch_bounds__(1024, 8) void k_explore_emit(const uint32_t* __restrict__ core_bits, uint32_t n_words, uint64_t n,
+// Ordered emission from the sure bitmap (chosen candidates included) minus the core.  One wave per tile and BPW batches.
+// NT = 1024: with the rerun flag up the first BPW blocks of a batch group redo the request instead, one batch each
+// (k_explore_select and everything before it is void then); at most 64 registers, two blocks to a compute unit.
+// NT = 256, for a request on the side stream: beside a kernel of small blocks that fills the chip a block of sixteen waves
+// waits until so many are free at once on one unit (beside k_merge 330 to 600 us for 138*10^6 parameters and 8 workers,
+// 59 alone); the rerun is then a launch of its own (k_explore_rerun).
+// grid (max(BPW, ceil(T / waves of a block)), ceil(nbatch / BPW)).
+template <int BPW, int NT>
+__global__ __launch_bounds__(NT, 8) void k_explore_emit(const uint32_t* __restrict__ core_bits, uint32_t n_words, uint64_t n,
                                                        const uint32_t* __restrict__ tile_start,
                                                        const uint32_t* __restrict__ tile_seg,
                                                        const uint32_t* __restrict__ seg_first_tile, uint32_t T, uint32_t n_seg,
                                                        uint32_t nbatch, const SegState* __restrict__ states, uint32_t worker0,
                                                        PhiloxKey pk, const uint32_t* __restrict__ sure_bits, MutPtrTab out_off,
-                                                       MutPtrTab out_idx, uint32_t expected, uint32_t* __restrict__ flags)
+                                                       MutPtrTab out_idx, uint32_t expected, RerunFlag rerun, uint32_t* __restrict__ flags)
 {
-    __shared__ uint16_t stage[16][EMIT_STAGE];
+    constexpr uint32_t WAVES = NT / 64;
+    __shared__ uint16_t stage[WAVES][EMIT_STAGE];
     const uint32_t b0 = blockIdx.y * BPW;
-    if (flags[0] != 0) {                         // nobody raises the flag while this kernel runs
-        const uint32_t b = b0 + blockIdx.x;
-        if (blockIdx.x < (uint32_t)BPW && b < nbatch)
-            explore_exact(core_bits, tile_start, seg_first_tile, T, n_seg, states + (size_t)b * n_seg, worker0 + b, pk,
-                          static_cast<uint32_t*>(out_idx.p[b]), static_cast<uint32_t*>(out_off.p[b]), expected, flags);
+    if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) *rerun.next = 0;
+    if (*rerun.now != 0) {                       // nobody raises the flag while this kernel runs
+        if constexpr (NT == 1024) {
+            const uint32_t b = b0 + blockIdx.x;
+            if (blockIdx.x < (uint32_t)BPW && b < nbatch)
+                explore_exact(core_bits, tile_start, seg_first_tile, T, n_seg, states, worker0 + b, pk,
+                              static_cast<uint32_t*>(out_idx.p[b]), static_cast<uint32_t*>(out_off.p[b]), expected, flags);
+        }
         return;
     }
-    const uint32_t t = blockIdx.x * 16 + (threadIdx.x >> 6), lane = lane_id();
+    const uint32_t t = blockIdx.x * WAVES + (threadIdx.x >> 6), lane = lane_id();
     if (t >= T) return;
     const TileRef tr = tile_ref(t, n_seg, n, tile_start, tile_seg);
     uint2 s2[BPW];
@@ -547,6 +565,19 @@ __global__ __launch_bounds__(1024, 8) void k_explore_emit(const uint32_t* __rest
         if (t == T - 1 && lane == 63 && off_t[bb] + incl != expected) atomicOr(&flags[1], 1u);
         emit_indices(fm0, fm1, incl, tr.start, off_t[bb], expected, stage[threadIdx.x >> 6], out);
     }
+}
+
+// The rerun after an emission that left it out.  grid n_workers, 1024 threads.
+__global__ __launch_bounds__(1024) void k_explore_rerun(const uint32_t* __restrict__ core_bits, const uint32_t* __restrict__ tile_start,
+                                                        const uint32_t* __restrict__ seg_first_tile, uint32_t T, uint32_t n_seg,
+                                                        const SegState* __restrict__ states, uint32_t worker0, PhiloxKey pk,
+                                                        MutPtrTab out_off, MutPtrTab out_idx, uint32_t expected, RerunFlag rerun,
+                                                        uint32_t* __restrict__ flags)
+{
+    if (*rerun.now == 0) return;
+    const uint32_t b = blockIdx.x;
+    explore_exact(core_bits, tile_start, seg_first_tile, T, n_seg, states, worker0 + b, pk, static_cast<uint32_t*>(out_idx.p[b]),
+                  static_cast<uint32_t*>(out_off.p[b]), expected, flags);
 }
 
 }  // namespace slimdp

@@ -1197,19 +1197,19 @@ __global__ __launch_bounds__(BLOCK) void k_gather(PtrTab src, int shared_src, ui
 // capture (rank of the parameter among the captured ones of its sub-tile), not from the
 // update vectors.  Tiles that were not captured (ragged, unaligned, or a segment whose
 // threshold fell below the capture bound) gather from the update vectors.
-// One wave per tile, all workers (the rank is the same for all).  grid ceil(T/4).
+// One wave per tile, all workers (the rank is the same for all); ceil(T/4) blocks.
 // ---------------------------------------------------------------------------------------
-__global__ __launch_bounds__(BLOCK) void k_pack_core_spec(PtrTab g, uint32_t nw, uint64_t n,
-                                                          const uint32_t* __restrict__ tile_start,
-                                                          const uint32_t* __restrict__ tile_seg, uint32_t T,
-                                                          const uint32_t* __restrict__ core_idx,
-                                                          const uint32_t* __restrict__ core_off,
-                                                          const uint2* __restrict__ spec_bits,
-                                                          const float* __restrict__ spec_vals,
-                                                          const uint32_t* __restrict__ spec_fail, int vec_ok, MutPtrTab core_val)
+__device__ __forceinline__ void pack_core_spec(uint32_t block, const PtrTab& g, uint32_t nw, uint64_t n,
+                                               const uint32_t* __restrict__ tile_start,
+                                               const uint32_t* __restrict__ tile_seg, uint32_t T,
+                                               const uint32_t* __restrict__ core_idx,
+                                               const uint32_t* __restrict__ core_off,
+                                               const uint2* __restrict__ spec_bits,
+                                               const float* __restrict__ spec_vals,
+                                               const uint32_t* __restrict__ spec_fail, int vec_ok, const MutPtrTab& core_val)
 {
     __shared__ uint32_t wd[4][TILE_WORDS], pre[4][TILE_WORDS];
-    const uint32_t wid = threadIdx.x >> 6, t = blockIdx.x * 4 + wid, lane = lane_id();
+    const uint32_t wid = threadIdx.x >> 6, t = block * 4 + wid, lane = lane_id();
     if (t >= T) return;
     const uint32_t start = tile_start[t], len = tile_start[t + 1] - start;
     const uint32_t j0 = core_off[t], j1 = core_off[t + 1];
@@ -1291,17 +1291,17 @@ __global__ __launch_bounds__(BLOCK) void k_pack_core_spec(PtrTab g, uint32_t nw,
 // The same for a flat model, one thread per list entry: the tile and the bitmap word follow
 // from the index itself, the word's first entry number is stored beside the word.  Every wave
 // writes 64 consecutive list positions per worker (whole, aligned lines: a store that covers
-// a line only in part makes the memory side read it first).  grid: any, grid-stride.
-__global__ __launch_bounds__(256) void k_pack_core_flat(PtrTab g, uint32_t nw, uint64_t n, uint32_t T_full,
-                                                        const uint32_t* __restrict__ core_idx, uint32_t k,
-                                                        const uint2* __restrict__ spec_bits,
-                                                        const float* __restrict__ spec_vals,
-                                                        const uint32_t* __restrict__ spec_fail, int vec_ok, MutPtrTab core_val)
+// a line only in part makes the memory side read it first).  Any number of blocks.
+__device__ __forceinline__ void pack_core_flat(uint32_t block, uint32_t blocks, const PtrTab& g, uint32_t nw, uint64_t n, uint32_t T_full,
+                                               const uint32_t* __restrict__ core_idx, uint32_t k,
+                                               const uint2* __restrict__ spec_bits,
+                                               const float* __restrict__ spec_vals,
+                                               const uint32_t* __restrict__ spec_fail, int vec_ok, const MutPtrTab& core_val)
 {
     constexpr int U = 4;
     const bool ok = vec_ok && spec_fail[0] == 0;
-    const uint32_t stride = gridDim.x * 256u;
-    for (uint32_t jb = blockIdx.x * 256u + threadIdx.x; jb < k; jb += U * stride) {
+    const uint32_t stride = blocks * 256u;
+    for (uint32_t jb = block * 256u + threadIdx.x; jb < k; jb += U * stride) {
         uint32_t i[U];
 #pragma unroll
         for (int u = 0; u < U; ++u) i[u] = (jb + u * stride < k) ? core_idx[jb + u * stride] : 0xFFFFFFFFu;
@@ -1363,17 +1363,17 @@ __global__ __launch_bounds__(256) void k_pack_core_flat(PtrTab g, uint32_t nw, u
     }
 }
 
-// Explorer values by gathering from the update vectors.  grid (blocks, n_workers).
+// Explorer values by gathering from the update vectors: block `block` of `blocks` of worker q.
 struct CountTab { uint32_t c[MAXW]; };
-__global__ __launch_bounds__(256) void k_pack_expl_gather(PtrTab g, uint64_t n, PtrTab expl_idx, CountTab m_w,
-                                                          MutPtrTab expl_val)
+__device__ __forceinline__ void pack_expl_gather(uint32_t block, uint32_t blocks, uint32_t q, const PtrTab& g, uint64_t n, const PtrTab& expl_idx,
+                                                 const CountTab& m_w, const MutPtrTab& expl_val)
 {
-    const uint32_t q = blockIdx.y, cnt = m_w.c[q];
+    const uint32_t cnt = m_w.c[q];
     const float* src = static_cast<const float*>(g.p[q]);
     const uint32_t* idx = static_cast<const uint32_t*>(expl_idx.p[q]);
     float* out = static_cast<float*>(expl_val.p[q]);
-    const uint32_t stride = gridDim.x * 256u;
-    for (uint32_t j = blockIdx.x * 256u + threadIdx.x; j < cnt; j += 4u * stride) {
+    const uint32_t stride = blocks * 256u;
+    for (uint32_t j = block * 256u + threadIdx.x; j < cnt; j += 4u * stride) {
         uint32_t i[4];
         float v[4];
 #pragma unroll
@@ -1382,6 +1382,25 @@ __global__ __launch_bounds__(256) void k_pack_expl_gather(PtrTab g, uint64_t n, 
         for (int u = 0; u < 4; ++u) v[u] = (j + u * stride < cnt && i[u] < n) ? ld1<NT_EXPLG>(src + i[u]) : 0.f;
 #pragma unroll
         for (int u = 0; u < 4; ++u) if (j + u * stride < cnt) out[j + u * stride] = v[u];
+    }
+}
+
+// Core values from the capture (the first core_blocks blocks) and explorer values by gathering (expl_blocks blocks a worker):
+// either alone, or both in one launch where nothing has to be waited for in between.
+template <int FLAT>
+__global__ __launch_bounds__(BLOCK) void k_pack_spec(uint32_t core_blocks, uint32_t expl_blocks, PtrTab g, uint32_t nw, uint64_t n,
+                                                     const uint32_t* __restrict__ tile_start, const uint32_t* __restrict__ tile_seg, uint32_t T,
+                                                     const uint32_t* __restrict__ core_idx, const uint32_t* __restrict__ core_off, uint32_t k,
+                                                     const uint2* __restrict__ spec_bits, const float* __restrict__ spec_vals,
+                                                     const uint32_t* __restrict__ spec_fail, int vec_ok, MutPtrTab core_val,
+                                                     PtrTab expl_idx, CountTab m_w, MutPtrTab expl_val)
+{
+    if (blockIdx.x < core_blocks) {
+        if (FLAT) pack_core_flat(blockIdx.x, core_blocks, g, nw, n, (uint32_t)(n / TILE), core_idx, k, spec_bits, spec_vals, spec_fail, vec_ok, core_val);
+        else pack_core_spec(blockIdx.x, g, nw, n, tile_start, tile_seg, T, core_idx, core_off, spec_bits, spec_vals, spec_fail, vec_ok, core_val);
+    } else {
+        const uint32_t x = blockIdx.x - core_blocks;
+        pack_expl_gather(x % expl_blocks, expl_blocks, x / expl_blocks, g, n, expl_idx, m_w, expl_val);
     }
 }
 

@@ -381,6 +381,72 @@ def test_explorer_values_kept_by_the_scoring_pass(W, pct):
     sd.close()
 
 
+@pytest.mark.parametrize("n,W,segments", [(60_001, 2, 1), (60_001, 3, 5), (4096 * 545 + 3, 16, 1), (4096 * 545 + 3, 16, 3)])
+def test_requests_of_changing_sizes_follow_each_other(n, W, segments):
+    """What one request leaves for the next (zones kept while the sizes stay, counters and the rerun flag cleared by their last
+    reader), through changes of size, draws that miss their zones on either side, and announced draws; on the context's own stream
+    (few tiles) and on the side stream."""
+    so = offsets([n]) if segments == 1 else offsets([n // 3 + 1] + [n // 9] * (segments - 2) + [n - n // 3 - 1 - n // 9 * (segments - 2)])
+    sizes = np.diff(so)
+    ks = [int(s) // 10 for s in sizes]
+    rng = np.random.default_rng(n + W)
+    core = oracle.select_core(np.abs(rng.standard_normal(n)).astype(np.float32), ks, so)
+    bits = to_dev(oracle.core_bits(n, core))
+    sd = binding.SlimDP(n, W, seg_off=so, seed=workloads.EXPLORE_SEED)
+    sd.set_option("explore_async", 1)
+    sd.set_option("explore_hint_mode", 1)
+    ts = sd.tile_starts().astype(np.int64)
+    small, large = [int(s) // 50 for s in sizes], [int(s) // 9 for s in sizes]
+    for it, (ms, miss, hint) in enumerate([(small, 0, 0), (small, 0, 1), (large, 0, 0), (small, 1, 0), (small, 0, 0), (small, 2, 1),
+                                           (large, 2, 0), (large, 0, 1), (large, 0, 0)]):
+        sd.set_option("explore_force_fallback", miss)
+        if hint:
+            sd.explore_hint(ks, it, ms, 0, W)
+        idx, off = sd.sample_explore(bits, ks, it, ms, 0, W)
+        sd.synchronize()
+        for q in {0, W - 1}:
+            want = oracle.sample_explore(n, core, workloads.EXPLORE_SEED, it, q, ms, so)
+            assert np.array_equal(u32(idx[q]), want), (it, q)
+            assert np.array_equal(u32(off[q]), np.searchsorted(want.astype(np.int64), ts).astype(np.uint32)), (it, q)
+    sd.close()
+
+
+def test_recorded_request_replays_beside_eager_ones():
+    """A replay finds counters, zones and the rerun flag as it needs them, whatever eager requests (other sizes, a missed draw)
+    ran since it was recorded, and so do eager requests after a replay."""
+    n, W = 60_001, 2
+    k, m, other = n // 10, n // 50, n // 9
+    rng = np.random.default_rng(3)
+    core = oracle.select_core(np.abs(rng.standard_normal(n)).astype(np.float32), k)
+    bits = to_dev(oracle.core_bits(n, core))
+    want = [oracle.sample_explore(n, core, workloads.EXPLORE_SEED, 1, q, m) for q in range(W)]
+    want_other = [oracle.sample_explore(n, core, workloads.EXPLORE_SEED, 2, q, other) for q in range(W)]
+    st = torch.cuda.Stream()
+    sd = binding.SlimDP(n, W, seed=workloads.EXPLORE_SEED, stream=st)
+    idx = [torch.empty(m, dtype=torch.int32, device=dev()) for _ in range(W)]
+    off = [torch.empty(sd.T + 1, dtype=torch.int32, device=dev()) for _ in range(W)]
+    torch.cuda.synchronize()
+    with torch.cuda.stream(st):
+        sd.sample_explore(bits, [k], 2, [other], 0, W)
+    sd.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph, stream=st):
+        sd.sample_explore(bits, [k], 1, [m], 0, W, expl_idx=idx, expl_off=off)
+    for turn in range(4):
+        with torch.cuda.stream(st):
+            if turn:
+                sd.set_option("explore_force_fallback", turn - 1)
+                got, _ = sd.sample_explore(bits, [k], 2, [other], 0, W)
+                sd.synchronize()
+                assert all(np.array_equal(u32(got[q]), want_other[q]) for q in range(W)), turn
+            for x in idx:
+                x.zero_()
+            graph.replay()
+        sd.synchronize()
+        assert all(np.array_equal(u32(idx[q]), want[q]) for q in range(W)), turn
+    sd.close()
+
+
 @pytest.mark.parametrize("per_tile_tail", [0, 1])
 @pytest.mark.parametrize("W", [1, 5, 9])
 @pytest.mark.parametrize("name", sorted(SEGMENTS) + ["one_segment", "more_blocks_than_run_at_a_time"])
