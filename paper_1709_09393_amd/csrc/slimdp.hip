@@ -364,14 +364,14 @@ size_t expl_capture_words(uint64_t T, uint32_t max_workers, uint32_t n_seg)
 }
 
 // Slots for the explorer values of a sub-tile, from the share of the words in the sure zone: of its 256 blocks of four those
-// with a sure parameter, two standard deviations more (what does not fit, under one in a thousand, is gathered).  Above EXPL_SLOTS_MAX nothing is
-// kept: 6 % of the parameters, where a gather reads nearly every line anyway.
+// with a sure parameter.  What does not fit is gathered: under one in a thousand with the few, up to 4 % with the larger
+// number; above that (5 % of the parameters) nothing is kept.
 uint32_t expl_slots(const SegInit& in)
 {
     if (!in.has_gt) return 0;
     const double p = ((double)in.sure_m1 + 1.0) / 4294967296.0, full = 1.0 - std::pow(1.0 - p, 4.0);
-    const double want = 256.0 * full + 2.0 * std::sqrt(256.0 * full * (1.0 - full));
-    return want <= 32.0 ? 32u : want <= (double)EXPL_SLOTS_MAX ? EXPL_SLOTS_MAX : 0u;
+    if (256.0 * full + 2.0 * std::sqrt(256.0 * full * (1.0 - full)) <= (double)EXPL_SLOTS_FEW) return EXPL_SLOTS_FEW;
+    return 256.0 * full <= (double)EXPL_SLOTS_MAX ? EXPL_SLOTS_MAX : 0u;
 }
 
 template <class P> bool table_ok(P const* tab, uint32_t nw, bool allow_null_entries = false)

@@ -257,7 +257,7 @@ __device__ __forceinline__ void flush_hist(uint32_t* lds, uint32_t nb, uint32_t*
 // kept by the scoring pass for the pack.  A sub-tile has PreArgs::slots values for each worker scored, in the order of
 // the parameters' blocks of four: the first sure parameter of every block that has one.  Which those are is told by the
 // sure bitmap as the draw left it.
-constexpr uint32_t EXPL_SLOTS_MAX = 64;
+constexpr uint32_t EXPL_SLOTS_FEW = 32, EXPL_SLOTS_MAX = 48;        // whole lines for two workers and more
 struct PreArgs {
     uint32_t nw, worker0, n_seg;
     const SegState* states;
@@ -690,9 +690,11 @@ __global__ __launch_bounds__(BLOCK, SCOREF_MINB) void k_score_flat(const float* 
             ecount = 0;
             if (pre.slots) {
                 const __amdgpu_buffer_rsrc_t rv = buffer_of(pre.vals + ((size_t)t * SUBS + wid) * WT * pre.slots, WT * pre.slots * 4u);
-                const uint32_t sh = pre.slots == 32u ? 3u : 4u;   // 16-byte pieces of a worker's line, as a power of two
-                for (uint32_t k = lane; k < ((uint32_t)WT << sh); k += 64)
-                    buffer_store4_aux<SCOREF_CAP_AUX>(rv, k * 16u, *reinterpret_cast<const float4*>(es + (k >> sh) * EXPL_SLOTS_MAX + (k & ((1u << sh) - 1u)) * 4u));
+                const bool few = pre.slots == EXPL_SLOTS_FEW;     // 16-byte pieces: the worker and the piece of its line
+                for (uint32_t k = lane; k < WT * pre.slots / 4u; k += 64) {
+                    const uint32_t b = few ? k / (EXPL_SLOTS_FEW / 4u) : k / (EXPL_SLOTS_MAX / 4u);
+                    buffer_store4_aux<SCOREF_CAP_AUX>(rv, k * 16u, *reinterpret_cast<const float4*>(es + b * EXPL_SLOTS_MAX + (k - b * (pre.slots / 4u)) * 4u));
+                }
             }
             wave_sync();
         }

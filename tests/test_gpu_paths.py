@@ -337,7 +337,7 @@ def test_capture_of_clustered_parameters(W, spills):
 
 @pytest.mark.parametrize("W,pct", [(1, 2), (2, 1), (4, 5), (8, 2), (16, 2), (16, 5)])
 def test_explorer_values_kept_by_the_scoring_pass(W, pct):
-    """The draw by rounds and the values it keeps (32 or 64 slots a sub-tile, a ragged tile, more workers announced than scored),
+    """The draw by rounds and the values it keeps (32 or 48 slots a sub-tile, a ragged tile, more workers announced than scored),
     and packs whose lists are not, or no longer, the ones that were drawn with it."""
     n, more = 4096 * (220 if pct < 5 else 520) + 777, 2          # narrow zones
     wl = workloads.TINY.scaled(n)
