@@ -400,7 +400,7 @@ __global__ __launch_bounds__(BLOCK) void k_core_count(CoreArgs a, SpecTau sp, ui
                 const uint2 v = (x < seg_t1) ? cnt[x - g0] : make_uint2(0u, 0u);
                 const uint32_t is = wave_incl_scan(v.x), it = wave_incl_scan(v.y);
                 if (x < seg_t1) a.tile_pre[x] = make_uint2(run.x + is - v.x, run.y + it - v.y);
-                run.x += __shfl(is, 63, 64); run.y += __shfl(it, 63, 64);
+                run.x += last_lane(is); run.y += last_lane(it);
             }
             tail = run;
         }

@@ -45,16 +45,24 @@ struct SegInitChunk { SegInit s[INIT_CHUNK]; };
 // ---------------------------------------------------------------------------------------
 __device__ __forceinline__ uint32_t lane_id() { return threadIdx.x & 63u; }
 
-__device__ __forceinline__ uint32_t wave_incl_scan(uint32_t v)
+// Scans and reductions over a wave by data-parallel moves: shifts by 1, 2, 4, 8 lanes inside the rows of 16, then the last
+// lane of a row, and of the lower half, to the rows above.  Six vector instructions, where six trips through the LDS
+// crossbar take about 700 cycles, which the short kernels of a selection spend several times over in their chains.
+// Every lane of the wave must be active.
+template <class OP> __device__ __forceinline__ uint32_t wave_scan(uint32_t v, OP op)      // op(x, 0) == x
 {
-    const uint32_t lane = lane_id();
-#pragma unroll
-    for (int d = 1; d < 64; d <<= 1) {
-        uint32_t t = __shfl_up(v, d, 64);
-        if (lane >= (uint32_t)d) v += t;
-    }
+    v = op(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x111, 0xF, 0xF, true));       // row_shr:1
+    v = op(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x112, 0xF, 0xF, true));
+    v = op(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x114, 0xF, 0xF, true));
+    v = op(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x118, 0xF, 0xF, true));
+    v = op(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x142, 0xA, 0xF, false));      // row_bcast:15 into rows 1 and 3
+    v = op(v, (uint32_t)__builtin_amdgcn_update_dpp(0, (int)v, 0x143, 0xC, 0xF, false));      // row_bcast:31 into rows 2 and 3
     return v;
 }
+__device__ __forceinline__ uint32_t wave_incl_scan(uint32_t v) { return wave_scan(v, [](uint32_t a, uint32_t b) { return a + b; }); }
+__device__ __forceinline__ uint32_t last_lane(uint32_t v) { return (uint32_t)__builtin_amdgcn_readlane((int)v, 63); }
+__device__ __forceinline__ uint32_t wave_sum(uint32_t v) { return last_lane(wave_incl_scan(v)); }
+__device__ __forceinline__ uint32_t wave_max(uint32_t v) { return last_lane(wave_scan(v, [](uint32_t a, uint32_t b) { return a > b ? a : b; })); }
 
 // Buffer addressing: a 128-bit descriptor in scalar registers (base, byte range, no stride)
 // plus one 32-bit per-lane byte offset and a scalar offset.  Compared with flat 64-bit
@@ -166,13 +174,6 @@ __device__ __forceinline__ uint32_t transpose_flags(uint32_t v)              // 
 {
     v = (v | (v << 8)) & 0x00FF00FFu;
     return transpose_spread((v | (v << 4)) & 0x0F0F0F0Fu);
-}
-
-__device__ __forceinline__ uint32_t wave_sum(uint32_t v)
-{
-#pragma unroll
-    for (int d = 32; d >= 1; d >>= 1) v += __shfl_xor(v, d, 64);
-    return v;
 }
 
 // Exclusive prefix sum over the block (NWAVES*64 threads, all must call).  wtot: NWAVES words

@@ -142,7 +142,7 @@ __global__ __launch_bounds__(BLOCK) void k_explore_collect(const uint32_t* __res
             const int leader = __ffsll((long long)todo) - 1;
             const uint32_t seg = __shfl(tr.seg, leader, 64);
             const bool in = mine != 0u && tr.seg == seg;
-            const uint32_t v = in ? mine : 0u, incl = wave_incl_scan(v), total = __shfl(incl, 63, 64);
+            const uint32_t v = in ? mine : 0u, incl = wave_incl_scan(v), total = last_lane(incl);
             uint32_t base = NONE;
             if ((int)lane == leader) base = reserve(seg, total);
             base = __shfl(base, leader, 64);
@@ -217,7 +217,7 @@ __global__ __launch_bounds__(BLOCK) void k_explore_collect_wide(const uint32_t* 
         if (lane == 0) cnt_sel[bt] = sure;
         const uint32_t cw[2] = {c2.x, c2.y};
         const uint32_t newc = __popc(cw[0] & ~kw[0]) + __popc(cw[1] & ~kw[1]);
-        const uint32_t incl = wave_incl_scan(newc), total = __shfl(incl, 63, 64);
+        const uint32_t incl = wave_incl_scan(newc), total = last_lane(incl);
         if (total == 0) continue;
         const bool direct = total > WIDE_STAGE;
         if (fill && (held != tr.seg || direct || fill + total > WIDE_STAGE)) flush();
@@ -400,7 +400,7 @@ __global__ __launch_bounds__(NT) void k_explore_select(const SegState* __restric
             if (x0 + e * 64u >= w1) break;                   // uniform: a scan costs a short segment a microsecond
             const uint32_t x = x0 + e * 64u + lane, incl = wave_incl_scan(v[e]);
             if (x < w1) off[x] = run + incl - v[e];
-            run += __shfl(incl, 63, 64);
+            run += last_lane(incl);
         }
     }
     if (f1 == T && tid == 0) off[nt] = base + need0;

@@ -1068,7 +1068,7 @@ __device__ __forceinline__ void emit_indices(uint32_t w0, uint32_t w1, uint32_t 
                                              uint16_t* stage, uint32_t* __restrict__ out)
 {
     const uint32_t lane = lane_id();
-    const uint32_t total = __shfl(incl, 63, 64), excl = incl - __popc(w0) - __popc(w1);
+    const uint32_t total = last_lane(incl), excl = incl - __popc(w0) - __popc(w1);
     if (total > EMIT_STAGE) {                         // uniform
 #pragma unroll 4
         for (uint32_t l = 0; l < 64; ++l) {
@@ -2205,6 +2205,9 @@ __global__ __launch_bounds__(BLOCK) void k_pull_local_step(const float* __restri
 // (seed low ^ 0x51534744, seed high ^ kind).  One wave per bucket: lane L holds entries
 // 4L..4L+3 and 256+4L..256+4L+3 (two Philox calls), the maximum is a wave reduction (exact,
 // whatever the order), the 512 codes leave as two stores of whole lines.
+// Bound by the vector unit while every value took a division of its own: 53 instructions a value, 149 us for 8 workers'
+// 110*10^6 values.  A bucket has one divisor: with its reciprocal, correctly rounded, a quotient takes a product and two
+// corrections of two fused steps each (see quant_quotient).  QUANTNOW
 // grid (ceil(buckets / 4), n_workers).
 // ---------------------------------------------------------------------------------------
 constexpr uint32_t QB = 512;
@@ -2218,6 +2221,24 @@ __device__ __forceinline__ uint32_t quant_code(float v, float s, uint32_t word)
         const float u = (float)(word >> 8) * 0x1p-24f;
         level = (uint32_t)l + ((u < y - l) ? 1u : 0u);
     }
+    return ((__float_as_uint(v) >> 24) & 0x80u) | level;
+}
+
+// a / s, correctly rounded, from r = 1 / s correctly rounded: the first correction leaves the quotient within one unit in the last
+// place, and a correction of such a quotient by its exact remainder is the correctly rounded one (Markstein, IBM J. Res.
+// Dev. 34 (1990)).  Exact while nothing leaves the normal numbers: s in [2^-40, 2^40], a zero or in [2^-80, s].
+__device__ __forceinline__ float quant_quotient(float a, float s, float r)
+{
+    float q = a * r;
+    q = __builtin_fmaf(__builtin_fmaf(-q, s, a), r, q);
+    return __builtin_fmaf(__builtin_fmaf(-q, s, a), r, q);
+}
+// quant_code's level from its quotient: fraction and whole part of the same y (a NaN has level 0 in both).
+__device__ __forceinline__ uint32_t quant_code_of(float v, float quotient, uint32_t word)
+{
+    const float y = quotient * 127.0f;
+    const float u = (float)(word >> 8) * 0x1p-24f;
+    const uint32_t level = (uint32_t)y + ((u < __builtin_amdgcn_fractf(y)) ? 1u : 0u);
     return ((__float_as_uint(v) >> 24) & 0x80u) | level;
 }
 
@@ -2253,25 +2274,36 @@ __global__ __launch_bounds__(BLOCK) void k_quantize(PtrTab val, Count64Tab count
     for (int h = 0; h < 2; ++h)
 #pragma unroll
         for (int c = 0; c < 4; ++c) s = __builtin_fmaxf(s, __builtin_fabsf(x[h][c]));
-#pragma unroll
-    for (int d = 32; d >= 1; d >>= 1) s = __builtin_fmaxf(s, __shfl_xor(s, d, 64));
+    s = __uint_as_float(wave_max(__float_as_uint(s)));       // no NaN left, no sign: the bits are in the values' order
     if (lane == 0) static_cast<float*>(scale.p[q])[b] = s;
+    // the smallest magnitude that is not zero (zero wraps to the largest), as bits
+    uint32_t low = 0xFFFFFFFFu;
 #pragma unroll
-    for (int h = 0; h < 2; ++h) {
-        uint32_t r[4];
-        philox4x32_10((uint32_t)((j0 + h * 256 + lane * 4) >> 2), worker0 + q, pk.it_lo, pk.it_hi, pk.seed_lo ^ 0x51534744u,
-                      pk.seed_hi ^ kind, r);
-        uint32_t packed = 0;
+    for (int h = 0; h < 2; ++h)
 #pragma unroll
-        for (int c = 0; c < 4; ++c) packed |= quant_code(x[h][c], s, r[c]) << (8 * c);
-        const uint32_t e = h * 256 + lane * 4;
-        if (vec_ok && len == QB) *reinterpret_cast<uint32_t*>(out + j0 + e) = packed;
-        else {
+        for (int c = 0; c < 4; ++c) low = min(low, (__float_as_uint(x[h][c]) & 0x7FFFFFFFu) - 1u);
+    const bool usual = __ballot(low < __float_as_uint(0x1p-80f) - 1u || !(s >= 0x1p-40f && s <= 0x1p40f)) == 0ull;      // uniform
+    const float rs = 1.0f / s;
+    auto codes = [&](auto&& code_of) {
 #pragma unroll
-            for (int c = 0; c < 4; ++c)
-                if (e + c < len) out[j0 + e + c] = (uint8_t)(packed >> (8 * c));
+        for (int h = 0; h < 2; ++h) {
+            uint32_t r[4];
+            philox4x32_10((uint32_t)((j0 + h * 256 + lane * 4) >> 2), worker0 + q, pk.it_lo, pk.it_hi, pk.seed_lo ^ 0x51534744u,
+                          pk.seed_hi ^ kind, r);
+            uint32_t packed = 0;
+#pragma unroll
+            for (int c = 0; c < 4; ++c) packed |= code_of(x[h][c], r[c]) << (8 * c);
+            const uint32_t e = h * 256 + lane * 4;
+            if (vec_ok && len == QB) *reinterpret_cast<uint32_t*>(out + j0 + e) = packed;
+            else {
+#pragma unroll
+                for (int c = 0; c < 4; ++c)
+                    if (e + c < len) out[j0 + e + c] = (uint8_t)(packed >> (8 * c));
+            }
         }
-    }
+    };
+    if (usual) codes([&](float v, uint32_t word) { return quant_code_of(v, quant_quotient(__builtin_fabsf(v), s, rs), word); });
+    else codes([&](float v, uint32_t word) { return quant_code(v, s, word); });
 }
 
 // value = sign * ((scale * level) / 127): two binary32 roundings.  Four codes per thread.  grid (blocks, n_workers).

@@ -551,3 +551,34 @@ def check_merge(n, W, pct, overlap):
     want = np.where(sent, exact.astype(np.float32), w_h)
     assert np.array_equal(u32(w), want.view(np.uint32))
     sd.close()
+
+
+@pytest.mark.parametrize("exponent", [-140, -126, -81, -80, -79, -41, -40, -39, 0, 39, 40, 41, 120])
+def test_quantisation_on_both_sides_of_the_range_of_the_common_reciprocal(exponent):
+    """Buckets whose largest, or smallest, magnitude lies at the edges inside which quotients come from the bucket's
+    reciprocal; zeros, infinities and NaN among them; a ragged last bucket."""
+    n, per = 512 * 24 + 77, 512
+    rng = np.random.default_rng(1000 + exponent)
+    buckets = []
+    for j in range(25):
+        x = rng.standard_normal(per) * rng.choice([1.0, 2.0 ** -23, 2.0 ** -60], per)
+        top = np.ldexp(1.0 + rng.random(), exponent)
+        x = x / np.abs(x).max() * top
+        if j % 3 == 1:                           # the other end: a small value in a bucket of usual size
+            x = rng.standard_normal(per)
+            x[rng.integers(per)] = np.ldexp(1.0 + rng.random(), min(exponent, 0))
+        if j % 5 == 2:
+            x[rng.integers(per, size=9)] = 0.0
+        if j % 8 == 3:
+            x[rng.integers(per)] = np.inf
+        buckets.append(x)
+    with np.errstate(over="ignore"):
+        v = np.concatenate(buckets)[:n].astype(np.float32)
+    sd = binding.SlimDP(n, 1, seed=5)
+    code, scale = sd.quantize([to_dev(v)], 0, 7)
+    sd.synchronize()
+    code_o, scale_o = oracle.quantize(v, 5, 7, 0, 0)
+    assert np.array_equal(u32(scale[0]), scale_o.view(np.uint32))
+    finite = np.repeat(np.isfinite(scale_o), per)[:n]
+    assert np.array_equal(code[0].cpu().numpy()[finite], code_o[finite])
+    sd.close()
