@@ -374,6 +374,22 @@ uint32_t expl_slots(const SegInit& in)
     return 256.0 * full <= (double)EXPL_SLOTS_MAX ? EXPL_SLOTS_MAX : 0u;
 }
 
+// Whether the local models, gradients and updates (three arrays a worker) pass the caches by: they do not where the next pass
+// finds a good part of them in the 256 MB of the last level.  One round of a worker's side, non-temporal / not, us: 10^6
+// parameters, 4 workers (48 MB) 54 / 48; 3*10^6, 8 (288 MB) 212 / 191; 8*10^6, 4 (384 MB) 287 / 271; but 5*10^6, 8 (480 MB)
+// 341 / 352 and 16*10^6, 8 1,090 / 1,239.
+bool local_streams(const slimdp_ctx* c, uint32_t n_workers) { return c->n * n_workers * 12u > 400000000u; }
+
+// How many workers a block of the passes over tiles takes in turn: all of them, so that what they share is read once, unless
+// that leaves compute units without a block (one round of 10^6 parameters and 4 workers in 245 tiles: 50.7 us with all four,
+// 48.0 with two a block, 51.2 with one; 2*10^6: 74.6 with four, 83.3 with one).
+uint32_t workers_per_block(const slimdp_ctx* c, uint32_t n_workers)
+{
+    uint32_t per = n_workers;
+    while (per > 1 && (uint64_t)c->T * ((n_workers + per - 1) / per) < (uint32_t)c->cus) per = (per + 1) / 2;
+    return per;
+}
+
 template <class P> bool table_ok(P const* tab, uint32_t nw, bool allow_null_entries = false)
 {
     if (!tab) return false;
@@ -1546,22 +1562,29 @@ int slimdp_pull(slimdp_ctx* ctx, const float* w, uint64_t core_epoch, uint32_t n
     const float* src = w;
     bool any_local = false;
     for (uint32_t q = 0; w_local && q < n_workers; ++q) any_local = any_local || w_local[q] != nullptr;
-    // the values at the communication sets; the local models are patched by a pass of their own that streams them (a
-    // scattered 4-byte write per value would touch nearly every line of every local model, at a fraction of the rate)
+    // The local models are patched by a pass that streams them (a scattered 4-byte write per value would touch nearly every
+    // line of every local model, at a fraction of the rate); the values at the communication sets leave from the same pass.
+    if (any_local && ctx->opt_pull_kernel == 1) {
+        int vec_ok = aligned16(w);
+        for (uint32_t q = 0; q < n_workers; ++q) vec_ok = vec_ok && (!w_local[q] || aligned16(w_local[q]));
+        const uint32_t per = workers_per_block(ctx, n_workers);
+        auto launch = [&](auto kernel) {
+            hipLaunchKernelGGL(kernel, dim3(ctx->T, (n_workers + per - 1) / per), dim3(BLOCK), 0, ctx->stream, w,
+                               make_tab<MutPtrTab>(w_local, n_workers), PtrTab{}, MutPtrTab{}, 0.0f, 1, n_workers, per, ctx->n, ctx->n_seg,
+                               ctx->d_tile_start, core_idx, core_off, make_tab<PtrTab>(expl_idx, n_workers),
+                               make_tab<PtrTab>(expl_off, n_workers), make_tab<MutPtrTab>(core_out, n_workers),
+                               make_tab<MutPtrTab>(expl_out, n_workers), vec_ok);
+        };
+        if (local_streams(ctx, n_workers)) launch(k_pull_local_step<0, 1>); else launch(k_pull_local_step<0, 0>);
+        SLIMDP_LAUNCHED(ctx, "k_pull_local_step<0>");
+        return SLIMDP_OK;
+    }
     hipLaunchKernelGGL(k_gather, dim3(ctx->T), dim3(BLOCK), 0, ctx->stream, make_tab<PtrTab, const float*>(&src, 1), 1,
                        n_workers, ctx->n, core_idx, core_off, make_tab<PtrTab>(expl_idx, n_workers),
                        make_tab<PtrTab>(expl_off, n_workers), make_tab<MutPtrTab>(core_out, n_workers),
                        make_tab<MutPtrTab>(expl_out, n_workers),
-                       make_tab<MutPtrTab>(w_local, (w_local && ctx->opt_pull_kernel == 0) ? n_workers : 0));
+                       make_tab<MutPtrTab>(w_local, w_local ? n_workers : 0));
     SLIMDP_LAUNCHED(ctx, "k_gather(pull)");
-    if (any_local && ctx->opt_pull_kernel == 1) {
-        int vec_ok = aligned16(w);
-        for (uint32_t q = 0; q < n_workers; ++q) vec_ok = vec_ok && (!w_local[q] || aligned16(w_local[q]));
-        hipLaunchKernelGGL(k_pull_local_step<0>, dim3(ctx->T), dim3(BLOCK), 0, ctx->stream, w,
-                           make_tab<MutPtrTab>(w_local, n_workers), PtrTab{}, MutPtrTab{}, 0.0f, 1, n_workers, ctx->d_tile_start,
-                           core_idx, core_off, make_tab<PtrTab>(expl_idx, n_workers), make_tab<PtrTab>(expl_off, n_workers), vec_ok);
-        SLIMDP_LAUNCHED(ctx, "k_pull_local_step<0>");
-    }
     return SLIMDP_OK;
 }
 
@@ -1587,9 +1610,12 @@ int slimdp_local_step(slimdp_ctx* ctx, uint32_t n_workers, float* const* w_local
     const uint64_t cap = (uint64_t)ctx->cus * 16 / n_workers + 1;
     if (blocks > cap) blocks = cap;
     if (blocks < 1) blocks = 1;
-    hipLaunchKernelGGL(k_local_step, dim3((uint32_t)blocks, n_workers), dim3(256), 0, ctx->stream, make_tab<MutPtrTab>(w_local, n_workers),
-                       make_tab<PtrTab>(grad, n_workers), make_tab<MutPtrTab>(delta, n_workers), ctx->n, eta,
-                       (int)((flags & SLIMDP_LOCAL_FIRST) != 0), vec_ok);
+    auto launch = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3((uint32_t)blocks, n_workers), dim3(256), 0, ctx->stream, make_tab<MutPtrTab>(w_local, n_workers),
+                           make_tab<PtrTab>(grad, n_workers), make_tab<MutPtrTab>(delta, n_workers), ctx->n, eta,
+                           (int)((flags & SLIMDP_LOCAL_FIRST) != 0), vec_ok);
+    };
+    if (local_streams(ctx, n_workers)) launch(k_local_step<1>); else launch(k_local_step<0>);
     SLIMDP_LAUNCHED(ctx, "k_local_step");
     return SLIMDP_OK;
 }
@@ -1621,18 +1647,18 @@ int slimdp_local_step_pack(slimdp_ctx* ctx, uint32_t n_workers, float* const* w_
     rc = wait_for_lists(ctx, n_workers, expl_idx, expl_off, m_w);
     if (rc) return rc;
     const int first = (flags & SLIMDP_LOCAL_FIRST) != 0;
-    if (ctx->opt_pack_nbuf == 2)
-        hipLaunchKernelGGL(k_local_step_pack<2>, dim3(ctx->T), dim3(BLOCK), 0, ctx->stream, make_tab<MutPtrTab>(w_local, n_workers),
-                           make_tab<PtrTab>(grad, n_workers), make_tab<MutPtrTab>(delta, n_workers), eta, first, n_workers,
-                           ctx->d_tile_start, core_idx, core_off, make_tab<PtrTab>(expl_idx, n_workers),
+    const uint32_t per = workers_per_block(ctx, n_workers);
+    const dim3 grid(ctx->T, (n_workers + per - 1) / per);
+    auto launch = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, grid, dim3(BLOCK), 0, ctx->stream, make_tab<MutPtrTab>(w_local, n_workers),
+                           make_tab<PtrTab>(grad, n_workers), make_tab<MutPtrTab>(delta, n_workers), eta, first, n_workers, per, ctx->n,
+                           ctx->n_seg, ctx->d_tile_start, core_idx, core_off, make_tab<PtrTab>(expl_idx, n_workers),
                            make_tab<PtrTab>(expl_off, n_workers), make_tab<MutPtrTab>(core_val, n_workers),
                            make_tab<MutPtrTab>(expl_val, n_workers), vec_ok);
-    else
-        hipLaunchKernelGGL(k_local_step_pack<1>, dim3(ctx->T), dim3(BLOCK), 0, ctx->stream, make_tab<MutPtrTab>(w_local, n_workers),
-                           make_tab<PtrTab>(grad, n_workers), make_tab<MutPtrTab>(delta, n_workers), eta, first, n_workers,
-                           ctx->d_tile_start, core_idx, core_off, make_tab<PtrTab>(expl_idx, n_workers),
-                           make_tab<PtrTab>(expl_off, n_workers), make_tab<MutPtrTab>(core_val, n_workers),
-                           make_tab<MutPtrTab>(expl_val, n_workers), vec_ok);
+    };
+    const bool streams = local_streams(ctx, n_workers);
+    if (ctx->opt_pack_nbuf == 2) { if (streams) launch(k_local_step_pack<2, 1>); else launch(k_local_step_pack<2, 0>); }
+    else { if (streams) launch(k_local_step_pack<1, 1>); else launch(k_local_step_pack<1, 0>); }
     SLIMDP_LAUNCHED(ctx, "k_local_step_pack");
     return SLIMDP_OK;
 }
@@ -1661,10 +1687,15 @@ int slimdp_pull_local_step(slimdp_ctx* ctx, const float* w, uint64_t core_epoch,
     if (rc) return rc;
     rc = wait_for_lists(ctx, n_workers, expl_idx, expl_off, m_w);
     if (rc) return rc;
-    hipLaunchKernelGGL(k_pull_local_step<1>, dim3(ctx->T), dim3(BLOCK), 0, ctx->stream, w, make_tab<MutPtrTab>(w_local, n_workers),
-                       make_tab<PtrTab>(grad, n_workers), make_tab<MutPtrTab>(delta, n_workers), eta,
-                       (int)((flags & SLIMDP_LOCAL_FIRST) != 0), n_workers, ctx->d_tile_start, core_idx, core_off,
-                       make_tab<PtrTab>(expl_idx, n_workers), make_tab<PtrTab>(expl_off, n_workers), vec_ok);
+    const uint32_t per = workers_per_block(ctx, n_workers);
+    auto launch = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3(ctx->T, (n_workers + per - 1) / per), dim3(BLOCK), 0, ctx->stream, w,
+                           make_tab<MutPtrTab>(w_local, n_workers), make_tab<PtrTab>(grad, n_workers), make_tab<MutPtrTab>(delta, n_workers),
+                           eta, (int)((flags & SLIMDP_LOCAL_FIRST) != 0), n_workers, per, ctx->n, ctx->n_seg, ctx->d_tile_start, core_idx,
+                           core_off, make_tab<PtrTab>(expl_idx, n_workers), make_tab<PtrTab>(expl_off, n_workers), MutPtrTab{}, MutPtrTab{},
+                           vec_ok);
+    };
+    if (local_streams(ctx, n_workers)) launch(k_pull_local_step<1, 1>); else launch(k_pull_local_step<1, 0>);
     SLIMDP_LAUNCHED(ctx, "k_pull_local_step");
     return SLIMDP_OK;
 }

@@ -1898,8 +1898,10 @@ __global__ __launch_bounds__(BLOCK) void k_merge(float* __restrict__ w, float lr
 // model, w_q <- fma(-eta, grad_q, w_q), and the accumulation of the update that the next
 // push sends, delta_q = grad_1 + grad_2 + ... in binary32 in mini-batch order (first: a new
 // accumulation starts with this gradient; delta is then not read).  20 bytes per parameter
-// and worker (16 when first).  grid (blocks, n_workers).
+// and worker (16 when first).  NT: as in the two kernels below, streams pass the caches by (see local_streams).
+// grid (blocks, n_workers).
 // ---------------------------------------------------------------------------------------
+template <int NT>
 __global__ __launch_bounds__(256) void k_local_step(MutPtrTab w_local, PtrTab grad, MutPtrTab delta, uint64_t n, float eta,
                                                     int first, int vec_ok)
 {
@@ -1912,25 +1914,25 @@ __global__ __launch_bounds__(256) void k_local_step(MutPtrTab w_local, PtrTab gr
     for (uint64_t x = (uint64_t)blockIdx.x * 256 + threadIdx.x; x < n4; x += 2 * stride) {       // two vectors per turn in flight
         const uint64_t x2 = x + stride;
         const bool two = x2 < n4;
-        const float4 ga = ld4<1>(g + 4 * x), wa = ld4<1>(w + 4 * x);
-        const float4 gb = two ? ld4<1>(g + 4 * x2) : make_float4(0.f, 0.f, 0.f, 0.f);
-        const float4 wb = two ? ld4<1>(w + 4 * x2) : make_float4(0.f, 0.f, 0.f, 0.f);
+        const float4 ga = ld4<NT>(g + 4 * x), wa = ld4<NT>(w + 4 * x);
+        const float4 gb = two ? ld4<NT>(g + 4 * x2) : make_float4(0.f, 0.f, 0.f, 0.f);
+        const float4 wb = two ? ld4<NT>(w + 4 * x2) : make_float4(0.f, 0.f, 0.f, 0.f);
         float4 da = ga, db = gb;
         if (!first) {
-            const float4 oa = ld4<1>(d + 4 * x);
+            const float4 oa = ld4<NT>(d + 4 * x);
             da = make_float4(oa.x + ga.x, oa.y + ga.y, oa.z + ga.z, oa.w + ga.w);
             if (two) {
-                const float4 ob = ld4<1>(d + 4 * x2);
+                const float4 ob = ld4<NT>(d + 4 * x2);
                 db = make_float4(ob.x + gb.x, ob.y + gb.y, ob.z + gb.z, ob.w + gb.w);
             }
         }
-        st4<1>(w + 4 * x, make_float4(__builtin_fmaf(-eta, ga.x, wa.x), __builtin_fmaf(-eta, ga.y, wa.y),
+        st4<NT>(w + 4 * x, make_float4(__builtin_fmaf(-eta, ga.x, wa.x), __builtin_fmaf(-eta, ga.y, wa.y),
                                       __builtin_fmaf(-eta, ga.z, wa.z), __builtin_fmaf(-eta, ga.w, wa.w)));
-        st4<1>(d + 4 * x, da);
+        st4<NT>(d + 4 * x, da);
         if (two) {
-            st4<1>(w + 4 * x2, make_float4(__builtin_fmaf(-eta, gb.x, wb.x), __builtin_fmaf(-eta, gb.y, wb.y),
+            st4<NT>(w + 4 * x2, make_float4(__builtin_fmaf(-eta, gb.x, wb.x), __builtin_fmaf(-eta, gb.y, wb.y),
                                            __builtin_fmaf(-eta, gb.z, wb.z), __builtin_fmaf(-eta, gb.w, wb.w)));
-            st4<1>(d + 4 * x2, db);
+            st4<NT>(d + 4 * x2, db);
         }
     }
     for (uint64_t i = 4 * n4 + (uint64_t)blockIdx.x * 256 + threadIdx.x; i < n; i += stride) {      // tail, or unaligned arrays
@@ -1945,12 +1947,12 @@ __global__ __launch_bounds__(256) void k_local_step(MutPtrTab w_local, PtrTab gr
 // communication already streams the accumulated update of every worker; picking the values at
 // the communication set while a tile of the new update sits in LDS saves the extraction its own
 // scan of the update vectors (the full scan that section 3.5 counts per extraction).  Same
-// results as k_local_step followed by k_pack_stream on delta.  One block per tile, workers in
-// turn, the next worker's three tiles in flight while the current one is picked from.
+// results as k_local_step followed by k_pack_stream on delta.  One block per tile and per_block
+// workers in turn, the next worker's three tiles in flight while the current one is picked from.
 // ---------------------------------------------------------------------------------------
-template <int NBUF>
+template <int NBUF, int NT>
 __global__ __launch_bounds__(BLOCK) void k_local_step_pack(MutPtrTab w_local, PtrTab grad, MutPtrTab delta, float eta, int first,
-                                                           uint32_t nw, const uint32_t* __restrict__ tile_start,
+                                                           uint32_t nw, uint32_t per_block, uint64_t n, uint32_t n_seg, const uint32_t* __restrict__ tile_start,
                                                            const uint32_t* __restrict__ core_idx,
                                                            const uint32_t* __restrict__ core_off, PtrTab expl_idx, PtrTab expl_off,
                                                            MutPtrTab core_val, MutPtrTab expl_val, int vec_ok)
@@ -1958,24 +1960,13 @@ __global__ __launch_bounds__(BLOCK) void k_local_step_pack(MutPtrTab w_local, Pt
     __shared__ float buf[NBUF][TILE];
     __shared__ uint16_t cpos[TILE];          // the tile's core positions: the same for every worker
     __shared__ uint32_t elo[MAXW], ehi[MAXW];
-    const uint32_t t = blockIdx.x;
-    const uint32_t start = tile_start[t], len = tile_start[t + 1] - start;
+    const uint32_t t = blockIdx.x, q0 = blockIdx.y * per_block, q1 = min(q0 + per_block, nw);
+    const TileRef tr = tile_ref(t, n_seg, n, tile_start, tile_start);      // the segment is not asked for
+    const uint32_t start = tr.start, len = tr.len;
     const bool vec = vec_ok && len == TILE && (start & 3u) == 0;
-    const uint32_t c0 = core_off[t], c1 = core_off[t + 1];
-    const uint32_t ccnt = (c1 - c0 < TILE) ? c1 - c0 : TILE;
-    if (threadIdx.x < nw) {
-        const uint32_t* eo = static_cast<const uint32_t*>(expl_off.p[threadIdx.x]);
-        elo[threadIdx.x] = eo[t];
-        ehi[threadIdx.x] = eo[t + 1];
-    }
-    for (uint32_t x = threadIdx.x; x < ccnt; x += BLOCK) {
-        const uint32_t pos = core_idx[c0 + x] - start;
-        cpos[x] = (pos < len) ? (uint16_t)pos : (uint16_t)0xFFFF;
-    }
-    __syncthreads();
     float rg[EPT], rw[EPT], rd[EPT];
     uint32_t epos = 0xFFFFFFFFu;
-    auto fetch = [&](uint32_t q) {
+    auto fetch_tiles = [&](uint32_t q) {
         const float* g = static_cast<const float*>(grad.p[q]) + start;
         const float* w = static_cast<const float*>(w_local.p[q]) + start;
         const float* d = static_cast<const float*>(delta.p[q]) + start;
@@ -1983,11 +1974,11 @@ __global__ __launch_bounds__(BLOCK) void k_local_step_pack(MutPtrTab w_local, Pt
 #pragma unroll
             for (int k = 0; k < 4; ++k) {
                 const uint32_t o = k * 1024 + threadIdx.x * 4;
-                const float4 a = ld4<1>(g + o), b = ld4<1>(w + o);
+                const float4 a = ld4<NT>(g + o), b = ld4<NT>(w + o);
                 rg[4 * k + 0] = a.x; rg[4 * k + 1] = a.y; rg[4 * k + 2] = a.z; rg[4 * k + 3] = a.w;
                 rw[4 * k + 0] = b.x; rw[4 * k + 1] = b.y; rw[4 * k + 2] = b.z; rw[4 * k + 3] = b.w;
                 if (!first) {
-                    const float4 c = ld4<1>(d + o);
+                    const float4 c = ld4<NT>(d + o);
                     rd[4 * k + 0] = c.x; rd[4 * k + 1] = c.y; rd[4 * k + 2] = c.z; rd[4 * k + 3] = c.w;
                 }
             }
@@ -2000,18 +1991,34 @@ __global__ __launch_bounds__(BLOCK) void k_local_step_pack(MutPtrTab w_local, Pt
                 rd[j] = (e < len && !first) ? d[e] : 0.0f;
             }
         }
+    };
+    auto fetch_epos = [&](uint32_t q) {
         // the index itself: anything computed from it here would make the wave wait for this load, and with it for the
         // tile requested just before, on the spot
         const uint32_t j = elo[q] + threadIdx.x;
         epos = 0xFFFFFFFFu;
         if (j < ehi[q]) epos = static_cast<const uint32_t*>(expl_idx.p[q])[j];
     };
-    fetch(0);
-    for (uint32_t q = 0; q < nw; ++q) {
+    // the first worker's tiles are on their way while the lists' slices are looked up
+    fetch_tiles(q0);
+    const uint32_t c0 = core_off[t], c1 = core_off[t + 1];
+    const uint32_t ccnt = (c1 - c0 < TILE) ? c1 - c0 : TILE;
+    if (threadIdx.x < nw) {
+        const uint32_t* eo = static_cast<const uint32_t*>(expl_off.p[threadIdx.x]);
+        elo[threadIdx.x] = eo[t];
+        ehi[threadIdx.x] = eo[t + 1];
+    }
+    for (uint32_t x = threadIdx.x; x < ccnt; x += BLOCK) {
+        const uint32_t pos = core_idx[c0 + x] - start;
+        cpos[x] = (pos < len) ? (uint16_t)pos : (uint16_t)0xFFFF;
+    }
+    __syncthreads();
+    fetch_epos(q0);
+    for (uint32_t q = q0; q < q1; ++q) {
         float* b = buf[NBUF == 2 ? (q & 1u) : 0];
         float* w = static_cast<float*>(w_local.p[q]) + start;
         float* d = static_cast<float*>(delta.p[q]) + start;
-        if (NBUF == 1 && q) __syncthreads();     // the previous worker's readers are done with the buffer
+        if (NBUF == 1 && q != q0) __syncthreads();     // the previous worker's readers are done with the buffer
         // the step and the accumulation; the new update goes to memory and to LDS
 #pragma unroll
         for (int j = 0; j < EPT; ++j) {
@@ -2022,8 +2029,8 @@ __global__ __launch_bounds__(BLOCK) void k_local_step_pack(MutPtrTab w_local, Pt
 #pragma unroll
             for (int k = 0; k < 4; ++k) {
                 const uint32_t o = k * 1024 + threadIdx.x * 4;
-                st4<1>(w + o, make_float4(rw[4 * k], rw[4 * k + 1], rw[4 * k + 2], rw[4 * k + 3]));
-                st4<1>(d + o, make_float4(rd[4 * k], rd[4 * k + 1], rd[4 * k + 2], rd[4 * k + 3]));
+                st4<NT>(w + o, make_float4(rw[4 * k], rw[4 * k + 1], rw[4 * k + 2], rw[4 * k + 3]));
+                st4<NT>(d + o, make_float4(rd[4 * k], rd[4 * k + 1], rd[4 * k + 2], rd[4 * k + 3]));
                 *reinterpret_cast<float4*>(b + o) = make_float4(rd[4 * k], rd[4 * k + 1], rd[4 * k + 2], rd[4 * k + 3]);
             }
         } else {
@@ -2036,7 +2043,7 @@ __global__ __launch_bounds__(BLOCK) void k_local_step_pack(MutPtrTab w_local, Pt
         }
         const uint32_t my_epos = epos - start;      // no entry: wraps to a position beyond any tile (start + len < 2^32)
         __syncthreads();     // with two buffers this also orders a buffer's readers (two workers ago) before its writers
-        if (q + 1 < nw) fetch(q + 1);
+        if (q + 1 < q1) { fetch_tiles(q + 1); fetch_epos(q + 1); }
         float* cv = static_cast<float*>(core_val.p[q]);
         for (uint32_t x = threadIdx.x; x < ccnt; x += BLOCK) {
             const uint32_t pos = cpos[x];
@@ -2060,24 +2067,27 @@ __global__ __launch_bounds__(BLOCK) void k_local_step_pack(MutPtrTab w_local, Pt
 // is overwritten with the global one at the worker's communication set, then stepped.  The first local step after a
 // communication streams every local model anyway; applying the pulled values there saves the pull its own pass,
 // whose scattered 4-byte writes touch nearly every line of every local model.  Same results as k_gather with a
-// scatter destination followed by k_local_step.  STEP = 0: the overwrite alone (the write half of a pull with local
-// models: workers without one are skipped).  One block per tile: the tile of the global model stays in
+// scatter destination followed by k_local_step.  STEP = 0: a pull with local models, whose values at the communication
+// sets leave from the same pass (as a kernel of its own the gather read model and lists a second time: 10^6 parameters, 4 workers
+// 6 + 11 us, 14 together); workers without a local model are not patched.  One block per tile and per_block workers: the tile of the global model stays in
 // registers for all workers, the communication set of a worker is a bitmap in LDS (core positions once per tile,
 // explorer positions per worker, marked one worker ahead), the next worker's three tiles travel meanwhile.
 // ---------------------------------------------------------------------------------------
-template <int STEP>
+template <int STEP, int NT>
 __global__ __launch_bounds__(BLOCK) void k_pull_local_step(const float* __restrict__ w, MutPtrTab w_local, PtrTab grad, MutPtrTab delta,
-                                                           float eta, int first, uint32_t nw,
+                                                           float eta, int first, uint32_t nw, uint32_t per_block, uint64_t n, uint32_t n_seg,
                                                            const uint32_t* __restrict__ tile_start,
                                                            const uint32_t* __restrict__ core_idx,
                                                            const uint32_t* __restrict__ core_off, PtrTab expl_idx, PtrTab expl_off,
-                                                           int vec_ok)
+                                                           MutPtrTab core_out, MutPtrTab expl_out, int vec_ok)
 {
     __shared__ uint32_t cm[TILE_WORDS];          // core positions of the tile
     __shared__ uint32_t em[2][TILE_WORDS];       // explorer positions of a worker
     __shared__ uint32_t elo[MAXW], ehi[MAXW];
-    const uint32_t t = blockIdx.x;
-    const uint32_t start = tile_start[t], len = tile_start[t + 1] - start;
+    __shared__ __align__(16) float ws[STEP ? 4 : TILE];      // the tile of the global model, for the values that leave
+    const uint32_t t = blockIdx.x, q0 = blockIdx.y * per_block, q1 = min(q0 + per_block, nw);
+    const TileRef tr = tile_ref(t, n_seg, n, tile_start, tile_start);      // the segment is not asked for
+    const uint32_t start = tr.start, len = tr.len;
     const bool vec = vec_ok && len == TILE && (start & 3u) == 0;
     const uint32_t c0 = core_off[t], c1 = core_off[t + 1];
     if (threadIdx.x < nw) {
@@ -2085,13 +2095,13 @@ __global__ __launch_bounds__(BLOCK) void k_pull_local_step(const float* __restri
         elo[threadIdx.x] = eo[t];
         ehi[threadIdx.x] = eo[t + 1];
     }
-    if (threadIdx.x < TILE_WORDS) { cm[threadIdx.x] = 0; em[0][threadIdx.x] = 0; }
+    if (threadIdx.x < TILE_WORDS) { cm[threadIdx.x] = 0; em[q0 & 1u][threadIdx.x] = 0; }
     // this thread's elements of the global model: the same positions as its elements of every local model
     float wv[EPT];
     if (vec) {
 #pragma unroll
         for (int k = 0; k < 4; ++k) {
-            const float4 v = ld4<1>(w + (size_t)start + k * 1024 + threadIdx.x * 4);
+            const float4 v = ld4<NT>(w + (size_t)start + k * 1024 + threadIdx.x * 4);
             wv[4 * k + 0] = v.x; wv[4 * k + 1] = v.y; wv[4 * k + 2] = v.z; wv[4 * k + 3] = v.w;
         }
     } else {
@@ -2101,21 +2111,40 @@ __global__ __launch_bounds__(BLOCK) void k_pull_local_step(const float* __restri
             wv[j] = (e < len) ? w[(size_t)start + e] : 0.0f;
         }
     }
+    if (!STEP) {
+        if (vec) {
+#pragma unroll
+            for (int k = 0; k < 4; ++k)
+                *reinterpret_cast<float4*>(ws + k * 1024 + threadIdx.x * 4) = make_float4(wv[4 * k], wv[4 * k + 1], wv[4 * k + 2], wv[4 * k + 3]);
+        } else {
+#pragma unroll
+            for (int j = 0; j < EPT; ++j) ws[elem_scl(j)] = wv[j];
+        }
+    }
     __syncthreads();
     for (uint32_t j = c0 + threadIdx.x; j < c1; j += BLOCK) {
-        const uint32_t pos = core_idx[j] - start;
+        const uint32_t i = core_idx[j], pos = i - start;
         if (pos < len) atomicOr(&cm[pos >> 5], 1u << (pos & 31u));
+        if (!STEP && i < n) {
+            const float v = pos < len ? ws[pos] : w[i];
+            for (uint32_t q = q0; q < q1; ++q) static_cast<float*>(core_out.p[q])[j] = v;
+        }
     }
     // explorer positions of worker q into em[q & 1] (zeroed before): the first BLOCK entries from the index each
     // thread already holds (requested a turn ago with the tiles), the rest, if any, read here
     uint32_t epre = 0xFFFFFFFFu;
+    auto value_out = [&](uint32_t q, uint32_t j, uint32_t i) {
+        if (!STEP && i < n) static_cast<float*>(expl_out.p[q])[j] = i - start < len ? ws[i - start] : w[i];
+    };
     auto mark = [&](uint32_t q, uint32_t held, uint32_t from) {
         const uint32_t p0 = held - start;        // no entry: wraps beyond any tile
         if (p0 < len) atomicOr(&em[q & 1u][p0 >> 5], 1u << (p0 & 31u));
+        if (from) value_out(q, elo[q] + threadIdx.x, held);      // no entry: beyond any model
         const uint32_t* ei = static_cast<const uint32_t*>(expl_idx.p[q]);
         for (uint32_t j = elo[q] + from + threadIdx.x; j < ehi[q]; j += BLOCK) {
-            const uint32_t pos = ei[j] - start;
+            const uint32_t i = ei[j], pos = i - start;
             if (pos < len) atomicOr(&em[q & 1u][pos >> 5], 1u << (pos & 31u));
+            value_out(q, j, i);
         }
     };
     float rg[EPT], rl[EPT], rd[EPT];
@@ -2129,14 +2158,14 @@ __global__ __launch_bounds__(BLOCK) void k_pull_local_step(const float* __restri
 #pragma unroll
             for (int k = 0; k < 4; ++k) {
                 const uint32_t o = k * 1024 + threadIdx.x * 4;
-                const float4 b = ld4<1>(l + o);
+                const float4 b = ld4<NT>(l + o);
                 rl[4 * k + 0] = b.x; rl[4 * k + 1] = b.y; rl[4 * k + 2] = b.z; rl[4 * k + 3] = b.w;
                 if (STEP) {
-                    const float4 a = ld4<1>(g + o);
+                    const float4 a = ld4<NT>(g + o);
                     rg[4 * k + 0] = a.x; rg[4 * k + 1] = a.y; rg[4 * k + 2] = a.z; rg[4 * k + 3] = a.w;
                 }
                 if (STEP && !first) {
-                    const float4 c = ld4<1>(d + o);
+                    const float4 c = ld4<NT>(d + o);
                     rd[4 * k + 0] = c.x; rd[4 * k + 1] = c.y; rd[4 * k + 2] = c.z; rd[4 * k + 3] = c.w;
                 }
             }
@@ -2151,14 +2180,14 @@ __global__ __launch_bounds__(BLOCK) void k_pull_local_step(const float* __restri
         }
         // this thread's explorer index of the worker after: held, not used, until that worker's marks are made
         epre = 0xFFFFFFFFu;
-        if (q + 1 < nw) {
+        if (q + 1 < q1) {
             const uint32_t j = elo[q + 1] + threadIdx.x;
             if (j < ehi[q + 1]) epre = static_cast<const uint32_t*>(expl_idx.p[q + 1])[j];
         }
     };
-    mark(0, 0xFFFFFFFFu, 0u);
-    fetch(0);
-    for (uint32_t q = 0; q < nw; ++q) {
+    mark(q0, 0xFFFFFFFFu, 0u);
+    fetch(q0);
+    for (uint32_t q = q0; q < q1; ++q) {
         // the marks of worker q (made a turn ago) are complete; the other bitmap is free (its reader finished a turn ago)
         __syncthreads();
         if (threadIdx.x < TILE_WORDS) em[(q + 1u) & 1u][threadIdx.x] = 0;
@@ -2177,14 +2206,14 @@ __global__ __launch_bounds__(BLOCK) void k_pull_local_step(const float* __restri
         __syncthreads();                         // the other bitmap is zero everywhere before the next worker's marks go in
         // the next worker's marks and tiles, requested before this worker's stores: the wait for them need not cover the
         // stores' acknowledgements
-        if (q + 1 < nw) { mark(q + 1, epre, BLOCK); fetch(q + 1); }
+        if (q + 1 < q1) { mark(q + 1, epre, BLOCK); fetch(q + 1); }
         if (!patch) {
         } else if (vec) {
 #pragma unroll
             for (int k = 0; k < 4; ++k) {
                 const uint32_t o = k * 1024 + threadIdx.x * 4;
-                st4<1>(l + o, make_float4(nl[4 * k], nl[4 * k + 1], nl[4 * k + 2], nl[4 * k + 3]));
-                if (STEP) st4<1>(d + o, make_float4(nd[4 * k], nd[4 * k + 1], nd[4 * k + 2], nd[4 * k + 3]));
+                st4<NT>(l + o, make_float4(nl[4 * k], nl[4 * k + 1], nl[4 * k + 2], nl[4 * k + 3]));
+                if (STEP) st4<NT>(d + o, make_float4(nd[4 * k], nd[4 * k + 1], nd[4 * k + 2], nd[4 * k + 3]));
             }
         } else {
 #pragma unroll
@@ -2207,7 +2236,7 @@ __global__ __launch_bounds__(BLOCK) void k_pull_local_step(const float* __restri
 // whatever the order), the 512 codes leave as two stores of whole lines.
 // Bound by the vector unit while every value took a division of its own: 53 instructions a value, 149 us for 8 workers'
 // 110*10^6 values.  A bucket has one divisor: with its reciprocal, correctly rounded, a quotient takes a product and two
-// corrections of two fused steps each (see quant_quotient).  QUANTNOW
+// corrections of two fused steps each (see quant_quotient): 102 us, 5.4 TB/s.
 // grid (ceil(buckets / 4), n_workers).
 // ---------------------------------------------------------------------------------------
 constexpr uint32_t QB = 512;

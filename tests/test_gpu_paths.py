@@ -582,3 +582,46 @@ def test_quantisation_on_both_sides_of_the_range_of_the_common_reciprocal(expone
     finite = np.repeat(np.isfinite(scale_o), per)[:n]
     assert np.array_equal(code[0].cpu().numpy()[finite], code_o[finite])
     sd.close()
+
+
+@pytest.mark.parametrize("sizes", [[4096 * 3 + 5], [4096 * 256], [4096 + 7, 33, 9000], [4096 * 2, 5]])
+@pytest.mark.parametrize("W", [1, 3, 5])
+def test_worker_side_with_several_workers_to_a_block_and_few(sizes, W):
+    """Local step with extraction, a pull whose values leave with the overwrite (one worker has no local model), and the pull
+    with a local step, with one, some and all workers to a block."""
+    so, n = offsets(sizes), sum(sizes)
+    rng = np.random.default_rng(n + W)
+    ks = [s // 9 for s in sizes]
+    sd = binding.SlimDP(n, W, seg_off=so, seed=workloads.EXPLORE_SEED)
+    core, bits, off, epoch = sd.select_core(to_dev(np.abs(rng.standard_normal(n)).astype(np.float32)), ks)
+    for it, pct in enumerate((2, 40)):           # few explorers, and more than a block holds at a time
+        ms = [(s - k) * pct // 100 for s, k in zip(sizes, ks)]
+        idx, eoff = sd.sample_explore(bits, ks, it, ms, 0, W)
+        new = lambda: [rng.standard_normal(n).astype(np.float32) for _ in range(W)]
+        w_h, l_h, g_h, d_h = rng.standard_normal(n).astype(np.float32), new(), new(), new()
+        w, l, g, d = to_dev(w_h), [to_dev(x) for x in l_h], [to_dev(x) for x in g_h], [to_dev(x) for x in d_h]
+        sets = (core, off, idx, eoff)
+        cv, ev = sd.local_step_pack(l, g, d, 0.25, False, *sets, epoch)
+        c = u32(core)
+        for q in range(W):
+            l_h[q], d_h[q] = oracle.local_step(l_h[q], d_h[q], g_h[q], 0.25)
+            assert np.array_equal(u32(l[q]), l_h[q].view(np.uint32)) and np.array_equal(u32(d[q]), d_h[q].view(np.uint32))
+            assert np.array_equal(u32(cv[q]), d_h[q][c].view(np.uint32))
+            assert np.array_equal(u32(ev[q]), d_h[q][u32(idx[q])].view(np.uint32))
+        co, eo = sd.pull(w, epoch, *sets, w_local=[None if (q == 1) else l[q] for q in range(W)])
+        sd.synchronize()
+        for q in range(W):
+            e = u32(idx[q])
+            assert np.array_equal(u32(co[q]), w_h[c].view(np.uint32)) and np.array_equal(u32(eo[q]), w_h[e].view(np.uint32))
+            if q != 1:
+                l_h[q][c] = w_h[c]
+                l_h[q][e] = w_h[e]
+            assert np.array_equal(u32(l[q]), l_h[q].view(np.uint32)), q
+        sd.pull_local_step(w, epoch, *sets, l, g, d, 0.5, first=True)
+        sd.synchronize()
+        for q in range(W):
+            l_h[q][c] = w_h[c]
+            l_h[q][u32(idx[q])] = w_h[u32(idx[q])]
+            l_h[q], d_h[q] = oracle.local_step(l_h[q], None, g_h[q], 0.5)
+            assert np.array_equal(u32(l[q]), l_h[q].view(np.uint32)) and np.array_equal(u32(d[q]), d_h[q].view(np.uint32))
+    sd.close()
