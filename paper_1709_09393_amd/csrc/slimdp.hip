@@ -195,7 +195,6 @@ struct slimdp_ctx {
         const float* score = nullptr;
         const float* g[MAXW] = {};
         uint32_t W = 0;
-        int vec_ok = 0;
         uint64_t core_epoch = 0;                // 0: no selection on the captured score yet
         // explorer values kept beside it: slots a sub-tile and worker (0: none), for how many workers; void once another draw
         // has gone to the bitmap that tells which they are
@@ -928,7 +927,7 @@ static int score_impl(slimdp_ctx* ctx, const float* w, const float* const* g, ui
         ctx->cls_by_score = true;
         if (presample) { ctx->pre = ctx->hint; ctx->pre.pairs = pairs; }
         if (capture) {
-            ctx->spec.captured = true; ctx->spec.score = score; ctx->spec.W = W; ctx->spec.vec_ok = vec_ok; ctx->spec.core_epoch = 0;
+            ctx->spec.captured = true; ctx->spec.score = score; ctx->spec.W = W; ctx->spec.core_epoch = 0;
             for (uint32_t q = 0; q < W; ++q) ctx->spec.g[q] = g[q];
         }
         ctx->hint.valid = false;
@@ -942,7 +941,7 @@ static int score_impl(slimdp_ctx* ctx, const float* w, const float* const* g, ui
     const bool strided = ctx->n_seg == 1 && ctx->opt_strided && W <= 8;
 #define LAUNCH_SCORE_Q(WT, PRE, SPEC, DENSE, STRIDED)                                                                 \
     hipLaunchKernelGGL((k_score<WT, PRE, SPEC, DENSE, STRIDED>), grid, block, 0, ctx->stream, w, gt, (int)W, c, score, \
-                       ctx->d_tile_start, ctx->d_tile_seg, ctx->T, ctx->c_hist, vec_ok, pre, sa, w_new, lr)
+                       ctx->d_tile_start, ctx->d_tile_seg, ctx->T, ctx->c_hist, pre, sa, w_new, lr)
 #define LAUNCH_SCORE_P(WT, PRE, SPEC, DENSE)                                                                          \
     do {                                                                                                              \
         if constexpr ((WT) >= 1 && (WT) <= 8) {                                                                       \
@@ -980,7 +979,7 @@ static int score_impl(slimdp_ctx* ctx, const float* w, const float* const* g, ui
     SLIMDP_LAUNCHED(ctx, "k_score");
     if (presample) { ctx->pre = ctx->hint; ctx->pre.pairs = pairs; }
     if (capture) {
-        ctx->spec.captured = true; ctx->spec.score = score; ctx->spec.W = W; ctx->spec.vec_ok = vec_ok; ctx->spec.core_epoch = 0;
+        ctx->spec.captured = true; ctx->spec.score = score; ctx->spec.W = W; ctx->spec.core_epoch = 0;
         for (uint32_t q = 0; q < W; ++q) ctx->spec.g[q] = g[q];
     }
     ctx->hint.valid = false;
@@ -1054,7 +1053,7 @@ static int select_core_impl(slimdp_ctx* ctx, const float* score, const uint64_t*
         ctx->hist_clean = false;
         uint32_t P0 = persistent_blocks(ctx, 4, 1);
         if (S == 1) P0 = (uint32_t)std::min<uint64_t>((uint64_t)ctx->cus * 4, (ctx->n / 4 + BLOCK - 1) / BLOCK + 1);
-        hipLaunchKernelGGL(k_core_hist0, dim3(P0), dim3(BLOCK), 0, ctx->stream, score, a, (int)aligned16(score));
+        hipLaunchKernelGGL(k_core_hist0, dim3(P0), dim3(BLOCK), 0, ctx->stream, score, a);
         SLIMDP_LAUNCHED(ctx, "k_core_hist0");
     }
     // did the scoring pass that made this histogram already sort the whole tiles against a predicted bin?
@@ -1063,7 +1062,7 @@ static int select_core_impl(slimdp_ctx* ctx, const float* score, const uint64_t*
     ctx->hist_clean = false;
     const uint32_t P = persistent_blocks(ctx, (uint32_t)ctx->opt_build_blocks, 1);
     hipLaunchKernelGGL(k_core_build, dim3(P), dim3(BLOCK), 0, ctx->stream, score, a, ctx->c_used, (int)classified, (int)reuse,
-                       (int)aligned16(score), (int)(S == 1 && ctx->opt_strided), S > 1 ? core_bits : nullptr);
+                       (int)(S == 1 && ctx->opt_strided), S > 1 ? core_bits : nullptr);
     SLIMDP_LAUNCHED(ctx, "k_core_build");
     hipLaunchKernelGGL(k_core_hist2, dim3(a.groups), dim3(BLOCK), 0, ctx->stream, a);
     SLIMDP_LAUNCHED(ctx, "k_core_hist2");
@@ -1455,7 +1454,7 @@ int slimdp_pack(slimdp_ctx* ctx, uint32_t n_workers, const float* const* g, cons
             auto go = [&](auto kernel) {
                 hipLaunchKernelGGL(kernel, grid, dim3(BLOCK), 0, ctx->stream, (uint32_t)cb, (uint32_t)gb, make_tab<PtrTab>(g, n_workers), n_workers,
                                    ctx->n, ctx->d_tile_start, ctx->d_tile_seg, ctx->T, core_idx, core_off, (uint32_t)k, ctx->spec.bits,
-                                   ctx->spec.vals, ctx->spec.fail, ctx->spec.vec_ok, make_tab<MutPtrTab>(core_val, n_workers),
+                                   ctx->spec.vals, ctx->spec.fail, make_tab<MutPtrTab>(core_val, n_workers),
                                    make_tab<PtrTab>(expl_idx, n_workers), mt, make_tab<MutPtrTab>(expl_val, n_workers));
             };
             if (ctx->n_seg == 1) go(k_pack_spec<1>); else go(k_pack_spec<0>);
@@ -1478,16 +1477,16 @@ int slimdp_pack(slimdp_ctx* ctx, uint32_t n_workers, const float* const* g, cons
     }
     rc = wait_for_lists(ctx, n_workers, expl_idx, expl_off, m_w);
     if (rc) return rc;
-    int vec_ok = 1;
-    for (uint32_t q = 0; q < n_workers; ++q) vec_ok = vec_ok && aligned16(g[q]);
     if (ctx->opt_pack_kernel == 1) {
         hipLaunchKernelGGL(k_pack_stream_ws, dim3(8 * ((ctx->T + 7) / 8)), dim3(2 * BLOCK), 0, ctx->stream,
                            make_tab<PtrTab>(g, n_workers), n_workers, ctx->T, ctx->d_tile_start, core_idx, core_off,
                            make_tab<PtrTab>(expl_idx, n_workers), make_tab<PtrTab>(expl_off, n_workers),
-                           make_tab<MutPtrTab>(core_val, n_workers), make_tab<MutPtrTab>(expl_val, n_workers), vec_ok);
+                           make_tab<MutPtrTab>(core_val, n_workers), make_tab<MutPtrTab>(expl_val, n_workers));
         SLIMDP_LAUNCHED(ctx, "k_pack_stream_ws");
         return SLIMDP_OK;
     }
+    int vec_ok = 1;
+    for (uint32_t q = 0; q < n_workers; ++q) vec_ok = vec_ok && aligned16(g[q]);
     if (ctx->opt_pack_nbuf == 2)
         hipLaunchKernelGGL(k_pack_stream<2>, dim3(ctx->T), dim3(BLOCK), 0, ctx->stream, make_tab<PtrTab>(g, n_workers),
                            n_workers, ctx->d_tile_start, core_idx, core_off, make_tab<PtrTab>(expl_idx, n_workers),
@@ -1528,11 +1527,13 @@ int slimdp_merge(slimdp_ctx* ctx, float* w, float lr, uint64_t core_epoch, uint3
     for (uint32_t q = 0; q < n_workers; ++q) per_tile += (double)m_w[q] * TILE / (double)ctx->n;
     const double room = per_tile + 6.0 * std::sqrt(per_tile);
     const bool few_tiles = ctx->T <= 8u * (uint32_t)ctx->cus;
-#define LAUNCH_MERGE(R)                                                                                                        \
-    hipLaunchKernelGGL(k_merge<R>, dim3(ctx->T), dim3(BLOCK), 0, ctx->stream, w, lr, n_workers, ctx->d_tile_start, core_idx,  \
-                       core_off, make_tab<PtrTab>(core_val, n_workers), make_tab<PtrTab>(expl_idx, n_workers),                \
-                       make_tab<PtrTab>(expl_off, n_workers), make_tab<PtrTab>(expl_val, n_workers), (int)aligned16(w),       \
-                       ctx->n, ctx->n_seg)
+    auto launch = [&](auto kernel) {
+        hipLaunchKernelGGL(kernel, dim3(ctx->T), dim3(BLOCK), 0, ctx->stream, w, lr, n_workers, ctx->d_tile_start, core_idx, core_off,
+                           make_tab<PtrTab>(core_val, n_workers), make_tab<PtrTab>(expl_idx, n_workers),
+                           make_tab<PtrTab>(expl_off, n_workers), make_tab<PtrTab>(expl_val, n_workers), ctx->n, ctx->n_seg);
+    };
+    const bool lines = ctx->n_seg == 1 && aligned16(w);
+#define LAUNCH_MERGE(R) do { if (lines) launch(k_merge<R, 1>); else launch(k_merge<R, 0>); } while (0)
     if (room <= 4.0 * BLOCK) LAUNCH_MERGE(4);
     else if ((few_tiles ? room : per_tile) <= 8.0 * BLOCK) LAUNCH_MERGE(8);
     else if (few_tiles && room <= 16.0 * BLOCK) LAUNCH_MERGE(16);

@@ -110,12 +110,12 @@ __device__ __forceinline__ BinPick pick_bin(const uint32_t* __restrict__ hp, uin
 // ---------------------------------------------------------------------------------------
 // The 1024 scores of sub-tile `wid` of a tile as keys: lane L holds parameters 4L..4L+3 of each round of 256.
 __device__ __forceinline__ void core_load_keys(const float* __restrict__ S, uint32_t start, uint32_t len, uint32_t wid,
-                                               uint32_t lane, int vec_ok, uint32_t key[4][4])
+                                               uint32_t lane, uint32_t key[4][4])
 {
     const uint32_t off = wid * SUB;
     const uint32_t sub_len = (len > off) ? ((len - off < SUB) ? len - off : SUB) : 0u;
     const float* src = S + (size_t)start + off;
-    if (vec_ok && sub_len == SUB && (start & 3u) == 0) {
+    if (sub_len == SUB) {
 #pragma unroll
         for (int it = 0; it < 4; ++it) {
             const uint4 v = ld4u<NT_BUILD>(reinterpret_cast<const uint32_t*>(src + it * 256 + lane * 4));
@@ -181,14 +181,14 @@ __device__ __forceinline__ void core_classify(const uint32_t key[4][4], uint32_t
 
 // Level-0 histogram of a score array that did not come from a scoring pass (any bit pattern).  Flat model: the array
 // in one run of 16-byte loads; otherwise contiguous tile ranges.  grid: any (segmented: at most T blocks).
-__global__ __launch_bounds__(BLOCK) void k_core_hist0(const float* __restrict__ S, CoreArgs a, int vec_ok)
+__global__ __launch_bounds__(BLOCK) void k_core_hist0(const float* __restrict__ S, CoreArgs a)
 {
     __shared__ uint32_t h[CORE_NB0];
     for (uint32_t b = threadIdx.x; b < CORE_NB0; b += BLOCK) h[b] = 0;
     __syncthreads();
     const uint32_t* keys = reinterpret_cast<const uint32_t*>(S);
     if (a.n_seg == 1) {
-        const uint64_t n4 = vec_ok ? a.n / 4 : 0, stride = (uint64_t)gridDim.x * BLOCK;
+        const uint64_t n4 = a.n / 4, stride = (uint64_t)gridDim.x * BLOCK;
         for (uint64_t x = (uint64_t)blockIdx.x * BLOCK + threadIdx.x; x < n4; x += stride) {
             const uint4 v = ld4u<0>(keys + 4 * x);
             atomicAdd(&h[v.x >> CORE_SHIFT0], 1u); atomicAdd(&h[v.y >> CORE_SHIFT0], 1u);
@@ -227,7 +227,7 @@ __global__ __launch_bounds__(PLAN_CHUNK) void k_core_plan(CorePlan* __restrict__
 // zero_bits: public bitmap of a model whose tiles may start inside a word: the words that two tiles share are
 // cleared here and filled with atomics by k_core_emit.
 __global__ __launch_bounds__(BLOCK) void k_core_build(const float* __restrict__ S, CoreArgs a, const uint32_t* __restrict__ used,
-                                                      int check, int half, int vec_ok, int strided, uint32_t* __restrict__ zero_bits)
+                                                      int check, int half, int strided, uint32_t* __restrict__ zero_bits)
 {
     __shared__ uint32_t h[CORE_NB1];
     __shared__ uint32_t wtot[4], sh[4];
@@ -278,8 +278,8 @@ __global__ __launch_bounds__(BLOCK) void k_core_build(const float* __restrict__ 
             const TileRef A = tile_ref(tt, a.n_seg, a.n, a.tile_start, a.tile_seg);
             const TileRef B = two ? tile_ref(tB, a.n_seg, a.n, a.tile_start, a.tile_seg) : TileRef{0u, 0u, 0u};
             uint32_t keyA[4][4], keyB[4][4];
-            core_load_keys(S, A.start, A.len, wid, lane, vec_ok, keyA);
-            if (two) core_load_keys(S, B.start, B.len, wid, lane, vec_ok, keyB);
+            core_load_keys(S, A.start, A.len, wid, lane, keyA);
+            if (two) core_load_keys(S, B.start, B.len, wid, lane, keyB);
             core_classify(keyA, tt, A.start, A.len, wid, lane, p.bin, h, a);
             if (two) core_classify(keyB, tB, B.start, B.len, wid, lane, p.bin, h, a);
         }

@@ -206,31 +206,29 @@ __device__ __forceinline__ uint32_t mask_below(uint32_t bit) { return (1u << bit
 
 // Accesses to data that is touched once (streamed): NT != 0 marks them non-temporal, so that they do not
 // push lines that will be used again out of the caches.  A non-temporal store must cover whole 128-byte lines
-// per instruction (a partial one goes to memory as a read-modify-write).
-typedef float f32x4_t __attribute__((ext_vector_type(4)));
-typedef uint32_t u32x4_t __attribute__((ext_vector_type(4)));
+// per instruction (a partial one goes to memory as a read-modify-write).  Sixteen bytes from any address that a float
+// may have: the hardware asks for no more than that of them, and the types say so to the compiler.
+typedef float f32x4_t __attribute__((ext_vector_type(4), aligned(4)));
+typedef uint32_t u32x4_t __attribute__((ext_vector_type(4), aligned(4)));
 template <int NT> __device__ __forceinline__ float4 ld4(const float* p)
 {
-    if (NT) {
-        const f32x4_t v = __builtin_nontemporal_load(reinterpret_cast<const f32x4_t*>(p));
-        return make_float4(v.x, v.y, v.z, v.w);
-    }
-    return *reinterpret_cast<const float4*>(p);
+    f32x4_t v;
+    if (NT) v = __builtin_nontemporal_load(reinterpret_cast<const f32x4_t*>(p));
+    else v = *reinterpret_cast<const f32x4_t*>(p);
+    return make_float4(v.x, v.y, v.z, v.w);
 }
 template <int NT> __device__ __forceinline__ uint4 ld4u(const uint32_t* p)
 {
-    if (NT) {
-        const u32x4_t v = __builtin_nontemporal_load(reinterpret_cast<const u32x4_t*>(p));
-        return make_uint4(v.x, v.y, v.z, v.w);
-    }
-    return *reinterpret_cast<const uint4*>(p);
+    u32x4_t v;
+    if (NT) v = __builtin_nontemporal_load(reinterpret_cast<const u32x4_t*>(p));
+    else v = *reinterpret_cast<const u32x4_t*>(p);
+    return make_uint4(v.x, v.y, v.z, v.w);
 }
 template <int NT> __device__ __forceinline__ void st4(float* p, float4 v)
 {
-    if (NT) {
-        f32x4_t o; o.x = v.x; o.y = v.y; o.z = v.z; o.w = v.w;
-        __builtin_nontemporal_store(o, reinterpret_cast<f32x4_t*>(p));
-    } else *reinterpret_cast<float4*>(p) = v;
+    f32x4_t o; o.x = v.x; o.y = v.y; o.z = v.z; o.w = v.w;
+    if (NT) __builtin_nontemporal_store(o, reinterpret_cast<f32x4_t*>(p));
+    else *reinterpret_cast<f32x4_t*>(p) = o;
 }
 template <int NT, class Tp> __device__ __forceinline__ Tp ld1(const Tp* p)
 {

@@ -303,7 +303,7 @@ template <int WT, int PRE, int SPEC, int DENSE, int STRIDED>
 __global__ __launch_bounds__(BLOCK, SCORE_MINB) void k_score(const float* __restrict__ w, PtrTab g, int Wrt, float c,
                                                  float* __restrict__ S, const uint32_t* __restrict__ tile_start,
                                                  const uint32_t* __restrict__ tile_seg, uint32_t T,
-                                                 uint32_t* __restrict__ hist, int vec_ok, PreArgs pre, SpecArgs spec,
+                                                 uint32_t* __restrict__ hist, PreArgs pre, SpecArgs spec,
                                                  float* __restrict__ w_new, float lr)
 {
     static_assert(!SPEC || WT != 0, "capture needs the update values in registers");
@@ -343,7 +343,9 @@ __global__ __launch_bounds__(BLOCK, SCORE_MINB) void k_score(const float* __rest
             const SegState* st = &pre.states[seg];
             pre_bound = st->bound_m1; pre_sure = st->sure_m1; pre_has_sure = st->has_gt; pre_skip = st->need0 == 0;
         }
-        const bool vec = vec_ok && len == TILE && (start & 3u) == 0;
+        // Sixteen bytes at a time wherever a tile begins: three of four segments do not begin on a multiple of four, and by single
+        // floats, uncaptured besides, they kept an iteration of 7*10^6 parameters in 57 segments at 216 us (195 now).
+        const bool vec = len == TILE;
         uint32_t spec_lo = 0xFFFFFFFFu, spec_run = 0;
         if (SPEC) spec_lo = spec.lo[seg];
         if (!vec) {
@@ -1208,7 +1210,7 @@ __device__ __forceinline__ void pack_core_spec(uint32_t block, const PtrTab& g, 
                                                const uint32_t* __restrict__ core_off,
                                                const uint2* __restrict__ spec_bits,
                                                const float* __restrict__ spec_vals,
-                                               const uint32_t* __restrict__ spec_fail, int vec_ok, const MutPtrTab& core_val)
+                                               const uint32_t* __restrict__ spec_fail, const MutPtrTab& core_val)
 {
     __shared__ uint32_t wd[4][TILE_WORDS], pre[4][TILE_WORDS];
     const uint32_t wid = threadIdx.x >> 6, t = block * 4 + wid, lane = lane_id();
@@ -1216,7 +1218,7 @@ __device__ __forceinline__ void pack_core_spec(uint32_t block, const PtrTab& g, 
     const uint32_t start = tile_start[t], len = tile_start[t + 1] - start;
     const uint32_t j0 = core_off[t], j1 = core_off[t + 1];
     if (j0 >= j1) return;
-    const bool captured = vec_ok && len == TILE && (start & 3u) == 0 && spec_fail[tile_seg[t]] == 0;
+    const bool captured = len == TILE && spec_fail[tile_seg[t]] == 0;
     if (captured) {
         // entry number of every captured parameter inside its sub-tile: lanes 4r..4r+3 hold the eight bitmap
         // words of round r (16 rounds a tile, 4 a sub-tile); a round's entries start on a multiple of A
@@ -1298,10 +1300,10 @@ __device__ __forceinline__ void pack_core_flat(uint32_t block, uint32_t blocks, 
                                                const uint32_t* __restrict__ core_idx, uint32_t k,
                                                const uint2* __restrict__ spec_bits,
                                                const float* __restrict__ spec_vals,
-                                               const uint32_t* __restrict__ spec_fail, int vec_ok, const MutPtrTab& core_val)
+                                               const uint32_t* __restrict__ spec_fail, const MutPtrTab& core_val)
 {
     constexpr int U = 4;
-    const bool ok = vec_ok && spec_fail[0] == 0;
+    const bool ok = spec_fail[0] == 0;
     const uint32_t stride = blocks * 256u;
     for (uint32_t jb = block * 256u + threadIdx.x; jb < k; jb += U * stride) {
         uint32_t i[U];
@@ -1394,12 +1396,12 @@ __global__ __launch_bounds__(BLOCK) void k_pack_spec(uint32_t core_blocks, uint3
                                                      const uint32_t* __restrict__ tile_start, const uint32_t* __restrict__ tile_seg, uint32_t T,
                                                      const uint32_t* __restrict__ core_idx, const uint32_t* __restrict__ core_off, uint32_t k,
                                                      const uint2* __restrict__ spec_bits, const float* __restrict__ spec_vals,
-                                                     const uint32_t* __restrict__ spec_fail, int vec_ok, MutPtrTab core_val,
+                                                     const uint32_t* __restrict__ spec_fail, MutPtrTab core_val,
                                                      PtrTab expl_idx, CountTab m_w, MutPtrTab expl_val)
 {
     if (blockIdx.x < core_blocks) {
-        if (FLAT) pack_core_flat(blockIdx.x, core_blocks, g, nw, n, (uint32_t)(n / TILE), core_idx, k, spec_bits, spec_vals, spec_fail, vec_ok, core_val);
-        else pack_core_spec(blockIdx.x, g, nw, n, tile_start, tile_seg, T, core_idx, core_off, spec_bits, spec_vals, spec_fail, vec_ok, core_val);
+        if (FLAT) pack_core_flat(blockIdx.x, core_blocks, g, nw, n, (uint32_t)(n / TILE), core_idx, k, spec_bits, spec_vals, spec_fail, core_val);
+        else pack_core_spec(blockIdx.x, g, nw, n, tile_start, tile_seg, T, core_idx, core_off, spec_bits, spec_vals, spec_fail, core_val);
     } else {
         const uint32_t x = blockIdx.x - core_blocks;
         pack_expl_gather(x % expl_blocks, expl_blocks, x / expl_blocks, g, n, expl_idx, m_w, expl_val);
@@ -1593,7 +1595,7 @@ __global__ __launch_bounds__(2 * BLOCK) void k_pack_stream_ws(PtrTab g, uint32_t
                                                                const uint32_t* __restrict__ tile_start,
                                                                const uint32_t* __restrict__ core_idx,
                                                                const uint32_t* __restrict__ core_off, PtrTab expl_idx,
-                                                               PtrTab expl_off, MutPtrTab core_val, MutPtrTab expl_val, int vec_ok)
+                                                               PtrTab expl_off, MutPtrTab core_val, MutPtrTab expl_val)
 {
     __shared__ float buf[2][TILE];
     __shared__ uint16_t cpos[TILE];          // the tile's core positions: the same for every worker
@@ -1603,7 +1605,7 @@ __global__ __launch_bounds__(2 * BLOCK) void k_pack_stream_ws(PtrTab g, uint32_t
     const uint32_t t = (blockIdx.x & 7u) * chunk + (blockIdx.x >> 3);
     if (t >= T) return;                      // uniform over the block
     const uint32_t start = tile_start[t], len = tile_start[t + 1] - start;
-    const bool vec = vec_ok && len == TILE && (start & 3u) == 0;
+    const bool vec = len == TILE;
     const uint32_t c0 = core_off[t], c1 = core_off[t + 1];
     const uint32_t ccnt = (c1 - c0 < TILE) ? c1 - c0 : TILE;
     const bool loader = threadIdx.x < BLOCK;
@@ -1717,12 +1719,14 @@ __device__ __forceinline__ float core_sum(const PtrTab& core_val, uint32_t nw, u
 // generic path, which stages its entries through LDS 256 at a time.
 constexpr uint32_t MERGE_STAGE = 256;
 
-template <int R>
+// LINES: a flat model at an aligned address, whose tiles are whole lines and leave non-temporally; a choice at run time kept
+// two forms of the stores apart and cost the kernel a third (138*10^6 parameters, 8 workers).
+template <int R, int LINES>
 __global__ __launch_bounds__(BLOCK) void k_merge(float* __restrict__ w, float lr, uint32_t nw,
                                                  const uint32_t* __restrict__ tile_start,
                                                  const uint32_t* __restrict__ core_idx, const uint32_t* __restrict__ core_off,
                                                  PtrTab core_val, PtrTab expl_idx, PtrTab expl_off, PtrTab expl_val,
-                                                 int vec_ok, uint64_t n, uint32_t n_seg)
+                                                 uint64_t n, uint32_t n_seg)
 {
     __shared__ float acc[TILE];
     __shared__ uint32_t cnt[TILE / 4];     // one byte per position: bit 7 = core, low bits = explorer entries
@@ -1740,7 +1744,7 @@ __global__ __launch_bounds__(BLOCK) void k_merge(float* __restrict__ w, float lr
     } else {
         start = tile_start[t]; len = tile_start[t + 1] - start;
     }
-    const bool vec = vec_ok && len == TILE && (start & 3u) == 0;
+    const bool vec = len == TILE;
     const uint32_t c0 = core_off[t], c1 = core_off[t + 1];
     float wv[EPT];
     if (vec) {
@@ -1888,7 +1892,7 @@ __global__ __launch_bounds__(BLOCK) void k_merge(float* __restrict__ w, float lr
     if (vec) {
 #pragma unroll
         for (int r = 0; r < 4; ++r)
-            st4<NT_MERGE_ST>(w + (size_t)start + r * 1024 + threadIdx.x * 4,
+            st4<LINES && NT_MERGE_ST>(w + (size_t)start + r * 1024 + threadIdx.x * 4,
                              make_float4(wv[4 * r], wv[4 * r + 1], wv[4 * r + 2], wv[4 * r + 3]));
     }
 }
