@@ -109,7 +109,7 @@ int slimdp_synchronize(slimdp_ctx* ctx);
  *   "speculative_pack" (0/1, default 0): slimdp_score additionally keeps the update values of
  *       every parameter whose significance reaches the threshold of the previous
  *       slimdp_select_core less a small margin, up to a quarter of every 1024 parameters (own device
- *       allocation of about W*n bytes, made by this call: slimdp_capture_bytes); if the following slimdp_select_core(..REUSE_HISTOGRAM) finds its
+ *       allocation of about 1.2*W*n bytes, made by this call: slimdp_capture_bytes); if the following slimdp_select_core(..REUSE_HISTOGRAM) finds its
  *       threshold at or above that bound, the next slimdp_pack takes the core values from
  *       there instead of scanning the update vectors again, PROVIDED that call carries the
  *       flag SLIMDP_PACK_UPDATES_AS_SCORED (see slimdp_pack); without the flag a pack always
@@ -123,7 +123,7 @@ int slimdp_synchronize(slimdp_ctx* ctx);
  *   "expected_core" (-1 = unknown, default; else k of the next slimdp_select_core, flat model).
  *   "explore_hint_mode" (0/1, default 0): where an announced explorer draw runs: 0 inside
  *       the next slimdp_score, 1 at once on a side stream of the library (default priority),
- *       beside whatever runs on the context's stream.
+ *       beside whatever runs on the context's stream (few tiles: not ahead at all, the request draws).
  *   "explore_async" (0/1, default 0): slimdp_sample_explore runs on the library's side stream, beside whatever is
  *       enqueued on the context's stream AFTER the call (its many small kernels are bound by latency, not by memory).
  *       It starts once everything enqueued before the call is done.  slimdp_pack, slimdp_merge and slimdp_pull wait
@@ -133,7 +133,12 @@ int slimdp_synchronize(slimdp_ctx* ctx);
  *       touch the lists before one of those calls.  A pack that takes kept values
  *       (SLIMDP_PACK_UPDATES_AS_SCORED) extracts the core values meanwhile.  With cached core keys the request for
  *       iteration t+1 can be issued before the pack of iteration t (other output arrays) and then runs beside pack
- *       and merge.
+ *       and merge.  Requests of few tiles run on the context's stream all the same: the way to another stream and back
+ *       would take longer than they do.
+ *   "explore_keep" (0/1/2, default 1): with "speculative_pack", a flat model and a draw announced for at least the W workers
+ *       scored, slimdp_score also keeps the update values of most of the coming explorers, and a slimdp_pack with
+ *       SLIMDP_PACK_UPDATES_AS_SCORED looks its explorer values up there instead of gathering them.  1: where the updates
+ *       exceed 256 MB and W is at least 2; 2: always; 0: never.  Results do not depend on it.
  *   "side_blocks" (1..8): blocks per compute unit of a side-stream draw.
  *   "pull_kernel" (0/1, default 1): how slimdp_pull patches local models (1: a pass that streams them; 0: scattered
  *       writes); results do not depend on it.

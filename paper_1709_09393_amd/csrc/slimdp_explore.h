@@ -2,8 +2,8 @@
 // (Philox word, index).  Included only by slimdp.hip, after slimdp_kernels.h.
 //
 // The draw (explore_subtile*, in the scoring pass or k_explore_keys) has sorted every word into a sure zone (bitmap) and
-// a candidate zone of about twice the zone's slack, without looking at the core.  What remains takes four launches:
-//   k_explore_init      state per (worker, segment), list counters and rerun flag cleared
+// a candidate zone of about twice the zone's slack, without looking at the core.  What remains takes three launches (and
+// k_explore_init, the zones of every segment, where the sizes are not those of the request before):
 //   k_explore_collect   per tile the sure parameters outside the core; the candidates outside the core go to the
 //                       list of their (worker, segment)
 //   k_explore_select    one block per (worker, segment): the demand left by the sure ones, a radix descent over the
