@@ -111,6 +111,7 @@ struct slimdp_ctx {
     hipEvent_t ev_consumed = nullptr;      // main stream: everything enqueued before a side-stream draw (readers of its buffers)
     hipEvent_t ev_drawn = nullptr;         // side stream: the announced draw is complete
     bool side_pending = false;             // a side draw was launched and the main stream has not waited for it yet
+    bool draw_fresh = false;               // ... and no call that takes lists has been enqueued since
     // asynchronous slimdp_sample_explore requests (option "explore_async") that the main stream has not waited for yet:
     // their completion events on the side stream and the address ranges they write
     static constexpr int N_PENDING = 4;
@@ -425,10 +426,17 @@ bool device_state_known(slimdp_ctx* c)
 // slower.  Measured whole iterations, own stream / side stream, us, by tiles times workers:
 //   to be drawn first   10^6 parameters, 4 workers (980) 46 / 91; 2*10^6, 8 (3,900) 69 / 118; 7*10^6 in 57 segments, 4 (7,000) 119 / 134;
 //                       10^7 in 57 segments, 4 (9,900) 157 / 146; 8*10^6, 8 (15,600) 158 / 143; 138*10^6, 8 1,820 / 1,480
-//   drawn already       8*10^6, 8 (15,600) 207 / 226; 16*10^6, 8 (31,000) 330 / 335; 64*10^6, 4 (62,500) 658 / 644; 138*10^6, 8 2,150 / 2,115;
+//   drawn by the scoring pass of a reselecting iteration
+//                       8*10^6, 8 (15,600) 207 / 226; 16*10^6, 8 (31,000) 330 / 335; 64*10^6, 4 (62,500) 658 / 644; 138*10^6, 8 2,150 / 2,115;
 //                       but 138*10^6, 2 (67,500) 1,016 / 1,133: one or two workers' pack is too short to hide it
+// The lines of "drawn" are also right for a draw that the side stream has made beside a pack and a merge since.  A request that
+// follows its announcement at once stays behind the draw on the side stream, for the next calls to run beside both: on its own
+// stream the context would wait for the draw, and pack and merge for the request's chain.  Cached core keys, request one iteration
+// ahead, own / side: 8*10^6, 8 176 / 128; 10^7 in 57 segments, 4 186 / 135; 64*10^6, 2 385 / 300; 138*10^6, 1 561 / 464; 2 742 / 593.
+// Announced before pack and merge, requested after them: 8*10^6, 8 137 / 150; 64*10^6, 2 327 / 341; 138*10^6, 1 505 / 520; 2 642 / 656.
 bool stays_on_main(const slimdp_ctx* c, uint32_t n_workers, bool drawn)
 {
+    if (c->side_pending && c->draw_fresh) return false;
     const uint64_t work = (uint64_t)c->T * n_workers;
     return drawn ? work <= 32000 || n_workers <= 2 : work <= 8500;
 }
@@ -459,6 +467,7 @@ int wait_for_lists(slimdp_ctx* c, uint32_t nw, const uint32_t* const* expl_idx, 
                    const uint64_t* m_w)
 {
     int hit = -1;
+    c->draw_fresh = false;
     for (int j = 0; j < slimdp_ctx::N_PENDING; ++j) {
         const slimdp_ctx::PendingExplore& p = c->pend[j];
         if (!p.live) continue;
@@ -1366,7 +1375,7 @@ int slimdp_explore_hint(slimdp_ctx* ctx, const uint64_t* k_seg, uint32_t worker0
 #undef LAUNCH_SIDE_DRAW
     SLIMDP_LAUNCHED(ctx, "k_explore_keys(side stream)");
     SLIMDP_HIP(ctx, hipEventRecord(ctx->ev_drawn, ctx->side));
-    ctx->side_pending = true;
+    ctx->side_pending = ctx->draw_fresh = true;
     ctx->pre = ctx->hint;
     ctx->pre.valid = true;
     ctx->pre.pairs = short_list;

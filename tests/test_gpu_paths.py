@@ -411,6 +411,38 @@ def test_requests_of_changing_sizes_follow_each_other(n, W, segments):
     sd.close()
 
 
+@pytest.mark.parametrize("n,W", [(64_000_003, 1), (64_000_003, 2), (16_000_001, 8)])
+def test_request_behind_a_draw_on_the_side_stream_leaves_the_own_stream_free(n, W):
+    """Cached core keys, the draw announced on the side stream and "explore_async" on: neither the draw nor the request's chain
+    stands in the context's own stream, whatever the number of workers and tiles.  What stands in it is timed on the device
+    (two events around announcement and request, behind a fill that hides the host's part) and compared with the same calls
+    without "explore_async", for which the stream waits; the lists are the same."""
+    k, m = len(range(5, n, 32)), n // 50
+    sd = binding.SlimDP(n, W, seed=workloads.EXPLORE_SEED)
+    sd.set_option("explore_hint_mode", 1)
+    bits = torch.full(((n + 31) // 32,), 1 << 5, dtype=torch.int32, device=dev())     # every thirty-second parameter is in the core
+    blocker = torch.empty(1 << 28, dtype=torch.float32, device=dev())
+    a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+    idx, off, took = {}, {}, {0: [], 1: []}
+    for turn in range(8):
+        for asyn in (0, 1):
+            sd.set_option("explore_async", asyn)
+            torch.cuda.synchronize()
+            blocker.zero_()
+            a.record()
+            sd.explore_hint([k], turn, [m], 0, W)
+            idx[asyn], off[asyn] = sd.sample_explore(bits, [k], turn, [m], 0, W, expl_idx=idx.get(asyn), expl_off=off.get(asyn))
+            b.record()
+            sd.synchronize()
+            torch.cuda.synchronize()
+            took[asyn].append(a.elapsed_time(b) * 1e3)
+        for q in range(W):
+            assert torch.equal(idx[0][q], idx[1][q]) and torch.equal(off[0][q], off[1][q]), (turn, q)
+    sd.close()
+    waits, free = min(took[0][2:]), min(took[1][2:])
+    assert free < 0.5 * waits, "own stream held for %.0f us, %.0f without the option" % (free, waits)
+
+
 def test_recorded_request_replays_beside_eager_ones():
     """A replay finds counters, zones and the rerun flag as it needs them, whatever eager requests (other sizes, a missed draw)
     ran since it was recorded, and so do eager requests after a replay."""
