@@ -123,8 +123,8 @@ int slimdp_synchronize(slimdp_ctx* ctx);
  *   "expected_core" (-1 = unknown, default; else k of the next slimdp_select_core, flat model).
  *   "explore_hint_mode" (0/1, default 0): where an announced explorer draw runs: 0 inside
  *       the next slimdp_score, 1 at once on a side stream of the library (default priority),
- *       beside whatever runs on the context's stream (few tiles: not ahead at all, the request draws).
- *   "explore_async" (0/1, default 0): slimdp_sample_explore runs on the library's side stream, beside whatever is
+ *       beside whatever runs on the context's stream (few tiles: not ahead at all, the request draws; see "explore_async").
+ *   "explore_async" (0/1/2, default 0): slimdp_sample_explore runs on the library's side stream, beside whatever is
  *       enqueued on the context's stream AFTER the call (its many small kernels are bound by latency, not by memory).
  *       It starts once everything enqueued before the call is done.  slimdp_pack, slimdp_merge and slimdp_pull wait
  *       for the requests that write the lists they are given (and do not wait for requests into other arrays);
@@ -136,7 +136,7 @@ int slimdp_synchronize(slimdp_ctx* ctx);
  *       and merge.  Requests whose way to another stream and back would take longer than it hides run on the context's
  *       stream all the same: those of few tiles; where their draw has been made beside other calls also larger ones, and
  *       any of one or two workers.  A request that follows its slimdp_explore_hint ("explore_hint_mode" = 1) at once stays
- *       behind the draw on the side stream.
+ *       behind the draw on the side stream.  2 is a test switch: every request and every announced draw on the side stream.
  *   "explore_keep" (0/1/2, default 1): with "speculative_pack", a flat model and a draw announced for at least the W workers
  *       scored, slimdp_score also keeps the update values of most of the coming explorers, and a slimdp_pack with
  *       SLIMDP_PACK_UPDATES_AS_SCORED looks its explorer values up there instead of gathering them.  1: where the updates

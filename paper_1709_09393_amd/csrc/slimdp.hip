@@ -124,7 +124,7 @@ struct slimdp_ctx {
         uint64_t idx_bytes = 0, off_bytes = 0;
     } pend[N_PENDING];
     uint64_t pend_seq = 0;
-    int64_t opt_explore_async = 0;
+    int64_t opt_explore_async = 0;         // 1: requests on the side stream where that pays (stays_on_main), 2: test, all of them
     int device = 0, cus = 256;
     std::vector<uint64_t> seg_off;
     Tiling tl;
@@ -436,7 +436,7 @@ bool device_state_known(slimdp_ctx* c)
 // Announced before pack and merge, requested after them: 8*10^6, 8 137 / 150; 64*10^6, 2 327 / 341; 138*10^6, 1 505 / 520; 2 642 / 656.
 bool stays_on_main(const slimdp_ctx* c, uint32_t n_workers, bool drawn)
 {
-    if (c->side_pending && c->draw_fresh) return false;
+    if (c->opt_explore_async == 2 || (c->side_pending && c->draw_fresh)) return false;
     const uint64_t work = (uint64_t)c->T * n_workers;
     return drawn ? work <= 32000 || n_workers <= 2 : work <= 8500;
 }
@@ -743,7 +743,7 @@ int slimdp_set_option(slimdp_ctx* ctx, const char* name, int64_t value)
     if (strcmp(name, "explore_per_tile_tail") == 0) { ctx->opt_per_tile_tail = value; return SLIMDP_OK; }
     if (strcmp(name, "strided_tiles") == 0 && (value == 0 || value == 1)) { ctx->opt_strided = value; return SLIMDP_OK; }
     if (strcmp(name, "side_blocks") == 0 && value >= 1 && value <= 8) { ctx->opt_side_blocks = value; return SLIMDP_OK; }
-    if (strcmp(name, "explore_async") == 0 && (value == 0 || value == 1)) { ctx->opt_explore_async = value; return SLIMDP_OK; }
+    if (strcmp(name, "explore_async") == 0 && value >= 0 && value <= 2) { ctx->opt_explore_async = value; return SLIMDP_OK; }
     if (strcmp(name, "explore_hint_mode") == 0 && (value == 0 || value == 1)) { ctx->opt_hint_mode = value; return SLIMDP_OK; }
     if (strcmp(name, "core_predict") == 0 && value >= 0 && value <= 2) { ctx->opt_core_predict = value; return SLIMDP_OK; }
     if (strcmp(name, "pack_core_blocks") == 0 && value >= 0 && value <= 64) { ctx->opt_pack_core_blocks = value; return SLIMDP_OK; }

@@ -58,7 +58,10 @@ def run_iteration(wl, iteration=0, w_h=None, sd=None, force_fallback=False, chec
     sd.set_option("explore_hint_mode", hint_mode)
     sd.set_option("explore_async", explore_async)
     if hint:        # the explorer zones are drawn ahead: on the library's side stream (1) or inside the scoring kernel (0)
+        if hint_mode == 1 and explore_async == 0:
+            sd.set_option("explore_async", 2)       # whatever the number of tiles; the request itself on the own stream
         sd.explore_hint(ks, iteration, ms, 0, wl.W)
+        sd.set_option("explore_async", explore_async)
     S = sd.score(w, g, wl.c)
     core_idx, core_bits, core_off, epoch = sd.select_core(S, ks, reuse_histogram=True)
     expl_idx, expl_off = sd.sample_explore(core_bits, ks, iteration, ms, 0, wl.W)
@@ -494,32 +497,34 @@ def test_selection_with_the_scoring_pass_classifying_against_a_predicted_bin(mod
 
 @pytest.mark.parametrize("hint_mode", [0, 1])
 @pytest.mark.parametrize("spec", [0, 1])
-def test_asynchronous_explorer_requests(hint_mode, spec):
-    """Option explore_async: the explorer request runs on the library's side stream; pack (after extracting the core
-    values from what the scoring pass kept, if it did), merge and pull wait for it.  Flat, segmented, wide zones,
-    forced exact rerun; a few iterations on one context."""
+@pytest.mark.parametrize("explore_async", [1, 2])
+def test_asynchronous_explorer_requests(explore_async, hint_mode, spec):
+    """Option explore_async: the explorer request runs on the library's side stream (2; with 1 these few tiles stay on the own
+    stream); pack (after extracting the core values from what the scoring pass kept, if it did), merge and pull wait for
+    it.  Flat, segmented, wide zones, forced exact rerun; a few iterations on one context."""
     cases = [workloads.TINY.scaled(300_007), workloads.GOOGLENET.scaled(300_001), workloads.STRESS.scaled(100_003, W=5),
              workloads.TINY.scaled(20_005, core_pct=10, explore_pct=60)]
     for wl in cases:
         sd = binding.SlimDP(wl.n, wl.W, seg_off=[int(x) for x in wl.segment_offsets()], seed=workloads.EXPLORE_SEED)
         sd.set_option("speculative_pack", spec)
         for t in range(3):
-            got, want = run_iteration(wl, iteration=t, sd=sd, hint=True, hint_mode=hint_mode, explore_async=1,
+            got, want = run_iteration(wl, iteration=t, sd=sd, hint=True, hint_mode=hint_mode, explore_async=explore_async,
                                       force_fallback=(1 if t == 2 else 0))
             assert_iteration_matches(wl, got, want)
         sd.close()
 
 
 @pytest.mark.parametrize("hint_mode", [0, 1])
-def test_asynchronous_explorer_one_iteration_ahead(hint_mode):
+@pytest.mark.parametrize("explore_async", [1, 2])
+def test_asynchronous_explorer_one_iteration_ahead(explore_async, hint_mode):
     """Steady iterations with cached core keys: the request for iteration t+1 (other output arrays) is issued before
-    the pack of iteration t and runs on the side stream beside pack and merge (hint_mode 1: after its announced draw
-    on the same stream; 0: nothing announced, the request draws itself).  Every set, and the model after every
-    iteration, as in the oracle."""
+    the pack of iteration t and runs on the side stream beside pack and merge (explore_async 2; 1: on the own stream, there
+    are few tiles; hint_mode 1: after its announced draw on the same stream; 0: nothing announced, the request draws
+    itself).  Every set, and the model after every iteration, as in the oracle."""
     wl = workloads.LOOP.scaled(250_007, W=4)
     n, W, k, m = wl.n, wl.W, wl.k, wl.m
     sd = binding.SlimDP(n, W, seed=workloads.EXPLORE_SEED)
-    sd.set_option("explore_async", 1)
+    sd.set_option("explore_async", explore_async)
     sd.set_option("explore_hint_mode", hint_mode)
     w_h = wl.weights()
     w = to_dev(w_h)
@@ -588,6 +593,7 @@ def test_hint_that_does_not_match_the_request_is_ignored(hint_mode):
     g_h = wl.gradients(0)
     g = [to_dev(x) for x in g_h]
     k, m = wl.k, wl.m
+    sd.set_option("explore_async", 2 * hint_mode)             # on the side stream: drawn there whatever the number of tiles
     sd.explore_hint([k], 7, [m], 0, 2)                        # announced: iteration 7, workers 0..1
     S = sd.score(w, g, wl.c)
     core_idx, core_bits, core_off, epoch = sd.select_core(S, [k], reuse_histogram=True)
@@ -1021,7 +1027,7 @@ def test_local_step_and_pack_in_one_pass(n, W, segmented, shift, nbuf):
     rng = np.random.default_rng(n + W)
     sd = binding.SlimDP(n, W, seg_off=seg_off, seed=workloads.EXPLORE_SEED)
     sd.set_option("pack_nbuf", nbuf)
-    sd.set_option("explore_async", 1)
+    sd.set_option("explore_async", 2)                        # whatever the number of tiles
     eta = 0.05
 
     def dev_arr(a):
@@ -1080,7 +1086,7 @@ def test_pull_and_local_step_in_one_pass(n, W, segmented, shift, explore_pct):
     so = None if wl.n_seg == 1 and wl.seg_off is None else seg_off
     rng = np.random.default_rng(n + 7 * W)
     sd = binding.SlimDP(n, W, seg_off=seg_off, seed=workloads.EXPLORE_SEED)
-    sd.set_option("explore_async", 1)
+    sd.set_option("explore_async", 2)                        # whatever the number of tiles
     eta = 0.05
 
     def dev_arr(a):

@@ -381,8 +381,9 @@ def test_explorer_values_kept_by_the_scoring_pass(W, pct):
     sd.close()
 
 
-@pytest.mark.parametrize("n,W,segments", [(60_001, 2, 1), (60_001, 3, 5), (4096 * 545 + 3, 16, 1), (4096 * 545 + 3, 16, 3)])
-def test_requests_of_changing_sizes_follow_each_other(n, W, segments):
+@pytest.mark.parametrize("n,W,segments,explore_async", [(60_001, 2, 1, 1), (60_001, 3, 5, 1), (60_001, 2, 1, 2), (60_001, 3, 5, 2),
+                                                        (4096 * 545 + 3, 16, 1, 1), (4096 * 545 + 3, 16, 3, 1)])
+def test_requests_of_changing_sizes_follow_each_other(n, W, segments, explore_async):
     """What one request leaves for the next (zones kept while the sizes stay, counters and the rerun flag cleared by their last
     reader), through changes of size, draws that miss their zones on either side, and announced draws; on the context's own stream
     (few tiles) and on the side stream."""
@@ -393,7 +394,7 @@ def test_requests_of_changing_sizes_follow_each_other(n, W, segments):
     core = oracle.select_core(np.abs(rng.standard_normal(n)).astype(np.float32), ks, so)
     bits = to_dev(oracle.core_bits(n, core))
     sd = binding.SlimDP(n, W, seg_off=so, seed=workloads.EXPLORE_SEED)
-    sd.set_option("explore_async", 1)
+    sd.set_option("explore_async", explore_async)
     sd.set_option("explore_hint_mode", 1)
     ts = sd.tile_starts().astype(np.int64)
     small, large = [int(s) // 50 for s in sizes], [int(s) // 9 for s in sizes]
@@ -441,6 +442,55 @@ def test_request_behind_a_draw_on_the_side_stream_leaves_the_own_stream_free(n, 
     sd.close()
     waits, free = min(took[0][2:]), min(took[1][2:])
     assert free < 0.5 * waits, "own stream held for %.0f us, %.0f without the option" % (free, waits)
+
+
+@pytest.mark.parametrize("hint", [0, 1])
+@pytest.mark.parametrize("name", ["flat", "words_shared_by_long_tiles", "wide zones"])
+def test_more_requests_on_the_side_stream_than_the_context_has_notes_for(name, hint):
+    """Seven requests in a row before any list is used (four are noted, the oldest makes room), into arrays of their own, some of
+    them missing their zones; then their packs in another order, each right behind a new request into the arrays of the one
+    packed before.  Every list and every pack as in the oracle."""
+    sizes = SEGMENTS.get(name, [90_001])
+    so, n, W, rounds = offsets(sizes), sum(sizes), 3, 7
+    part = 2 if name == "wide zones" else 40
+    ks, ms = [s // 10 for s in sizes], [s // part for s in sizes]
+    rng = np.random.default_rng(len(name) + hint)
+    core = oracle.select_core(np.abs(rng.standard_normal(n)).astype(np.float32), ks, so)
+    g_h = [rng.standard_normal(n).astype(np.float32) for _ in range(W)]
+    g, core_idx = [to_dev(x) for x in g_h], to_dev(core)
+    sd = binding.SlimDP(n, W, seg_off=so, seed=workloads.EXPLORE_SEED)
+    sd.set_option("explore_async", 2)
+    sd.set_option("explore_hint_mode", 1)
+    bits, off, epoch = sd.import_core(core_idx, ks)
+
+    def request(it, lists=(None, None)):
+        sd.set_option("explore_force_fallback", it % 3 if name != "wide zones" else 0)
+        if hint:
+            sd.explore_hint(ks, it, ms, 0, W)
+        return sd.sample_explore(bits, ks, it, ms, 0, W, expl_idx=lists[0], expl_off=lists[1])
+
+    def check(it, idx, expl_val):
+        for q in range(W):
+            want = oracle.sample_explore(n, core, workloads.EXPLORE_SEED, it, q, ms, so)
+            assert np.array_equal(u32(idx[q]), want), (it, q)
+            assert np.array_equal(u32(expl_val[q]), g_h[q][want].view(np.uint32)), (it, q)
+    lists = [request(it) for it in range(rounds)]
+    order = [6, 1, 4, 0, 5, 2, 3]
+    held, kept = [], None
+    for j, it in enumerate(order):
+        if kept is not None:                     # new entries into the lists of the pack before: they are copied first
+            held.append((order[j - 1], [x.clone() for x in lists[order[j - 1]][0]], kept))
+            lists[order[j - 1]] = request(100 + order[j - 1], lists[order[j - 1]])
+        kept = sd.pack(g, core_idx, off, *lists[it], epoch)[1]
+    held.append((order[-1], lists[order[-1]][0], kept))
+    sd.synchronize()
+    for it, idx, expl_val in held:
+        check(it, idx, expl_val)
+    for it in order[:-1]:
+        expl_val = sd.pack(g, core_idx, off, *lists[it], epoch)[1]
+        sd.synchronize()
+        check(100 + it, lists[it][0], expl_val)
+    sd.close()
 
 
 def test_recorded_request_replays_beside_eager_ones():
