@@ -1298,12 +1298,7 @@ int slimdp_sample_explore(slimdp_ctx* ctx, const uint32_t* core_bits, const uint
                            ctx->e_state, worker0, pk, ctx->e_sure_bits, off_tab, idx_tab, (uint32_t)M, rerun, ctx->d_flags);     \
         SLIMDP_LAUNCHED(ctx, "k_explore_emit");                                                                                  \
     } while (0)
-    if (async) {
-        LAUNCH_EMIT(256);
-        hipLaunchKernelGGL(k_explore_rerun, dim3(B), dim3(1024), 0, st, core_bits, ctx->d_tile_start, ctx->d_seg_first_tile, T, S,
-                           ctx->e_state, worker0, pk, off_tab, idx_tab, (uint32_t)M, rerun, ctx->d_flags);
-        SLIMDP_LAUNCHED(ctx, "k_explore_rerun");
-    } else LAUNCH_EMIT(1024);
+    if (async) LAUNCH_EMIT(256); else LAUNCH_EMIT(1024);
 #undef LAUNCH_EMIT
     ctx->lists_clean = known;                // a recorded request has cleared nothing yet
     ctx->rerun_turn ^= 1u;

@@ -413,7 +413,7 @@ __global__ __launch_bounds__(NT) void k_explore_select(const SegState* __restric
 // finds the need-th smallest Philox word among the parameters outside the core by a
 // three-pass radix descent over ALL of them (11 + 11 + 10 bits, words recomputed in every
 // pass), then emits tile by tile in index order, ties at the threshold word going to the
-// lowest indices.  By a block of 1024 threads.
+// lowest indices.  By a block of NT threads; h: EXACT_NBIN words of LDS.
 // =======================================================================================
 __device__ __forceinline__ uint32_t explore_word(uint32_t i, uint32_t worker, PhiloxKey pk)
 {
@@ -423,14 +423,17 @@ __device__ __forceinline__ uint32_t explore_word(uint32_t i, uint32_t worker, Ph
     return c == 0 ? r[0] : c == 1 ? r[1] : c == 2 ? r[2] : r[3];
 }
 
-__device__ __forceinline__ void explore_exact(const uint32_t* __restrict__ core_bits, const uint32_t* __restrict__ tile_start,
+constexpr uint32_t EXACT_NBIN = 2048;
+template <int NT>
+__device__ __forceinline__ void explore_exact(uint32_t* h, const uint32_t* __restrict__ core_bits, const uint32_t* __restrict__ tile_start,
                               const uint32_t* __restrict__ seg_first_tile, uint32_t T, uint32_t n_seg,
                               const SegState* __restrict__ states, uint32_t worker, PhiloxKey pk, uint32_t* __restrict__ out,
                               uint32_t* __restrict__ off, uint32_t expected, uint32_t* __restrict__ flags)
 {
-    constexpr uint32_t NBIN = 2048;
-    __shared__ uint32_t h[NBIN];
-    __shared__ uint32_t wtot[16];
+    constexpr uint32_t PER = EXACT_NBIN / NT, EACH = TILE / NT;      // bins, and parameters of a tile, per thread
+    constexpr int NWV = NT / 64;
+    static_assert(EACH <= 32, "a thread's parameters of a tile are flags of one word");
+    __shared__ uint32_t wtot[NWV];
     __shared__ uint32_t sh[4];
     const uint32_t tid = threadIdx.x;
     uint32_t run = 0;                                // indices emitted so far (uniform)
@@ -441,12 +444,12 @@ __device__ __forceinline__ void explore_exact(const uint32_t* __restrict__ core_
         uint32_t prefix = 0, short_of = 0;
         const uint32_t shifts[3] = {21u, 10u, 0u}, nbits[3] = {11u, 11u, 10u};
         for (int p = 0; p < 3 && need != 0 && !short_of; ++p) {
-            for (uint32_t x = tid; x < NBIN; x += 1024) h[x] = 0;
+            for (uint32_t x = tid; x < EXACT_NBIN; x += NT) h[x] = 0;
             __syncthreads();
             const uint32_t hi_shift = shifts[p] + nbits[p];        // bits above this pass's digit
             for (uint32_t t = f0; t < f1; ++t) {
                 const uint32_t start = tile_start[t], len = tile_start[t + 1] - start;
-                for (uint32_t e = tid; e < len; e += 1024) {
+                for (uint32_t e = tid; e < len; e += NT) {
                     const uint32_t i = start + e;
                     if ((core_bits[i >> 5] >> (i & 31u)) & 1u) continue;
                     const uint32_t r = explore_word(i, worker, pk);
@@ -455,13 +458,18 @@ __device__ __forceinline__ void explore_exact(const uint32_t* __restrict__ core_
                 }
             }
             __syncthreads();
-            // the bin that holds the need-th smallest: two bins per thread, ascending
-            const uint32_t c0 = h[2 * tid], c1 = h[2 * tid + 1];
+            // the bin that holds the need-th smallest: consecutive bins per thread, ascending
+            uint32_t sum = 0;
+#pragma unroll
+            for (uint32_t e = 0; e < PER; ++e) sum += h[PER * tid + e];
             uint32_t total;
-            const uint32_t excl = block_excl_scan<16>(c0 + c1, wtot, total);
+            const uint32_t excl = block_excl_scan<NWV>(sum, wtot, total);
             if (tid == 0) sh[2] = (total < need) ? 1u : 0u;
-            if (excl < need && need <= excl + c0) { sh[0] = 2 * tid; sh[1] = need - excl; }
-            else if (excl + c0 < need && need <= excl + c0 + c1) { sh[0] = 2 * tid + 1; sh[1] = need - excl - c0; }
+            if (excl < need && need <= excl + sum) {
+                uint32_t before = excl, bin = PER * tid;
+                while (need > before + h[bin]) before += h[bin++];
+                sh[0] = bin; sh[1] = need - before;
+            }
             __syncthreads();
             if (sh[2]) { short_of = 1; if (tid == 0) atomicOr(&flags[1], 2u); }     // fewer eligible parameters than requested
             else { prefix = (prefix << nbits[p]) | sh[0]; need = sh[1]; }
@@ -472,14 +480,14 @@ __device__ __forceinline__ void explore_exact(const uint32_t* __restrict__ core_
         const uint32_t take_all = short_of;
         const uint32_t want = states[seg].need0;
         uint32_t ties_seen = 0;                      // uniform
-        // ---- ordered emission, tile by tile (four consecutive parameters per thread)
+        // ---- ordered emission, tile by tile (consecutive parameters per thread)
         for (uint32_t t = f0; t < f1; ++t) {
             const uint32_t start = tile_start[t], len = tile_start[t + 1] - start;
             uint32_t sel = 0, tie = 0;
             if (want != 0) {
-#pragma unroll
-                for (int c = 0; c < 4; ++c) {
-                    const uint32_t e = 4u * tid + c;
+#pragma unroll 1
+                for (uint32_t c = 0; c < EACH; ++c) {
+                    const uint32_t e = EACH * tid + c;
                     if (e >= len) continue;
                     const uint32_t i = start + e;
                     if ((core_bits[i >> 5] >> (i & 31u)) & 1u) continue;
@@ -489,18 +497,18 @@ __device__ __forceinline__ void explore_exact(const uint32_t* __restrict__ core_
                 }
             }
             uint32_t tie_total;
-            const uint32_t tie_excl = block_excl_scan<16>(__popc(tie), wtot, tie_total);
+            const uint32_t tie_excl = block_excl_scan<NWV>(__popc(tie), wtot, tie_total);
             uint32_t rank = ties_seen + tie_excl;
-#pragma unroll
-            for (int c = 0; c < 4; ++c)
+#pragma unroll 1
+            for (uint32_t c = 0; c < EACH; ++c)
                 if ((tie >> c) & 1u) { if (rank < need) sel |= 1u << c; ++rank; }
             ties_seen += tie_total;
             uint32_t sel_total;
-            uint32_t o = run + block_excl_scan<16>(__popc(sel), wtot, sel_total);
+            uint32_t o = run + block_excl_scan<NWV>(__popc(sel), wtot, sel_total);
             if (tid == 0) off[t] = run;
-#pragma unroll
-            for (int c = 0; c < 4; ++c)
-                if ((sel >> c) & 1u) { if (o < expected) out[o] = start + 4u * tid + c; ++o; }
+#pragma unroll 1
+            for (uint32_t c = 0; c < EACH; ++c)
+                if ((sel >> c) & 1u) { if (o < expected) out[o] = start + EACH * tid + c; ++o; }
             run += sel_total;
         }
     }
@@ -511,11 +519,11 @@ __device__ __forceinline__ void explore_exact(const uint32_t* __restrict__ core_
 }
 
 // Ordered emission from the sure bitmap (chosen candidates included) minus the core.  One wave per tile and BPW batches.
-// NT = 1024: with the rerun flag up the first BPW blocks of a batch group redo the request instead, one batch each
-// (k_explore_select and everything before it is void then); at most 64 registers, two blocks to a compute unit.
+// With the rerun flag up the first BPW blocks of a batch group redo the request instead, one batch each (k_explore_select and
+// everything before it is void then); at most 64 registers, eight waves to a SIMD.
 // NT = 256, for a request on the side stream: beside a kernel of small blocks that fills the chip a block of sixteen waves
 // waits until so many are free at once on one unit (beside k_merge 330 to 600 us for 138*10^6 parameters and 8 workers,
-// 59 alone); the rerun is then a launch of its own (k_explore_rerun).
+// 59 alone; a launch of sixteen-wave blocks that read the flag and end, as the rerun was there, 4 to 275 us).
 // grid (max(BPW, ceil(T / waves of a block)), ceil(nbatch / BPW)).
 template <int BPW, int NT>
 __global__ __launch_bounds__(NT, 8) void k_explore_emit(const uint32_t* __restrict__ core_bits, uint32_t n_words, uint64_t n,
@@ -527,16 +535,15 @@ __global__ __launch_bounds__(NT, 8) void k_explore_emit(const uint32_t* __restri
                                                        MutPtrTab out_idx, uint32_t expected, RerunFlag rerun, uint32_t* __restrict__ flags)
 {
     constexpr uint32_t WAVES = NT / 64;
-    __shared__ uint16_t stage[WAVES][EMIT_STAGE];
+    __shared__ __align__(8) uint16_t stage[WAVES][EMIT_STAGE];
+    static_assert(sizeof stage >= EXACT_NBIN * sizeof(uint32_t), "the rerun counts in the stage");
     const uint32_t b0 = blockIdx.y * BPW;
     if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) *rerun.next = 0;
     if (*rerun.now != 0) {                       // nobody raises the flag while this kernel runs
-        if constexpr (NT == 1024) {
-            const uint32_t b = b0 + blockIdx.x;
-            if (blockIdx.x < (uint32_t)BPW && b < nbatch)
-                explore_exact(core_bits, tile_start, seg_first_tile, T, n_seg, states, worker0 + b, pk,
+        const uint32_t b = b0 + blockIdx.x;
+        if (blockIdx.x < (uint32_t)BPW && b < nbatch)
+            explore_exact<NT>(reinterpret_cast<uint32_t*>(stage), core_bits, tile_start, seg_first_tile, T, n_seg, states, worker0 + b, pk,
                               static_cast<uint32_t*>(out_idx.p[b]), static_cast<uint32_t*>(out_off.p[b]), expected, flags);
-        }
         return;
     }
     const uint32_t t = blockIdx.x * WAVES + (threadIdx.x >> 6), lane = lane_id();
@@ -565,19 +572,6 @@ __global__ __launch_bounds__(NT, 8) void k_explore_emit(const uint32_t* __restri
         if (t == T - 1 && lane == 63 && off_t[bb] + incl != expected) atomicOr(&flags[1], 1u);
         emit_indices(fm0, fm1, incl, tr.start, off_t[bb], expected, stage[threadIdx.x >> 6], out);
     }
-}
-
-// The rerun after an emission that left it out.  grid n_workers, 1024 threads.
-__global__ __launch_bounds__(1024) void k_explore_rerun(const uint32_t* __restrict__ core_bits, const uint32_t* __restrict__ tile_start,
-                                                        const uint32_t* __restrict__ seg_first_tile, uint32_t T, uint32_t n_seg,
-                                                        const SegState* __restrict__ states, uint32_t worker0, PhiloxKey pk,
-                                                        MutPtrTab out_off, MutPtrTab out_idx, uint32_t expected, RerunFlag rerun,
-                                                        uint32_t* __restrict__ flags)
-{
-    if (*rerun.now == 0) return;
-    const uint32_t b = blockIdx.x;
-    explore_exact(core_bits, tile_start, seg_first_tile, T, n_seg, states, worker0 + b, pk, static_cast<uint32_t*>(out_idx.p[b]),
-                  static_cast<uint32_t*>(out_off.p[b]), expected, flags);
 }
 
 }  // namespace slimdp

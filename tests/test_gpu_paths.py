@@ -493,6 +493,40 @@ def test_more_requests_on_the_side_stream_than_the_context_has_notes_for(name, h
     sd.close()
 
 
+@pytest.mark.parametrize("segments,pct", [(1, 2), (3, 2), (1, 60), (5, 60)])
+def test_exact_rerun_on_the_side_stream_is_waited_for(segments, pct):
+    """A draw that misses its zones (on either side) on the side stream: the emission's small blocks redo the request, and the pack
+    enqueued right behind it waits for them.  Ragged tiles and an empty segment's list, demands that most parameters meet, more
+    workers than one group of the emission has."""
+    W = 5
+    n = 4096 * 66 + 77
+    so = offsets([n]) if segments == 1 else offsets([4096 * 11 + 5] * (segments - 1) + [n - (4096 * 11 + 5) * (segments - 1)])
+    sizes = np.diff(so)
+    ks = [int(s) // 10 for s in sizes]
+    ms = [(s - k) * pct // 100 if j != 1 else 0 for j, (s, k) in enumerate(zip((int(x) for x in sizes), ks))]
+    rng = np.random.default_rng(segments * 100 + pct)
+    core = oracle.select_core(np.abs(rng.standard_normal(n)).astype(np.float32), ks, so)
+    g_h = [rng.standard_normal(n).astype(np.float32) for _ in range(2)]
+    g = [to_dev(g_h[q & 1]) for q in range(W)]
+    sd = binding.SlimDP(n, W, seg_off=so, seed=workloads.EXPLORE_SEED)
+    sd.set_option("explore_async", 2)
+    core_idx = to_dev(core)
+    bits, off, epoch = sd.import_core(core_idx, ks)
+    ts = sd.tile_starts().astype(np.int64)
+    for miss in (1, 2):
+        sd.set_option("explore_force_fallback", miss)
+        idx, eoff = sd.sample_explore(bits, ks, miss, ms, 0, W)
+        core_val, expl_val = sd.pack(g, core_idx, off, idx, eoff, epoch)
+        sd.synchronize()
+        for q in range(W):
+            want = oracle.sample_explore(n, core, workloads.EXPLORE_SEED, miss, q, ms, so)
+            assert np.array_equal(u32(idx[q]), want), (miss, q)
+            assert np.array_equal(u32(eoff[q]), np.searchsorted(want.astype(np.int64), ts).astype(np.uint32)), (miss, q)
+            assert np.array_equal(u32(expl_val[q]), g_h[q & 1][want].view(np.uint32)), (miss, q)
+            assert np.array_equal(u32(core_val[q]), g_h[q & 1][core].view(np.uint32)), (miss, q)
+    sd.close()
+
+
 def test_recorded_request_replays_beside_eager_ones():
     """A replay finds counters, zones and the rerun flag as it needs them, whatever eager requests (other sizes, a missed draw)
     ran since it was recorded, and so do eager requests after a replay."""
