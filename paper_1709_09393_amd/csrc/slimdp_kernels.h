@@ -314,7 +314,7 @@ __global__ __launch_bounds__(BLOCK, SCORE_MINB) void k_score(const float* __rest
     const int W = WT ? WT : Wrt;
     // the wave's number as a scalar: addresses below are then a scalar base plus a small per-lane offset
     const uint32_t lane = lane_id(), wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const uint32_t lane16 = lane * 16u;      // byte offset of the lane's float4: a 32-bit offset beside a scalar base
+    const uint32_t lane16 = lane * 16u;      // byte offset of the lane's sixteen bytes inside a round
     for (uint32_t b = threadIdx.x; b < NB; b += BLOCK) h[b] = 0;
     __syncthreads();
     // A block's tiles: a contiguous range (few segment changes, each of which flushes the histogram), or - flat model,
@@ -405,9 +405,9 @@ __global__ __launch_bounds__(BLOCK, SCORE_MINB) void k_score(const float* __rest
 #pragma unroll
                     for (int k = 1; k < WT; ++k) { a.x = a.x + x[k].x; a.y = a.y + x[k].y; a.z = a.z + x[k].z; a.w = a.w + x[k].w; }
                 } else {
-                    a = *reinterpret_cast<const float4*>(reinterpret_cast<const char*>(static_cast<const float*>(g.p[0]) + e0) + lane16);
+                    a = ld4<0>(static_cast<const float*>(g.p[0]) + e0 + 4u * lane);
                     for (int k = 1; k < W; ++k) {
-                        const float4 y = *reinterpret_cast<const float4*>(reinterpret_cast<const char*>(static_cast<const float*>(g.p[k]) + e0) + lane16);
+                        const float4 y = ld4<0>(static_cast<const float*>(g.p[k]) + e0 + 4u * lane);
                         a.x = a.x + y.x; a.y = a.y + y.y; a.z = a.z + y.z; a.w = a.w + y.w;
                     }
                 }

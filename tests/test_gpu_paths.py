@@ -381,6 +381,62 @@ def test_explorer_values_kept_by_the_scoring_pass(W, pct):
     sd.close()
 
 
+@pytest.mark.parametrize("segmented", [False, True])
+@pytest.mark.parametrize("W,shift", [(1, 1), (2, 3), (3, 2), (5, 1), (8, 1), (8, 2), (12, 3), (16, 1), (20, 2)])
+def test_sixteen_byte_access_from_any_float_address(W, shift, segmented):
+    """Model, updates and scores that begin 4, 8 or 12 bytes past a multiple of 16, for every form of the scoring kernels (fixed
+    numbers of workers and any), the dense update, selection with and without the pass's histogram, both packs and the merge: the
+    same bits as the oracle, and nothing written outside the arrays."""
+    sizes = SEGMENTS["words_shared_by_long_tiles"] if segmented else [4096 * 5 + 1234]
+    so, n = offsets(sizes), sum(sizes)
+    ks, ms = [s // 9 for s in sizes], [s // 30 for s in sizes]
+    rng = np.random.default_rng(10 * W + shift + segmented)
+    guard = np.float32(123.0)
+
+    def place(a):
+        buf = torch.full((shift + n + 5,), float(guard), dtype=torch.float32, device=dev())
+        buf[shift:shift + n] = torch.from_numpy(a)
+        return buf, buf[shift:shift + n]
+    w_h = rng.standard_normal(n).astype(np.float32)
+    g_h = [(0.1 * rng.standard_normal(n)).astype(np.float32) for _ in range(W)]
+    w_all, w = place(w_h)
+    S_all, S = place(np.zeros(n, np.float32))
+    g = [place(x)[1] for x in g_h]
+    sd = binding.SlimDP(n, W, seg_off=so, seed=workloads.EXPLORE_SEED)
+    sd.set_option("speculative_pack", 1)
+    for t in range(2):                           # the second pass captures
+        sd.score(w, g, 1.0, out=S)
+        core, bits, off, epoch = sd.select_core(S, ks, reuse_histogram=True)
+        again = sd.select_core(S, ks)[0]
+        sd.score(w, g, 1.0, out=S)
+        core, bits, off, epoch = sd.select_core(S, ks, reuse_histogram=True)
+        idx, eoff = sd.sample_explore(bits, ks, t, ms, 0, W)
+        kept = sd.pack(g, core, off, idx, eoff, epoch, updates_as_scored=True)
+        plain = sd.pack(g, core, off, idx, eoff, epoch)
+        sd.merge(w, 0.1, epoch, core, off, plain[0], idx, eoff, plain[1])
+        sd.synchronize()
+        S_o = oracle.score(w_h, g_h, 1.0)
+        core_o = oracle.select_core(S_o, ks, so)
+        assert np.array_equal(u32(S), S_o.view(np.uint32))
+        assert np.array_equal(u32(core), core_o) and np.array_equal(u32(again), core_o)
+        lists = [oracle.sample_explore(n, core_o, workloads.EXPLORE_SEED, t, q, ms, so) for q in range(W)]
+        packs = [oracle.pack(g_h[q], core_o, lists[q]) for q in range(W)]
+        for q in range(W):
+            for got in (kept, plain):
+                assert np.array_equal(u32(got[0][q]), packs[q][0].view(np.uint32)), (t, q)
+                assert np.array_equal(u32(got[1][q]), packs[q][1].view(np.uint32)), (t, q)
+        w_h = oracle.merge(w_h, 0.1, core_o, [x[0] for x in packs], lists, [x[1] for x in packs])
+        assert np.array_equal(u32(w), w_h.view(np.uint32))
+    w_h, S_o = oracle.dense_update_score(w_h, g_h, 0.1, 1.0)
+    sd.dense_update_score(w, g, 0.1, 1.0, out=S)
+    sd.synchronize()
+    assert np.array_equal(u32(w), w_h.view(np.uint32)) and np.array_equal(u32(S), S_o.view(np.uint32))
+    for buf in (w_all, S_all):
+        outside = torch.cat([buf[:shift], buf[shift + n:]]).cpu().numpy()
+        assert np.all(outside == guard)
+    sd.close()
+
+
 @pytest.mark.parametrize("n,W,segments,explore_async", [(60_001, 2, 1, 1), (60_001, 3, 5, 1), (60_001, 2, 1, 2), (60_001, 3, 5, 2),
                                                         (4096 * 545 + 3, 16, 1, 1), (4096 * 545 + 3, 16, 3, 1)])
 def test_requests_of_changing_sizes_follow_each_other(n, W, segments, explore_async):
