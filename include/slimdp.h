@@ -20,8 +20,8 @@
  *    and explorer requests (option "explore_async" = 1) on the library's own side stream; the
  *    calls that need their results make the caller's stream wait for them.
  *  - The library allocates device memory in slimdp_create, once more when the option
- *    "speculative_pack" is first switched on (slimdp_capture_bytes), and once more on the first
- *    explorer request that needs the large key buffer (see slimdp_capture_bytes); never otherwise.
+ *    "speculative_pack" is first switched on (slimdp_capture_bytes; again with "explore_keep" = 2), and once more on the
+ *    first explorer request that needs the large key buffer (see slimdp_capture_bytes); never otherwise.
  *  - Same inputs give the same output bits, whatever the launch geometry.
  *  - Indices are 0-based uint32 (the paper counts from 1); n <= SLIMDP_MAX_N = 2^31 (indices and loop counters are
  *    32-bit and no loop steps by 2^31 or more, so none can wrap).
@@ -140,7 +140,8 @@ int slimdp_synchronize(slimdp_ctx* ctx);
  *   "explore_keep" (0/1/2, default 1): with "speculative_pack", a flat model and a draw announced for at least the W workers
  *       scored, slimdp_score also keeps the update values of most of the coming explorers, and a slimdp_pack with
  *       SLIMDP_PACK_UPDATES_AS_SCORED looks its explorer values up there instead of gathering them.  1: where the updates
- *       exceed 256 MB and W is at least 2; 2: always; 0: never.  Results do not depend on it.
+ *       exceed 256 MB and W is at least 2; 2: always (the room for it, where 1 needs none, is allocated by the call that sets
+ *       the later of the two options); 0: never.  Results do not depend on it.
  *   "side_blocks" (1..8): blocks per compute unit of a side-stream draw.
  *   "pull_kernel" (0/1, default 1): how slimdp_pull patches local models (1: a pass that streams them; 0: scattered
  *       writes); results do not depend on it.

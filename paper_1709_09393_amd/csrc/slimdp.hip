@@ -186,7 +186,8 @@ struct slimdp_ctx {
         uint32_t* fail = nullptr;               // per segment: the selection's threshold fell below the capture bound
         uint2* bits = nullptr;
         float* vals = nullptr;
-        float* evals = nullptr;                 // explorer capture (flat models)
+        float* evals = nullptr;                 // explorer capture, where there is room for one (see expl_capture_words)
+        char* evals_mem = nullptr;              // ... of its own, for option "explore_keep" = 2 where the sizes ask for none
         int cur = 0;
         bool next_written = false;              // a selection has refreshed lo[cur ^ 1] since the last capture
         bool bound_valid = false;               // lo[cur] comes from a selection (else: nothing, or a sampled estimate)
@@ -357,10 +358,21 @@ uint32_t draw_group(const slimdp_ctx* c, uint32_t per_cu, uint32_t n_workers)
     return g;
 }
 
-// Room of the explorer capture: the pipelined scoring kernel's, which serves flat models and up to 16 workers.
-size_t expl_capture_words(uint64_t T, uint32_t max_workers, uint32_t n_seg)
+// Whether a scoring pass of W workers keeps the explorers' update values, if it is left to the sizes.  A gather of 2 % of the
+// parameters reads 44 % of the updates' lines, which costs little only while they come from the caches (256 MB), and one worker's
+// too little for the scoring pass to earn it.  Whole iteration with and without, us: 138*10^6 parameters, 8 workers 2,140 / 2,320
+// (5 %: 2,475 / 2,827), 16*10^6 and 8 339 / 355, 8*10^6 and 8 232 / 237, 32*10^6 and 2 316 / 322, but 8*10^6 and 4 185 / 184, 10^6 and
+// 4 (scoring and pack alone) 31 / 24, 64*10^6 and 1 481 / 475.
+bool expl_worth_keeping(uint64_t n, uint32_t W) { return W >= 2 && n * W * 4u >= (256ull << 20); }
+
+// Room of the explorer capture, in words: the pipelined scoring kernel's, which serves flat models below 2^30 parameters and
+// captures for 1, 2, 4, 8 or 16 workers.  Only where some number of workers that the context serves is worth keeping, or for all (forced).
+size_t expl_capture_words(uint64_t n, uint64_t T, uint32_t max_workers, uint32_t n_seg, bool forced)
 {
-    return n_seg == 1 ? (size_t)T * SUBS * std::min(max_workers, 16u) * EXPL_SLOTS_MAX : 0;
+    if (n_seg != 1 || n >= (1ull << 30)) return 0;
+    uint32_t most = 1;
+    while (most < 16 && 2 * most <= max_workers) most *= 2;
+    return forced || expl_worth_keeping(n, most) ? (size_t)T * SUBS * most * EXPL_SLOTS_MAX : 0;
 }
 
 // Slots for the explorer values of a sub-tile, from the share of the words in the sure zone: of its 256 blocks of four those
@@ -512,6 +524,21 @@ int ensure_wide_keys(slimdp_ctx* c)
     return SLIMDP_OK;
 }
 
+// The explorer capture that option "explore_keep" = 2 asks for beside "speculative_pack", where the sizes alone ask for none.
+int ensure_expl_capture(slimdp_ctx* c)
+{
+    if (!c->spec.mem || c->spec.evals) return SLIMDP_OK;
+    const size_t bytes = expl_capture_words(c->n, c->T, c->maxW, c->n_seg, true) * sizeof(float);
+    if (bytes == 0) return SLIMDP_OK;
+    const hipError_t e = hipMalloc(reinterpret_cast<void**>(&c->spec.evals_mem), bytes);
+    if (e != hipSuccess) {
+        c->spec.evals_mem = nullptr;
+        return fail(c, SLIMDP_ERR_WORKSPACE, "slimdp_set_option(explore_keep): hipMalloc(%zu bytes): %s", bytes, hipGetErrorString(e));
+    }
+    c->spec.evals = reinterpret_cast<float*>(c->spec.evals_mem);
+    return SLIMDP_OK;
+}
+
 // Probability that one sub-tile holds more than PAIR_CAP candidates of one draw when lambda are expected (the draw
 // marks each of its up to 1024 words independently: Poisson tail, summed directly so that tiny values keep their digits).
 double pair_overflow_prob(double lambda)
@@ -632,7 +659,7 @@ uint64_t slimdp_capture_bytes(uint64_t n, uint32_t max_workers, uint32_t n_seg, 
     cv.take<uint32_t>(n_seg); cv.take<uint32_t>(n_seg); cv.take<uint32_t>(n_seg);
     cv.take<uint2>((size_t)T * TILE_WORDS);
     cv.take<float>((size_t)max_workers * T * SUBS * SPEC_CAP);
-    cv.take<float>(expl_capture_words(T, max_workers, n_seg));
+    cv.take<float>(expl_capture_words(n, T, max_workers, n_seg, false));
     cv.take<uint32_t>((size_t)T * SAMPLE_PER);
     return align_up(cv.pos, 256);
 }
@@ -724,6 +751,7 @@ int slimdp_destroy(slimdp_ctx* ctx)
     (void)hipStreamDestroy(ctx->side);
     hipError_t e = hipFree(ctx->ws);
     if (ctx->spec.mem) (void)hipFree(ctx->spec.mem);
+    if (ctx->spec.evals_mem) (void)hipFree(ctx->spec.evals_mem);
     if (ctx->e_cand_keys) (void)hipFree(ctx->e_cand_keys);
     delete ctx;
     return e == hipSuccess ? SLIMDP_OK : SLIMDP_ERR_HIP;
@@ -752,7 +780,11 @@ int slimdp_set_option(slimdp_ctx* ctx, const char* name, int64_t value)
     if (strcmp(name, "pack_kernel") == 0 && (value == 0 || value == 1)) { ctx->opt_pack_kernel = value; return SLIMDP_OK; }
     if (strcmp(name, "pull_kernel") == 0 && (value == 0 || value == 1)) { ctx->opt_pull_kernel = value; return SLIMDP_OK; }
     if (strcmp(name, "expected_core") == 0 && value >= -1 && (value < 0 || (uint64_t)value <= ctx->n)) { ctx->opt_expected_core = value; return SLIMDP_OK; }
-    if (strcmp(name, "explore_keep") == 0 && value >= 0 && value <= 2) { ctx->opt_explore_keep = value; return SLIMDP_OK; }
+    if (strcmp(name, "explore_keep") == 0 && value >= 0 && value <= 2) {
+        const int rc = value == 2 ? ensure_expl_capture(ctx) : SLIMDP_OK;
+        if (!rc) ctx->opt_explore_keep = value;
+        return rc;
+    }
     if (strcmp(name, "score_pipeline") == 0 && (value == 0 || value == 1)) { ctx->opt_score_pipeline = value; return SLIMDP_OK; }
     if (strcmp(name, "capture_estimate_bias") == 0) { ctx->opt_estimate_bias = value; return SLIMDP_OK; }
     if (strcmp(name, "speculative_pack") == 0) {
@@ -766,7 +798,8 @@ int slimdp_set_option(slimdp_ctx* ctx, const char* name, int64_t value)
                 ctx->spec.fail = cv.take<uint32_t>(S);
                 ctx->spec.bits = cv.take<uint2>((size_t)ctx->T * TILE_WORDS);
                 ctx->spec.vals = cv.take<float>((size_t)ctx->maxW * ctx->T * SUBS * SPEC_CAP);
-                ctx->spec.evals = cv.take<float>(expl_capture_words(ctx->T, ctx->maxW, ctx->n_seg));
+                const size_t ew = expl_capture_words(ctx->n, ctx->T, ctx->maxW, ctx->n_seg, false);
+                if (ew) ctx->spec.evals = cv.take<float>(ew);
                 ctx->spec.sample = cv.take<uint32_t>((size_t)ctx->T * SAMPLE_PER);
             };
             carve_spec(sizing);
@@ -787,6 +820,7 @@ int slimdp_set_option(slimdp_ctx* ctx, const char* name, int64_t value)
             ctx->spec.next_written = false;
             ctx->spec.bound_valid = false;
         }
+        if (value && ctx->opt_explore_keep == 2) { const int rc = ensure_expl_capture(ctx); if (rc) return rc; }
         ctx->spec.on = value != 0;
         return SLIMDP_OK;
     }
@@ -889,14 +923,11 @@ static int score_impl(slimdp_ctx* ctx, const float* w, const float* const* g, ui
     if (ctx->n_seg == 1 && vec_ok && ctx->opt_strided && ctx->opt_score_pipeline && ctx->n < (1ull << 30) &&
         (W <= 8 || W == 16)) {
         const dim3 fgrid(persistent_blocks(ctx, SCOREF_MINB, 1)), fblock(BLOCK);
-        // The explorers' values too: a gather of 2 % of the parameters reads 44 % of the updates' lines, which costs little only
-        // while they come from the caches (256 MB), and one worker's too little for the scoring pass to earn it.  Whole iteration
-        // with and without, us: 138*10^6 parameters, 8 workers 2,140 / 2,320 (5 %: 2,475 / 2,827), 16*10^6 and 8 339 / 355, 8*10^6 and 8
-        // 232 / 237, 32*10^6 and 2 316 / 322, but 8*10^6 and 4 185 / 184, 10^6 and 4 (scoring and pack alone) 31 / 24, 64*10^6 and 1 481 / 475.
-        // Fewer workers announced than scored: the draw for its own sake.  A context with recorded calls: a replay may draw
-        // again between a scoring pass and its pack, unknown to the host.
-        if (!capture || pre.nw < W || !known || ctx->opt_explore_keep == 0 ||
-            (ctx->opt_explore_keep == 1 && (W < 2 || ctx->n * W * 4u < (256ull << 20))))
+        // The explorers' values too, where that pays (expl_worth_keeping).  Fewer workers announced than scored: the draw for
+        // its own sake.  A context with recorded calls: a replay may draw again between a scoring pass and its pack, unknown to
+        // the host.
+        if (!capture || !ctx->spec.evals || pre.nw < W || !known || ctx->opt_explore_keep == 0 ||
+            (ctx->opt_explore_keep == 1 && !expl_worth_keeping(ctx->n, W)))
             slots = 0;
         pre.vals = ctx->spec.evals; pre.slots = slots;
         ctx->spec.expl_slots = slots;

@@ -61,6 +61,27 @@ def test_num_tiles_and_workspace_are_pure_host_functions():
     assert binding.capture_bytes(10, 0) == 0
 
 
+def test_capture_has_room_for_explorer_values_only_where_they_are_kept():
+    """Per tile and worker a quarter of the values for the core, bitmaps and a sample beside them; 192 slots a worker more where a
+    scoring pass keeps the explorers' values without being told to: flat models, two workers and more, 256 MB of updates."""
+    def core_only(n, W, seg_off=None):
+        return binding.num_tiles(n, seg_off) * (W * 4096 + 1024 + 8)
+
+    def extra(n, W, seg_off=None):
+        return binding.capture_bytes(n, W, seg_off) - core_only(n, W, seg_off)
+    slack = 4096
+    n = 138_357_544
+    T = binding.num_tiles(n)
+    for W in (2, 3, 8, 16, 32):
+        kept = max(w for w in (1, 2, 4, 8, 16) if w <= W)
+        assert 0 <= extra(n, W) - T * 768 * kept < slack, W
+    assert 0 <= extra(n, 1) < slack                                    # one worker
+    assert 0 <= extra(1_000_000, 4) < slack                            # updates that the caches hold
+    assert 0 <= extra(n, 8, [0, n // 3, n]) < slack                    # layered models
+    assert 0 <= extra(2 ** 30, 4) < slack                              # beyond the kernel that keeps them
+    assert extra(8_388_608, 8) > slack > extra(8_388_607, 8)
+
+
 def test_create_rejects_bad_arguments_before_touching_the_gpu():
     L = binding.load()
     h = C.c_void_p()
