@@ -121,13 +121,15 @@ __device__ __forceinline__ uint32_t or_reduce8(uint32_t v)
 
 // Distances of four words above a bound, and whether they are below it: the borrow of the subtraction is shifted into acc
 // by an addition with carry (the first word's ends up highest).  Eight instructions; from the comparisons the compiler
-// makes masks, selects and ors, sixteen.  All four borrows are written before the first is read: a mask that the
-// vector unit wrote may be read by it two instructions later.
+// makes masks, selects and ors, sixteen.  All four borrows are written before the first is read: a scalar that the
+// vector unit wrote may be read by it two instructions later.  The compiler keeps that distance itself, but does not look
+// into these blocks: where a scalar operand may come from a lane read just before (a spilled register), they begin by waiting.
 struct Masks4 { uint64_t m0, m1, m2, m3; };
 __device__ __forceinline__ Masks4 sub4_borrow(const uint32_t r[4], uint32_t bound, uint32_t d[4], uint32_t& acc)
 {
     Masks4 m;
-    asm("v_subrev_co_u32_e64 %0, %5, %9, %10\n\t"
+    asm("s_nop 1\n\t"
+        "v_subrev_co_u32_e64 %0, %5, %9, %10\n\t"
         "v_subrev_co_u32_e64 %1, %6, %9, %11\n\t"
         "v_subrev_co_u32_e64 %2, %7, %9, %12\n\t"
         "v_subrev_co_u32_e64 %3, %8, %9, %13\n\t"
@@ -144,7 +146,8 @@ __device__ __forceinline__ Masks4 sub4_borrow(const uint32_t r[4], uint32_t boun
 __device__ __forceinline__ float first_masked(const float4& x, const Masks4& m)
 {
     float v;
-    asm("v_cndmask_b32_e64 %0, %1, %2, %5\n\t"
+    asm("s_nop 1\n\t"
+        "v_cndmask_b32_e64 %0, %1, %2, %5\n\t"
         "v_cndmask_b32_e64 %0, %0, %3, %6\n\t"
         "v_cndmask_b32_e64 %0, %0, %4, %7"
         : "=&v"(v) : "v"(x.w), "v"(x.z), "v"(x.y), "v"(x.x), "s"(m.m2), "s"(m.m1), "s"(m.m0));
