@@ -387,10 +387,18 @@ uint32_t expl_slots(const SegInit& in)
 }
 
 // Whether the local models, gradients and updates (three arrays a worker) pass the caches by: they do not where the next pass
-// finds a good part of them in the 256 MB of the last level.  One round of a worker's side, non-temporal / not, us: 10^6
-// parameters, 4 workers (48 MB) 54 / 48; 3*10^6, 8 (288 MB) 212 / 191; 8*10^6, 4 (384 MB) 287 / 271; but 5*10^6, 8 (480 MB)
+// finds a good part of them in the 256 MB of the last level.  One round of a worker's side in separate calls, non-temporal / not, us:
+// 10^6 parameters, 4 workers (48 MB) 54 / 48; 3*10^6, 8 (288 MB) 212 / 191; 8*10^6, 4 (384 MB) 287 / 271; but 5*10^6, 8 (480 MB)
 // 341 / 352 and 16*10^6, 8 1,090 / 1,239.
-bool local_streams(const slimdp_ctx* c, uint32_t n_workers) { return c->n * n_workers * 12u > 400000000u; }
+constexpr uint64_t STREAMS_HELD = 400000000u;
+bool local_streams(const slimdp_ctx* c, uint32_t n_workers, uint64_t held = STREAMS_HELD) { return c->n * n_workers * 12u > held; }
+// The two fused passes follow each other with little in between: where both leave their arrays in the caches, they evict each other's
+// before the line above.  Step with extraction and pull with step, one round, both non-temporal / neither / the first only: 8*10^6
+// parameters, 2 workers (192 MB) 131 / 129 / 126; 12*10^6, 2 (288 MB) 182 / 179 / 175; 7*10^6, 4 (336 MB) 200 / 198 / 189; 8*10^6, 4 (384 MB)
+// 230 / 250 / 218; 16*10^6, 2 243 / 272 / 236.  One worker's are better off non-temporal at any size: 3*10^6 32.5 / 35.4 / 32.8, 5*10^6 50.7 /
+// 53.7 / 51.6, 30*10^6 264 / 294 / 264.
+constexpr uint64_t FUSED_PACK_HELD = 300000000u;
+bool fused_streams(const slimdp_ctx* c, uint32_t n_workers, uint64_t held) { return n_workers == 1 || local_streams(c, n_workers, held); }
 
 // How many workers a block of the passes over tiles takes in turn: all of them, so that what they share is read once, unless
 // that leaves compute units without a block (one round of 10^6 parameters and 4 workers in 245 tiles: 50.7 us with all four,
@@ -1606,12 +1614,14 @@ int slimdp_pull(slimdp_ctx* ctx, const float* w, uint64_t core_epoch, uint32_t n
         const uint32_t per = workers_per_block(ctx, n_workers);
         auto launch = [&](auto kernel) {
             hipLaunchKernelGGL(kernel, dim3(ctx->T, (n_workers + per - 1) / per), dim3(BLOCK), 0, ctx->stream, w,
-                               make_tab<MutPtrTab>(w_local, n_workers), PtrTab{}, MutPtrTab{}, 0.0f, 1, n_workers, per, ctx->n, ctx->n_seg,
+                               make_tab<MutPtrTab>(w_local, n_workers), PtrTab{}, MutPtrTab{}, 0.0f, 1, n_workers, per, ctx->n,
                                ctx->d_tile_start, core_idx, core_off, make_tab<PtrTab>(expl_idx, n_workers),
                                make_tab<PtrTab>(expl_off, n_workers), make_tab<MutPtrTab>(core_out, n_workers),
                                make_tab<MutPtrTab>(expl_out, n_workers), vec_ok);
         };
-        if (local_streams(ctx, n_workers)) launch(k_pull_local_step<0, 1>); else launch(k_pull_local_step<0, 0>);
+        if (per < n_workers) launch(k_pull_local_step<0, 0, 1>);       // under 2^20 parameters: the caches hold them
+        else if (local_streams(ctx, n_workers)) launch(k_pull_local_step<0, 1, 0>);
+        else launch(k_pull_local_step<0, 0, 0>);
         SLIMDP_LAUNCHED(ctx, "k_pull_local_step<0>");
         return SLIMDP_OK;
     }
@@ -1687,14 +1697,15 @@ int slimdp_local_step_pack(slimdp_ctx* ctx, uint32_t n_workers, float* const* w_
     const dim3 grid(ctx->T, (n_workers + per - 1) / per);
     auto launch = [&](auto kernel) {
         hipLaunchKernelGGL(kernel, grid, dim3(BLOCK), 0, ctx->stream, make_tab<MutPtrTab>(w_local, n_workers),
-                           make_tab<PtrTab>(grad, n_workers), make_tab<MutPtrTab>(delta, n_workers), eta, first, n_workers, per, ctx->n,
-                           ctx->n_seg, ctx->d_tile_start, core_idx, core_off, make_tab<PtrTab>(expl_idx, n_workers),
+                           make_tab<PtrTab>(grad, n_workers), make_tab<MutPtrTab>(delta, n_workers), eta, first, n_workers, per,
+                           ctx->d_tile_start, core_idx, core_off, make_tab<PtrTab>(expl_idx, n_workers),
                            make_tab<PtrTab>(expl_off, n_workers), make_tab<MutPtrTab>(core_val, n_workers),
                            make_tab<MutPtrTab>(expl_val, n_workers), vec_ok);
     };
-    const bool streams = local_streams(ctx, n_workers);
-    if (ctx->opt_pack_nbuf == 2) { if (streams) launch(k_local_step_pack<2, 1>); else launch(k_local_step_pack<2, 0>); }
-    else { if (streams) launch(k_local_step_pack<1, 1>); else launch(k_local_step_pack<1, 0>); }
+    const bool streams = fused_streams(ctx, n_workers, FUSED_PACK_HELD);
+    if (per < n_workers) { if (ctx->opt_pack_nbuf == 2) launch(k_local_step_pack<2, 0, 1>); else launch(k_local_step_pack<1, 0, 1>); }
+    else if (streams) { if (ctx->opt_pack_nbuf == 2) launch(k_local_step_pack<2, 1, 0>); else launch(k_local_step_pack<1, 1, 0>); }
+    else { if (ctx->opt_pack_nbuf == 2) launch(k_local_step_pack<2, 0, 0>); else launch(k_local_step_pack<1, 0, 0>); }
     SLIMDP_LAUNCHED(ctx, "k_local_step_pack");
     return SLIMDP_OK;
 }
@@ -1727,11 +1738,13 @@ int slimdp_pull_local_step(slimdp_ctx* ctx, const float* w, uint64_t core_epoch,
     auto launch = [&](auto kernel) {
         hipLaunchKernelGGL(kernel, dim3(ctx->T, (n_workers + per - 1) / per), dim3(BLOCK), 0, ctx->stream, w,
                            make_tab<MutPtrTab>(w_local, n_workers), make_tab<PtrTab>(grad, n_workers), make_tab<MutPtrTab>(delta, n_workers),
-                           eta, (int)((flags & SLIMDP_LOCAL_FIRST) != 0), n_workers, per, ctx->n, ctx->n_seg, ctx->d_tile_start, core_idx,
+                           eta, (int)((flags & SLIMDP_LOCAL_FIRST) != 0), n_workers, per, ctx->n, ctx->d_tile_start, core_idx,
                            core_off, make_tab<PtrTab>(expl_idx, n_workers), make_tab<PtrTab>(expl_off, n_workers), MutPtrTab{}, MutPtrTab{},
                            vec_ok);
     };
-    if (local_streams(ctx, n_workers)) launch(k_pull_local_step<1, 1>); else launch(k_pull_local_step<1, 0>);
+    if (per < n_workers) launch(k_pull_local_step<1, 0, 1>);
+    else if (fused_streams(ctx, n_workers, STREAMS_HELD)) launch(k_pull_local_step<1, 1, 0>);
+    else launch(k_pull_local_step<1, 0, 0>);
     SLIMDP_LAUNCHED(ctx, "k_pull_local_step");
     return SLIMDP_OK;
 }

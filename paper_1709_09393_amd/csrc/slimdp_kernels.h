@@ -1953,10 +1953,13 @@ __global__ __launch_bounds__(256) void k_local_step(MutPtrTab w_local, PtrTab gr
 // scan of the update vectors (the full scan that section 3.5 counts per extraction).  Same
 // results as k_local_step followed by k_pack_stream on delta.  One block per tile and per_block
 // workers in turn, the next worker's three tiles in flight while the current one is picked from.
+// SPLIT = 0: all workers.  Their pointers are then found at fixed places of the arguments and come together; by a number
+// worked out first they come one after the other, before the first tile can be asked for (one worker, 8*10^6 parameters:
+// 28.9 us without a split, 30.8 with the form for one).
 // ---------------------------------------------------------------------------------------
-template <int NBUF, int NT>
+template <int NBUF, int NT, int SPLIT>
 __global__ __launch_bounds__(BLOCK) void k_local_step_pack(MutPtrTab w_local, PtrTab grad, MutPtrTab delta, float eta, int first,
-                                                           uint32_t nw, uint32_t per_block, uint64_t n, uint32_t n_seg, const uint32_t* __restrict__ tile_start,
+                                                           uint32_t nw, uint32_t per_block, const uint32_t* __restrict__ tile_start,
                                                            const uint32_t* __restrict__ core_idx,
                                                            const uint32_t* __restrict__ core_off, PtrTab expl_idx, PtrTab expl_off,
                                                            MutPtrTab core_val, MutPtrTab expl_val, int vec_ok)
@@ -1964,9 +1967,8 @@ __global__ __launch_bounds__(BLOCK) void k_local_step_pack(MutPtrTab w_local, Pt
     __shared__ float buf[NBUF][TILE];
     __shared__ uint16_t cpos[TILE];          // the tile's core positions: the same for every worker
     __shared__ uint32_t elo[MAXW], ehi[MAXW];
-    const uint32_t t = blockIdx.x, q0 = blockIdx.y * per_block, q1 = min(q0 + per_block, nw);
-    const TileRef tr = tile_ref(t, n_seg, n, tile_start, tile_start);      // the segment is not asked for
-    const uint32_t start = tr.start, len = tr.len;
+    const uint32_t t = blockIdx.x, q0 = SPLIT ? blockIdx.y * per_block : 0u, q1 = SPLIT ? min(q0 + per_block, nw) : nw;
+    const uint32_t start = tile_start[t], len = tile_start[t + 1] - start;
     const bool vec = vec_ok && len == TILE && (start & 3u) == 0;
     float rg[EPT], rw[EPT], rd[EPT];
     uint32_t epos = 0xFFFFFFFFu;
@@ -2003,8 +2005,10 @@ __global__ __launch_bounds__(BLOCK) void k_local_step_pack(MutPtrTab w_local, Pt
         epos = 0xFFFFFFFFu;
         if (j < ehi[q]) epos = static_cast<const uint32_t*>(expl_idx.p[q])[j];
     };
-    // the first worker's tiles are on their way while the lists' slices are looked up
-    fetch_tiles(q0);
+    // several workers: the first one's tiles are on their way while the lists' slices are looked up; one alone gains nothing by
+    // it (30*10^6 parameters 106 us so, 103 after the lists)
+    const bool early = q1 - q0 > 1;
+    if (early) fetch_tiles(q0);
     const uint32_t c0 = core_off[t], c1 = core_off[t + 1];
     const uint32_t ccnt = (c1 - c0 < TILE) ? c1 - c0 : TILE;
     if (threadIdx.x < nw) {
@@ -2017,6 +2021,7 @@ __global__ __launch_bounds__(BLOCK) void k_local_step_pack(MutPtrTab w_local, Pt
         cpos[x] = (pos < len) ? (uint16_t)pos : (uint16_t)0xFFFF;
     }
     __syncthreads();
+    if (!early) fetch_tiles(q0);
     fetch_epos(q0);
     for (uint32_t q = q0; q < q1; ++q) {
         float* b = buf[NBUF == 2 ? (q & 1u) : 0];
@@ -2075,11 +2080,11 @@ __global__ __launch_bounds__(BLOCK) void k_local_step_pack(MutPtrTab w_local, Pt
 // sets leave from the same pass (as a kernel of its own the gather read model and lists a second time: 10^6 parameters, 4 workers
 // 6 + 11 us, 14 together); workers without a local model are not patched.  One block per tile and per_block workers: the tile of the global model stays in
 // registers for all workers, the communication set of a worker is a bitmap in LDS (core positions once per tile,
-// explorer positions per worker, marked one worker ahead), the next worker's three tiles travel meanwhile.
+// explorer positions per worker, marked one worker ahead), the next worker's three tiles travel meanwhile.  SPLIT: as above.
 // ---------------------------------------------------------------------------------------
-template <int STEP, int NT>
+template <int STEP, int NT, int SPLIT>
 __global__ __launch_bounds__(BLOCK) void k_pull_local_step(const float* __restrict__ w, MutPtrTab w_local, PtrTab grad, MutPtrTab delta,
-                                                           float eta, int first, uint32_t nw, uint32_t per_block, uint64_t n, uint32_t n_seg,
+                                                           float eta, int first, uint32_t nw, uint32_t per_block, uint64_t n,
                                                            const uint32_t* __restrict__ tile_start,
                                                            const uint32_t* __restrict__ core_idx,
                                                            const uint32_t* __restrict__ core_off, PtrTab expl_idx, PtrTab expl_off,
@@ -2089,9 +2094,8 @@ __global__ __launch_bounds__(BLOCK) void k_pull_local_step(const float* __restri
     __shared__ uint32_t em[2][TILE_WORDS];       // explorer positions of a worker
     __shared__ uint32_t elo[MAXW], ehi[MAXW];
     __shared__ __align__(16) float ws[STEP ? 4 : TILE];      // the tile of the global model, for the values that leave
-    const uint32_t t = blockIdx.x, q0 = blockIdx.y * per_block, q1 = min(q0 + per_block, nw);
-    const TileRef tr = tile_ref(t, n_seg, n, tile_start, tile_start);      // the segment is not asked for
-    const uint32_t start = tr.start, len = tr.len;
+    const uint32_t t = blockIdx.x, q0 = SPLIT ? blockIdx.y * per_block : 0u, q1 = SPLIT ? min(q0 + per_block, nw) : nw;
+    const uint32_t start = tile_start[t], len = tile_start[t + 1] - start;
     const bool vec = vec_ok && len == TILE && (start & 3u) == 0;
     const uint32_t c0 = core_off[t], c1 = core_off[t + 1];
     if (threadIdx.x < nw) {
