@@ -148,7 +148,7 @@ struct slimdp_ctx {
     SegState* e_state = nullptr;           // per segment, the same for every worker
     SegState* e_draw_state = nullptr;      // zone bounds of the announced draw (side stream)
     std::vector<SegInit> e_state_holds, e_draw_holds;      // what they hold; empty: not known
-    bool lists_clean = true;               // the lists' counters and the coming request's rerun flag are zero
+    bool lists_clean = false;              // the lists' counters and the coming request's rerun flag are zero
     uint32_t rerun_turn = 0;               // which of the two rerun flags that is
     // sizes and zones of the last requests, kept while the sizes stay the same
     struct Plan {
@@ -715,7 +715,6 @@ int slimdp_create(slimdp_ctx** out, uint64_t n, uint32_t max_workers, uint32_t n
     // A clear histogram; the tables, an empty prediction and the cleared flags, in one copy.  Both run on the default
     // stream, and the context's stream need not wait for that one (a non-blocking stream does not): the host waits here.
     e = hipMemset(c->c_hist, 0, (size_t)n_seg * H_STRIDE * 4);
-    if (e == hipSuccess) e = hipMemset(c->e_list_count, 0, max_workers * align_up(n_seg, 32) * 4);
     if (e == hipSuccess) {
         const size_t words = (size_t)(c->d_flags + 64 - c->d_tile_start);
         std::vector<uint32_t> up(words, 0u);
