@@ -302,7 +302,7 @@ __device__ __forceinline__ PhiloxRoundKeys philox_round_keys(uint32_t k0, uint32
     }
     return rk;
 }
-// The rest for one worker: vh, vl = high and low word of the second round's product that only the worker decides (philox_worker).
+// The rest for one worker: v = the second round's product that only the worker decides.
 __device__ __forceinline__ uint64_t philox_worker(uint32_t worker, uint32_t it_lo, uint32_t k0)
 {
     return (uint64_t)0xD2511F53u * ((uint32_t)(((uint64_t)0xCD9E8D57u * it_lo) >> 32) ^ worker ^ k0);

@@ -267,11 +267,11 @@ struct PreArgs {
     uint32_t* cnt_cand;
     uint64_t keys_stride;
     PhiloxKey pk;
-    float* vals;             // explorer capture (see ExplCapture); slots: entries a sub-tile and worker, 0: none
+    float* vals;             // explorer capture (see above); slots: entries a sub-tile and worker, 0: none
     uint32_t slots;
 };
 
-// SPEC = 1 (speculative packing, WT != 0 only) keeps, for every parameter of a full aligned
+// SPEC = 1 (speculative packing, WT != 0 only) keeps, for every parameter of a whole
 // tile whose significance reaches spec.lo[segment] - a little below the core threshold of
 // the previous selection -, the W update values while they are in registers: one bit in
 // spec.bits (beside each bitmap word: the entry number of its first parameter), and one
@@ -485,8 +485,8 @@ __global__ __launch_bounds__(BLOCK, SCORE_MINB) void k_score(const float* __rest
 // the loads of the NEXT round of 256 parameters per wave (the next tile's first round after
 // a tile's last) requested before the current round is worked on, so that a wave always has
 // two rounds of W + 1 16-byte loads in flight, also while it draws explorer zones.  Whole
-// arrays are addressed through one descriptor each (n < 2^30 parameters: byte offsets fit 32
-// bits); block b takes the whole tiles b, b + gridDim.x, ...; the ragged last tile, if any,
+// arrays are addressed by a scalar base (the stores by a descriptor) and one 32-bit lane offset
+// for all of them (n < 2^30 parameters: byte offsets fit); block b takes the whole tiles b, b + gridDim.x, ...; the ragged last tile, if any,
 // goes to one block after its loop, element by element.
 // 1 to 8 and 16 workers come here (16 with two parts of capture staging and no round keys in registers), because a
 // selection then finds its candidates sorted: k_core_build falls from 209 to 14 us at 138*10^6 parameters and 16 workers
@@ -556,8 +556,8 @@ __global__ __launch_bounds__(BLOCK, SCOREF_MINB) void k_score_flat(const float* 
 #pragma unroll
         for (int k = 0; k < WT; ++k) x[k] = ld4<1>(reinterpret_cast<const float*>(static_cast<const char*>(g.p[k]) + o));
     };
-    // PRE = 3: a round draws its own 256 parameters for every worker, so that the flags meet the update values in registers;
-    // otherwise a round draws the whole sub-tile for its share of the workers
+    // PRE = 3 (pre.slots is not zero): a round draws its own 256 parameters for every worker, so that the flags meet the update
+    // values in registers; otherwise a round draws the whole sub-tile for its share of the workers
     constexpr bool KEEP_EXPL = PRE == 3;
     constexpr int PAIRS_W = (WT + 1) / 2;
     constexpr bool PACK_FILL = WT > 8;           // the workers' fill counts as bytes: registers are short there
@@ -605,8 +605,9 @@ __global__ __launch_bounds__(BLOCK, SCOREF_MINB) void k_score_flat(const float* 
     };
     // One round of a whole tile for every worker that is scored.  A lane with a sure parameter among its four leaves the
     // first one's update value in the worker's line of the wave's stage, lanes in order: about 20 values a sub-tile at the
-    // paper's ratio, 4 % of the sure ones are not the first in their lane and are not kept.  Two workers at a time: the
-    // chains of multiplications are long, and eight waves to a unit leave little else to fill them with.
+    // paper's ratio; 3 % of the sure ones are not the first in their lane and are not kept.  Two workers at a time: the
+    // chains of multiplications are long, and eight waves to a unit leave little else to fill them with.  (One worker, the only
+    // odd number that has a capture, is kept for by option "explore_keep" = 2 alone.)
     auto draw_round = [&](float4 (&x)[WT + 1], uint32_t t, uint32_t r) {
         PhiloxKey pk = pre.pk;
         uint32_t worker0 = pre.worker0;
@@ -663,7 +664,9 @@ __global__ __launch_bounds__(BLOCK, SCOREF_MINB) void k_score_flat(const float* 
                 candidates(A, da);
                 if (B != A) candidates(B, db);
             }
-            if (pre.slots) {                                     // uniform
+            // Always so; as a branch, which sets these steps apart from the products of the next pair: 138*10^6 parameters, 8 workers
+            // 1,202 us, 1,213 without, but 64*10^6, 2 234 and 227, 32*10^6, 4 172 and 168; 16 alike.
+            if (WT < 8 || pre.slots != 0) {
                 keep(A, ma);
                 if (B != A) keep(B, mb);
             }
@@ -690,13 +693,11 @@ __global__ __launch_bounds__(BLOCK, SCOREF_MINB) void k_score_flat(const float* 
             }
             if (lane < (uint32_t)WT) pre.cnt_cand[((size_t)lane * T + t) * SUBS + wid] = ecount;
             ecount = 0;
-            if (pre.slots) {
-                const __amdgpu_buffer_rsrc_t rv = buffer_of(pre.vals + ((size_t)t * SUBS + wid) * WT * pre.slots, WT * pre.slots * 4u);
-                const bool few = pre.slots == EXPL_SLOTS_FEW;     // 16-byte pieces: the worker and the piece of its line
-                for (uint32_t k = lane; k < WT * pre.slots / 4u; k += 64) {
-                    const uint32_t b = few ? k / (EXPL_SLOTS_FEW / 4u) : k / (EXPL_SLOTS_MAX / 4u);
-                    buffer_store4_aux<SCOREF_CAP_AUX>(rv, k * 16u, *reinterpret_cast<const float4*>(es + b * EXPL_SLOTS_MAX + (k - b * (pre.slots / 4u)) * 4u));
-                }
+            const __amdgpu_buffer_rsrc_t rv = buffer_of(pre.vals + ((size_t)t * SUBS + wid) * WT * pre.slots, WT * pre.slots * 4u);
+            const bool few = pre.slots == EXPL_SLOTS_FEW;         // 16-byte pieces: the worker and the piece of its line
+            for (uint32_t k = lane; k < WT * pre.slots / 4u; k += 64) {
+                const uint32_t b = few ? k / (EXPL_SLOTS_FEW / 4u) : k / (EXPL_SLOTS_MAX / 4u);
+                buffer_store4_aux<SCOREF_CAP_AUX>(rv, k * 16u, *reinterpret_cast<const float4*>(es + b * EXPL_SLOTS_MAX + (k - b * (pre.slots / 4u)) * 4u));
             }
             wave_sync();
         }
@@ -1199,7 +1200,7 @@ __global__ __launch_bounds__(BLOCK) void k_gather(PtrTab src, int shared_src, ui
 // Pack after a scoring pass that captured the update values of every parameter at or above
 // spec_lo (k_score<.., SPEC = 1>): the core values of a captured tile come from the compact
 // capture (rank of the parameter among the captured ones of its sub-tile), not from the
-// update vectors.  Tiles that were not captured (ragged, unaligned, or a segment whose
+// update vectors.  Tiles that were not captured (ragged ones, or those of a segment whose
 // threshold fell below the capture bound) gather from the update vectors.
 // One wave per tile, all workers (the rank is the same for all); ceil(T/4) blocks.
 // ---------------------------------------------------------------------------------------
@@ -1410,7 +1411,8 @@ __global__ __launch_bounds__(BLOCK) void k_pack_spec(uint32_t core_blocks, uint3
 
 // Explorer values from the scoring pass's capture.  A list entry is looked up by its own index: a parameter that is set in the
 // draw's sure bitmap, is the first such of its block of four and lies within the slots was kept, whatever list names it;
-// the others (4 % at the paper's ratio, chosen candidates, the ragged tile) are gathered.  A later request may have marked
+// the others are gathered: of 2 % of the parameters 3.0 % that are not the first of their block and 0.03 % beyond the slots, 0.4 %
+// chosen candidates, and the ragged tile.  A later request may have marked
 // chosen candidates in the bitmap (or be about to): the slots of the draw's candidates name those bits, and they are taken out.
 // One wave per tile and four workers, every load of a step requested for all four before any is used: a chain of three
 // trips to memory.  grid (ceil(T / 4), ceil(nw / 4)).
@@ -1419,7 +1421,7 @@ __global__ __launch_bounds__(BLOCK) void k_pack_expl_spec(PtrTab g, uint32_t nw,
                                                           PtrTab expl_off, CountTab m_w, const uint32_t* __restrict__ sure_bits,
                                                           const uint32_t* __restrict__ pairs, uint64_t pair_stride,
                                                           const uint32_t* __restrict__ cnt_cand, const float* __restrict__ vals,
-                                                          uint32_t slots, uint32_t drawn, MutPtrTab expl_val)
+                                                          uint32_t slots, MutPtrTab expl_val)
 {
     __shared__ uint32_t wd[4][PEXP][TILE_WORDS];
     __shared__ uint16_t pre[4][PEXP][TILE_WORDS];
@@ -1436,7 +1438,7 @@ __global__ __launch_bounds__(BLOCK) void k_pack_expl_spec(PtrTab g, uint32_t nw,
         if (q < nw) {
             const uint32_t* eo = static_cast<const uint32_t*>(expl_off.p[q]);
             lo[u] = eo[t]; hi[u] = min(eo[t + 1], m_w.c[q]);
-            if (t < T_full && q < drawn) {
+            if (t < T_full) {
                 w2[u] = *reinterpret_cast<const uint2*>(sure_bits + ((size_t)q * T + t) * TILE_WORDS + 2 * lane);
                 cc[u] = cnt_cand[((size_t)q * T + t) * SUBS + (lane >> 4)];
             }
@@ -1477,7 +1479,7 @@ __global__ __launch_bounds__(BLOCK) void k_pack_expl_spec(PtrTab g, uint32_t nw,
             const uint32_t at = pre[wid][u][pos >> 5] + __popc(blocks_of(w) & mask_below(bit & 28u));
             // set, and no bit of its block of four below it
             if ((((w >> (bit & 28u)) & 15u) & ((2u << (bit & 3u)) - 1u)) == (1u << (bit & 3u)) && at < slots)
-                src = vals + (((size_t)t * SUBS + (pos >> 10)) * drawn + q) * slots + at;
+                src = vals + (((size_t)t * SUBS + (pos >> 10)) * nw + q) * slots + at;
         }
         return src;
     };
@@ -2263,14 +2265,16 @@ __device__ __forceinline__ uint32_t quant_code(float v, float s, uint32_t word)
 
 // a / s, correctly rounded, from r = 1 / s correctly rounded: the first correction leaves the quotient within one unit in the last
 // place, and a correction of such a quotient by its exact remainder is the correctly rounded one (Markstein, IBM J. Res.
-// Dev. 34 (1990)).  Exact while nothing leaves the normal numbers: s in [2^-40, 2^40], a zero or in [2^-80, s].
+// Dev. 34 (1990)).  The remainders are exact for s in [2^-40, 2^40] and a zero or in [2^-80, s]: multiples of 2^-127, which
+// binary32 holds as a subnormal, and the quotient itself is a normal number.
 __device__ __forceinline__ float quant_quotient(float a, float s, float r)
 {
     float q = a * r;
     q = __builtin_fmaf(__builtin_fmaf(-q, s, a), r, q);
     return __builtin_fmaf(__builtin_fmaf(-q, s, a), r, q);
 }
-// quant_code's level from its quotient: fraction and whole part of the same y (a NaN has level 0 in both).
+// quant_code's level from its quotient: fraction and whole part of the same y.  Values are finite (the interface asks for
+// it); of a NaN the conversion to a whole number is undefined, here as in quant_code.
 __device__ __forceinline__ uint32_t quant_code_of(float v, float quotient, uint32_t word)
 {
     const float y = quotient * 127.0f;
