@@ -729,7 +729,8 @@ def check_merge(n, W, pct, overlap):
 @pytest.mark.parametrize("exponent", [-140, -126, -81, -80, -79, -41, -40, -39, 0, 39, 40, 41, 120])
 def test_quantisation_on_both_sides_of_the_range_of_the_common_reciprocal(exponent):
     """Buckets whose largest, or smallest, magnitude lies at the edges inside which quotients come from the bucket's
-    reciprocal; zeros, infinities and NaN among them; a ragged last bucket."""
+    reciprocal; zeros among them, and a ragged last bucket.  Values are finite by the interface: of a bucket that holds an
+    infinity the scale alone is compared."""
     n, per = 512 * 24 + 77, 512
     rng = np.random.default_rng(1000 + exponent)
     buckets = []
