@@ -30,6 +30,7 @@ struct Tiling {
     std::vector<uint32_t> seg_first_tile;  // n_seg+1
     bool word_aligned = true;              // every tile starts on a bitmap word
     bool quad_aligned = true;              // every tile starts on a Philox block (index divisible by 4)
+    bool mostly_quads = true;              // ... at least every other one does
 };
 
 bool valid_shape(uint64_t n, uint32_t n_seg, const uint64_t* seg_off)
@@ -45,16 +46,18 @@ Tiling make_tiling(uint64_t n, uint32_t n_seg, const uint64_t* seg_off)
 {
     Tiling tl;
     tl.seg_first_tile.resize(n_seg + 1);
+    uint64_t quads = 0;
     for (uint32_t s = 0; s < n_seg; ++s) {
         tl.seg_first_tile[s] = (uint32_t)tl.tile_seg.size();
         for (uint64_t a = seg_off[s]; a < seg_off[s + 1]; a += TILE) {
             tl.tile_start.push_back((uint32_t)a);
             tl.tile_seg.push_back(s);
             if (a & 31u) tl.word_aligned = false;
-            if (a & 3u) tl.quad_aligned = false;
+            if (a & 3u) tl.quad_aligned = false; else ++quads;
         }
     }
     tl.seg_first_tile[n_seg] = (uint32_t)tl.tile_seg.size();
+    tl.mostly_quads = 2 * quads >= tl.tile_seg.size();
     tl.tile_start.push_back((uint32_t)n);   // n <= 2^31
     return tl;
 }
@@ -397,8 +400,14 @@ bool local_streams(const slimdp_ctx* c, uint32_t n_workers, uint64_t held = STRE
 // parameters, 2 workers (192 MB) 131 / 129 / 126; 12*10^6, 2 (288 MB) 182 / 179 / 175; 7*10^6, 4 (336 MB) 200 / 198 / 189; 8*10^6, 4 (384 MB)
 // 230 / 250 / 218; 16*10^6, 2 243 / 272 / 236.  One worker's are better off non-temporal at any size: 3*10^6 32.5 / 35.4 / 32.8, 5*10^6 50.7 /
 // 53.7 / 51.6, 30*10^6 264 / 294 / 264.
-constexpr uint64_t FUSED_PACK_HELD = 300000000u;
-bool fused_streams(const slimdp_ctx* c, uint32_t n_workers, uint64_t held) { return n_workers == 1 || local_streams(c, n_workers, held); }
+// Where most tiles go by single floats (layered models whose tiles do not begin on multiples of four), both are better off
+// non-temporal from 150 MB on: 57 segments, both / as above, 8*10^6, 2 124 / 131; 16*10^6, 2 236 / 254; 4*10^6, 4 120 / 128; 8*10^6, 4 227 / 242;
+// 4*10^6, 8 223 / 230; but 6*10^6, 2 (144 MB) 93 / 89.
+constexpr uint64_t FUSED_PACK_HELD = 300000000u, FUSED_FLOATS_HELD = 150000000u;
+bool fused_streams(const slimdp_ctx* c, uint32_t n_workers, uint64_t held)
+{
+    return n_workers == 1 || local_streams(c, n_workers, c->tl.mostly_quads ? held : FUSED_FLOATS_HELD);
+}
 
 // How many workers a block of the passes over tiles takes in turn: all of them, so that what they share is read once, unless
 // that leaves compute units without a block (one round of 10^6 parameters and 4 workers in 245 tiles: 50.7 us with all four,

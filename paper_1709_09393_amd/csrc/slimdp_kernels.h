@@ -1974,7 +1974,7 @@ __global__ __launch_bounds__(BLOCK) void k_local_step_pack(MutPtrTab w_local, Pt
     const bool vec = vec_ok && len == TILE && (start & 3u) == 0;
     float rg[EPT], rw[EPT], rd[EPT];
     uint32_t epos = 0xFFFFFFFFu;
-    auto fetch_tiles = [&](uint32_t q) {
+    auto fetch = [&](uint32_t q) {
         const float* g = static_cast<const float*>(grad.p[q]) + start;
         const float* w = static_cast<const float*>(w_local.p[q]) + start;
         const float* d = static_cast<const float*>(delta.p[q]) + start;
@@ -1999,18 +1999,12 @@ __global__ __launch_bounds__(BLOCK) void k_local_step_pack(MutPtrTab w_local, Pt
                 rd[j] = (e < len && !first) ? d[e] : 0.0f;
             }
         }
-    };
-    auto fetch_epos = [&](uint32_t q) {
         // the index itself: anything computed from it here would make the wave wait for this load, and with it for the
         // tile requested just before, on the spot
         const uint32_t j = elo[q] + threadIdx.x;
         epos = 0xFFFFFFFFu;
         if (j < ehi[q]) epos = static_cast<const uint32_t*>(expl_idx.p[q])[j];
     };
-    // several workers: the first one's tiles are on their way while the lists' slices are looked up; one alone gains nothing by
-    // it (30*10^6 parameters 106 us so, 103 after the lists)
-    const bool early = q1 - q0 > 1;
-    if (early) fetch_tiles(q0);
     const uint32_t c0 = core_off[t], c1 = core_off[t + 1];
     const uint32_t ccnt = (c1 - c0 < TILE) ? c1 - c0 : TILE;
     if (threadIdx.x < nw) {
@@ -2023,8 +2017,9 @@ __global__ __launch_bounds__(BLOCK) void k_local_step_pack(MutPtrTab w_local, Pt
         cpos[x] = (pos < len) ? (uint16_t)pos : (uint16_t)0xFFFF;
     }
     __syncthreads();
-    if (!early) fetch_tiles(q0);
-    fetch_epos(q0);
+    // not before the lists: one round with it there / here, us: 30*10^6 parameters in 57 segments, 1 worker 282 / 269, 8*10^6, 4 217 / 213,
+    // 10^6, 8 61.7 / 60.4
+    fetch(q0);
     for (uint32_t q = q0; q < q1; ++q) {
         float* b = buf[NBUF == 2 ? (q & 1u) : 0];
         float* w = static_cast<float*>(w_local.p[q]) + start;
@@ -2054,7 +2049,7 @@ __global__ __launch_bounds__(BLOCK) void k_local_step_pack(MutPtrTab w_local, Pt
         }
         const uint32_t my_epos = epos - start;      // no entry: wraps to a position beyond any tile (start + len < 2^32)
         __syncthreads();     // with two buffers this also orders a buffer's readers (two workers ago) before its writers
-        if (q + 1 < q1) { fetch_tiles(q + 1); fetch_epos(q + 1); }
+        if (q + 1 < q1) fetch(q + 1);
         float* cv = static_cast<float*>(core_val.p[q]);
         for (uint32_t x = threadIdx.x; x < ccnt; x += BLOCK) {
             const uint32_t pos = cpos[x];
