@@ -134,8 +134,8 @@ int slimdp_synchronize(slimdp_ctx* ctx);
  *       (SLIMDP_PACK_UPDATES_AS_SCORED) extracts the core values meanwhile.  With cached core keys the request for
  *       iteration t+1 can be issued before the pack of iteration t (other output arrays) and then runs beside pack
  *       and merge.  Requests whose way to another stream and back would take longer than it hides run on the context's
- *       stream all the same: those of few tiles; where their draw has been made beside other calls also larger ones, and
- *       any of one or two workers.  A request that follows its slimdp_explore_hint ("explore_hint_mode" = 1) at once stays
+ *       stream all the same: those of few tiles (fewer where the core is that of the request before); where their draw has
+ *       been made beside other calls also larger ones, and any of one or two workers.  A request that follows its slimdp_explore_hint ("explore_hint_mode" = 1) at once stays
  *       behind the draw on the side stream.  2 is a test switch: every request and every announced draw on the side stream.
  *   "explore_keep" (0/1/2, default 1): with "speculative_pack", a flat model and a draw announced for at least the W workers
  *       scored, slimdp_score also keeps the update values of most of the coming explorers, and a slimdp_pack with

@@ -127,6 +127,7 @@ struct slimdp_ctx {
         uint64_t idx_bytes = 0, off_bytes = 0;
     } pend[N_PENDING];
     uint64_t pend_seq = 0;
+    uint64_t asked_epoch = ~0ull;          // the core epoch at the last explorer request
     int64_t opt_explore_async = 0;         // 1: requests on the side stream where that pays (stays_on_main), 2: test, all of them
     int device = 0, cus = 256;
     std::vector<uint64_t> seg_off;
@@ -452,9 +453,15 @@ bool device_state_known(slimdp_ctx* c)
 
 // Whether an explorer request runs on the context's own stream although the options would have it on the side stream: an event
 // and a wait across streams, there and back, leave the device idle for some 20 us, and beside other work the request's chain is
-// slower.  Measured whole iterations, own stream / side stream, us, by tiles times workers:
-//   to be drawn first   10^6 parameters, 4 workers (980) 46 / 91; 2*10^6, 8 (3,900) 69 / 118; 7*10^6 in 57 segments, 4 (7,000) 119 / 134;
-//                       10^7 in 57 segments, 4 (9,900) 157 / 146; 8*10^6, 8 (15,600) 158 / 143; 138*10^6, 8 1,820 / 1,480
+// slower.  Measured whole iterations, own stream / side stream, us:
+//   to be drawn first, after a reselection: the lists are wanted at once.  By tiles times workers
+//                       10^6 parameters, 4 workers (980) 46 / 91; 2*10^6, 8 (3,900) 106 / 128; 20*10^6, 1 (4,900) 204 / 216; 30*10^6, 1 (7,300)
+//                       261 / 274; 8*10^6, 4 (7,800) 162 / 179; 8*10^6, 8 (15,600) 158 / 143; 138*10^6, 8 1,820 / 1,480
+//   to be drawn first, for the same core as the request before: one iteration ahead, beside a pack and a merge that take the
+//   longer the larger the model is even of one worker.  By tiles times (workers + 4), on two machines
+//                       5*10^6, 1 (6,100) 43 / 56 to 65; 4*10^6, 4 (7,800) 64 / 65 to 74; 2*10^6, 16 (9,800) 92 / 93 to 103; 4*10^6, 8 (11,700) 90 / 77
+//                       to 83; 8*10^6, 2 (11,700) 72 / 59 to 70; 12*10^6, 1 (14,600) 72 / 67; 20*10^6, 1 105 / 88; 30*10^6, 1 145 / 122; 8*10^6, 4 98 / 77;
+//                       7*10^6 in 57 segments, 4 113 / 96; 30*10^6 in 57 segments, 1 199 / 185
 //   drawn by the scoring pass of a reselecting iteration
 //                       8*10^6, 8 (15,600) 207 / 226; 16*10^6, 8 (31,000) 330 / 335; 64*10^6, 4 (62,500) 658 / 644; 138*10^6, 8 2,150 / 2,115;
 //                       but 138*10^6, 2 (67,500) 1,016 / 1,133: one or two workers' pack is too short to hide it
@@ -467,7 +474,17 @@ bool stays_on_main(const slimdp_ctx* c, uint32_t n_workers, bool drawn)
 {
     if (c->opt_explore_async == 2 || (c->side_pending && c->draw_fresh)) return false;
     const uint64_t work = (uint64_t)c->T * n_workers;
-    return drawn ? work <= 32000 || n_workers <= 2 : work <= 8500;
+    if (drawn) return work <= 32000 || n_workers <= 2;
+    return work <= 8500 && (c->asked_epoch != c->epoch || work + 4ull * c->T <= 10700);
+}
+
+// Whether an announced draw is left to its request, although it could begin on the side stream now.  Cached core keys, announced and
+// requested one iteration ahead, draw with the request / ahead, us, by tiles times (workers + 4): 12*10^6, 1 worker (14,600) 66 / 82;
+// 8*10^6, 4 (15,600) 77 / 90; 16*10^6, 2 (23,400) 90 / 90; 20*10^6, 1 (24,400) 88 / 90; 30*10^6, 1 (36,600) 122 / 117; in 57 segments 185 / 162.
+bool draw_waits(const slimdp_ctx* c, uint32_t n_workers)
+{
+    const uint64_t work = (uint64_t)c->T * n_workers;
+    return c->opt_explore_async != 2 && work <= 8500 && work + 4ull * c->T <= 24000;
 }
 
 // The context's stream waits for whatever the side stream still has in flight (an announced draw, asynchronous
@@ -1272,6 +1289,7 @@ int slimdp_sample_explore(slimdp_ctx* ctx, const uint32_t* core_bits, const uint
     // Option "explore_async": the whole request runs on the library's side stream, beside whatever the caller enqueues
     // on the context's stream after this call; the calls that take the lists make the context's stream wait for them.
     const bool async = ctx->opt_explore_async != 0 && !stays_on_main(ctx, B, cached);
+    ctx->asked_epoch = ctx->epoch;
     hipStream_t st = async ? ctx->side : ctx->stream;
     if (async) {
         // everything enqueued so far comes first: the selection that wrote core_bits, readers of the output arrays
@@ -1393,7 +1411,7 @@ int slimdp_explore_hint(slimdp_ctx* ctx, const uint64_t* k_seg, uint32_t worker0
     }
     if (!ctx->plan.narrow || ctx->plan.M == 0) return SLIMDP_OK;  // nothing worth drawing ahead: slimdp_sample_explore draws itself
     if (!short_list) { rc = ensure_wide_keys(ctx); if (rc) return rc; }
-    if (stays_on_main(ctx, n_workers, false)) return SLIMDP_OK;      // nor this: the request will draw
+    if (draw_waits(ctx, n_workers)) return SLIMDP_OK;                // nor this: the request will draw
     const bool known = device_state_known(ctx);
     // the draw starts now on the side stream, once the previous draw's buffers have been read
     // (the event is recorded here, not after every slimdp_sample_explore: an event on a stream costs a gap between kernels)

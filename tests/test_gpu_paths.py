@@ -469,10 +469,11 @@ def test_requests_of_changing_sizes_follow_each_other(n, W, segments, explore_as
     sd.close()
 
 
-@pytest.mark.parametrize("n,W", [(64_000_003, 1), (64_000_003, 2), (16_000_001, 8)])
-def test_request_behind_a_draw_on_the_side_stream_leaves_the_own_stream_free(n, W):
-    """Cached core keys, the draw announced on the side stream and "explore_async" on: neither the draw nor the request's chain
-    stands in the context's own stream, whatever the number of workers and tiles.  What stands in it is timed on the device
+@pytest.mark.parametrize("n,W,announced", [(64_000_003, 1, True), (64_000_003, 2, True), (16_000_001, 8, True), (30_000_003, 1, True),
+                                           (30_000_003, 1, False), (8_000_003, 4, False), (4_500_003, 8, False)])
+def test_request_for_a_core_that_stays_leaves_the_own_stream_free(n, W, announced):
+    """Cached core keys and "explore_async" on: neither the draw, announced on the side stream or not, nor the request's chain
+    stands in the context's own stream, from a moderate number of tiles on.  What stands in it is timed on the device
     (two events around announcement and request, behind a fill that hides the host's part) and compared with the same calls
     without "explore_async", for which the stream waits; the lists are the same."""
     k, m = len(range(5, n, 32)), n // 50
@@ -488,7 +489,8 @@ def test_request_behind_a_draw_on_the_side_stream_leaves_the_own_stream_free(n, 
             torch.cuda.synchronize()
             blocker.zero_()
             a.record()
-            sd.explore_hint([k], turn, [m], 0, W)
+            if announced:
+                sd.explore_hint([k], turn, [m], 0, W)
             idx[asyn], off[asyn] = sd.sample_explore(bits, [k], turn, [m], 0, W, expl_idx=idx.get(asyn), expl_off=off.get(asyn))
             b.record()
             sd.synchronize()
