@@ -1307,8 +1307,10 @@ int slimdp_sample_explore(slimdp_ctx* ctx, const uint32_t* core_bits, const uint
     const uint32_t P = persistent_blocks(ctx, 8, B);
     const uint32_t G = draw_group(ctx, 4, B);
     // a tile or a few to a block, so that no unit is left with a whole turn more than the others (20*10^6 parameters, 3 workers:
-    // 36 us with at most eight blocks a unit, 33 with one tile to a block)
-    const dim3 draw_grid(persistent_blocks(ctx, 32, (B + G - 1) / G), (B + G - 1) / G);
+    // 36 us with at most eight blocks a unit, 33 with one tile to a block).  Beside other work one or two workers' draw leaves it more
+    // room in few blocks (cached core keys, one iteration ahead, eight / thirty-two a unit, us: 20*10^6, 1 worker 86 / 88; 60*10^6, 1 220 /
+    // 224; 64*10^6, 2 300 / 305), more workers' does not end in time (10^7 in 57 segments, 4 123 / 118; 30*10^6, 8 361 / 358).
+    const dim3 draw_grid(persistent_blocks(ctx, async && B <= 2 ? 8 : 32, (B + G - 1) / G), (B + G - 1) / G);
     const uint32_t n_words = (uint32_t)((ctx->n + 31) / 32);
     const PhiloxKey pk{(uint32_t)ctx->seed, (uint32_t)(ctx->seed >> 32), (uint32_t)iteration, (uint32_t)(iteration >> 32)};
     MutPtrTab off_tab = make_tab<MutPtrTab>(expl_off, B);
