@@ -91,7 +91,7 @@ __device__ __forceinline__ uint32_t inside_mask(uint32_t e0, uint32_t sub_len)
 // candidates in earlier rounds plus a wave ballot count.  Bound by the vector unit: 15 wide multiplications and 17
 // exclusive ors for four words, then a subtraction whose borrow is the sure flag and an addition with carry that files it
 // for each of them; the four rounds' flags become bitmap words together (transpose_flags): 51 instructions a round and worker,
-// 93 % of the issue slots when it runs alone.  With every worker's words from the beginning, masks and a reduction for each
+// the vector units busy all the time when it runs alone.  With every worker's words from the beginning, masks and a reduction for each
 // round's words (67 instructions): 138*10^6 parameters, 8 workers 535 -> 407 us, 20*10^6 and 3 workers 38 -> 33 us.
 // MIS = 1: tiles may begin inside a Philox block (segmented models).  Everything above then counts from the start of that
 // block, mis = start mod 4 positions earlier; the bitmaps are shifted down by mis at the end, and the block that holds the
